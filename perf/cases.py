@@ -1,0 +1,360 @@
+"""The work that a program has this library do, as a list of cases.
+
+Every case is one pass through a public entry point of the package: the
+barcode of one cloud (resident on the GPU, or a host distance matrix), the
+barcodes of a batch of clouds, or a training step through the bars of a
+batch. The shapes are those of the workloads that the tests and bench.py
+run (points on a sphere, rotations and orthogonal matrices as points of R^9,
+a torus in R^4, mixtures of circles and blobs, noisy circles), at their sizes
+and at the sizes around them; the inputs are drawn here from the seed.
+
+A pass returns the bars whole, the thresholds, the numbers of simplices and
+the counters that the complex and the method define. The other counters
+(emergent, reduced, additions, entries_added, entries_stored) tell how much
+work a reduction took and not what it found, so they are no result.
+"""
+
+import numpy as np
+import torch
+
+import paper_1908_02518_amd as rips
+
+INF = float("inf")
+DEFINED = ("candidates", "cleared", "apparent_col", "apparent_pivot", "columns", "bars_nonzero",
+           "essential")
+MAX_SINGLE_N = 10000
+
+
+def listed():
+    return [
+        # the smallest call, where launches and waits are all there is: a handful of points
+        dict(name="sphere-24", kind="cloud", data="sphere", n=24, max_dim=1, t=INF, p=2),
+        # one small cloud, full Rips, the first benchmark workload
+        dict(name="sphere-100", kind="cloud", data="sphere", n=100, max_dim=1, t=INF, p=2),
+        # the paper's sphere3 run: 192 points, full Rips, up to dimension 2
+        dict(name="sphere-192-d2", kind="cloud", data="sphere", n=192, max_dim=2, t=INF, p=2),
+        # a distance matrix in host memory, the host entry point, another field, an odd size
+        dict(name="matrix-171-p5", kind="matrix", n=171, m=3, max_dim=1, t=INF, p=5),
+        # one sparse cloud with a threshold up to dimension 2, the second benchmark workload
+        dict(name="so3-1000", kind="cloud", data="so3", n=1000, max_dim=2, t=1.4, p=2),
+        # the third one: more points, Z/3
+        dict(name="torus4-2000-p3", kind="cloud", data="torus", n=2000, max_dim=2, t=0.5, p=3),
+        # the paper's smaller o3 run, up to dimension 3
+        dict(name="o3-1024-d3", kind="cloud", data="o3", n=1024, max_dim=3, t=1.8, p=2),
+        # the paper's larger o3 run, the largest cloud by work
+        dict(name="o3-4096-d3", kind="cloud", data="o3", n=4096, max_dim=3, t=1.4, p=2),
+        # many points, a short threshold
+        dict(name="torus4-10000", kind="cloud", data="torus", n=10000, max_dim=2, t=0.25, p=2),
+        # many small clouds of uneven sizes in one launch, the fourth benchmark workload
+        dict(name="mixture-512", kind="batch", data="mixture", B=512, n_min=32, n_max=256),
+        # fewer and larger ones, the headline workload of bench.py
+        dict(name="circles-64x400", kind="batch", data="circles", B=64, n_min=400, n_max=400),
+        # a training step: the bars of a batch, a loss on them, the gradient of the points
+        dict(name="train-48", kind="train", data="mixture", B=48, n_min=20, n_max=90),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, max(lo, int(round(float(lo) * (float(hi) / lo) ** rng.random()))))
+
+
+def draw(rng):
+    kind = rng.choice(["sphere", "sphere2", "matrix", "so3", "torus", "o3", "mixture", "circles",
+                       "train"])
+    if kind == "sphere":
+        return dict(kind="cloud", data="sphere", n=_log_int(rng, 8, 400), max_dim=1, t=INF,
+                    p=rng.choice([2, 2, 3]))
+    if kind == "sphere2":
+        return dict(kind="cloud", data="sphere", n=_log_int(rng, 12, 192), max_dim=2, t=INF,
+                    p=rng.choice([2, 2, 3]))
+    if kind == "matrix":
+        return dict(kind="matrix", n=_log_int(rng, 10, 300), m=rng.choice([2, 3, 4]), max_dim=1,
+                    t=INF, p=rng.choice([2, 3, 5]))
+    if kind == "so3":
+        return dict(kind="cloud", data="so3", n=_log_int(rng, 100, 1300),
+                    max_dim=rng.choice([1, 2]), t=rng.choice([1.2, 1.3, 1.4]),
+                    p=rng.choice([2, 2, 3]))
+    if kind == "torus":
+        n = _log_int(rng, 500, MAX_SINGLE_N)
+        return dict(kind="cloud", data="torus", n=n, max_dim=rng.choice([1, 2]),
+                    t=round(min(0.5, 0.5 * (2000.0 / n) ** 0.45), 3), p=rng.choice([2, 3]))
+    if kind == "o3":
+        n = _log_int(rng, 256, 3000)
+        return dict(kind="cloud", data="o3", n=n, max_dim=3, t=1.8 if n <= 1024 else 1.4, p=2)
+    if kind == "mixture":
+        lo = _log_int(rng, 8, 64)
+        return dict(kind="batch", data="mixture", B=_log_int(rng, 8, 512), n_min=lo,
+                    n_max=_log_int(rng, 2 * lo, 256))
+    if kind == "circles":
+        n = _log_int(rng, 60, 400)
+        return dict(kind="batch", data="circles", B=_log_int(rng, 2, 64), n_min=n, n_max=n)
+    return dict(kind="train", data=rng.choice(["mixture", "circles"]), B=_log_int(rng, 4, 48),
+                n_min=20, n_max=_log_int(rng, 30, 90))
+
+
+# ---- inputs -----------------------------------------------------------------
+
+def _rotations(g, k):
+    q = g.standard_normal((k, 4))
+    q /= np.linalg.norm(q, axis=1, keepdims=True)
+    w, x, y, z = q.T
+    r = np.stack([1 - 2 * (y * y + z * z), 2 * (x * y - z * w), 2 * (x * z + y * w),
+                  2 * (x * y + z * w), 1 - 2 * (x * x + z * z), 2 * (y * z - x * w),
+                  2 * (x * z - y * w), 2 * (y * z + x * w), 1 - 2 * (x * x + y * y)], axis=1)
+    return r
+
+
+def _cloud(data, n, g):
+    if data == "sphere":
+        x = g.standard_normal((n, 3))
+        x /= np.linalg.norm(x, axis=1, keepdims=True)
+    elif data == "so3":
+        x = _rotations(g, n)
+    elif data == "o3":
+        x = _rotations(g, n) * np.where(g.random(n) < 0.5, -1.0, 1.0)[:, None]
+    elif data == "torus":
+        a, b = g.uniform(0.0, 2.0 * np.pi, (2, n))
+        x = np.stack([np.cos(a), np.sin(a), np.cos(b), np.sin(b)], axis=1)
+        x += 0.02 * g.standard_normal((n, 4))
+    elif data == "circles":  # a noisy unit circle and one outlier in ten
+        k = n - n // 10
+        a = g.uniform(0.0, 2.0 * np.pi, k)
+        x = np.stack([np.cos(a), np.sin(a)], axis=1) + 0.1 * g.standard_normal((k, 2))
+        x = np.concatenate([x, g.uniform(-2.0, 2.0, (n - k, 2))])[g.permutation(n)]
+    else:  # mixture: one to three noisy circles and up to two blobs in R^3
+        n_circ, n_blob = int(g.integers(1, 4)), int(g.integers(0, 3))
+        k = n_circ + n_blob
+        sizes = 1 + g.multinomial(n - k, np.full(k, 1.0 / k))
+        parts = []
+        for c in range(k):
+            centre, m = g.uniform(-4.0, 4.0, 3), int(sizes[c])
+            if c < n_circ:
+                a = g.uniform(0.0, 2.0 * np.pi, m)
+                flat = g.uniform(0.5, 2.0) * np.stack([np.cos(a), np.sin(a), np.zeros(m)], axis=1)
+                parts.append(flat @ _rotations(g, 1).reshape(3, 3).T + centre
+                             + 0.05 * g.standard_normal((m, 3)))
+            else:
+                parts.append(centre + 0.3 * g.standard_normal((m, 3)))
+        x = np.concatenate(parts)[g.permutation(n)]
+    return np.ascontiguousarray(x.astype(np.float32))
+
+
+def _inputs(case, seed):
+    """The case's clouds (float32 arrays), or its distance matrix."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    if case["kind"] == "cloud":
+        return [_cloud(case["data"], case["n"], g)]
+    if case["kind"] == "matrix":
+        x = g.uniform(0.0, 1.0, (case["n"], case["m"]))
+        d = np.sqrt(((x[:, None, :] - x[None, :, :]) ** 2).sum(-1))
+        return [np.ascontiguousarray(d.astype(np.float32))]
+    return [_cloud(case["data"], int(g.integers(case["n_min"], case["n_max"] + 1)), g)
+            for _ in range(case["B"])]
+
+
+def prepare(case, seed):
+    xs = _inputs(case, seed)
+    if case["kind"] == "cloud":
+        return dict(case=case, x=torch.from_numpy(xs[0]).cuda())
+    if case["kind"] == "matrix":
+        return dict(case=case, dist=xs[0])
+    x, offsets, n_max = rips.pack_clouds(xs)
+    return dict(case=case, x=x, offsets=offsets, n_max=n_max)
+
+
+def run(state):
+    case = state["case"]
+    if case["kind"] == "cloud":
+        bars, info = rips.barcode_device(state["x"], max_dim=case["max_dim"], threshold=case["t"],
+                                         p=case["p"])
+        return dict(bars=[list(b) for b in bars], threshold=info["threshold"],
+                    simplex_count=info["simplex_count"],
+                    stats=[[s[f] for f in DEFINED] for s in info["stats"]])
+    if case["kind"] == "matrix":
+        r = rips.barcode(dist=state["dist"], max_dim=case["max_dim"], threshold=case["t"],
+                         p=case["p"])
+        return dict(bars=[[b.birth, b.death, b.birth_simplex, b.death_simplex] for b in r.bars],
+                    threshold=r.threshold, simplex_count=r.simplex_count,
+                    stats=[[s[f] for f in DEFINED] for s in r.stats],
+                    columns=[list(c) for c in r.columns])
+    if case["kind"] == "batch":
+        bb = rips.barcode_batched(state["x"], state["offsets"], state["n_max"], max_dim=1, p=2)
+        total = int(bb.offsets_host[-1])
+        return dict(birth=bb.birth[:total], death=bb.death[:total],
+                    birth_simplex=bb.birth_simplex[:total], death_simplex=bb.death_simplex[:total],
+                    offsets=bb.offsets, thresholds=bb.thresholds,
+                    stats=[bb.stats[:, :, rips.STAT_FIELDS.index(f)] for f in DEFINED])
+    # the sum of the squared lengths of the finite bars, pulled apart by gradient descent
+    x = state["x"].detach().requires_grad_(True)
+    birth, death, bs, ds, seg = rips.batched_diagram(x, state["offsets"], state["n_max"])
+    length = torch.where(ds >= 0, death - birth, torch.zeros_like(birth))
+    (grad,) = torch.autograd.grad((length * length).sum(), x)
+    return dict(birth=birth.detach(), death=death.detach(), birth_simplex=bs, death_simplex=ds,
+                offsets=seg, grad=grad)
+
+
+def work(case):
+    """Points (or distances) in, bars out: a bar is 24 bytes, and there is
+    about one per point in dimension 0 and one per eight points above it. The
+    arithmetic that no method is spared: every distance once."""
+    if case["kind"] == "matrix":
+        n = case["n"]
+        return dict(bytes=2 * n * (n - 1) + 24 * n * 9 // 8, flops=n * (n - 1) // 2)
+    if case["kind"] == "cloud":
+        n, count = case["n"], 1
+    else:
+        n, count = (case["n_min"] + case["n_max"]) // 2, case["B"]
+    m = {"sphere": 3, "so3": 9, "o3": 9, "torus": 4, "circles": 2, "mixture": 3}[case["data"]]
+    back = 4 * n * m if case["kind"] == "train" else 0
+    return dict(bytes=count * (4 * n * m + 24 * n * 9 // 8 + back),
+                flops=count * (n * (n - 1) // 2) * 3 * m)
+
+
+# ---- the same in 64 bits ----------------------------------------------------
+# Which simplices pair is decided by the float32 edge lengths (that is how the
+# library defines its filtration); the value of a bar's end is then the length
+# of its edge in 64 bits. Z/2, dimensions 0 and 1: components by union-find,
+# and for the loops one bit per open loop on every edge, carried from edge to
+# edge along its oldest triangle where that one's other edges are older than the
+# edge; a triangle whose three edges do not cancel ends the youngest of the
+# loops it holds.
+
+def _lengths32(x):
+    s = np.zeros((len(x), len(x)), dtype=np.float32)
+    for c in range(x.shape[1]):
+        d = x[:, None, c] - x[None, :, c]
+        s = s + d * d
+    return np.sqrt(s)
+
+
+def _bars(x, max_dim):
+    """Per dimension the (birth edge or vertex, death edge or None, birth
+    index, death index) of the bars, in the library's order."""
+    n = len(x)
+    D = _lengths32(x)
+    t = D.max(axis=1).min() if n > 1 else np.float32(0)
+    hi, lo = np.tril_indices(n, -1)
+    keep = D[hi, lo] <= t
+    hi, lo = hi[keep], lo[keep]
+    index = hi.astype(np.int64) * (hi - 1) // 2 + lo
+    order = np.lexsort((-index, D[hi, lo]))
+    hi, lo, index = hi[order], lo[order], index[order]
+    parent = list(range(n))
+
+    def find(v):
+        while parent[v] != v:
+            parent[v] = parent[parent[v]]
+            v = parent[v]
+        return v
+
+    ends, loops, open_loops = {}, [], {}
+    mask = np.zeros((n, n), dtype=np.uint64)
+    seen = np.zeros((n, n), dtype=bool)
+    free = list(range(63, -1, -1))
+    at = 0
+    while at < len(hi):
+        stop = at
+        while stop < len(hi) and D[hi[stop], lo[stop]] == D[hi[at], lo[at]]:
+            stop += 1
+        tied, length = [], D[hi[at], lo[at]]
+        for a, b, e in zip(hi[at:stop].tolist(), lo[at:stop].tolist(), index[at:stop].tolist()):
+            ra, rb = find(a), find(b)
+            if ra != rb:
+                if ra < rb:
+                    ra, rb = rb, ra
+                parent[rb] = ra  # the root is the component's largest, its oldest, vertex
+                if length > 0:
+                    ends[rb] = ((a, b), e)
+            if max_dim >= 1:
+                third = np.nonzero(seen[a] & seen[b])[0]
+                close = (D[a] <= length) & (D[b] <= length)
+                close[a] = close[b] = False
+                c = np.nonzero(close)[0][-1] if close.any() else -1
+                if ra == rb and c >= 0 and seen[a, c] and seen[b, c]:
+                    mask[a, b] = mask[b, a] = mask[a, c] ^ mask[b, c]
+                elif ra == rb:
+                    s = free.pop()  # a loop opens
+                    open_loops[s] = ((a, b), e, len(loops))
+                    loops.append(None)
+                    mask[a, b] = mask[b, a] = np.uint64(1 << s)
+                seen[a, b] = seen[b, a] = True
+                if len(third):
+                    tied.append((a, b, third))
+        cand = []
+        for a, b, third in tied:
+            for c in third.tolist():
+                v = sorted((a, b, c), reverse=True)
+                cand.append((v[0] * (v[0] - 1) * (v[0] - 2) // 6 + v[1] * (v[1] - 1) // 2 + v[2], v))
+        for tri, (a, b, c) in sorted(cand, reverse=True):
+            word = int(mask[a, b] ^ mask[a, c] ^ mask[b, c])
+            if not word:
+                continue
+            s = max((s for s in open_loops if word >> s & 1), key=lambda s: open_loops[s][2])
+            edge, e, k = open_loops.pop(s)
+            if length > D[edge]:
+                loops[k] = (edge, (hi[at], lo[at]), e, tri)
+            hit = (mask >> np.uint64(s)) & np.uint64(1)
+            mask ^= hit * np.uint64(word)
+            free.append(s)
+        at = stop
+    for edge, e, k in open_loops.values():
+        loops[k] = (edge, None, e, -1)
+    h0 = [(None, ends[v][0] if v in ends else None, v, ends[v][1] if v in ends else -1)
+          for v in range(n - 1, -1, -1) if v in ends or find(v) == v]
+    return [h0, [q for q in loops if q is not None]][:max_dim + 1]
+
+
+def _length64(x, edge):
+    d = x[edge[0]].astype(np.float64) - x[edge[1]].astype(np.float64)
+    return float(np.sqrt((d * d).sum()))
+
+
+def _flat(x, bars):
+    return ([0.0 if q[0] is None else _length64(x, q[0]) for q in bars],
+            [INF if q[1] is None else _length64(x, q[1]) for q in bars],
+            [q[2] for q in bars], [q[3] for q in bars])
+
+
+def exact(case, seed):
+    """Values in 64 bits for one small cloud and for the training step; the
+    others would take minutes."""
+    small = case["kind"] == "cloud" and case["max_dim"] == 1 and case["p"] == 2 and case["n"] <= 200
+    if not small and case["kind"] != "train":
+        return None
+    xs = _inputs(case, seed)
+    per = [_bars(x, 1) for x in xs]
+    if case["kind"] == "cloud":
+        rows = []
+        for d in (0, 1):
+            b, e, bs, ds = _flat(xs[0], per[0][d])
+            rows.append([torch.tensor(b, dtype=torch.float64), torch.tensor(e, dtype=torch.float64),
+                         torch.tensor(bs, dtype=torch.int64), torch.tensor(ds, dtype=torch.int64)])
+        return dict(bars=rows, threshold=None, simplex_count=[None] * 2,
+                    stats=[[None] * len(DEFINED)] * 2)
+    flat, offsets, grads = [[], [], [], []], [0], []
+    for x, bars in zip(xs, per):
+        g = np.zeros(x.shape, dtype=np.float64)
+        for d in (0, 1):
+            for out, col in zip(flat, _flat(x, bars[d])):
+                out += col
+            offsets.append(len(flat[0]))
+            for birth, death, _, _ in bars[d]:
+                if death is None:
+                    continue
+                size = _length64(x, death) - (_length64(x, birth) if birth else 0.0)
+                for sign, edge in ((1.0, death), (-1.0, birth)):
+                    if edge is None:
+                        continue
+                    u, v = edge
+                    step = x[u].astype(np.float64) - x[v].astype(np.float64)
+                    far = np.sqrt((step * step).sum())
+                    if far > 0:
+                        g[u] += sign * 2.0 * size * step / far
+                        g[v] -= sign * 2.0 * size * step / far
+        grads.append(g)
+    return dict(birth=torch.tensor(flat[0], dtype=torch.float64),
+                death=torch.tensor(flat[1], dtype=torch.float64),
+                birth_simplex=torch.tensor(flat[2], dtype=torch.int64),
+                death_simplex=torch.tensor(flat[3], dtype=torch.int64),
+                offsets=torch.tensor(offsets, dtype=torch.int64),
+                grad=torch.from_numpy(np.concatenate(grads)))
