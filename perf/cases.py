@@ -8,10 +8,11 @@ run (points on a sphere, rotations and orthogonal matrices as points of R^9,
 a torus in R^4, mixtures of circles and blobs, noisy circles), at their sizes
 and at the sizes around them; the inputs are drawn here from the seed.
 
-A pass returns the bars whole, the thresholds, the numbers of simplices and
-the counters that the complex and the method define. The other counters
-(emergent, reduced, additions, entries_added, entries_stored) tell how much
-work a reduction took and not what it found, so they are no result.
+A pass returns the bars whole (padded to a size that no input exceeds), the
+thresholds, the numbers of simplices and the counters that the complex and the
+method define. The other counters (emergent, reduced, additions,
+entries_added, entries_stored) tell how much work a reduction took and not
+what it found, so they are no result.
 """
 
 import numpy as np
@@ -148,8 +149,13 @@ def _inputs(case, seed):
         x = g.uniform(0.0, 1.0, (case["n"], case["m"]))
         d = np.sqrt(((x[:, None, :] - x[None, :, :]) ** 2).sum(-1))
         return [np.ascontiguousarray(d.astype(np.float32))]
-    return [_cloud(case["data"], int(g.integers(case["n_min"], case["n_max"] + 1)), g)
-            for _ in range(case["B"])]
+    return [_cloud(case["data"], n, g) for n in _sizes(case)]
+
+
+def _sizes(case):
+    """The clouds' sizes of a batch: the case's own, whatever the seed."""
+    g = np.random.Generator(np.random.PCG64([case["B"], case["n_min"], case["n_max"]]))
+    return g.integers(case["n_min"], case["n_max"] + 1, case["B"]).tolist()
 
 
 def prepare(case, seed):
@@ -162,35 +168,63 @@ def prepare(case, seed):
     return dict(case=case, x=x, offsets=offsets, n_max=n_max)
 
 
+def _rows(case):
+    """How many rows the case's diagrams are padded to, as a program does that
+    stacks them or feeds them on: the number of bars depends on the input."""
+    if case["kind"] in ("cloud", "matrix"):
+        return 4 * case["n"] * max(1, case["max_dim"])
+    return 2 * case["n_max"] * case["B"]
+
+
+def _padded(case, bars, device):
+    """(values, simplices): birth and death, and their simplices, of each
+    list of bars, rows beyond its bars zero."""
+    rows = _rows(case)
+    ends = torch.zeros((len(bars), 2, rows), dtype=torch.float32, device=device)
+    ids = torch.zeros((len(bars), 2, rows), dtype=torch.int64, device=device)
+    for d, (birth, death, bs, ds) in enumerate(bars):
+        c = birth.shape[0]
+        ends[d, 0, :c], ends[d, 1, :c] = birth, death
+        ids[d, 0, :c], ids[d, 1, :c] = bs, ds
+    return ends, ids
+
+
 def run(state):
     case = state["case"]
     if case["kind"] == "cloud":
         bars, info = rips.barcode_device(state["x"], max_dim=case["max_dim"], threshold=case["t"],
                                          p=case["p"])
-        return dict(bars=[list(b) for b in bars], threshold=info["threshold"],
-                    simplex_count=info["simplex_count"],
+        ends, ids = _padded(case, bars, state["x"].device)
+        return dict(ends=ends, ids=ids, counts=[b[0].shape[0] for b in bars],
+                    threshold=info["threshold"], simplex_count=info["simplex_count"],
                     stats=[[s[f] for f in DEFINED] for s in info["stats"]])
     if case["kind"] == "matrix":
         r = rips.barcode(dist=state["dist"], max_dim=case["max_dim"], threshold=case["t"],
                          p=case["p"])
-        return dict(bars=[[b.birth, b.death, b.birth_simplex, b.death_simplex] for b in r.bars],
-                    threshold=r.threshold, simplex_count=r.simplex_count,
-                    stats=[[s[f] for f in DEFINED] for s in r.stats],
-                    columns=[list(c) for c in r.columns])
+        bars = [[torch.from_numpy(v) for v in (b.birth, b.death, b.birth_simplex, b.death_simplex)]
+                for b in r.bars]
+        ends, ids = _padded(case, bars, "cpu")
+        pairs = case["n"] * (case["n"] + 1) // 2
+        index, diam = np.zeros((2, pairs), np.int64), np.zeros((2, pairs), np.float32)
+        for d, (i, v) in enumerate(r.columns):
+            index[d, :len(i)], diam[d, :len(v)] = i, v
+        return dict(ends=ends, ids=ids, counts=[len(b) for b in r.bars], threshold=r.threshold,
+                    simplex_count=r.simplex_count, column_index=index, column_diam=diam,
+                    stats=[[s[f] for f in DEFINED] for s in r.stats])
     if case["kind"] == "batch":
         bb = rips.barcode_batched(state["x"], state["offsets"], state["n_max"], max_dim=1, p=2)
         total = int(bb.offsets_host[-1])
-        return dict(birth=bb.birth[:total], death=bb.death[:total],
-                    birth_simplex=bb.birth_simplex[:total], death_simplex=bb.death_simplex[:total],
-                    offsets=bb.offsets, thresholds=bb.thresholds,
+        ends, ids = _padded(case, [[bb.birth[:total], bb.death[:total], bb.birth_simplex[:total],
+                                    bb.death_simplex[:total]]], state["x"].device)
+        return dict(ends=ends, ids=ids, offsets=bb.offsets, thresholds=bb.thresholds,
                     stats=[bb.stats[:, :, rips.STAT_FIELDS.index(f)] for f in DEFINED])
     # the sum of the squared lengths of the finite bars, pulled apart by gradient descent
     x = state["x"].detach().requires_grad_(True)
     birth, death, bs, ds, seg = rips.batched_diagram(x, state["offsets"], state["n_max"])
     length = torch.where(ds >= 0, death - birth, torch.zeros_like(birth))
     (grad,) = torch.autograd.grad((length * length).sum(), x)
-    return dict(birth=birth.detach(), death=death.detach(), birth_simplex=bs, death_simplex=ds,
-                offsets=seg, grad=grad)
+    ends, ids = _padded(case, [[birth.detach(), death.detach(), bs, ds]], x.device)
+    return dict(ends=ends, ids=ids, offsets=seg, grad=grad)
 
 
 def work(case):
@@ -323,14 +357,21 @@ def exact(case, seed):
         return None
     xs = _inputs(case, seed)
     per = [_bars(x, 1) for x in xs]
+    rows = _rows(case)
+
+    def padded(lists):
+        ends = torch.zeros((len(lists), 2, rows), dtype=torch.float64)
+        ids = torch.zeros((len(lists), 2, rows), dtype=torch.int64)
+        for d, cols in enumerate(lists):
+            for k in (0, 1):
+                ends[d, k, :len(cols[k])] = torch.tensor(cols[k], dtype=torch.float64)
+                ids[d, k, :len(cols[k])] = torch.tensor(cols[2 + k], dtype=torch.int64)
+        return ends, ids
+
     if case["kind"] == "cloud":
-        rows = []
-        for d in (0, 1):
-            b, e, bs, ds = _flat(xs[0], per[0][d])
-            rows.append([torch.tensor(b, dtype=torch.float64), torch.tensor(e, dtype=torch.float64),
-                         torch.tensor(bs, dtype=torch.int64), torch.tensor(ds, dtype=torch.int64)])
-        return dict(bars=rows, threshold=None, simplex_count=[None] * 2,
-                    stats=[[None] * len(DEFINED)] * 2)
+        ends, ids = padded([_flat(xs[0], per[0][d]) for d in (0, 1)])
+        return dict(ends=ends, ids=ids, counts=[len(b) for b in per[0]], threshold=None,
+                    simplex_count=[None] * 2, stats=[[None] * len(DEFINED)] * 2)
     flat, offsets, grads = [[], [], [], []], [0], []
     for x, bars in zip(xs, per):
         g = np.zeros(x.shape, dtype=np.float64)
@@ -352,9 +393,6 @@ def exact(case, seed):
                         g[u] += sign * 2.0 * size * step / far
                         g[v] -= sign * 2.0 * size * step / far
         grads.append(g)
-    return dict(birth=torch.tensor(flat[0], dtype=torch.float64),
-                death=torch.tensor(flat[1], dtype=torch.float64),
-                birth_simplex=torch.tensor(flat[2], dtype=torch.int64),
-                death_simplex=torch.tensor(flat[3], dtype=torch.int64),
-                offsets=torch.tensor(offsets, dtype=torch.int64),
+    ends, ids = padded([flat])
+    return dict(ends=ends, ids=ids, offsets=torch.tensor(offsets, dtype=torch.int64),
                 grad=torch.from_numpy(np.concatenate(grads)))
