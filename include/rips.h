@@ -79,6 +79,9 @@ typedef struct {
     int64_t apparent_col;   /* candidates sigma in a zero apparent pair (sigma, tau) */
     int64_t apparent_pivot; /* candidates sigma in a zero apparent pair (rho, sigma), d >= 2 */
     int64_t columns;        /* columns left for the reduction */
+    /* the work of the reduction: it depends on the method that ran (see
+       rips_set_working_column; the sweep has no emergent columns, counts as
+       reduced every class that a triangle closes, and adds row vectors) */
     int64_t emergent;       /* columns resolved by the emergent shortcut */
     int64_t reduced;        /* columns that needed at least one column addition */
     int64_t additions;      /* column additions in total */
@@ -219,9 +222,12 @@ rips_status rips_simplex_counts_device(const float *d_data, int64_t n, int32_t d
 
 /*
  * rips_barcode_batched_device -- barcodes of B point clouds of uneven sizes
- * in one persistent launch (one workgroup per cloud from a queue ordered by
- * decreasing size), replayed from a cached hipGraph when the arguments
- * repeat. Same method and conventions as rips_barcode, per cloud.
+ * in one persistent launch (workgroups that take the clouds from a queue
+ * ordered by decreasing size). Over Z/2 that is the sweep of
+ * rips_set_working_column; for other fields, or where a cloud exceeds the
+ * sweep's tables (more than 2048 open classes, say), the column reduction,
+ * replayed from a cached hipGraph when the arguments repeat. Same results
+ * and conventions as rips_barcode, per cloud.
  *   d_points   device float32, all clouds' points concatenated row-major
  *              (dim coordinates each); cloud b has rows
  *              [d_offsets[b], d_offsets[b+1]).
@@ -359,19 +365,23 @@ rips_status rips_set_reduced_storage(int32_t mode);
 rips_status rips_get_reduced_storage(int32_t *mode);
 
 /*
- * The working column of the dimension-1 reduction (per device, the current
- * one; single-cloud and batched paths). Its rows are triangles, and over
- * Z/2 with every shortcut on it can be held direct-mapped: one bit per
+ * The method of dimension 1 (per device, the current one; single-cloud and
+ * batched paths). AUTO takes the sweep where it applies (Z/2, the batched
+ * path): one pass over the edges in order of length that carries on every
+ * edge the vector of the open classes, closed by the first triangle whose
+ * three vectors do not cancel; no coboundary column is reduced. Otherwise the
+ * columns are reduced, with one of two working columns. A column's rows are
+ * triangles, and over Z/2 with every shortcut on it can be held direct-mapped: one bit per
  * (longest edge, third vertex), the edges <= t in order of length, so that
  * an addition is one XOR per entry and the oldest entry is the highest bit
  * of the first nonempty edge (the refined order of section "Lexicographic
  * refinement"; the implicit columns of section "Implicit matrix
  * reduction").
- *   RIPS_WORKING_COLUMN_AUTO (default): direct-mapped where it applies and
- *     fits (n <= 1920, at most 2^18 edges <= t, its bitmaps within 8 GiB),
- *     else the general working column;
- *   RIPS_WORKING_COLUMN_GENERAL: always the general one (LDS delta, sorted
- *     base, far list).
+ *   RIPS_WORKING_COLUMN_AUTO (default): the sweep, else direct-mapped where
+ *     that applies and fits (n <= 1920, at most 2^18 edges <= t, its bitmaps
+ *     within 8 GiB), else the general working column;
+ *   RIPS_WORKING_COLUMN_GENERAL: always the columns, with the general one
+ *     (LDS delta, sorted base, far list).
  * The bars are the same either way. Other values: RIPS_E_INVALID_ARG.
  */
 #define RIPS_WORKING_COLUMN_AUTO 0

@@ -17,6 +17,7 @@
 
 #include "../../include/rips.h"
 #include "rips_batched.hpp"
+#include "rips_sweep.hpp"
 
 using namespace rips;
 
@@ -234,6 +235,18 @@ enum BufId {
     B_EXP_WD1,
     B_EXP_WC0,
     B_EXP_WC1,
+    // the sweep (dimensions 0 and 1 over Z/2)
+    B_SW_D,
+    B_SW_IDS,
+    B_SW_ZC,
+    B_SW_LIST,
+    B_SW_AUX,
+    B_SW_SV,
+    B_SW_CKEY,
+    B_SW_KKEY,
+    B_SW_POOL,
+    B_SW_MASK,
+    B_SW_SCAL,
     B_NUM
 };
 
@@ -1520,6 +1533,120 @@ BarBuf internal_bars(DevCtx &C, int d) {
 // set the device "nbars" scalar before an emit
 __global__ void k_set_nbars(Scalars *s, int64_t v) { s->nbars = v; }
 
+// The words a sweep launch reports.
+struct SweepScal {
+    unsigned long long queue, ucount;
+    int64_t total;
+    int status;
+};
+
+// The per-workgroup buffers of `grid` sweep workgroups for clouds of up to
+// n_max points.
+rips_status sweep_buffers(DevCtx &C, int n_max, int64_t grid, SweepArgs &A, SweepScal **scal) {
+    void *q;
+    const int64_t npairs = (int64_t)n_max * (n_max - 1) / 2;
+    A.nmax = n_max;
+    A.d_stride = (int64_t)n_max * n_max;
+    A.e_stride = (npairs + 16) / 8 * 8;
+    A.sv_cap = sweep_sv_cap(n_max);
+    A.pool_stride = sweep_pool_words(n_max);
+    A.mask_stride = (int64_t)n_max * sweep_mask_words(n_max);
+#define ENS(id, bytes, field, T)                                                                   \
+    do {                                                                                           \
+        HIP_TRY(C.ensure(id, (size_t)(bytes), &q));                                                \
+        field = as<T>(q);                                                                          \
+    } while (0)
+    ENS(B_SW_D, grid * A.d_stride * 4, A.D, float);
+    ENS(B_SW_IDS, grid * A.d_stride * 4, A.ids, u32);
+    ENS(B_SW_ZC, grid * A.e_stride * 2, A.zc, uint16_t);
+    ENS(B_SW_LIST, grid * A.e_stride * 8, A.list, u64);
+    ENS(B_SW_AUX, grid * A.e_stride * 4, A.aux, u32);
+    ENS(B_SW_SV, grid * A.sv_cap * 8, A.sv, u64);
+    ENS(B_SW_CKEY, grid * A.sv_cap * 8, A.ckey, u64);
+    ENS(B_SW_KKEY, grid * A.sv_cap * 8, A.kkey, u64);
+    ENS(B_SW_POOL, grid * A.pool_stride * 4, A.pool, u32);
+    ENS(B_SW_MASK, grid * A.mask_stride * 8, A.mask, u64);
+    ENS(B_SW_SCAL, sizeof(SweepScal), *scal, SweepScal);
+#undef ENS
+    A.queue = &(*scal)->queue;
+    A.ucount = &(*scal)->ucount;
+    A.status = &(*scal)->status;
+    HIP_TRY(sweep_prepare(n_max, A.sv_cap));
+    return RIPS_OK;
+}
+
+// The batch by the sweep, one workgroup per cloud from a queue by decreasing
+// size. *full: some cloud exceeds the sweep's tables; nothing was written to
+// the bar arrays and the caller runs the column reduction.
+rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_offsets, int32_t B, int32_t dim,
+                          int32_t n_max, int32_t max_dim, float threshold, rips_batch_out *out,
+                          hipStream_t st, bool *full) {
+    void *q;
+    const int D1 = max_dim + 1;
+    const int64_t grid = std::min<int64_t>(std::max(1, C.num_cus), B);
+    SweepArgs A;
+    memset(&A, 0, sizeof(A));
+    SweepScal *scal;
+    rips_status rs = sweep_buffers(C, n_max, grid, A, &scal);
+    if (rs) return rs;
+    A.X = d_points;
+    A.offsets = d_offsets;
+    A.B = B;
+    A.m = dim;
+    A.max_dim = max_dim;
+    A.threshold = threshold;
+    BatchArgs F;
+    memset(&F, 0, sizeof(F));
+    F.B = B;
+    F.max_dim = max_dim;
+    int *order;
+#define ENS(id, bytes, field, T)                                                                   \
+    do {                                                                                           \
+        HIP_TRY(C.ensure(id, (size_t)(bytes), &q));                                                \
+        field = as<T>(q);                                                                          \
+    } while (0)
+    ENS(BB_ORDER, (int64_t)B * 4, order, int);
+    A.order = order;
+    const int64_t ucap = std::max<int64_t>(out->cap, 1);
+    ENS(BB_UB, ucap * 4, F.ub, float);
+    ENS(BB_UD, ucap * 4, F.ud, float);
+    ENS(BB_UBS, ucap * 8, F.ubs, int64_t);
+    ENS(BB_UDS, ucap * 8, F.uds, int64_t);
+    ENS(BB_SEG_START, (int64_t)B * D1 * 8, F.seg_start, int64_t);
+    ENS(BB_SEG_COUNT, (int64_t)B * D1 * 8, F.seg_count, int64_t);
+    if (out->stats) A.stats = out->stats;
+    else ENS(BB_STATS, (int64_t)B * D1 * sizeof(rips_dim_stats), A.stats, rips_dim_stats);
+    if (out->threshold_used) A.t_used = out->threshold_used;
+    else ENS(BB_TUSED, (int64_t)B * 4, A.t_used, float);
+#undef ENS
+    A.ub = F.ub;
+    A.ud = F.ud;
+    A.ubs = F.ubs;
+    A.uds = F.uds;
+    A.ucap = out->cap;
+    A.seg_start = F.seg_start;
+    A.seg_count = F.seg_count;
+    launch_sweep_order(d_offsets, B, n_max, order, A.queue, A.ucount, A.status, st);
+    {
+        PROF(P_BATCHED);
+        launch_sweep(A, (int)grid, st);
+    }
+    launch_batch_finalize(F, out->bar_offsets, &scal->total, out->cap, out->birth, out->death,
+                          out->birth_simplex, out->death_simplex, st);
+    HIP_TRY(hipGetLastError());
+    static_assert(sizeof(SweepScal) <= sizeof(Scalars), "read back through the pinned scalar block");
+    const SweepScal *hs = (const SweepScal *)C.host_scal;
+    HIP_TRY(hipMemcpyAsync(C.host_scal, scal, sizeof(SweepScal), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    prof_resolve();
+    out->needed = hs->total;
+    if (hs->status & 16) return fail(RIPS_E_INVALID_ARG, "a cloud is empty or larger than n_max");
+    if (hs->status & 4) return fail(RIPS_E_NONFINITE, "input holds NaN/Inf");
+    *full = (hs->status & kSweepFull) != 0;
+    if (!*full && hs->total > out->cap) return fail(RIPS_E_CAPACITY, "bar capacity too small");
+    return RIPS_OK;
+}
+
 rips_status batched_once(DevCtx &Cref, const float *d_points, const int64_t *d_offsets,
                                 int32_t B, int32_t dim, int32_t n_max, int32_t max_dim,
                                 float threshold, uint32_t p, rips_batch_out *out, void *hip_stream,
@@ -2279,6 +2406,12 @@ rips_status rips_barcode_batched_device(const float *d_points, const int64_t *d_
     rips_status rs;
     if ((rs = get_ctx(&C))) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
+    if (p == 2 && C->working_column == RIPS_WORKING_COLUMN_AUTO) {
+        bool full = false;
+        rs = batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
+                           (hipStream_t)hip_stream, &full);
+        if (rs || !full) return rs;
+    }
     for (int attempt = 0;; ++attempt) {
         bool retry = false;
         rs = batched_once(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out,
