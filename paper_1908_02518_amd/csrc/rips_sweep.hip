@@ -38,8 +38,6 @@ constexpr u32 kNone = 0xffffu;     // no zero apparent cofacet
 constexpr u32 kNotEdge = 0xfffeu;  // longer than the threshold
 constexpr int kProbe = 32;         // third vertices one lane tries before a whole wave takes over
 constexpr int kMaxChunks = 1024;
-constexpr int kItemWords = 4;      // work items one edge adds at a time
-constexpr int kItems = 4;          // work items a wave has in flight
 constexpr int kPoolLdsWords = 4096;
 
 struct SweepShared {
@@ -52,7 +50,7 @@ struct SweepShared {
     int nb0, nb1, ness;
     unsigned long long ncand0, nzap;
     int scan[kWaves + 1];
-    u32 work[kT * kItemWords];
+    u32 work[kT];
     u32 cstart[kMaxChunks + 1]; // first list entry of a chunk
     u32 cbin[kMaxChunks + 1];   // first bin after a chunk
     int kp[kSweepCand], ki[kSweepCand]; // kills: class, candidate
@@ -213,6 +211,119 @@ struct MaskPtr<false> {
     typedef u64 *T;
 };
 
+// Half a word of them. In global memory the other waves' updates are atomics,
+// which execute in the L2, so a plain load could return a stale line of the L1.
+__device__ __forceinline__ u32 mask_half(const LDS u64 *m, int i) { return ((const LDS u32 *)m)[i]; }
+__device__ __forceinline__ u32 mask_half(const u64 *m, int i) { return ld((const u32 *)m + i); }
+
+struct TestArgs {
+    const float *D;
+    const u32 *ids;
+    int n, MW, nw, ccap;
+    u64 lo, hi;
+};
+
+// The triangles of the listed edges whose vectors do not cancel, appended to
+// the candidates: NE edges a wave at once, their third vertices over the
+// lanes, NW words of 64 of them in flight. The pass is bound by instruction
+// issue, so what an edge has in common is in scalar registers, every load is
+// unconditional (from a clamped place) and all are issued before the first is
+// used. (With one work item per edge and word, the setup of each cost more
+// than its test: circles-64x400 5.8 ms, so 41,000 items a cloud at 440
+// instructions each.)
+template <int NE, int NW, class Mask>
+__device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const Rows &P, SweepShared &Sh,
+                                           const SweepLds &L, int wave, int lane) {
+    constexpr int N = NE * NW;
+    const int n = T.n, MW = T.MW, W = P.W, half = lane >> 5, bit = lane & 31;
+    for (int q = wave * NE; q < T.nw; q += kWaves * NE)
+        for (int w0 = 0; w0 < MW; w0 += NW) {
+            int ea[NE], ev[NE];
+            float len[NE], x[N], y[N];
+            u32 r0[NE], r1[N], r2[N], fa[N], fv[N], fo[NE];
+#pragma unroll
+            for (int g = 0; g < NE; ++g) {
+                const u32 ab = __builtin_amdgcn_readfirstlane(Sh.work[min(q + g, T.nw - 1)]);
+                ea[g] = (int)(ab >> 16);
+                ev[g] = (int)(ab & 0xffff);
+                const float *Da = T.D + (int64_t)ea[g] * n, *Dv = T.D + (int64_t)ev[g] * n;
+                const u32 *Ia = T.ids + (int64_t)ea[g] * n, *Iv = T.ids + (int64_t)ev[g] * n;
+                len[g] = Da[ev[g]];
+                r0[g] = Ia[ev[g]];
+                fo[g] = mask_half(mask, ea[g] * MW * 2 + (ev[g] >> 5)) >> (ev[g] & 31);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const int u = g * NW + w, mw = min(w0 + w, MW - 1);
+                    const int at = min(mw * 64 + lane, n - 1);
+                    x[u] = Da[at];
+                    y[u] = Dv[at];
+                    r1[u] = Ia[at];
+                    r2[u] = Iv[at];
+                    fa[u] = mask_half(mask, ea[g] * MW * 2 + mw * 2 + half);
+                    fv[u] = mask_half(mask, ev[g] * MW * 2 + mw * 2 + half);
+                }
+            }
+            bool nz[N];
+            bool some = false, tie = false;
+#pragma unroll
+            for (int g = 0; g < NE; ++g) {
+                const bool own = fo[g] & 1u;
+                r0[g] = own ? r0[g] : 0u;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const int u = g * NW + w, c = (w0 + w) * 64 + lane;
+                    const bool ba = (fa[u] >> bit) & 1u, bv = (fv[u] >> bit) & 1u;
+                    const float far = fmaxf(x[u], y[u]);
+                    r1[u] = ba ? r1[u] : 0u;
+                    r2[u] = bv ? r2[u] : 0u;
+                    // two equal rows and a zero one cancel
+                    const u32 sum = r0[g] ^ r1[u] ^ r2[u];
+                    const bool gone = sum == 0 && (r0[g] == 0 || r1[u] == 0 || r2[u] == 0);
+                    nz[u] = far <= len[g] && !gone && c < n && q + g < T.nw;
+                    some = some || nz[u];
+                    tie = tie || (nz[u] && far == len[g]);
+                }
+            }
+            if (!__any(some)) continue;
+            if (__any(tie)) { // equal lengths: the larger index is older
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const int g = u / NW, c = (w0 + u % NW) * 64 + lane;
+                    const u32 e = pair_index(ea[g], ev[g]);
+                    nz[u] = nz[u] && older(x[u], ea[g], c, len[g], e) && older(y[u], ev[g], c, len[g], e);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int g = u / NW, a = ea[g], v = ev[g], c = (w0 + u % NW) * 64 + lane;
+                if (!__any(nz[u])) continue;
+                const u32 p0 = r0[g], p1 = r1[u], p2 = r2[u];
+                u32 any = 0;
+                u64 key = 0;
+                if (nz[u]) {
+                    for (int w = 0; w < W; ++w) any |= row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
+                    key = ((u64)__float_as_uint(len[g]) << 32) | (u64)(0xffffffffu - triangle_index(a, v, c));
+                }
+                const bool open = nz[u] && any != 0 && key > T.lo && key <= T.hi;
+                // one triangle of each sum is enough: the oldest, with the largest c
+                u64 todo = __ballot(open);
+                while (todo) {
+                    const int l = 63 - __clzll((long long)todo);
+                    const u32 q1 = __builtin_amdgcn_readlane(p1, l), q2 = __builtin_amdgcn_readlane(p2, l);
+                    todo &= ~__ballot(open && ((p1 == q1 && p2 == q2) || (p1 == q2 && p2 == q1)));
+                    if (lane == l) {
+                        const int s = atomicAdd(&Sh.ncand, 1);
+                        if (s < T.ccap) {
+                            L.keys[s] = key;
+                            for (int w = 0; w < W; ++w)
+                                L.vec[s * W + w] = row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
+                        }
+                    }
+                }
+            }
+        }
+}
+
 // One cloud. Returns through the queue loop; every thread of the workgroup calls it.
 template <bool kMaskLds>
 __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem, SweepShared &Sh) {
@@ -337,16 +448,17 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
             int c = -1;
             u64 open = __ballot(edge);
             const int col = v < a ? v : 0;
-            for (int p = 0; p < kProbe && open; p += 8) {
+            const float *Dc = D + (int64_t)top * n;
+            for (int p = 0; p < kProbe && p < n && open; p += 8, Dc -= 8 * (int64_t)n) {
                 float yy[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) yy[u] = D[(int64_t)max(top - p - u, 0) * n + col];
+                for (int u = 0; u < 8; ++u) yy[u] = (p + u < n ? Dc - u * (int64_t)n : D)[col];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     // +inf past the last vertex
                     const float xx = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xr), p + u));
-                    const u64 hit = __ballot(xx <= len && yy[u] <= len) & open;
-                    if (__builtin_amdgcn_inverse_ballot_w64(hit)) c = top - p - u;
+                    const u64 hit = __ballot(fmaxf(xx, yy[u]) <= len) & open;
+                    c = __builtin_amdgcn_inverse_ballot_w64(hit) ? top - p - u : c;
                     open &= ~hit;
                 }
             }
@@ -376,7 +488,8 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int w = top - u * kWave - lane;
-                    far[u] = w >= 0 ? fmaxf(Da[w], Dv[w]) : INFINITY;
+                    const float d = fmaxf(Da[max(w, 0)], Dv[max(w, 0)]);
+                    far[u] = w >= 0 ? d : INFINITY;
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -499,9 +612,11 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
         }
         const int ccap = min(kSweepCand, kSweepCandWords / W);
         // ---- the edges by length bin, whole bins to a chunk of about as many
-        // edges as there are threads (more, where a cloud has very many)
+        // edges as there are threads (more, where a cloud has very many; fewer in
+        // a small one: the triangles of a chunk that a class closed in it leaves
+        // nonzero are all eliminated at once)
         const u32 E = (u32)Sh.ncand0;
-        const u32 target = max((u32)kT, (E + kMaxChunks - 3) / (kMaxChunks - 2));
+        const u32 target = max(min(max(E / 32, 256u), (u32)kT), (E + kMaxChunks - 3) / (kMaxChunks - 2));
         for (int q = tid; q <= kMaxChunks; q += kT) {
             Sh.cstart[q] = ~0u;
             Sh.cbin[q] = 0;
@@ -656,106 +771,26 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                 }
                 __syncthreads();
                 for (int t0 = c0; t0 < c1; t0 += kT) {
-                    // work items: an edge with a nonzero edge at one of its
-                    // vertices, and 64 third vertices of which one at least
-                    // makes a nonzero edge with it (or any, if the edge itself
-                    // is nonzero); kItemWords items an edge at a time
+                    // the edges with a nonzero edge at one of their vertices
                     const int i = t0 + tid;
-                    int a_i = 0, v_i = 0;
-                    bool look = false, own_i = false;
+                    u32 ab = 0;
+                    bool look = false;
                     if (i < c1) {
-                        const u32 ab = (u32)list[i];
-                        a_i = (int)(ab >> 16);
-                        v_i = (int)(ab & 0xffff);
-                        look = ((L.vnz[a_i >> 5] >> (a_i & 31)) & 1u) || ((L.vnz[v_i >> 5] >> (v_i & 31)) & 1u);
-                        if (look) own_i = (mask[a_i * MW + (v_i >> 6)] >> (v_i & 63)) & 1ull;
+                        ab = (u32)list[i];
+                        const int a = (int)(ab >> 16), v = (int)(ab & 0xffff);
+                        look = ((L.vnz[a >> 5] >> (a & 31)) & 1u) || ((L.vnz[v >> 5] >> (v & 31)) & 1u);
                     }
-                    for (int w0 = 0; w0 < MW; w0 += kItemWords) {
-                        for (int mw = w0; mw < min(MW, w0 + kItemWords); ++mw) {
-                            const bool item = look && (own_i || (mask[a_i * MW + mw] | mask[v_i * MW + mw]));
-                            const int at = wave_append(item, &Sh.nwork);
-                            if (item) Sh.work[at] = ((u32)a_i << 21) | ((u32)v_i << 10) | (u32)mw;
-                        }
-                        __syncthreads();
-                        const int nw = Sh.nwork;
-                        // kItems at a time, so that their loads are in flight
-                        // together; an item's vertices and bit words are
-                        // wave-uniform and stay in scalar registers
-                        for (int q = wave * kItems; q < nw; q += kWaves * kItems) {
-                            u32 it[kItems];
-                            float len[kItems], x[kItems], y[kItems];
-                            u64 want[kItems], ma[kItems], mv[kItems];
-#pragma unroll
-                            for (int u = 0; u < kItems; ++u) {
-                                it[u] = __builtin_amdgcn_readfirstlane(Sh.work[min(q + u, nw - 1)]);
-                                const int a = (int)(it[u] >> 21), v = (int)((it[u] >> 10) & 2047u);
-                                const int mw = (int)(it[u] & 1023u);
-                                ma[u] = first_u64(mask[a * MW + mw]);
-                                mv[u] = first_u64(mask[v * MW + mw]);
-                                const u64 mo = first_u64(mask[a * MW + (v >> 6)]);
-                                const bool own = (mo >> (v & 63)) & 1ull;
-                                const int rest = n - mw * 64;
-                                const u64 tail = rest >= 64 ? ~0ull : (1ull << rest) - 1;
-                                want[u] = q + u < nw ? (own ? tail : (ma[u] | mv[u])) : 0ull;
-                                const float *Da = D + ((int64_t)a * n + mw * 64);
-                                const float *Dv = D + ((int64_t)v * n + mw * 64);
-                                len[u] = D[(int64_t)a * n + v];
-                                const bool ok = __builtin_amdgcn_inverse_ballot_w64(want[u]);
-                                x[u] = ok ? Da[lane] : INFINITY;
-                                y[u] = ok ? Dv[lane] : INFINITY;
-                            }
-#pragma unroll
-                            for (int u = 0; u < kItems; ++u) {
-                                const int a = (int)(it[u] >> 21), v = (int)((it[u] >> 10) & 2047u);
-                                const int c0w = (int)(it[u] & 1023u) * 64, c = c0w + lane;
-                                const float far = fmaxf(x[u], y[u]);
-                                u64 in = __ballot(far < len[u]);
-                                const u64 tie = __ballot(far == len[u]);
-                                if (tie) // equal lengths: the larger index is older
-                                    in |= __ballot(far == len[u] && older(x[u], a, c, len[u], pair_index(a, v)) &&
-                                                   older(y[u], v, c, len[u], pair_index(a, v)));
-                                if (!in) continue;
-                                const bool own = (first_u64(mask[a * MW + (v >> 6)]) >> (v & 63)) & 1ull;
-                                const u32 p0 = own ? ids[(int64_t)a * n + v] : 0u;
-                                const u32 *Ia = ids + ((int64_t)a * n + c0w), *Iv = ids + ((int64_t)v * n + c0w);
-                                const u32 p1 = __builtin_amdgcn_inverse_ballot_w64(in & ma[u]) ? Ia[lane] : 0u;
-                                const u32 p2 = __builtin_amdgcn_inverse_ballot_w64(in & mv[u]) ? Iv[lane] : 0u;
-                                // two equal rows and a zero one cancel
-                                bool nzero = __builtin_amdgcn_inverse_ballot_w64(in) &&
-                                             !((p0 == p1 && p2 == 0) || (p0 == p2 && p1 == 0) ||
-                                               (p1 == p2 && p0 == 0));
-                                if (!__any(nzero)) continue;
-                                u32 any = 0;
-                                if (nzero)
-                                    for (int w = 0; w < W; ++w)
-                                        any |= row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
-                                const u64 key = nzero ? ((u64)__float_as_uint(len[u]) << 32) |
-                                                            (u64)(0xffffffffu - triangle_index(a, v, c))
-                                                      : 0;
-                                nzero = nzero && any != 0 && key > lo && key <= hi;
-                                // one triangle of each sum is enough: the oldest, with the largest c
-                                u64 todo = __ballot(nzero);
-                                while (todo) {
-                                    const int l = 63 - __clzll((long long)todo);
-                                    const u32 q1 = __builtin_amdgcn_readlane(p1, l);
-                                    const u32 q2 = __builtin_amdgcn_readlane(p2, l);
-                                    todo &= ~__ballot(nzero && ((p1 == q1 && p2 == q2) || (p1 == q2 && p2 == q1)));
-                                    if (lane == l) {
-                                        const int s = atomicAdd(&Sh.ncand, 1);
-                                        if (s < ccap) {
-                                            L.keys[s] = key;
-                                            for (int w = 0; w < W; ++w)
-                                                L.vec[s * W + w] =
-                                                    row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
-                                        }
-                                    }
-                                }
-                            }
-                        }
-                        __syncthreads();
-                        if (tid == 0) Sh.nwork = 0;
-                        __syncthreads();
-                    }
+                    const int at = wave_append(look, &Sh.nwork);
+                    if (look) Sh.work[at] = ab;
+                    __syncthreads();
+                    const int nw = Sh.nwork;
+                    const TestArgs TA{D, ids, n, MW, nw, ccap, lo, hi};
+                    if (MW == 1) test_edges<4, 1>(TA, mask, P, Sh, L, wave, lane);
+                    else if (MW == 2) test_edges<2, 2>(TA, mask, P, Sh, L, wave, lane);
+                    else test_edges<1, 4>(TA, mask, P, Sh, L, wave, lane);
+                    __syncthreads();
+                    if (tid == 0) Sh.nwork = 0;
+                    __syncthreads();
                 }
                 const int nc = __builtin_amdgcn_readfirstlane(Sh.ncand);
                 if (nc == 0) {
