@@ -80,8 +80,8 @@ typedef struct {
     int64_t apparent_pivot; /* candidates sigma in a zero apparent pair (rho, sigma), d >= 2 */
     int64_t columns;        /* columns left for the reduction */
     /* the work of the reduction: it depends on the method that ran (see
-       rips_set_working_column; the sweep has no emergent columns, counts as
-       reduced every class that a triangle closes, and adds row vectors) */
+       rips_set_working_column; the sweep counts as reduced every class whose
+       pair is not emergent, and adds row vectors, not columns) */
     int64_t emergent;       /* columns resolved by the emergent shortcut */
     int64_t reduced;        /* columns that needed at least one column addition */
     int64_t additions;      /* column additions in total */
@@ -303,8 +303,11 @@ rips_status rips_backward_device(const float *d_data, int64_t n, int32_t dim, in
  * (Algorithm 2 on the coboundary matrix, section "Persistent cohomology",
  * with the shortcut of section "Emergent persistence pairs"). 1: the
  * columns one after another in one workgroup.
- * Results are bit-identical either way. Returns RIPS_E_INVALID_ARG for a
- * negative count; rips_get_reduce_workgroups reads the setting back.
+ * Results are bit-identical either way. A call, with any count, asks for the
+ * column reduction in dimensions that the sweep would take (the counters of
+ * rips_dim_stats are then those of the columns, the same for every count);
+ * rips_set_working_column(RIPS_WORKING_COLUMN_AUTO) returns to the choice of
+ * the method. Returns RIPS_E_INVALID_ARG for a negative count; rips_get_reduce_workgroups reads the setting back.
  */
 rips_status rips_set_reduce_workgroups(int32_t workgroups);
 rips_status rips_get_reduce_workgroups(int32_t *workgroups);
@@ -366,10 +369,12 @@ rips_status rips_get_reduced_storage(int32_t *mode);
 
 /*
  * The method of dimension 1 (per device, the current one; single-cloud and
- * batched paths). AUTO takes the sweep where it applies (Z/2, the batched
- * path): one pass over the edges in order of length that carries on every
+ * batched paths). AUTO takes the sweep where it applies (Z/2, every shortcut
+ * and the default storage, no cocycles; in the single-cloud path dimension 2
+ * as well): one pass over the edges in order of length that carries on every
  * edge the vector of the open classes, closed by the first triangle whose
- * three vectors do not cancel; no coboundary column is reduced. Otherwise the
+ * three vectors do not cancel (triangles and tetrahedra in dimension 2); no
+ * coboundary column is reduced. Otherwise the
  * columns are reduced, with one of two working columns. A column's rows are
  * triangles, and over Z/2 with every shortcut on it can be held direct-mapped: one bit per
  * (longest edge, third vertex), the edges <= t in order of length, so that

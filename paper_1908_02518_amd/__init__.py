@@ -551,7 +551,9 @@ def barcode_batched(x, offsets, n_max: int, *, max_dim: int = 1,
 
 def set_reduce_workgroups(workgroups: int = 0):
     """Workgroups of the single-cloud reduction: 0 = one per compute unit,
-    1 = one workgroup, columns one after another (same bars either way)."""
+    1 = one workgroup, columns one after another (same bars either way). A
+    call asks for the column reduction where the sweep would run, until
+    set_working_column() returns to the choice of the method."""
     _check(_lib.rips_set_reduce_workgroups(int(workgroups)))
 
 
@@ -596,10 +598,11 @@ WORKING_COLUMN_GENERAL = 1
 
 
 def set_working_column(mode: int = WORKING_COLUMN_AUTO):
-    """Working column of the dimension-1 reduction: WORKING_COLUMN_AUTO uses
-    the direct-mapped one (one bit per longest edge and third vertex) where
-    it applies (Z/2, every shortcut on) and fits; WORKING_COLUMN_GENERAL
-    always the general one. The bars are the same either way."""
+    """Method of the low dimensions: WORKING_COLUMN_AUTO takes the sweep where
+    it applies (Z/2, every shortcut on), else reduces columns, direct-mapped
+    (one bit per longest edge and third vertex) where that fits;
+    WORKING_COLUMN_GENERAL always reduces columns with the general working
+    column. The bars are the same either way."""
     _check(_lib.rips_set_working_column(int(mode)))
 
 

@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librips.so")
 SOURCES = ["rips_kernels.hip", "rips_batched.hip", "rips_homology.hip", "rips_explicit.hip", "rips_sweep.hip",
-           "rips_api.hip"]
+           "rips_sweep_dim.hip", "rips_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -606,7 +606,9 @@ constexpr size_t kFilterLdsBinomMax = 16384;       // largest table staged in LD
 template <int G, int K, class Dist>
 __global__ void __launch_bounds__(256) k_filter(Ctx<Dist> c, SimplexList in, int64_t count,
                                                 const u32 *mst_bits, PivotHash prev, Scalars *s,
-                                                Columns out, PairHash app, int flags) {
+                                                Columns out, PairHash app, int flags, int *zj) {
+    // zj (or null): per candidate the vertex that its zero apparent cofacet adds, -1 for
+    // a survivor, -2 for neither
     // flags: kShortApparent (zero apparent pairs are no columns), kShortClearing,
     // kFilterLdsBinom (the binomial rows 0..K+2 staged in LDS, dynamic shared
     // memory; the launcher sets it for small tables only)
@@ -653,11 +655,14 @@ __global__ void __launch_bounds__(256) k_filter(Ctx<Dist> c, SimplexList in, int
         const int j = scan_max_k<G, K>(c, v, dm, -1, live);
         int tv[K + 2];
         int pos = 0;
+        bool done = false; // in a zero apparent pair with a cofacet
         insert_k<K>(v, j, tv, pos);
         if (apparent && live && j >= 0 && zero_pivot_facet_k<K + 1>(c, tv, dm) == pos) {
             // (sigma, sigma u {j}) is a zero apparent pair
             n_acol += leader;
             live = false;
+            if (leader && zj) zj[e] = j;
+            done = true;
             if (leader && app.keys) {
                 // capacity is twice the candidates: the insert cannot fail
                 u64 packed = kNoVerts;
@@ -706,6 +711,7 @@ __global__ void __launch_bounds__(256) k_filter(Ctx<Dist> c, SimplexList in, int
         const bool ttest = tj && mt >= 0;
         const int jt = scan_max_k<G, K>(c, rt, dm, pick_vertex(tv, mt), ttest);
         const uint8_t tapp = (ttest && jt < 0) ? 1 : 0;
+        if (zj && leader && e < count && !done) zj[e] = live ? -1 : -2;
         // survivors: one atomic per wave
         const u64 keep = __ballot(live && leader);
         if (keep) {
@@ -1099,7 +1105,7 @@ __global__ void k_emit(BarBuf in, Scalars *s, int reverse, BarBuf out) {
 // ---------------------------------------------------------------------------
 template <int G, int K>
 static void launch_filter_gk(const Ctx<DistFull> &c, SimplexList in, int64_t count, PairHash app,
-                             const u32 *bits, PivotHash prev, Scalars *s, Columns out, int flags,
+                             const u32 *bits, PivotHash prev, Scalars *s, Columns out, int flags, int *zj,
                              hipStream_t st) {
     const int gpb = 256 / G;
     int64_t blocks = (count + gpb - 1) / gpb;
@@ -1112,31 +1118,31 @@ static void launch_filter_gk(const Ctx<DistFull> &c, SimplexList in, int64_t cou
     const size_t lds = (size_t)(K + 3) * c.B.stride * 8;
     const bool stage = lds <= kFilterLdsBinomMax;
     hipLaunchKernelGGL((k_filter<G, K, DistFull>), dim3((unsigned)blocks), dim3(256), stage ? lds : 0, st, c,
-                       in, count, bits, prev, s, out, app, flags | (stage ? kFilterLdsBinom : 0));
+                       in, count, bits, prev, s, out, app, flags | (stage ? kFilterLdsBinom : 0), zj);
 }
 
 template <int G>
 static void launch_filter_g(const Ctx<DistFull> &c, int k, SimplexList in, int64_t count, PairHash app,
-                            const u32 *bits, PivotHash prev, Scalars *s, Columns out, int flags,
+                            const u32 *bits, PivotHash prev, Scalars *s, Columns out, int flags, int *zj,
                             hipStream_t st) {
     switch (k) {
-    case 1: launch_filter_gk<G, 1>(c, in, count, app, bits, prev, s, out, flags, st); break;
-    case 2: launch_filter_gk<G, 2>(c, in, count, app, bits, prev, s, out, flags, st); break;
-    default: launch_filter_gk<G, 3>(c, in, count, app, bits, prev, s, out, flags, st); break;
+    case 1: launch_filter_gk<G, 1>(c, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 2: launch_filter_gk<G, 2>(c, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    default: launch_filter_gk<G, 3>(c, in, count, app, bits, prev, s, out, flags, zj, st); break;
     }
 }
 
 void launch_filter(int G, const Ctx<DistFull> &c, int k, SimplexList in, int64_t count,
-                   const u32 *bits, PivotHash prev, Scalars *s, Columns out, PairHash app, int flags,
+                   const u32 *bits, PivotHash prev, Scalars *s, Columns out, PairHash app, int flags, int *zj,
                    hipStream_t st) {
     switch (G) {
-    case 1: launch_filter_g<1>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    case 2: launch_filter_g<2>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    case 4: launch_filter_g<4>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    case 8: launch_filter_g<8>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    case 16: launch_filter_g<16>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    case 32: launch_filter_g<32>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
-    default: launch_filter_g<64>(c, k, in, count, app, bits, prev, s, out, flags, st); break;
+    case 1: launch_filter_g<1>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 2: launch_filter_g<2>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 4: launch_filter_g<4>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 8: launch_filter_g<8>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 16: launch_filter_g<16>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    case 32: launch_filter_g<32>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
+    default: launch_filter_g<64>(c, k, in, count, app, bits, prev, s, out, flags, zj, st); break;
     }
 }
 
