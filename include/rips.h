@@ -370,12 +370,11 @@ rips_status rips_get_reduced_storage(int32_t *mode);
 /*
  * The method of dimension 1 (per device, the current one; single-cloud and
  * batched paths). AUTO takes the sweep where it applies (Z/2, every shortcut
- * and the default storage, no cocycles; in the single-cloud path dimension 2
- * as well): one pass over the edges in order of length that carries on every
- * edge the vector of the open classes, closed by the first triangle whose
- * three vectors do not cancel (triangles and tetrahedra in dimension 2); no
- * coboundary column is reduced. Otherwise the
- * columns are reduced, with one of two working columns. A column's rows are
+ * and the default storage, no cocycles, a cloud that is small or of a middling
+ * number of edges a point): one pass over the edges in order of length that
+ * carries on every edge the vector of the open classes, closed by the first
+ * triangle whose three vectors do not cancel; no coboundary column is reduced.
+ * Otherwise the columns are reduced, with one of two working columns. A column's rows are
  * triangles, and over Z/2 with every shortcut on it can be held direct-mapped: one bit per
  * (longest edge, third vertex), the edges <= t in order of length, so that
  * an addition is one XOR per entry and the oldest entry is the highest bit

@@ -642,6 +642,9 @@ struct Prepared {
     Ctx<DistFull> ctx;
 };
 
+// neighbour lists pay off below 30 % of the pairs
+bool sparse_complex(int n, int64_t edges) { return n > 64 && edges * 10 < (int64_t)n * (n - 1) / 2 * 3; }
+
 // distances, threshold, edges (and neighbour lists): everything up to H0
 rips_status prepare(DevCtx &C, const float *d_in, int n, int m, int jmax, float t, uint32_t p,
                     hipStream_t st, Prepared &P) {
@@ -703,7 +706,7 @@ rips_status prepare(DevCtx &C, const float *d_in, int n, int m, int jmax, float 
     if (P.nedges > C.hint_edges) C.hint_edges = P.nedges;
     P.maxdeg = C.host_scal->maxdeg;
     // neighbour lists pay off once the complex is sparse
-    P.sparse = n > 64 && P.nedges * 10 < all_edges * 3;
+    P.sparse = sparse_complex(n, P.nedges);
     P.off = P.nbr = nullptr;
     if (P.sparse) {
         HIP_TRY(C.ensure(B_OFF, (size_t)(n + 1) * 4, &q));
@@ -844,6 +847,135 @@ rips_status reduce_explicit(DevCtx &C, const Prepared &P, int k, uint32_t p, con
     o.stats[k].essential = h.essential;
     o.stats[k].entries_added = h.added;
     o.stats[k].entries_stored = nnz + h.stored;
+    return RIPS_OK;
+}
+
+// The words a sweep launch reports.
+struct SweepScal {
+    unsigned long long queue, ucount;
+    int64_t total;
+    int status;
+};
+
+// The per-workgroup buffers of `grid` sweep workgroups for clouds of up to
+// n_max points.
+rips_status sweep_buffers(DevCtx &C, int n_max, int64_t grid, SweepArgs &A, SweepScal **scal) {
+    void *q;
+    const int64_t npairs = (int64_t)n_max * (n_max - 1) / 2;
+    A.nmax = n_max;
+    A.d_stride = (int64_t)n_max * n_max;
+    A.e_stride = (npairs + 16) / 8 * 8;
+    A.sv_cap = sweep_sv_cap(n_max);
+    A.pool_stride = sweep_pool_words(n_max);
+    A.mask_stride = (int64_t)n_max * sweep_mask_words(n_max);
+#define ENS(id, bytes, field, T)                                                                   \
+    do {                                                                                           \
+        HIP_TRY(C.ensure(id, (size_t)(bytes), &q));                                                \
+        field = as<T>(q);                                                                          \
+    } while (0)
+    ENS(B_SW_D, grid * A.d_stride * 4, A.D, float);
+    ENS(B_SW_IDS, grid * A.d_stride * 4, A.ids, u32);
+    ENS(B_SW_ZC, grid * A.e_stride * 2, A.zc, uint16_t);
+    ENS(B_SW_LIST, grid * A.e_stride * 8, A.list, u64);
+    ENS(B_SW_AUX, grid * A.e_stride * 4, A.aux, u32);
+    ENS(B_SW_SV, grid * A.sv_cap * 8, A.sv, u64);
+    ENS(B_SW_CKEY, grid * A.sv_cap * 8, A.ckey, u64);
+    ENS(B_SW_KKEY, grid * A.sv_cap * 8, A.kkey, u64);
+    ENS(B_SW_POOL, grid * A.pool_stride * 4, A.pool, u32);
+    ENS(B_SW_MASK, grid * A.mask_stride * 8, A.mask, u64);
+    ENS(B_SW_SCAL, sizeof(SweepScal), *scal, SweepScal);
+#undef ENS
+    A.queue = &(*scal)->queue;
+    A.ucount = &(*scal)->ucount;
+    A.status = &(*scal)->status;
+    HIP_TRY(sweep_prepare(n_max, A.sv_cap));
+    return RIPS_OK;
+}
+
+// The default method may run: no setting asks for a reduction of columns.
+bool sweep_allowed(const DevCtx &C, uint32_t p) {
+    return p == 2 && !C.arena && C.cocycle_dim < 0 && C.working_column == RIPS_WORKING_COLUMN_AUTO &&
+           !C.by_columns && C.shortcuts == (kShortApparent | kShortEmergent | kShortClearing) &&
+           C.rstore == kRStoreAuto;
+}
+
+// Clouds that one workgroup sweeps whole, distances to bars in one launch. The
+// staged path's launches, waits and scalar reads cost 0.3 to 0.5 ms whatever
+// the size, which the one workgroup's passes over n^2 pairs reach at about 256
+// points (threshold 0.3 on the sphere: 200 points 0.23 and 0.35 ms, 256 points
+// 0.33 and 0.37, 320 points 0.49 and 0.40). Without a threshold the complex is
+// dense and the reduction itself decides, in favour of the sweep up to the
+// largest cloud it takes (sphere: 400 points 1.9 and 7.2 ms, 1000 points 10
+// and 36; noisy circles: 400 points 2.3 and 13.6, 1000 points 17 and 217).
+constexpr int kSweepSingleN = 256;
+
+bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint32_t p) {
+    return n >= 2 && max_dim <= 1 && n <= (std::isinf(threshold) ? kSweepMaxN : kSweepSingleN) && sweep_allowed(C, p);
+}
+
+// Edges per point between which a larger cloud's dimension 1 is swept in
+// chunks (rips_sweep_dim.hip). Below, the columns are few and short and the
+// chunks cost more than their work (2500 points of the Clifford torus, 25
+// edges a point: 4.0 ms swept, 2.8 reduced; 35: 4.4 and 9.0; so3-1200 at 18:
+// 2.7 and 1.4, at 25: 3.0 and 5.3). Above, the sweep's one workgroup looks at
+// too many triangles (sphere-1000: 200 edges a point 7.7 ms swept, 9.1
+// reduced; 300: 15 and 13; 1000: 290 and 36).
+constexpr int64_t kSweepDegMin = 32, kSweepDegMax = 200;
+
+// One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
+// report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
+// every dimension fits. *full as in batched_sweep.
+rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, BarBuf bars, int64_t cap,
+                         bool columns, hipStream_t st, RunOut &o, bool *full) {
+    SweepArgs A;
+    memset(&A, 0, sizeof(A));
+    SweepScal *scal;
+    rips_status rs = sweep_buffers(C, n, 1, A, &scal);
+    if (rs) return rs;
+    A.X = d_in;
+    A.B = 1;
+    A.m = m;
+    A.max_dim = max_dim;
+    A.threshold = t;
+    A.ub = bars.birth;
+    A.ud = bars.death;
+    A.ubs = bars.bs;
+    A.uds = bars.ds;
+    A.ucap = cap;
+    if (columns) {
+        void *q;
+        HIP_TRY(C.ensure(B_COL_IDX + 1, (size_t)A.sv_cap * 8, &q));
+        A.col_idx = as<int64_t>(q);
+        HIP_TRY(C.ensure(B_COL_DIAM + 1, (size_t)A.sv_cap * 4, &q));
+        A.col_diam = as<float>(q);
+    }
+    static_assert(sizeof(SweepSingle) <= sizeof(Scalars), "reported in the pinned scalar block");
+    A.res = (SweepSingle *)C.host_scal;
+    {
+        PROF(P_REDUCE1);
+        launch_sweep(A, 1, st);
+    }
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
+    prof_resolve();
+    const SweepSingle h = *(const SweepSingle *)C.host_scal;
+    *full = (h.status & kSweepFull) != 0;
+    if (*full) return RIPS_OK;
+    memset(&o, 0, sizeof(o));
+    o.n = n;
+    o.max_dim = max_dim;
+    o.t_eff = h.t;
+    o.r_enc = h.renc;
+    const int64_t edges = h.stats[1].candidates;
+    o.sparse = sparse_complex(n, edges);
+    o.simplex_count[0] = n;
+    o.simplex_count[1] = edges;
+    o.ncols[0] = n;
+    for (int d = 0; d <= max_dim; ++d) {
+        o.count[d] = h.count[d];
+        o.stats[d] = h.stats[d];
+    }
+    if (max_dim >= 1) o.ncols[1] = h.stats[1].columns;
     return RIPS_OK;
 }
 
@@ -1031,14 +1163,9 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
     for (int k = 1; k <= max_dim; ++k) {
         launch_reset_dim(P.scal, st);
         // dimension 1 over Z/2 takes the sweep, unless a setting asks for the
-        // reduction of columns (and for cocycles, which are its V_j); a small
-        // dense cloud's few short columns are reduced faster (sphere-100:
-        // 0.22 ms, and 0.36 ms by this sweep, whose chunks cost more than
-        // their work; sphere-192: 0.64 ms and 0.40 ms)
-        const bool sweep = p == 2 && k == 1 && (P.sparse || n >= 160) && k != swept_full && !C.arena && C.cocycle_dim < 0 &&
-                           C.working_column == RIPS_WORKING_COLUMN_AUTO && !C.by_columns &&
-                           C.shortcuts == (kShortApparent | kShortEmergent | kShortClearing) &&
-                           C.rstore == kRStoreAuto && n <= kDimMaxVert;
+        // reduction of columns (and for cocycles, which are its V_j)
+        const bool sweep = k == 1 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C, p) &&
+                           P.nedges >= kSweepDegMin * n / 2 && P.nedges <= kSweepDegMax * n / 2;
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {
@@ -1693,48 +1820,6 @@ BarBuf internal_bars(DevCtx &C, int d) {
 // set the device "nbars" scalar before an emit
 __global__ void k_set_nbars(Scalars *s, int64_t v) { s->nbars = v; }
 
-// The words a sweep launch reports.
-struct SweepScal {
-    unsigned long long queue, ucount;
-    int64_t total;
-    int status;
-};
-
-// The per-workgroup buffers of `grid` sweep workgroups for clouds of up to
-// n_max points.
-rips_status sweep_buffers(DevCtx &C, int n_max, int64_t grid, SweepArgs &A, SweepScal **scal) {
-    void *q;
-    const int64_t npairs = (int64_t)n_max * (n_max - 1) / 2;
-    A.nmax = n_max;
-    A.d_stride = (int64_t)n_max * n_max;
-    A.e_stride = (npairs + 16) / 8 * 8;
-    A.sv_cap = sweep_sv_cap(n_max);
-    A.pool_stride = sweep_pool_words(n_max);
-    A.mask_stride = (int64_t)n_max * sweep_mask_words(n_max);
-#define ENS(id, bytes, field, T)                                                                   \
-    do {                                                                                           \
-        HIP_TRY(C.ensure(id, (size_t)(bytes), &q));                                                \
-        field = as<T>(q);                                                                          \
-    } while (0)
-    ENS(B_SW_D, grid * A.d_stride * 4, A.D, float);
-    ENS(B_SW_IDS, grid * A.d_stride * 4, A.ids, u32);
-    ENS(B_SW_ZC, grid * A.e_stride * 2, A.zc, uint16_t);
-    ENS(B_SW_LIST, grid * A.e_stride * 8, A.list, u64);
-    ENS(B_SW_AUX, grid * A.e_stride * 4, A.aux, u32);
-    ENS(B_SW_SV, grid * A.sv_cap * 8, A.sv, u64);
-    ENS(B_SW_CKEY, grid * A.sv_cap * 8, A.ckey, u64);
-    ENS(B_SW_KKEY, grid * A.sv_cap * 8, A.kkey, u64);
-    ENS(B_SW_POOL, grid * A.pool_stride * 4, A.pool, u32);
-    ENS(B_SW_MASK, grid * A.mask_stride * 8, A.mask, u64);
-    ENS(B_SW_SCAL, sizeof(SweepScal), *scal, SweepScal);
-#undef ENS
-    A.queue = &(*scal)->queue;
-    A.ucount = &(*scal)->ucount;
-    A.status = &(*scal)->status;
-    HIP_TRY(sweep_prepare(n_max, A.sv_cap));
-    return RIPS_OK;
-}
-
 // The batch by the sweep, one workgroup per cloud from a queue by decreasing
 // size. *full: some cloud exceeds the sweep's tables; nothing was written to
 // the bar arrays and the caller runs the column reduction.
@@ -2085,8 +2170,18 @@ const char *rips_last_error(void) { return g_err.c_str(); }
 rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t dim, int32_t max_dim,
                            float threshold, uint32_t p, rips_device_out *out, hipStream_t st) {
     RunOut o;
-    rips_status rs = run_single(*C, d_data, (int)n, dim, max_dim, threshold, p, st, o);
-    if (rs) return rs;
+    rips_status rs;
+    bool done = false; // the bars are in the caller's buffers
+    if (sweeps_whole(*C, n, max_dim, threshold, p)) {
+        bool full = false;
+        const bool room = out->birth && out->death && out->birth_simplex && out->death_simplex && out->cap > 0;
+        rs = single_sweep(*C, d_data, (int)n, dim, max_dim, threshold,
+                          BarBuf{out->birth, out->death, out->birth_simplex, out->death_simplex}, room ? out->cap : -1,
+                          false, st, o, &full);
+        if (rs) return rs;
+        done = !full;
+    }
+    if (!done && (rs = run_single(*C, d_data, (int)n, dim, max_dim, threshold, p, st, o))) return rs;
     int64_t need = 0;
     for (int d = 0; d <= max_dim; ++d) need = std::max(need, o.count[d]);
     out->needed_cap = need;
@@ -2100,6 +2195,7 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
     if (need > out->cap) return fail(RIPS_E_CAPACITY, "bar capacity too small");
     if (!out->birth || !out->death || !out->birth_simplex || !out->death_simplex)
         return fail(RIPS_E_INVALID_ARG, "null output buffer");
+    if (done) return RIPS_OK;
     Scalars *scal = as<Scalars>(C->buf[B_SCAL]);
     for (int d = 0; d <= max_dim; ++d) {
         BarBuf dst{out->birth + d * out->cap, out->death + d * out->cap,
@@ -2171,7 +2267,25 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
     float *d_in = as<float>(q);
     HIP_TRY(hipMemcpyAsync(d_in, data, in_elems * 4, hipMemcpyHostToDevice, st));
     RunOut o;
-    rs = run_single(*C, d_in, (int)n, dim, max_dim, threshold, p, st, o);
+    int64_t swept_cap = 0; // > 0: the bars of dimension 1 follow those of dimension 0 after so many places
+    bool full = true;
+    if (sweeps_whole(*C, n, max_dim, threshold, p)) {
+        // internal bars of dimension 0 and 1, one after the other
+        const int64_t cap = sweep_sv_cap((int)n);
+        BarBuf bars;
+        HIP_TRY(C->ensure(B_BAR_BIRTH, (size_t)cap * 8, &q));
+        bars.birth = as<float>(q);
+        HIP_TRY(C->ensure(B_BAR_DEATH, (size_t)cap * 8, &q));
+        bars.death = as<float>(q);
+        HIP_TRY(C->ensure(B_BAR_BS, (size_t)cap * 16, &q));
+        bars.bs = as<int64_t>(q);
+        HIP_TRY(C->ensure(B_BAR_DS, (size_t)cap * 16, &q));
+        bars.ds = as<int64_t>(q);
+        full = false;
+        rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, bars, cap, true, st, o, &full);
+        swept_cap = full ? 0 : cap;
+    }
+    if (!rs && full) rs = run_single(*C, d_in, (int)n, dim, max_dim, threshold, p, st, o);
     if (rs) return rs;
     rips_result *r = (rips_result *)calloc(1, sizeof(rips_result));
     if (!r) return fail(RIPS_E_OOM, "host allocation");
@@ -2193,7 +2307,7 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
         rips_result_free(r);
         return fail(RIPS_E_OOM, "host allocation");
     }
-    Scalars *scal = as<Scalars>(C->buf[B_SCAL]);
+    Scalars *scal = as<Scalars>(C->buf[B_SCAL]); // null and not used if the cloud was swept whole
     for (int d = 0; d < nd; ++d) {
         const int64_t c = o.count[d];
         r->stats[d] = o.stats[d];
@@ -2221,8 +2335,14 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
             char *sg = as<char>(q);
             BarBuf dst{(float *)sg, (float *)(sg + c * 4), (int64_t *)(sg + c * 8),
                        (int64_t *)(sg + c * 16)};
-            hipLaunchKernelGGL(k_set_nbars, dim3(1), dim3(1), 0, st, scal, c);
-            launch_emit(internal_bars(*C, d), scal, d > 0 ? 1 : 0, dst, st);
+            if (swept_cap > 0) {
+                const BarBuf in = internal_bars(*C, 0);
+                const int64_t at = d * swept_cap;
+                dst = BarBuf{in.birth + at, in.death + at, in.bs + at, in.ds + at};
+            } else {
+                hipLaunchKernelGGL(k_set_nbars, dim3(1), dim3(1), 0, st, scal, c);
+                launch_emit(internal_bars(*C, d), scal, d > 0 ? 1 : 0, dst, st);
+            }
             hipError_t e1 = hipMemcpyAsync(b.birth, dst.birth, c * 4, hipMemcpyDeviceToHost, st);
             hipError_t e2 = hipMemcpyAsync(b.death, dst.death, c * 4, hipMemcpyDeviceToHost, st);
             hipError_t e3 = hipMemcpyAsync(b.birth_simplex, dst.bs, c * 8, hipMemcpyDeviceToHost, st);

@@ -325,6 +325,19 @@ __device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const R
 }
 
 // One cloud. Returns through the queue loop; every thread of the workgroup calls it.
+// A cloud that gives no bars: its segments are empty and the status says why.
+__device__ __forceinline__ void sweep_reject(const SweepArgs &A, int b, int D1, int why) {
+    if (A.res) {
+        if (threadIdx.x == 0) A.res->status = why;
+        return;
+    }
+    if ((int)threadIdx.x < D1) {
+        A.seg_start[(int64_t)b * D1 + threadIdx.x] = 0;
+        A.seg_count[(int64_t)b * D1 + threadIdx.x] = 0;
+    }
+    if (threadIdx.x == 0 && why) atomicOr(A.status, why);
+}
+
 template <bool kMaskLds>
 __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem, SweepShared &Sh) {
     const int tid = threadIdx.x, lane = lane_id();
@@ -334,11 +347,8 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     const int D1 = max_dim + 1;
     const int64_t o0 = A.offsets ? A.offsets[b] : 0;
     const int64_t nn = A.offsets ? A.offsets[b + 1] - o0 : A.nmax;
-    if (nn < 1 || nn > A.nmax) { // rejected by the order pass (status bit 16)
-        if (tid < D1) {
-            A.seg_start[(int64_t)b * D1 + tid] = 0;
-            A.seg_count[(int64_t)b * D1 + tid] = 0;
-        }
+    if (nn < 1 || nn > A.nmax) { // the order pass has set status bit 16
+        sweep_reject(A, b, D1, 0);
         return;
     }
     const int n = __builtin_amdgcn_readfirstlane((int)nn);
@@ -396,10 +406,10 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                     }
                     d = __builtin_sqrtf(s);
                 } else {
-                    d = X[(int64_t)max(i, j) * n + min(i, j)] + 0.0f; // -0 becomes +0
+                    d = X[(int64_t)max(i, j) * n + min(i, j)];
                 }
                 if (i != j) {
-                    fin = fin && isfinite(d) && d >= 0.0f;
+                    fin = fin && __float_as_uint(d) <= 0x7f7fffffu; // finite, the sign bit clear
                     mx = fmaxf(mx, d);
                 }
                 D[(int64_t)i * n + j] = d;
@@ -418,11 +428,9 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     for (int q = tid; q < MW * 2; q += kT) L.vnz[q] = 0;
     __syncthreads();
     if (!Sh.fin) {
-        if (tid < D1) {
-            A.seg_start[(int64_t)b * D1 + tid] = 0;
-            A.seg_count[(int64_t)b * D1 + tid] = 0;
-        }
-        if (tid == 0) atomicOr(A.status, 4);
+        // one cloud: the staged path says whether the input or only a
+        // distance is out of range, and handles the latter
+        sweep_reject(A, b, D1, A.res ? kSweepFull : 4);
         __syncthreads();
         return;
     }
@@ -514,11 +522,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     __syncthreads();
     const int ns = Sh.nsurv;
     if (ns > A.sv_cap) { // the caller runs the column reduction instead
-        if (tid < D1) {
-            A.seg_start[(int64_t)b * D1 + tid] = 0;
-            A.seg_count[(int64_t)b * D1 + tid] = 0;
-        }
-        if (tid == 0) atomicOr(A.status, kSweepFull);
+        sweep_reject(A, b, D1, kSweepFull);
         __syncthreads();
         return;
     }
@@ -602,11 +606,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     const int rcap = W > 0 ? (int)min((int64_t)(1 << 30), A.pool_stride / W) : 0;
     if (max_dim >= 1 && S > 0) {
         if (S > kSweepMaxClasses || S + 1 >= rcap) {
-            if (tid < D1) {
-                A.seg_start[(int64_t)b * D1 + tid] = 0;
-                A.seg_count[(int64_t)b * D1 + tid] = 0;
-            }
-            if (tid == 0) atomicOr(A.status, kSweepFull);
+            sweep_reject(A, b, D1, kSweepFull);
             __syncthreads();
             return;
         }
@@ -912,11 +912,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
         }
         __syncthreads();
         if (Sh.fail) {
-            if (tid < D1) {
-                A.seg_start[(int64_t)b * D1 + tid] = 0;
-                A.seg_count[(int64_t)b * D1 + tid] = 0;
-            }
-            if (tid == 0) atomicOr(A.status, kSweepFull);
+            sweep_reject(A, b, D1, kSweepFull);
             __syncthreads();
             return;
         }
@@ -950,32 +946,39 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     __syncthreads();
     const int nb0 = Sh.nb0, nb1 = Sh.act, ess0 = Sh.nb1, ess1 = Sh.ness;
     if (tid == 0) {
-        Sh.base = atomicAdd(A.ucount, (unsigned long long)(nb0 + nb1));
-        rips_dim_stats s0 = {};
+        Sh.base = A.res ? 0ull : atomicAdd(A.ucount, (unsigned long long)(nb0 + nb1));
+        rips_dim_stats s0 = {}, s1 = {};
         s0.candidates = n;
         s0.columns = n;
         s0.bars_nonzero = nb0 - ess0;
         s0.essential = ess0;
-        A.stats[(int64_t)b * D1] = s0;
-        A.t_used[b] = t;
-        if (max_dim >= 1) {
-            rips_dim_stats s1 = {};
-            s1.candidates = (int64_t)Sh.ncand0;
-            s1.cleared = ns - S;
-            s1.apparent_col = (int64_t)Sh.nzap;
-            s1.columns = S;
-            s1.reduced = S - ess1;
-            s1.additions = (int64_t)Sh.adds + (S > 0 ? Sh.nrows - S - 1 : 0);
-            s1.bars_nonzero = nb1 - ess1;
-            s1.essential = ess1;
-            s1.entries_added = s1.additions * W;
-            s1.entries_stored = S > 0 ? (int64_t)(Sh.nrows - 1) * W : 0;
-            A.stats[(int64_t)b * D1 + 1] = s1;
+        s1.candidates = (int64_t)Sh.ncand0;
+        s1.cleared = ns - S;
+        s1.apparent_col = (int64_t)Sh.nzap;
+        s1.columns = S;
+        s1.reduced = S - ess1;
+        s1.additions = (int64_t)Sh.adds + (S > 0 && max_dim >= 1 ? Sh.nrows - S - 1 : 0);
+        s1.bars_nonzero = nb1 - ess1;
+        s1.essential = ess1;
+        s1.entries_added = s1.additions * W;
+        s1.entries_stored = S > 0 && max_dim >= 1 ? (int64_t)(Sh.nrows - 1) * W : 0;
+        if (A.res) {
+            A.res->status = 0;
+            A.res->t = t;
+            A.res->renc = renc;
+            A.res->count[0] = nb0;
+            A.res->count[1] = nb1;
+            A.res->stats[0] = s0;
+            A.res->stats[1] = s1;
+        } else {
+            A.stats[(int64_t)b * D1] = s0;
+            A.t_used[b] = t;
+            if (max_dim >= 1) A.stats[(int64_t)b * D1 + 1] = s1;
         }
     }
     __syncthreads();
     const int64_t base = (int64_t)Sh.base;
-    const bool fits = base + nb0 + nb1 <= A.ucap;
+    const bool fits = A.res ? max(nb0, nb1) <= A.ucap : base + nb0 + nb1 <= A.ucap;
     int at = 0;
     for (int q0 = 0; q0 < n; q0 += kT) {
         const int v = n - 1 - (q0 + tid);
@@ -992,8 +995,13 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
         }
         at += tot;
     }
+    if (A.res && A.col_idx && max_dim >= 1)
+        for (int k = tid; k < S; k += kT) {
+            A.col_idx[S - 1 - k] = (int64_t)(0xffffffffu - (u32)ckey[k]);
+            A.col_diam[S - 1 - k] = __uint_as_float((u32)(ckey[k] >> 32));
+        }
     if (max_dim >= 1)
-        for (int q0 = 0; q0 < S; q0 += kT) {
+        for (int q0 = 0, at1 = 0; q0 < S; q0 += kT) {
             const int k = q0 + tid;
             const u64 ck = k < S ? ckey[k] : 0, kk = k < S ? kkey[k] : 0;
             const bool ess = kk == ~0ull;
@@ -1001,15 +1009,15 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
             int tot;
             const int ex = sweep_scan(has ? 1 : 0, Sh.scan, &tot);
             if (has && fits) {
-                const int64_t w = base + at + ex;
+                const int64_t w = A.res ? A.ucap + at1 + ex : base + nb0 + at1 + ex;
                 A.ub[w] = __uint_as_float((u32)(ck >> 32));
                 A.ud[w] = ess ? INFINITY : __uint_as_float((u32)(kk >> 32));
                 A.ubs[w] = (int64_t)(0xffffffffu - (u32)ck);
                 A.uds[w] = ess ? -1 : (int64_t)(0xffffffffu - (u32)kk);
             }
-            at += tot;
+            at1 += tot;
         }
-    if (tid == 0) {
+    if (tid == 0 && !A.res) {
         A.seg_start[(int64_t)b * D1] = base;
         A.seg_count[(int64_t)b * D1] = nb0;
         if (D1 > 1) {
@@ -1024,6 +1032,10 @@ template <bool kMaskLds>
 __global__ void __launch_bounds__(kT) k_sweep(SweepArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ SweepShared Sh;
+    if (A.res) {
+        sweep_cloud<kMaskLds>(A, 0, smem, Sh);
+        return;
+    }
     for (;;) {
         if (threadIdx.x == 0) Sh.cloud = (int)atomicAdd(A.queue, 1ull);
         __syncthreads();

@@ -19,6 +19,14 @@ constexpr int kSweepMaskBytes = 48 << 10; // nonzero-edge bits kept in LDS up to
 // its bars are not written and the caller takes the column reduction
 constexpr int kSweepFull = 512;
 
+// What the sweep of one cloud reports, in pinned host memory.
+struct SweepSingle {
+    int status; // 4: not finite, kSweepFull, else 0
+    float t, renc;
+    int64_t count[2];
+    rips_dim_stats stats[2];
+};
+
 struct SweepArgs {
     const float *X;         // points (m > 0), or the n x n distances of one cloud (m == 0)
     const int64_t *offsets; // B + 1, or null: one cloud of nmax points
@@ -51,6 +59,11 @@ struct SweepArgs {
     rips_dim_stats *stats;          // B * (max_dim + 1)
     float *t_used;                  // B
     int *status;
+    // one cloud (res not null, one workgroup, no queue): the bars of dimension
+    // d go to [d * ucap, d * ucap + count) of ub .. uds, if every dimension fits
+    SweepSingle *res;
+    int64_t *col_idx; // the columns of dimension 1, youngest first, or null
+    float *col_diam;
 };
 
 // words of one vertex's nonzero-edge bits

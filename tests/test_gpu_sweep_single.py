@@ -1,0 +1,117 @@
+"""GPU parity of the sweep of one cloud with the column reduction, bit for bit:
+the whole cloud by one workgroup (small clouds, and any without a threshold),
+and dimension 1 in chunks (larger ones of 32 to 200 edges a point), on both
+sides of each rule, from points and from a distance matrix; and where a table
+is full or a distance overflows and the other path takes over."""
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from tests.test_gpu_sweep import two_simplices
+
+pytestmark = pytest.mark.gpu
+INF = float("inf")
+
+
+def rips():
+    import paper_1908_02518_amd as r
+    return r
+
+
+def bars(x, **kw):
+    import torch
+    r = rips()
+    out, info = r.barcode_device(x, **kw)
+    torch.cuda.synchronize()
+    return [[t.cpu().numpy() for t in b] for b in out], info
+
+
+def both(x, **kw):
+    """Bars by the default method and by the reduction of columns."""
+    r = rips()
+    r.set_working_column()
+    one, i1 = bars(x, **kw)
+    r.set_reduce_workgroups(0)
+    try:
+        two, i2 = bars(x, **kw)
+    finally:
+        r.set_working_column()
+    for d, (a, b) in enumerate(zip(one, two)):
+        for u, v in zip(a, b):
+            assert np.array_equal(u, v), d
+    for f in ("threshold", "sparse", "simplex_count"):
+        assert i1[f] == i2[f], f
+    for f in ("candidates", "cleared", "apparent_col", "apparent_pivot", "columns", "bars_nonzero", "essential"):
+        assert [s[f] for s in i1["stats"]] == [s[f] for s in i2["stats"]], f
+
+
+def degree_threshold(x, degree):
+    d = np.sqrt(((x[::7, None, :].astype(np.float64) - x[None, :, :]) ** 2).sum(2)).ravel()
+    return float(np.float32(np.partition(d, int(degree / len(x) * d.size))[int(degree / len(x) * d.size)]))
+
+
+@pytest.mark.parametrize("max_dim", [0, 1])
+@pytest.mark.parametrize("matrix", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 3, 31, 33, 64, 65, 129, 255, 256, 257, 300])
+def test_whole_cloud_vs_column_reduction(n, matrix, max_dim):
+    import torch
+    x = workloads.sphere(n, workloads.SEED_BASE + n)
+    if matrix:
+        x = np.sqrt(((x[:, None] - x[None]) ** 2).sum(2, dtype=np.float32))
+        x = np.ascontiguousarray(np.tril(x) + np.triu(np.full_like(x, 7.0)))  # the part above is not read
+    for t in (INF, 0.9, 0.0):
+        print(f"[case] whole cloud n={n} matrix={matrix} t={t} max_dim={max_dim}", flush=True)
+        both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t, is_distance=matrix)
+
+
+@pytest.mark.parametrize("kind", ["ties", "loops", "full", "overflow"])
+def test_whole_cloud_special_inputs(kind):
+    import torch
+    r = rips()
+    r.set_working_column()
+    s = workloads.SEED_BASE
+    x = {"ties": lambda: workloads.integer_lattice(130, 3, s, side=3), "loops": lambda: two_simplices(24),
+         "full": lambda: two_simplices(40),
+         "overflow": lambda: workloads.sphere(40, s) * np.float32(3e38)}[kind]()
+    print(f"[case] whole cloud {kind}", flush=True)
+    if kind == "overflow":  # finite points, some distances are not
+        both(torch.from_numpy(x).cuda(), max_dim=1, threshold=2e38)
+        return
+    ref = oracle.barcode(x, max_dim=1, threshold=INF, p=2)
+    got, info = bars(torch.from_numpy(x).cuda(), max_dim=1)
+    for d in range(2):
+        want = (ref.bars[d].birth, ref.bars[d].death, ref.bars[d].birth_simplex, ref.bars[d].death_simplex)
+        for g, w in zip(got[d], want):
+            assert np.array_equal(g, w)
+    host = r.barcode(x, max_dim=1)  # through host memory
+    for d in range(2):
+        assert np.array_equal(host.bars[d].birth, ref.bars[d].birth)
+        assert np.array_equal(host.bars[d].death_simplex, ref.bars[d].death_simplex)
+
+
+def test_not_finite_is_refused():
+    import torch
+    r = rips()
+    r.set_working_column()
+    for bad in (float("nan"), INF):
+        for n in (1, 2, 40):
+            x = torch.from_numpy(workloads.sphere(n, 5)).cuda()
+            x[n - 1, 1] = bad
+            with pytest.raises(r.RipsError):
+                r.barcode_device(x, max_dim=1)
+
+
+@pytest.mark.parametrize("n,degree", [(260, 31), (260, 33), (700, 64), (700, 199), (700, 201), (3000, 40), (24000, 36)])
+@pytest.mark.parametrize("data", ["torus", "lattice"])
+def test_chunked_sweep_vs_column_reduction(data, n, degree):
+    """24,000 points: places by hashing (more than 2^28 possible edges)."""
+    import torch
+    if n == 24000 and data == "lattice":
+        pytest.skip("one large cloud is enough")
+    s = workloads.SEED_BASE + n
+    x = workloads.clifford_torus(n, 0.02, s) if data == "torus" else workloads.integer_lattice(n, 4, s, side=9)
+    t = degree_threshold(x, degree) if n < 24000 else 0.138
+    print(f"[case] chunked sweep {data} n={n} degree={degree} t={t}", flush=True)
+    both(torch.from_numpy(x).cuda(), max_dim=1, threshold=t)
