@@ -261,6 +261,14 @@ enum BufId {
     B_SD_HKEYS,
     B_SD_HVALS,
     B_SD_TAU,
+    B_SD_BLOCK,
+    B_SD_STATE,
+    B_SD_QBLK,
+    B_SD_BITS,
+    B_SD_PAIRS,
+    B_SD_CIDX,
+    B_SD_CDIAM,
+    B_SD_CJ,
     B_SD_BQ,
     B_SD_KIDX,
     B_SD_KDIAM,
@@ -981,13 +989,15 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
 
 // Dimension k (1 or 2) over Z/2 by the sweep: the bars in column order, the
 // counters and the pivot table of the next dimension's clearing. *full: a
-// table was too small, nothing is valid and the caller reduces the columns.
-rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, SimplexList cand, int64_t ncand, const int *zj,
+// table was too small (or, in dimension 2, edges of equal length met), nothing
+// is valid and the caller reduces the columns.
+rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexList cand, int64_t ncand, const int *zj,
                       const Columns &cols, int64_t S, PivotHash ph, uint32_t phcap, BarBuf bars, hipStream_t st,
                       RunOut &o, bool *full) {
     void *q;
     DimArgs A;
     memset(&A, 0, sizeof(A));
+    const int n = P.ctx.n;
     A.c = P.ctx;
     A.in = cand;
     A.N = ncand;
@@ -997,6 +1007,12 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, SimplexList cand, int
     A.nbins = 2048; // about eight simplices a bin
     while (A.nbins < kDimBins && (int64_t)A.nbins * 8 < ncand) A.nbins <<= 1;
     A.scale = P.ctx.t > 0.0f ? (float)A.nbins / P.ctx.t : 0.0f;
+    A.chunk_n = k == 1 ? 0.0f : std::max(4096.0f, (float)ncand / 64.0f);
+    *full = false;
+    if (ncand >= (1ll << 30)) {
+        *full = true;
+        return RIPS_OK;
+    }
 #define ENS(id, bytes, field, T)                                                                   \
     do {                                                                                           \
         HIP_TRY(C.ensure(id, (size_t)(bytes), &q));                                                \
@@ -1011,12 +1027,11 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, SimplexList cand, int
     A.ch_s = A.ch_t + chunks;
     ENS(B_SD_QDIAM, ncand * 4, A.qdiam, float);
     ENS(B_SD_QVERTS, ncand * 8, A.qverts, u64);
-    ENS(B_SD_QZJ, ncand * 4, A.qzj, int);
     ENS(B_SD_QDEP, ncand * 4 * (k + 1), A.qdep, u32);
     ENS(B_SD_IDS, ncand * 4, A.ids, u32);
     ENS(B_SD_NZL, ncand * 4, A.nzl, u32);
     // places by index: a table over all indices up to 1 GiB, else a hash
-    const long double every = choose_ld(P.ctx.n, k + 1);
+    const long double every = choose_ld(n, k + 1);
     if (every <= (long double)(1u << 28)) {
         ENS(B_SD_DIRECT, (size_t)every * 4 + 16, A.direct, u32);
     } else {
@@ -1025,57 +1040,106 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, SimplexList cand, int
         ENS(B_SD_HVALS, (size_t)cap * 4, A.ph.vals, int32_t);
         A.ph.mask = cap - 1;
     }
-    ENS(B_SD_BQ, S * 4, A.bq, u32);
-    ENS(B_SD_KIDX, S * 8, A.kidx, int64_t);
-    ENS(B_SD_KDIAM, S * 4, A.kdiam, float);
-    A.W = (int)std::min<int64_t>(kDimWords, (S + 31) / 32);
+    ENS(B_SD_OUT, sizeof(DimOut), A.out, DimOut);
+    static_assert(sizeof(DimOut) <= sizeof(Scalars), "read back through the pinned scalar block");
+    int64_t loc_emergent = 0, loc_reduced = 0;
+    launch_fill_i64(ph.keys, phcap, kEmpty, st);
+    if (k == 1) {
+        ENS(B_SD_QZJ, ncand * 4, A.qzj, int);
+        {
+            PROF(P_SORT1);
+            launch_dim_partition(A, st);
+        }
+        // the owned cofacets are counted: room for them
+        u32 *total_h = (u32 *)C.host_scal;
+        HIP_TRY(hipMemcpyAsync(total_h, A.bin_t + A.nbins, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        prof_resolve();
+        const int64_t total = (int64_t)*total_h;
+        if (total > (1ll << 28)) { // above 3 GiB of places
+            *full = true;
+            return RIPS_OK;
+        }
+        ENS(B_SD_TAU, (size_t)total * 12, A.tau, u32);
+    } else {
+        A.E = P.E;
+        A.nE = P.nedges;
+        A.fw = 2 * ((n + 63) / 64);
+        A.all = cols;
+        A.nall = (int)S;
+        A.strict = max_dim > 2;
+        A.paircap = 1 << 21;
+        ENS(B_SD_BLOCK, A.nE * 12, A.bstart, u32);
+        A.bcnt = A.bstart + A.nE;
+        A.tkey = A.bcnt + A.nE;
+        ENS(B_SD_STATE, dim_state_bytes(), A.state, void);
+        ENS(B_SD_QBLK, ncand * 32 + 64, A.qblk, u32);
+        A.qpar = A.qblk + ncand;
+        A.qkill = A.qpar + ncand;
+        A.rhead = A.qkill + ncand;
+        A.rnext = A.rhead + ncand;
+        A.need = A.rnext + 3 * ncand; // N / 32 + 1 words
+        ENS(B_SD_BITS, (size_t)n * A.fw * 8, A.fl, u32);
+        A.tied = A.fl + (size_t)n * A.fw;
+        ENS(B_SD_PAIRS, (size_t)A.paircap * 8, A.pairs, u64);
+        ENS(B_SD_CIDX, S * 8, A.cols.idx, int64_t);
+        ENS(B_SD_CDIAM, S * 4, A.cols.diam, float);
+        ENS(B_SD_CJ, S * 4, A.cols.j, int);
+        {
+            PROF(P_COB1 + k - 1);
+            launch_lune_partition(A, ph, st);
+        }
+        HIP_TRY(hipMemcpyAsync(C.host_scal, A.out, sizeof(DimOut), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        prof_resolve();
+        const DimOut h = *(const DimOut *)C.host_scal;
+        if (h.full > 1) return fail(RIPS_E_HIP, "sweep: internal consistency check failed");
+        if (h.full) {
+            *full = true;
+            return RIPS_OK;
+        }
+        A.S = h.nclasses;
+        loc_emergent = h.loc_emergent;
+        loc_reduced = h.loc_reduced;
+    }
+    ENS(B_SD_BQ, A.S * 4 + 16, A.bq, u32);
+    ENS(B_SD_KIDX, A.S * 8 + 16, A.kidx, int64_t);
+    ENS(B_SD_KDIAM, A.S * 4 + 16, A.kdiam, float);
+    A.W = std::max(1, std::min(kDimWords, (A.S + 31) / 32));
     ENS(B_SD_POOL, (size_t)kDimRows * A.W * 4, A.pool, u32);
     ENS(B_SD_RSUM, (size_t)kDimRows * 8, A.rsum, u64);
     ENS(B_SD_RFREE, (size_t)kDimRows * 4, A.rfree, u32);
     ENS(B_SD_RDEAD, (size_t)kDimRows * 4, A.rdead, u32);
     ENS(B_SD_RACT, (size_t)kDimRows * 4, A.ract, u32);
-    ENS(B_SD_OUT, sizeof(DimOut), A.out, DimOut);
-    *full = false;
-    {
-        PROF(P_SORT1 + k - 1);
-        launch_dim_partition(k, A, st);
-    }
-    // the owned cofacets are counted: room for them
-    u32 *total_h = (u32 *)C.host_scal;
-    HIP_TRY(hipMemcpyAsync(total_h, A.bin_t + A.nbins, 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    prof_resolve();
-    const int64_t total = (int64_t)*total_h;
-    if (total > (1ll << 28)) { // above 3 (4) GiB of places
-        *full = true;
-        return RIPS_OK;
-    }
-    ENS(B_SD_TAU, (size_t)total * 4 * (k + 2), A.tau, u32);
 #undef ENS
-    {
-        PROF(P_COB1 + k - 1);
-        launch_dim_fill(k, A, st);
-    }
-    {
-        PROF(P_REDUCE1 + k - 1);
-        HIP_TRY(launch_dim_sweep(k, A, st));
-    }
-    launch_fill_i64(ph.keys, phcap, kEmpty, st);
-    launch_dim_bars(k, A, bars, ph, st);
-    static_assert(sizeof(DimOut) <= sizeof(Scalars), "read back through the pinned scalar block");
-    HIP_TRY(hipMemcpyAsync(C.host_scal, A.out, sizeof(DimOut), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    prof_resolve();
-    const DimOut h = *(const DimOut *)C.host_scal;
-    if (h.full > 1) return fail(RIPS_E_HIP, "sweep: internal consistency check failed");
-    if (h.full) {
-        *full = true;
-        return RIPS_OK;
+    DimOut h;
+    memset(&h, 0, sizeof(h));
+    if (A.S > 0) {
+        {
+            PROF(P_COB1 + k - 1);
+            if (k == 1) launch_dim_fill(A, st);
+            else launch_lune_chunks(A, st);
+        }
+        {
+            PROF(P_REDUCE1 + k - 1);
+            if (k == 1) HIP_TRY(launch_dim_sweep(A, st));
+            else HIP_TRY(launch_lune_sweep(A, (int)((float)ncand / A.chunk_n) + A.S / 192 + 2, st));
+        }
+        launch_dim_bars(k, A, bars, ph, st);
+        HIP_TRY(hipMemcpyAsync(C.host_scal, A.out, sizeof(DimOut), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        prof_resolve();
+        h = *(const DimOut *)C.host_scal;
+        if (h.full > 1) return fail(RIPS_E_HIP, "sweep: internal consistency check failed");
+        if (h.full) {
+            *full = true;
+            return RIPS_OK;
+        }
     }
     o.count[k] = h.nbars;
-    o.stats[k].emergent = h.emergent;
-    o.stats[k].reduced = h.reduced;
-    o.stats[k].additions = (int64_t)(h.adds + h.rows) - S;
+    o.stats[k].emergent = h.emergent + loc_emergent;
+    o.stats[k].reduced = h.reduced + loc_reduced;
+    o.stats[k].additions = (int64_t)(h.adds + h.rows) - A.S;
     o.stats[k].bars_nonzero = h.nonzero;
     o.stats[k].essential = h.essential;
     o.stats[k].entries_added = o.stats[k].additions * A.W;
@@ -1164,8 +1228,8 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         launch_reset_dim(P.scal, st);
         // dimension 1 over Z/2 takes the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
-        const bool sweep = k == 1 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C, p) &&
-                           P.nedges >= kSweepDegMin * n / 2 && P.nedges <= kSweepDegMax * n / 2;
+        const bool sweep = k <= 2 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C, p) &&
+                           (k == 2 || (P.nedges >= kSweepDegMin * n / 2 && P.nedges <= kSweepDegMax * n / 2));
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {
@@ -1326,7 +1390,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
             if ((rs = ensure_bars(k, S))) return rs;
             bool full = false;
             if (S > 0)
-                rs = sweep_dim(C, P, k, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
+                rs = sweep_dim(C, P, k, max_dim, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
             else
                 launch_fill_i64(ph.keys, phcap, kEmpty, st);
             if (rs) return rs;

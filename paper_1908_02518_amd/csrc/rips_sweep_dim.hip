@@ -1,22 +1,41 @@
-// rips_sweep_dim.hip -- the sweep of one dimension K (1 or 2) of a single
-// cloud over Z/2 (the method of rips_sweep.hip, for any number of points and
-// for triangles).
+// rips_sweep_dim.hip -- the sweep of dimension 1 or 2 of a single cloud over
+// Z/2 (the method of rips_sweep.hip, for any number of points and for
+// triangles).
 //
-// Every K-simplex carries the vector of the open K-classes: the simplex of a
-// zero apparent pair (s, t) the sum over the other facets of t, a column of
-// the reduction (section "Assembling column indices") its unit vector, a
-// simplex that dimension K-1 has paired zero (its row can be left out: a
-// reduced boundary's pivot is never such a simplex). A (K+1)-simplex whose
-// facets do not sum to zero closes the youngest class of the sum.
+// Every K-simplex carries the vector of the open K-classes; a simplex that
+// dimension K-1 has paired has the vector zero (a reduced boundary's pivot is
+// never such a simplex), a class's own simplex its unit vector. A
+// (K+1)-simplex whose facets do not sum to zero closes the youngest class of
+// the sum.
+//
+// Dimension 1: an edge of a zero apparent pair (e, t) has the sum over the
+// other two edges of t; the columns of the reduction (section "Assembling
+// column indices") are the classes.
+//
+// Dimension 2: that would open thousands of classes of zero persistence and
+// close them one by one (so3-1000: 31 ms, columns 5.3). But a pair of zero
+// persistence lies in one block, the simplices with the same longest edge e:
+// the triangles e + c stand for the points c of e's lune, the tetrahedra
+// e + {c, d} for the lune's edges shorter than e, and the pairs are those of
+// a spanning forest of that graph, its edges taken in the order of the
+// tetrahedra: an edge that joins two trees pairs with the younger tree's
+// oldest triangle. Only the oldest triangle of a tree without the block's
+// oldest is a class (or closes one of dimension 1), and every other triangle
+// has the sum over the other facets of the tetrahedron that joins it to its
+// parent (so3-1000: 211 classes of 19,000 columns). Ties: edges of equal length are put in
+// order by index, which moves simplices of equal diameter among themselves;
+// that cannot change a pair unless one of the two is in a block that shares
+// a simplex with another of the same length (and that simplex joins trees);
+// a class opened or closed in such a block, and a pair within it that
+// dimension 3 has to know, is left to the columns.
 //
 // All passes over simplices are data-parallel over the chip: the simplices by
-// diameter bin, the place of each by index, and per simplex the cofacets it
-// owns (whose youngest facet it is) as the places of their facets, so that
-// the sweep itself, one workgroup, only follows places. It takes whole bins
-// in chunks: opens the chunk's classes, resolves its vectors, gathers the
-// cofacets that do not cancel, eliminates them in order and substitutes the
-// closed classes. Few vectors are nonzero and most of those are shared, so a
-// chunk is a few microseconds of one workgroup.
+// diameter bin, the place of each by index, and the places that the sweep
+// will look at, so that the sweep itself, one workgroup, only follows places.
+// It takes whole bins in chunks: opens the chunk's classes, resolves its
+// vectors, gathers the cofacets that do not cancel, eliminates them in order
+// and substitutes the closed classes. Few vectors are nonzero and most of
+// those are shared, so a chunk is a few microseconds of one workgroup.
 #include "rips_sweep_dim.hpp"
 
 #include <algorithm>
@@ -33,6 +52,7 @@ constexpr int kCand = 512;          // cofacets eliminated together
 constexpr int kCandWords = 16384;   // and their vectors, in words
 constexpr int kPurge = 32;          // eliminations between two purges
 constexpr int kTaus = 4;            // cofacets a lane has in flight
+constexpr int kLune = 1024;         // points of a lune
 
 __device__ __forceinline__ int dim_bin(const DimArgs &A, float d) {
     return min(A.nbins - 1, (int)(d * A.scale)); // monotone; equal diameters share a bin
@@ -83,7 +103,8 @@ __device__ __forceinline__ void facet_of(const int (&v)[K + 1], int i, int c, in
 template <int K>
 __global__ void __launch_bounds__(256) k_dim_hist(DimArgs A) {
     const int64_t stride = (int64_t)gridDim.x * 256, t0 = blockIdx.x * 256ll + threadIdx.x;
-    for (int64_t i = t0; i < A.N; i += stride) atomicAdd(&A.bin_n[dim_bin(A, A.in.diam[i])], 1u);
+    if (K == 1)
+        for (int64_t i = t0; i < A.N; i += stride) atomicAdd(&A.bin_n[dim_bin(A, A.in.diam[i])], 1u);
     for (int64_t i = t0; i < A.S; i += stride) atomicAdd(&A.bin_s[dim_bin(A, A.cols.diam[i])], 1u);
 }
 
@@ -115,8 +136,8 @@ __global__ void __launch_bounds__(1024) k_dim_scan(u32 *a0, u32 *a1, int nbins) 
     if (threadIdx.x == kT - 1) a[nbins] = base;
 }
 
-template <int K>
 __global__ void __launch_bounds__(256) k_dim_place(DimArgs A) {
+    constexpr int K = 1;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < A.N; i += stride) {
         const int64_t idx = A.in.idx[i];
@@ -137,12 +158,13 @@ __global__ void __launch_bounds__(256) k_dim_place(DimArgs A) {
     }
 }
 
-// ---- the cofacets a simplex owns: third vertices c with every new edge at
+// ---- the triangles an edge owns: third vertices c with every new edge at
 // most its diameter long and every other facet older (a facet of the same
 // diameter is older when its index is larger, that is when c is larger than
 // the vertex it replaces). A group of G lanes a simplex.
-template <int K, int G, bool kFill>
+template <int G, bool kFill>
 __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
+    constexpr int K = 1;
     const int lane = lane_id(), lg = lane & (G - 1), g0 = lane & ~(G - 1);
     const u64 gmask = G == 64 ? ~0ull : ((1ull << G) - 1) << g0;
     const int64_t groups = (int64_t)gridDim.x * (256 / G);
@@ -156,12 +178,6 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
         int v[K + 1];
         unpack<K>(live ? A.qverts[q] : 0, v);
         const float dm = live ? A.qdiam[q] : -1.0f;
-        float inner[3] = {0.0f, 0.0f, 0.0f}; // K == 2: the edge opposite to vertex i
-        if constexpr (K == 2) {
-            inner[0] = D[(int64_t)v[1] * n + v[2]];
-            inner[1] = D[(int64_t)v[0] * n + v[2]];
-            inner[2] = D[(int64_t)v[0] * n + v[1]];
-        }
         const int *nb = nullptr;
         int cnt = live ? n : 0;
         if (live && A.c.nb.off) {
@@ -202,7 +218,7 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
                     if (ok) {
 #pragma unroll
                         for (int i = 0; i <= K; ++i) {
-                            float fd = K == 2 ? inner[i] : 0.0f;
+                            float fd = 0.0f;
 #pragma unroll
                             for (int j = 0; j <= K; ++j)
                                 if (j != i) fd = fmaxf(fd, x[j]);
@@ -243,7 +259,9 @@ __global__ void __launch_bounds__(1024) k_dim_chunks(DimArgs A) {
     __shared__ int s_n;
     const u32 total = A.bin_t[A.nbins];
     const float n32 = (float)A.N / 32.0f, t32 = (float)total / 32.0f; // at least 32 chunks, but not tiny ones
-    const float wn = 1.0f / fmaxf(fminf(fmaxf(n32, 256.0f), 2048.0f), (float)A.N / 3000.0f), ws = 1.0f / 192.0f;
+    const float wn = A.chunk_n > 0.0f ? 1.0f / A.chunk_n
+                                      : 1.0f / fmaxf(fminf(fmaxf(n32, 256.0f), 2048.0f), (float)A.N / 3000.0f);
+    const float ws = 1.0f / 192.0f;
     const float wt = 1.0f / fmaxf(fminf(fmaxf(t32, 4096.0f), 16384.0f), (float)total / 3000.0f);
     auto first_n = [&](int b) { return b == 0 ? 0u : A.bin_n[b - 1]; };
     auto first_t = [&](int b) { return b == 0 ? 0u : A.bin_t[b - 1]; };
@@ -293,6 +311,305 @@ __global__ void __launch_bounds__(1024) k_dim_chunks(DimArgs A) {
     }
 }
 
+// ---- dimension 2: blocks and their forests
+
+// index of a triangle, of a tetrahedron given in any order
+__device__ __forceinline__ int64_t tri_index(int a, int b, int c) {
+    const int hi = max(a, max(b, c)), lo = min(a, min(b, c));
+    const int v[3] = {hi, a + b + c - hi - lo, lo};
+    return index_of<2>(v);
+}
+
+__device__ __forceinline__ u32 tri_place(const DimArgs &A, int a, int b, int c) {
+    const int64_t idx = tri_index(a, b, c);
+    if (A.direct) return A.direct[idx];
+    return (u32)ph_find(A.ph, idx);
+}
+
+__device__ __forceinline__ u64 tet_index(const DimArgs &A, int a, int b, int c, int d) {
+    const int h0 = max(a, b), l0 = min(a, b), h1 = max(c, d), l1 = min(c, d);
+    const int x = min(h0, h1), y = max(l0, l1);
+    const int v[4] = {max(h0, h1), max(x, y), min(x, y), min(l0, l1)};
+    return (u64)simplex_index(v, 3, A.c.B);
+}
+
+__device__ __forceinline__ int64_t pair_idx(int a, int b) {
+    const int64_t x = max(a, b);
+    return x * (x - 1) / 2 + min(a, b);
+}
+
+__device__ __forceinline__ bool bit_of(const DimArgs &A, const u32 *t, int a, int b) {
+    return (t[(int64_t)a * A.fw + (b >> 5)] >> (b & 31)) & 1u;
+}
+
+__device__ __forceinline__ void set_bit(const DimArgs &A, u32 *t, int a, int b) {
+    atomicOr(&t[(int64_t)a * A.fw + (b >> 5)], 1u << (b & 31));
+    atomicOr(&t[(int64_t)b * A.fw + (a >> 5)], 1u << (a & 31));
+}
+
+// vertices of the triangle at a place: the longest edge's two (a > b), and the third
+__device__ __forceinline__ void tri_verts(u64 p, int &a, int &b, int &c) {
+    c = (int)(p & 0xffff);
+    a = (int)((p >> 16) & 0xffff);
+    b = (int)((p >> 32) & 0xffff);
+}
+
+// edge (x, y) of length d comes before edge e of length len and index ei
+__device__ __forceinline__ bool edge_before(float d, int x, int y, float len, int64_t ei) {
+    return d < len || (d == len && pair_idx(x, y) < ei);
+}
+
+struct LuneLds {
+    uint16_t c[kLune];   // third vertices, largest first: oldest triangle first
+    uint16_t lab[kLune]; // oldest point of the tree; bit 15: the point has an edge
+    uint16_t par[kLune];
+    u32 kill[kLune];
+};
+
+// One wave an edge: its lune counted, or (kPlace) written out, and its forest.
+// The edges of the lune in the order of the tetrahedra are all (i, j), i < j,
+// by i and then by j: a point with no edge yet joins point i's tree at once, a
+// tree is joined by itself (rare) and turned so that its path to point i or j
+// leads up. Bound by the distances' gathers, a row of D for a point.
+template <bool kPlace>
+__global__ void __launch_bounds__(256) k_lune(DimArgs A) {
+    __shared__ LuneLds Ls[kPlace ? 4 : 1];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int n = A.c.n;
+    const float *D = A.c.d.D;
+    const int64_t waves = (int64_t)gridDim.x * 4;
+    for (int64_t e = blockIdx.x * 4ll + wave; e < A.nE; e += waves) {
+        const int a = __builtin_amdgcn_readfirstlane(A.E.a[e]), b = __builtin_amdgcn_readfirstlane(A.E.b[e]);
+        const float len = A.E.diam[e];
+        const int64_t ei = pair_idx(a, b);
+        const int bin = dim_bin(A, len);
+        const int *nb = nullptr;
+        int cnt = n;
+        if (A.c.nb.off) {
+            const int oa = A.c.nb.off[a], ob = A.c.nb.off[b];
+            const int la = A.c.nb.off[a + 1] - oa, lb = A.c.nb.off[b + 1] - ob;
+            nb = A.c.nb.idx + (la <= lb ? oa : ob);
+            cnt = min(la, lb);
+        }
+        u32 base = 0;
+        int size = 0;
+        if (kPlace) {
+            size = __builtin_amdgcn_readfirstlane((int)A.bcnt[e]);
+            if (lane == 0) {
+                base = atomicAdd(&A.bin_n[bin], (u32)size); // the bins' first places move up to their ends
+                A.bstart[e] = base;
+                A.tkey[e] = ~0u;
+            }
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (size == 0) continue;
+            if (size > kLune || base + (u32)size > (u32)A.N) {
+                if (lane == 0) A.out->full = 1;
+                continue;
+            }
+        }
+        LuneLds &L = Ls[kPlace ? wave : 0];
+        u32 first_tie = ~0u;
+        int k = 0;
+        for (int s = 0; s < cnt; s += kWave) {
+            const int i = s + lane;
+            const int c = i < cnt ? (nb ? nb[cnt - 1 - i] : n - 1 - i) : a;
+            const float x = D[(int64_t)a * n + c], y = D[(int64_t)b * n + c];
+            const bool in = c != a && c != b && x <= len && y <= len;
+            if (kPlace && in && (x == len || y == len)) {
+                set_bit(A, A.tied, a, b);
+                if (x == len) set_bit(A, A.tied, a, c);
+                if (y == len) set_bit(A, A.tied, b, c);
+                first_tie = 0;
+            }
+            const bool ok = in && edge_before(x, a, c, len, ei) && edge_before(y, b, c, len, ei);
+            const u64 hit = __ballot(ok);
+            if (kPlace && ok) {
+                const int at = k + __popcll(hit & ((1ull << lane) - 1));
+                if (at < size) {
+                    const u32 q = base + (u32)at;
+                    L.c[at] = (uint16_t)c;
+                    A.qdiam[q] = len;
+                    A.qverts[q] = (u64)c | ((u64)a << 16) | ((u64)b << 32);
+                    A.qblk[q] = (u32)e;
+                    const int64_t idx = tri_index(a, b, c);
+                    if (A.direct) A.direct[idx] = q;
+                    else (void)ph_insert(A.ph, idx, (int32_t)q); // room for twice the triangles: it cannot fail
+                }
+            }
+            k += __popcll(hit);
+        }
+        if (!kPlace) {
+            if (lane == 0) {
+                A.bcnt[e] = (u32)k;
+                atomicAdd(&A.bin_n[bin], (u32)k);
+            }
+            continue;
+        }
+        for (int i = lane; i < size; i += kWave) {
+            L.lab[i] = (uint16_t)i;
+            L.par[i] = 0xffff;
+            L.kill[i] = ~0u;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int i = 0; i + 1 < size; ++i) {
+            const int c = __builtin_amdgcn_readfirstlane((int)L.c[i]);
+            int li = __builtin_amdgcn_readfirstlane((int)L.lab[i] & 0x7fff);
+            for (int s = i + 1; s < size; s += kWave) {
+                const int j = s + lane;
+                const int d = j < size ? (int)L.c[j] : c;
+                const float z = D[(int64_t)c * n + d];
+                const bool adj = j < size && edge_before(z, c, d, len, ei);
+                const int lj = j < size ? (int)L.lab[j] : li;
+                if (j < size && z == len) { // a tetrahedron of two blocks: no matter, unless it joins trees
+                    first_tie = min(first_tie, ((u32)i << 16) | (u32)j);
+                    if ((lj & 0x7fff) != li) {
+                        set_bit(A, A.tied, a, b);
+                        set_bit(A, A.tied, c, d);
+                    }
+                }
+                const bool single = adj && lj == j; // bit 15 clear, and its own label
+                if (single) {
+                    L.lab[j] = (uint16_t)(li | 0x8000);
+                    L.par[j] = (uint16_t)i;
+                    L.kill[j] = ((u32)i << 16) | (u32)j;
+                }
+                if (__any(single) && lane == 0) L.lab[i] = (uint16_t)(li | 0x8000);
+                u64 m = __ballot(adj && !single && (lj & 0x7fff) != li);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                for (; m; m &= m - 1) {
+                    const int jj = s + __ffsll((unsigned long long)m) - 1;
+                    const int l2 = __builtin_amdgcn_readfirstlane((int)L.lab[jj] & 0x7fff);
+                    if (l2 == li) continue;
+                    const int young = max(li, l2), old = min(li, l2);
+                    if (lane == 0) {
+                        int q = l2 == young ? jj : i, up = l2 == young ? i : jj;
+                        for (int hops = 0; q != 0xffff && hops < kLune; ++hops) { // the path to the root, turned
+                            const int next = L.par[q];
+                            L.par[q] = (uint16_t)up;
+                            up = q;
+                            q = next;
+                        }
+                        L.kill[young] = ((u32)i << 16) | (u32)jj;
+                    }
+                    for (int v = lane; v < size; v += kWave)
+                        if ((L.lab[v] & 0x7fff) == young) L.lab[v] = (uint16_t)(old | 0x8000);
+                    li = old;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                }
+            }
+        }
+        for (int i = lane; i < size; i += kWave) {
+            const u32 up = L.par[i];
+            A.qpar[base + i] = up == 0xffff ? ~0u : base + up;
+            A.qkill[base + i] = L.kill[i];
+        }
+        if (first_tie != ~0u) atomicMin(&A.tkey[e], first_tie);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+// the facets a triangle's vector is the sum of: its parent, and the two older
+// ones of the tetrahedron that joins them; and the lists the other way round
+__global__ void __launch_bounds__(256) k_lune_deps(DimArgs A) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    if (A.out->full) return; // places are missing
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < A.N; q += stride) {
+        const u32 up = A.qpar[q];
+        int a, b, c, a1, b1, d;
+        tri_verts(A.qverts[q], a, b, c);
+        A.ids[q] = 0;
+        if (up >= (u32)A.N) {
+            // not the block's oldest: a class, or one of dimension 1 closes
+            if (A.bstart[A.qblk[q]] != (u32)q && bit_of(A, A.tied, a, b)) A.out->full = 1;
+            continue;
+        }
+        tri_verts(A.qverts[up], a1, b1, d);
+        const u32 dep[3] = {up, tri_place(A, a, c, d), tri_place(A, b, c, d)};
+        for (int i = 0; i < 3; ++i) {
+            if (dep[i] >= (u32)A.N) {
+                A.out->full = kDimBroken;
+                break;
+            }
+            const u32 o = (u32)(i * A.N + q);
+            A.qdep[o] = dep[i];
+            A.rnext[o] = atomicExch(&A.rhead[dep[i]], o);
+        }
+    }
+}
+
+// The columns that are roots of their block's forest, in column order; the
+// others pair with the tetrahedron at which their tree was joined to an older
+// one. One workgroup.
+__global__ void __launch_bounds__(1024) k_lune_classes(DimArgs A, PivotHash piv) {
+    __shared__ int s_w[kWaves];
+    __shared__ int s_red, s_emg, s_full;
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    if (threadIdx.x == 0) {
+        s_red = s_emg = 0;
+        s_full = A.out->full;
+    }
+    __syncthreads();
+    if (s_full) return; // places are missing
+    int at = 0, red = 0, emg = 0;
+    for (int c0 = 0; c0 < A.nall; c0 += kT) {
+        const int col = c0 + (int)threadIdx.x;
+        bool root = false;
+        if (col < A.nall) {
+            int v[3];
+            decode(A.all.idx[col], 2, A.c.n, A.c.B, v);
+            const u32 q = min(tri_place(A, v[0], v[1], v[2]), (u32)A.N - 1);
+            const u32 start = A.bstart[A.qblk[q]], k = A.qkill[q];
+            int a, b, c, d, a1, b1, own;
+            tri_verts(A.qverts[q], a, b, own);
+            root = A.qpar[q] >= (u32)A.N;
+            const u32 q1 = start + (k >> 16), q2 = start + (k & 0xffff);
+            if (root) {
+                // the block's oldest triangle pairs with the edge: no column, unless tied
+                if (start == q) {
+                    root = false;
+                    if (!bit_of(A, A.tied, a, b)) A.out->full = 1;
+                }
+            } else if (k == ~0u || q1 >= (u32)A.N || q2 >= (u32)A.N) {
+                A.out->full = kDimBroken;
+            } else {
+                tri_verts(A.qverts[q1], a1, b1, c);
+                tri_verts(A.qverts[q2], a1, b1, d);
+                (void)ph_insert(piv, (int64_t)tet_index(A, a, b, c, d), col);
+                // joined after an edge as long as the block's: the pair may be another one
+                if (A.strict && k >= A.tkey[A.qblk[q]] && bit_of(A, A.tied, a, b)) A.out->full = 1;
+                const int j = A.all.j[col];
+                if (j >= 0 && ((own == c && j == d) || (own == d && j == c))) ++emg;
+                else ++red;
+            }
+        }
+        const u64 bal = __ballot(root);
+        if (lane == 0) s_w[w] = __popcll(bal);
+        __syncthreads();
+        int base = at, tot = 0;
+        for (int q = 0; q < kWaves; ++q) {
+            if (q < w) base += s_w[q];
+            tot += s_w[q];
+        }
+        if (root) {
+            const int o = base + __popcll(bal & ((1ull << lane) - 1));
+            A.cols.idx[o] = A.all.idx[col];
+            A.cols.diam[o] = A.all.diam[col];
+            A.cols.j[o] = A.all.j[col];
+        }
+        at += tot;
+        __syncthreads();
+    }
+    if (red) atomicAdd(&s_red, red);
+    if (emg) atomicAdd(&s_emg, emg);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        A.out->nclasses = at;
+        A.out->loc_reduced = s_red;
+        A.out->loc_emergent = s_emg;
+        if (A.bin_n[A.nbins] != (u32)A.N) A.out->full = kDimBroken; // every triangle has one block
+    }
+}
+
 // place of every column, oldest first
 template <int K>
 __global__ void __launch_bounds__(256) k_dim_births(DimArgs A) {
@@ -309,6 +626,7 @@ __global__ void __launch_bounds__(256) k_dim_births(DimArgs A) {
 struct DimShared {
     int nrows, nact, nfree, ndead, nnz, ncand, nkill, fail, since;
     int sfree;                       // free slots
+    int again;
     unsigned long long adds, rows;
     u32 hi_d;
     u64 hi_i;
@@ -319,7 +637,6 @@ struct DimShared {
     u32 sage[kDimSlots];             // class of a slot
     uint16_t urow[kDimSlots];        // an open class's unit row, by slot
     uint16_t sl[kDimSlots];          // free slots
-    int scan[kWaves + 1];
 };
 
 __device__ __forceinline__ bool key_less(u32 d0, u64 i0, u32 d1, u64 i1) { return d0 < d1 || (d0 == d1 && i0 < i1); }
@@ -376,6 +693,156 @@ __device__ __forceinline__ int dim_append(bool want, int *counter) {
     return base + __popcll(bal & ((1ull << lane) - 1));
 }
 
+// the three edges of the triangle at place q have one with a nonzero vector
+__device__ __forceinline__ void mark(const DimArgs &A, u32 q) {
+    int a, b, c;
+    tri_verts(A.qverts[q], a, b, c);
+    set_bit(A, A.fl, a, b);
+    set_bit(A, A.fl, a, c);
+    set_bit(A, A.fl, b, c);
+}
+
+// the triangles whose sum the one at place q is part of have to be looked at
+__device__ __forceinline__ void call_on(const DimArgs &A, u32 q) {
+    u32 o = A.rhead[q];
+    for (int hops = 0; o < 3u * (u32)A.N && hops < 3 * kDimMaxVert; ++hops) {
+        const u32 s = o % (u32)A.N;
+        atomicOr(&A.need[s >> 5], 1u << (s & 31));
+        o = A.rnext[o];
+    }
+}
+
+// the sweep's LDS in global memory: DimShared, then the row map
+constexpr int kStateWords = sizeof(DimShared) / 4;
+
+// ---- dimension 2: the tetrahedra e + {c, d} of a chunk's blocks whose facets
+// do not cancel. One wave a triangle e + c, its lanes the d's of the block;
+// most have no nonzero triangle on the edges (a, c) and (b, c) and nothing to
+// do. A facet (a, c, d) can be nonzero only if each of its edges has a
+// nonzero triangle, which leaves few pairs to look up (of the 39 million
+// tetrahedra of 192 points on the sphere 1 to 2 million). By the whole chip:
+// one workgroup took 60 ms for that cloud, its lookups one line a clock.
+__global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
+    if (chunk >= A.out->nch || A.out->full) return;
+    const DimShared *S = (const DimShared *)A.state;
+    if (S->nnz == 0) return;
+    const uint16_t *rmap = (const uint16_t *)((const u32 *)A.state + kStateWords);
+    const int lane = lane_id(), n = A.c.n;
+    const float *D = A.c.d.D;
+    const u32 n0 = A.ch_n[chunk], n1 = A.ch_n[chunk + 1], waves = gridDim.x * 4;
+    for (u32 q = n0 + blockIdx.x * 4 + threadIdx.x / kWave; q < n1; q += waves) {
+        int a, b, c;
+        tri_verts(A.qverts[q], a, b, c);
+        const u32 own = rmap[A.ids[q] & (kDimRows - 1)] & (kDimRows - 1);
+        const bool fa = bit_of(A, A.fl, a, c), fb = bit_of(A, A.fl, b, c);
+        if (!own && !fa && !fb) continue;
+        const u32 blk = A.qblk[q], start = A.bstart[blk], size = A.bcnt[blk];
+        const float len = A.qdiam[q];
+        const int64_t ei = pair_idx(a, b);
+        for (u32 s = 0; s < size; s += kWave) {
+            const u32 j = s + (u32)lane, qd = min(start + min(j, size - 1), (u32)A.N - 1);
+            const int d = (int)(A.qverts[qd] & 0xffff);
+            bool ok = j < size && qd != q;
+            const float z = D[(int64_t)c * n + d];
+            const u32 other = rmap[A.ids[qd] & (kDimRows - 1)] & (kDimRows - 1);
+            const bool fc = bit_of(A, A.fl, c, d);
+            const bool ta = fc && fa && bit_of(A, A.fl, a, d), tb = fc && fb && bit_of(A, A.fl, b, d);
+            ok = ok && edge_before(z, c, d, len, ei) && (own || ta || tb);
+            // from d's side too, if that looks at it: only from the first
+            ok = ok && !(qd < q && (other || ta || tb));
+            if (!__any(ok)) continue;
+            u32 r[4] = {own, other, 0, 0};
+            if (ok && ta) r[2] = tri_place(A, a, c, d);
+            if (ok && tb) r[3] = tri_place(A, b, c, d);
+            if (ok && ((ta && r[2] >= (u32)A.N) || (tb && r[3] >= (u32)A.N))) A.out->full = kDimBroken;
+            r[2] = ta ? rmap[A.ids[min(r[2], (u32)A.N - 1)] & (kDimRows - 1)] & (kDimRows - 1) : 0;
+            r[3] = tb ? rmap[A.ids[min(r[3], (u32)A.N - 1)] & (kDimRows - 1)] & (kDimRows - 1) : 0;
+            ok = ok && cancel<4>(r) > 0;
+            bool nonzero = false;
+            if (ok)
+                for (u64 m = sum_words<4>(A, r); m && !nonzero; m &= m - 1)
+                    nonzero = sum_word<4>(A, r, __ffsll((unsigned long long)m) - 1) != 0;
+            const int at = dim_append(nonzero, &A.out->npair);
+            if (nonzero && at < A.paircap) A.pairs[at] = ((u64)q << 32) | (u32)d;
+        }
+    }
+}
+
+// The lanes with `ok` hold cofacets that do not cancel (rows r, key (kd, ki),
+// nonzero words z): of those with the same rows the oldest becomes a
+// candidate. (A cofacet that is found twice cancels in the elimination.)
+template <int M>
+__device__ __forceinline__ void candidates(const DimArgs &A, DimShared &Sh, LDS u32 *vec, int ccap, const u32 (&r)[M],
+                                           bool ok, u32 kd, u64 ki, u64 z) {
+    const int lane = lane_id();
+    for (u64 todo = __ballot(ok); todo;) {
+        int l = __ffsll((unsigned long long)todo) - 1;
+        bool same = ok;
+#pragma unroll
+        for (int i = 0; i < M; ++i) same = same & (r[i] == (u32)__builtin_amdgcn_readlane(r[i], l));
+        const u64 sm = __ballot(same);
+        todo &= ~sm;
+        for (u64 m = sm; m; m &= m - 1) { // the oldest of them
+            const int j = __ffsll((unsigned long long)m) - 1;
+            const u32 jd = __builtin_amdgcn_readlane(kd, j), bd = __builtin_amdgcn_readlane(kd, l);
+            const u64 ji = lane_u64(ki, j), bi = lane_u64(ki, l);
+            if (key_less(jd, ji, bd, bi)) l = j;
+        }
+        if (lane == l) {
+            const int s = atomicAdd(&Sh.ncand, 1);
+            if (s < ccap) {
+                Sh.cd[s] = kd;
+                Sh.ci[s] = ki;
+                Sh.cz[s] = z;
+                for (int w = 0; w < A.W; ++w) vec[s * A.W + w] = (z >> w) & 1ull ? sum_word<M>(A, r, w) : 0u;
+            }
+        }
+    }
+}
+
+// The row of the sum of the rows r: an old one where the sum is one of them,
+// zero or a unit vector, else a new one.
+template <int M>
+__device__ __forceinline__ u32 row_of_sum(const DimArgs &A, DimShared &Sh, LDS uint16_t *rmap, u32 (&r)[M]) {
+    const int W = A.W;
+        const int k = cancel<M>(r);
+        u32 x = 0;
+#pragma unroll
+        for (int i = 0; i < M; ++i) x |= r[i];
+        if (k > 1) {
+            u64 z = 0;
+            u32 one = 0; // the only nonzero word
+            for (u64 m = sum_words<M>(A, r); m; m &= m - 1) {
+                const int w = __ffsll((unsigned long long)m) - 1;
+                const u32 y = sum_word<M>(A, r, w);
+                if (y) {
+                    z |= 1ull << w;
+                    one = y;
+                }
+            }
+            x = 0;
+            if (is_unit(z, one)) {
+                x = Sh.urow[(__ffsll((unsigned long long)z) - 1) * 32 + __ffs((int)one) - 1];
+            } else if (z) {
+                const int f = atomicSub(&Sh.nfree, 1);
+                if (f > 0) x = A.rfree[f - 1];
+                else x = (u32)atomicAdd(&Sh.nrows, 1);
+                if (x < (u32)kDimRows) {
+                    for (int w = 0; w < W; ++w) A.pool[(int64_t)x * W + w] = sum_word<M>(A, r, w);
+                    A.rsum[x] = z;
+                    rmap[x] = (uint16_t)x;
+                    A.ract[atomicAdd(&Sh.nact, 1)] = x;
+                    atomicAdd(&Sh.rows, 1ull);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                } else {
+                    x = 0;
+                    Sh.fail = 1;
+                }
+            }
+        }
+    return x;
+}
+
 // A row's vector is shared by all simplices that hold its number, and rows
 // with equal unit vectors are one row: a row that becomes zero or a unit
 // vector keeps its number on the simplices and is replaced on the way, by
@@ -383,7 +850,7 @@ __device__ __forceinline__ int dim_append(bool want, int *counter) {
 // the vectors). Every kPurge eliminations the simplices' numbers are brought
 // up to date and the replaced rows are free again.
 template <int K>
-__global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
+__global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ DimShared Sh;
     LDS u32 *vec = (LDS u32 *)smem;                                // kCandWords
@@ -391,22 +858,34 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int W = A.W;
+    [[maybe_unused]] const int n = A.c.n;
     const int nslots = W * 32, ccap = min(kCand, kCandWords / W);
-    if (tid == 0) {
-        Sh.nact = Sh.nnz = Sh.fail = Sh.nfree = Sh.ndead = Sh.since = 0;
-        Sh.nrows = 1; // row 0: the zero vector
-        rmap[0] = 0;
-        Sh.sfree = nslots;
-        Sh.adds = Sh.rows = 0;
-    }
-    for (int q = tid; q < nslots; q += kT) Sh.sl[q] = (uint16_t)(nslots - 1 - q);
-    __syncthreads();
     const int nch = __builtin_amdgcn_readfirstlane(A.out->nch);
-    for (int ch = 0; ch < nch; ++ch) {
+    const bool more = K == 2 && chunk > 0; // the tables as the launch before left them
+    if (more) {
+        if (chunk > nch || A.out->full) return;
+        const u32 *from = (const u32 *)A.state;
+        for (int i = tid; i < kStateWords; i += kT) ((LDS u32 *)&Sh)[i] = from[i];
+        for (int i = tid; i < kDimRows / 2; i += kT) ((LDS u32 *)rmap)[i] = from[kStateWords + i];
+    } else {
+        if (tid == 0) {
+            Sh.nact = Sh.nnz = Sh.fail = Sh.nfree = Sh.ndead = Sh.since = 0;
+            Sh.nrows = 1; // row 0: the zero vector
+            rmap[0] = 0;
+            Sh.sfree = nslots;
+            Sh.adds = Sh.rows = 0;
+        }
+        for (int q = tid; q < nslots; q += kT) Sh.sl[q] = (uint16_t)(nslots - 1 - q);
+    }
+    __syncthreads();
+    // dimension 2: the end of the chunk before, whose cofacets k_lune_tests has
+    // looked at meanwhile, and the vectors of this one
+    for (int ch = K == 2 ? max(chunk - 1, 0) : 0; ch < (K == 2 ? min(chunk + 1, nch) : nch); ++ch) {
+        const bool vectors = K == 1 || ch == chunk;
         const u32 n0 = A.ch_n[ch], n1 = A.ch_n[ch + 1], t0 = A.ch_t[ch], t1 = A.ch_t[ch + 1];
         const int s0 = (int)A.ch_s[ch], s1 = (int)A.ch_s[ch + 1];
         // ---- the classes that open here
-        if (s1 > s0) {
+        if (vectors && s1 > s0) {
             const int ns = s1 - s0, nf = Sh.sfree, nr = Sh.nfree, top = Sh.nrows, na = Sh.nact, nz = Sh.nnz;
             const int fresh = max(0, ns - nr);
             if (ns > nf || top + fresh > kDimRows) {
@@ -430,6 +909,10 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                 const u32 q = min(pl, (u32)A.N - 1);
                 A.ids[q] = r;
                 A.nzl[nz + i] = q;
+                if constexpr (K == 2) {
+                    mark(A, q);
+                    call_on(A, q);
+                }
             }
             if (tid == 0) {
                 Sh.sfree = nf - ns;
@@ -442,6 +925,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
             __syncthreads();
         }
         // ---- the vectors of the chunk's simplices (see rips_sweep.hip)
+        if constexpr (K == 1)
         for (int tries = 0;; ++tries) {
             bool left = false;
             for (u32 q = n0 + tid; q < n1; q += kT) {
@@ -466,41 +950,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                     if (r[i] >= (u32)kDimRows) Sh.fail = kDimBroken;
                     r[i] = rmap[r[i] & (kDimRows - 1)] & (kDimRows - 1);
                 }
-                const int k = cancel<K + 1>(r);
-                u32 x = 0;
-#pragma unroll
-                for (int i = 0; i <= K; ++i) x |= r[i];
-                if (k > 1) {
-                    u64 z = 0;
-                    u32 one = 0; // the only nonzero word
-                    for (u64 m = sum_words<K + 1>(A, r); m; m &= m - 1) {
-                        const int w = __ffsll((unsigned long long)m) - 1;
-                        const u32 y = sum_word<K + 1>(A, r, w);
-                        if (y) {
-                            z |= 1ull << w;
-                            one = y;
-                        }
-                    }
-                    x = 0;
-                    if (is_unit(z, one)) {
-                        x = Sh.urow[(__ffsll((unsigned long long)z) - 1) * 32 + __ffs((int)one) - 1];
-                    } else if (z) {
-                        const int f = atomicSub(&Sh.nfree, 1);
-                        if (f > 0) x = A.rfree[f - 1];
-                        else x = (u32)atomicAdd(&Sh.nrows, 1);
-                        if (x < (u32)kDimRows) {
-                            for (int w = 0; w < W; ++w) A.pool[(int64_t)x * W + w] = sum_word<K + 1>(A, r, w);
-                            A.rsum[x] = z;
-                            rmap[x] = (uint16_t)x;
-                            A.ract[atomicAdd(&Sh.nact, 1)] = x;
-                            atomicAdd(&Sh.rows, 1ull);
-                            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                        } else {
-                            x = 0;
-                            Sh.fail = 1;
-                        }
-                    }
-                }
+                const u32 x = row_of_sum<K + 1>(A, Sh, rmap, r);
                 if (x) A.nzl[atomicAdd(&Sh.nnz, 1)] = q;
                 st(&A.ids[q], x);
             }
@@ -510,12 +960,70 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                 break;
             }
         }
+        // dimension 2: only the triangles that a nonzero one calls on. A sum
+        // taken too early is taken again: its last part calls once more.
+        if (K == 2 && vectors) {
+            const u32 w0 = n0 >> 5, w1 = n1 > n0 ? ((n1 - 1) >> 5) + 1 : w0;
+            for (int tries = 0;; ++tries) {
+                if (tid == 0) Sh.again = 0;
+                __syncthreads();
+                for (u32 w = w0 + tid; w < w1; w += kT) {
+                    const u32 from = w * 32 < n0 ? n0 & 31 : 0, to = n1 - w * 32 < 32 ? n1 & 31 : 32;
+                    const u32 in = (to == 32 ? ~0u : (1u << to) - 1) & ~((1u << from) - 1);
+                    u32 m = ld(&A.need[w]) & in;
+                    if (!m) continue;
+                    atomicAnd(&A.need[w], ~m);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                    Sh.again = 1;
+                    for (; m; m &= m - 1) {
+                        const u32 q = w * 32 + (u32)__ffs((int)m) - 1;
+                        u32 r[3];
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            r[i] = ld(&A.ids[min(A.qdep[(int64_t)i * A.N + q], (u32)A.N - 1)]);
+                            if (r[i] >= (u32)kDimRows) Sh.fail = kDimBroken;
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) r[i] = rmap[r[i] & (kDimRows - 1)] & (kDimRows - 1);
+                        const u32 was = ld(&A.ids[q]);
+                        const u32 x = row_of_sum<3>(A, Sh, rmap, r);
+                        if (x == was) continue;
+                        st(&A.ids[q], x);
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                        if (!was) {
+                            const int at = atomicAdd(&Sh.nnz, 1);
+                            if (at < (int)A.N) A.nzl[at] = q;
+                            else Sh.fail = 1;
+                            mark(A, q);
+                        }
+                        call_on(A, q);
+                    }
+                }
+                __syncthreads();
+                const bool again = Sh.again != 0;
+                __syncthreads();
+                if (!again) break;
+                if (tries > (1 << 16)) { // cannot happen: the order is acyclic
+                    if (tid == 0) Sh.fail = 1;
+                    break;
+                }
+            }
+        }
         __syncthreads();
         const bool none = Sh.nnz == 0, failed = Sh.fail != 0;
         if (tid == 0 && Sh.nfree < 0) Sh.nfree = 0;
         __syncthreads();
         if (failed) break;
+        if (K == 2 && vectors) break; // the last chunk of this launch
         if (none) continue;
+        const int np = K == 2 ? __builtin_amdgcn_readfirstlane(A.out->npair) : 0;
+        if (K == 2 && np > A.paircap) {
+            if (tid == 0) Sh.fail = 1;
+            __syncthreads();
+            break;
+        }
+        if (K == 2 && np == 0) continue;
         // ---- the owned cofacets whose facets do not cancel
         u32 lo_d = 0, hi_d = ~0u;
         u64 lo_i = 0, hi_i = ~0ull;
@@ -523,6 +1031,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
         for (;;) {
             if (tid == 0) Sh.ncand = 0;
             __syncthreads();
+            if constexpr (K == 1) {
             for (u32 b = t0 + (u32)wave * kWave; b < t1; b += kTaus * kT) {
                 // kTaus of them a lane, so that their loads are in flight together
                 u32 qs[kTaus], rs[kTaus][K + 2];
@@ -556,7 +1065,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
 #pragma unroll
                 for (int u = 0; u < kTaus; ++u) {
                 const u32 t = b + u * kT + (u32)lane;
-                u32 r[K + 2], id[K + 2];
+                u32 r[K + 2];
                 bool ok = false;
 #pragma unroll
                 for (int i = 0; i < K + 2; ++i) {
@@ -596,31 +1105,82 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                     ki = ~(u64)cofacet_index(v, K, c, A.c.B, &below);
                     ok = (first || key_less(lo_d, lo_i, kd, ki)) && !key_less(hi_d, hi_i, kd, ki);
                 }
-                // of the lanes with the same rows only the oldest cofacet
-                for (int i = 0; i < K + 2; ++i) id[i] = r[i];
-                for (u64 todo = __ballot(ok); todo;) {
-                    int l = __ffsll((unsigned long long)todo) - 1;
-                    bool same = ok;
+                candidates<K + 2>(A, Sh, vec, ccap, r, ok, kd, ki, z);
+                }
+            }
+            } else {
+                // those that k_lune_tests has found; a lane has several in flight
+                for (int b0 = wave * kWave; b0 < np; b0 += kTaus * kT) {
+                    u32 rs[kTaus][4];
+                    int va[kTaus], vb[kTaus], vc[kTaus], vd[kTaus];
+                    float len[kTaus];
+                    bool oks[kTaus], some = false, broken = false;
 #pragma unroll
-                    for (int i = 0; i < K + 2; ++i) same = same & (id[i] == (u32)__builtin_amdgcn_readlane(id[i], l));
-                    const u64 sm = __ballot(same);
-                    todo &= ~sm;
-                    for (u64 m = sm; m; m &= m - 1) { // the oldest of them
-                        const int j = __ffsll((unsigned long long)m) - 1;
-                        const u32 jd = __builtin_amdgcn_readlane(kd, j), bd = __builtin_amdgcn_readlane(kd, l);
-                        const u64 ji = lane_u64(ki, j), bi = lane_u64(ki, l);
-                        if (key_less(jd, ji, bd, bi)) l = j;
+                    for (int u = 0; u < kTaus; ++u) {
+                        const int i = b0 + u * kT + lane;
+                        const u64 pr = A.pairs[min(i, np - 1)];
+                        const u32 q = min((u32)(pr >> 32), (u32)A.N - 1);
+                        vd[u] = (int)(pr & 0xffff);
+                        tri_verts(A.qverts[q], va[u], vb[u], vc[u]);
+                        len[u] = A.qdiam[q];
+                        rs[u][0] = q;
+                        oks[u] = i < np;
                     }
-                    if (lane == l) {
-                        const int s = atomicAdd(&Sh.ncand, 1);
-                        if (s < ccap) {
-                            Sh.cd[s] = kd;
-                            Sh.ci[s] = ki;
-                            Sh.cz[s] = z;
-                            for (int w = 0; w < W; ++w) vec[s * W + w] = (z >> w) & 1ull ? sum_word<K + 2>(A, r, w) : 0u;
+#pragma unroll
+                    for (int u = 0; u < kTaus; ++u) {
+                        const int64_t ei = pair_idx(va[u], vb[u]);
+                        const float x = A.c.d.D[(int64_t)vd[u] * n + va[u]], y = A.c.d.D[(int64_t)vd[u] * n + vb[u]],
+                                    w = A.c.d.D[(int64_t)vd[u] * n + vc[u]];
+                        oks[u] = oks[u] && vd[u] != va[u] && vd[u] != vb[u] && vd[u] != vc[u] &&
+                                 edge_before(x, vd[u], va[u], len[u], ei) && edge_before(y, vd[u], vb[u], len[u], ei) &&
+                                 edge_before(w, vd[u], vc[u], len[u], ei);
+                        rs[u][1] = rs[u][2] = rs[u][3] = 0;
+                        if (oks[u]) {
+                            rs[u][1] = tri_place(A, va[u], vb[u], vd[u]);
+                            rs[u][2] = tri_place(A, va[u], vc[u], vd[u]);
+                            rs[u][3] = tri_place(A, vb[u], vc[u], vd[u]);
                         }
                     }
-                }
+#pragma unroll
+                    for (int u = 0; u < kTaus; ++u)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            broken = broken | (rs[u][i] >= (u32)A.N);
+                            rs[u][i] = A.ids[min(rs[u][i], (u32)A.N - 1)];
+                        }
+#pragma unroll
+                    for (int u = 0; u < kTaus; ++u) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            broken = broken | (rs[u][i] >= (u32)kDimRows);
+                            rs[u][i] = rmap[rs[u][i] & (kDimRows - 1)] & (kDimRows - 1);
+                        }
+                        oks[u] = oks[u] && cancel<4>(rs[u]) > 0;
+                        some = some | oks[u];
+                    }
+                    if (broken) Sh.fail = kDimBroken;
+                    if (!__any(some)) continue;
+#pragma unroll
+                    for (int u = 0; u < kTaus; ++u) {
+                        bool ok = oks[u];
+                        if (!__any(ok)) continue;
+                        u64 z = 0;
+                        if (ok)
+                            for (u64 m = sum_words<4>(A, rs[u]); m; m &= m - 1) {
+                                const int w = __ffsll((unsigned long long)m) - 1;
+                                if (sum_word<4>(A, rs[u], w)) z |= 1ull << w;
+                            }
+                        ok = ok && z != 0;
+                        u32 kd = 0;
+                        u64 ki = 0;
+                        if (ok) {
+                            if (bit_of(A, A.tied, va[u], vb[u])) Sh.fail = 1;
+                            kd = __float_as_uint(len[u]);
+                            ki = ~tet_index(A, va[u], vb[u], vc[u], vd[u]);
+                            ok = (first || key_less(lo_d, lo_i, kd, ki)) && !key_less(hi_d, hi_i, kd, ki);
+                        }
+                        candidates<4>(A, Sh, vec, ccap, rs[u], ok, kd, ki, z);
+                    }
                 }
             }
             __syncthreads();
@@ -781,6 +1341,16 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                 }
                 if (purge) {
                     // ---- the simplices' numbers brought up to date
+                    if constexpr (K == 2) {
+                        for (int i = tid; i < nz; i += kT) {
+                            int v[3];
+                            tri_verts(A.qverts[A.nzl[i]], v[0], v[1], v[2]);
+                            for (int x = 0; x < 3; ++x)
+                                for (int y = 0; y < 3; ++y)
+                                    if (x != y) A.fl[(int64_t)v[x] * A.fw + (v[y] >> 5)] = 0;
+                        }
+                        __syncthreads();
+                    }
                     for (int q0 = 0; q0 < nz; q0 += kT) {
                         const int i = q0 + tid;
                         const u32 q = i < nz ? A.nzl[i] : 0;
@@ -790,6 +1360,8 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
                             const u32 r = rmap[A.ids[q] & (kDimRows - 1)] & (kDimRows - 1);
                             A.ids[q] = r;
                             keep = r != 0;
+                            if constexpr (K == 2)
+                                if (keep) mark(A, q);
                         }
                         const int at = dim_append(keep, &Sh.nnz);
                         if (keep) A.nzl[at] = q;
@@ -817,6 +1389,12 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A) {
         if (Sh.fail) break;
     }
     __syncthreads();
+    if (K == 2) {
+        u32 *to = (u32 *)A.state;
+        for (int i = tid; i < kStateWords; i += kT) to[i] = ((LDS u32 *)&Sh)[i];
+        for (int i = tid; i < kDimRows / 2; i += kT) to[kStateWords + i] = ((LDS u32 *)rmap)[i];
+        if (tid == 0) A.out->npair = 0;
+    }
     if (tid == 0) {
         A.out->full = Sh.fail;
         A.out->adds = Sh.adds;
@@ -893,7 +1471,6 @@ __global__ void __launch_bounds__(1024) k_dim_bars(DimArgs A, BarBuf out, PivotH
         A.out->nonzero = at - s_ess;
         A.out->emergent = s_emg;
         A.out->reduced = s_red;
-        A.out->total = A.bin_t[A.nbins];
     }
 }
 
@@ -901,52 +1478,72 @@ unsigned blocks_for(int64_t n, int per) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, 16384));
 }
 
-template <int K>
-void partition_k(const DimArgs &A, hipStream_t st) {
-    launch_fill_u32(A.bin_n, 3 * (kDimBins + 64), 0u, st); // bin_n, bin_t and bin_s are one buffer
-    hipLaunchKernelGGL((k_dim_hist<K>), dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(2), dim3(kT), 0, st, A.bin_n, A.bin_s, A.nbins);
-    if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);
-    hipLaunchKernelGGL((k_dim_place<K>), dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
-    if (A.c.nb.off) hipLaunchKernelGGL((k_dim_own<K, 16, false>), dim3(blocks_for(A.N, 16)), dim3(256), 0, st, A);
-    else hipLaunchKernelGGL((k_dim_own<K, 64, false>), dim3(blocks_for(A.N, 4)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_t, A.bin_t, A.nbins);
-}
-
-template <int K>
-void fill_k(const DimArgs &A, hipStream_t st) {
-    if (A.c.nb.off) hipLaunchKernelGGL((k_dim_own<K, 16, true>), dim3(blocks_for(A.N, 16)), dim3(256), 0, st, A);
-    else hipLaunchKernelGGL((k_dim_own<K, 64, true>), dim3(blocks_for(A.N, 4)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL((k_dim_births<K>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_chunks, dim3(1), dim3(kT), 0, st, A);
-}
-
 constexpr int kSweepLds = kCandWords * 4 + kDimRows * 2;
-
-template <int K>
-hipError_t sweep_k(const DimArgs &A, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_dim_sweep<K>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kSweepLds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_dim_sweep<K>), dim3(1), dim3(kT), kSweepLds, st, A);
-    return hipSuccess;
-}
 
 } // namespace
 
-void launch_dim_partition(int K, const DimArgs &A, hipStream_t st) {
-    if (K == 1) partition_k<1>(A, st);
-    else partition_k<2>(A, st);
+void launch_dim_partition(const DimArgs &A, hipStream_t st) {
+    launch_fill_u32(A.bin_n, 3 * (kDimBins + 64), 0u, st); // bin_n, bin_t and bin_s are one buffer
+    hipLaunchKernelGGL((k_dim_hist<1>), dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_scan, dim3(2), dim3(kT), 0, st, A.bin_n, A.bin_s, A.nbins);
+    if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);
+    hipLaunchKernelGGL(k_dim_place, dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
+    if (A.c.nb.off) hipLaunchKernelGGL((k_dim_own<16, false>), dim3(blocks_for(A.N, 16)), dim3(256), 0, st, A);
+    else hipLaunchKernelGGL((k_dim_own<64, false>), dim3(blocks_for(A.N, 4)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_t, A.bin_t, A.nbins);
 }
 
-void launch_dim_fill(int K, const DimArgs &A, hipStream_t st) {
-    if (K == 1) fill_k<1>(A, st);
-    else fill_k<2>(A, st);
+void launch_dim_fill(const DimArgs &A, hipStream_t st) {
+    if (A.c.nb.off) hipLaunchKernelGGL((k_dim_own<16, true>), dim3(blocks_for(A.N, 16)), dim3(256), 0, st, A);
+    else hipLaunchKernelGGL((k_dim_own<64, true>), dim3(blocks_for(A.N, 4)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL((k_dim_births<1>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_chunks, dim3(1), dim3(kT), 0, st, A);
 }
 
-hipError_t launch_dim_sweep(int K, const DimArgs &A, hipStream_t st) {
-    return K == 1 ? sweep_k<1>(A, st) : sweep_k<2>(A, st);
+void launch_lune_partition(const DimArgs &A, PivotHash piv, hipStream_t st) {
+    const int64_t words = (int64_t)A.c.n * A.fw;
+    launch_fill_u32(A.bin_n, 3 * (kDimBins + 64), 0u, st);
+    launch_fill_u32((u32 *)A.out, sizeof(DimOut) / 4, 0u, st);
+    launch_fill_u32(A.fl, words, 0u, st);
+    launch_fill_u32(A.tied, words, 0u, st);
+    launch_fill_u32(A.rhead, A.N, ~0u, st);
+    launch_fill_u32(A.need, A.N / 32 + 1, 0u, st);
+    if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);
+    hipLaunchKernelGGL((k_lune<false>), dim3(blocks_for(A.nE, 4)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_n, A.bin_n, A.nbins);
+    hipLaunchKernelGGL((k_lune<true>), dim3(blocks_for(A.nE, 4)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_lune_deps, dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_lune_classes, dim3(1), dim3(kT), 0, st, A, piv);
 }
+
+void launch_lune_chunks(const DimArgs &A, hipStream_t st) {
+    hipLaunchKernelGGL((k_dim_hist<2>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_s, A.bin_s, A.nbins);
+    hipLaunchKernelGGL((k_dim_births<2>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
+    hipLaunchKernelGGL(k_dim_chunks, dim3(1), dim3(kT), 0, st, A);
+}
+
+hipError_t launch_dim_sweep(const DimArgs &A, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_dim_sweep<1>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kSweepLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_dim_sweep<1>), dim3(1), dim3(kT), kSweepLds, st, A, 0);
+    return hipSuccess;
+}
+
+hipError_t launch_lune_sweep(const DimArgs &A, int chunks, hipStream_t st) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_dim_sweep<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       kSweepLds);
+    if (e != hipSuccess) return e;
+    const unsigned grid = blocks_for((int64_t)A.chunk_n, 4);
+    for (int c = 0; c <= chunks; ++c) { // those past the last chunk end at once
+        hipLaunchKernelGGL((k_dim_sweep<2>), dim3(1), dim3(kT), kSweepLds, st, A, c);
+        if (c < chunks) hipLaunchKernelGGL(k_lune_tests, dim3(grid), dim3(256), 0, st, A, c);
+    }
+    return hipSuccess;
+}
+
+size_t dim_state_bytes() { return (size_t)kStateWords * 4 + (size_t)kDimRows * 2; }
 
 void launch_dim_bars(int K, const DimArgs &A, BarBuf bars, PivotHash piv, hipStream_t st) {
     if (K == 1) hipLaunchKernelGGL(k_dim_bars<1>, dim3(1), dim3(kT), 0, st, A, bars, piv);

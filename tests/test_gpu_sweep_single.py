@@ -1,8 +1,9 @@
 """GPU parity of the sweep of one cloud with the column reduction, bit for bit:
 the whole cloud by one workgroup (small clouds, and any without a threshold),
-and dimension 1 in chunks (larger ones of 32 to 200 edges a point), on both
-sides of each rule, from points and from a distance matrix; and where a table
-is full or a distance overflows and the other path takes over."""
+dimension 1 in chunks (larger ones of 32 to 200 edges a point) and dimension 2
+by blocks of one longest edge, on both sides of each rule, from points and from
+a distance matrix; and where a table is full, a distance overflows or edges of
+equal length meet and the other path takes over."""
 
 import numpy as np
 import pytest
@@ -115,3 +116,46 @@ def test_chunked_sweep_vs_column_reduction(data, n, degree):
     t = degree_threshold(x, degree) if n < 24000 else 0.138
     print(f"[case] chunked sweep {data} n={n} degree={degree} t={t}", flush=True)
     both(torch.from_numpy(x).cuda(), max_dim=1, threshold=t)
+
+
+def octahedra(k, seed):
+    """k crosses of R^3 side by side, points slightly moved: k voids."""
+    g = workloads.rng(seed)
+    a = np.concatenate([np.eye(3), -np.eye(3)])
+    x = np.concatenate([a + [5.0 * i, 0.0, 0.0] for i in range(k)]) + 0.02 * g.standard_normal((6 * k, 3))
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["sphere-5", "sphere-12", "sphere-64", "sphere-65", "sphere-129", "cube-70", "so3-300",
+                                  "o3-300", "mixture-90", "voids-80", "lattice-60", "line-40", "torus-1500"])
+def test_dimension_2_by_blocks_vs_column_reduction(kind):
+    import torch
+    name, n = kind.split("-")
+    n = int(n)
+    s = workloads.SEED_BASE + n
+    x, t, max_dim = {
+        "sphere": lambda: (workloads.sphere(n, s), INF, 2),
+        "cube": lambda: (workloads.uniform_cube(n, 5, s), INF, 2),      # trees joined late, many classes
+        "so3": lambda: (workloads.so3(n, s), 1.4, 2),
+        "o3": lambda: (workloads.orthogonal(n, s), 1.8, 3),             # a dimension follows: pivots handed on
+        "mixture": lambda: (workloads.mixture_cloud(s, n, n), INF, 2),
+        "voids": lambda: (octahedra(n, s), 2.1, 3),
+        "lattice": lambda: (workloads.integer_lattice(n, 3, s), INF, 2),  # ties everywhere: columns
+        "line": lambda: (workloads.uniform_cube(n, 1, s), INF, 2),      # no class at all
+        "torus": lambda: (workloads.clifford_torus(n, 0.02, s), 0.55, 2),
+    }[name]()
+    print(f"[case] dimension 2 {kind}", flush=True)
+    both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t)
+
+
+def test_dimension_2_large_lune():
+    """A lune of more points than one block's forest holds: columns."""
+    import torch
+    g = workloads.rng(workloads.SEED_BASE)
+    x = (0.01 * g.standard_normal((1100, 3))).astype(np.float32)
+    x[:2] = [[-1, 0, 0], [1, 0, 0]]
+    d = np.sqrt(((x[:, None] - x[None]) ** 2).sum(2, dtype=np.float32))
+    far = (d > 0.004) & (d < 0.9)  # the middle's own edges are too long but for a few
+    d[far] = 3.0
+    print("[case] dimension 2 large lune", flush=True)
+    both(torch.from_numpy(np.ascontiguousarray(d)).cuda(), max_dim=2, threshold=2.5, is_distance=True)
