@@ -714,6 +714,7 @@ __device__ __forceinline__ void call_on(const DimArgs &A, u32 q) {
 
 // the sweep's LDS in global memory: DimShared, then the row map
 constexpr int kStateWords = sizeof(DimShared) / 4;
+constexpr int kStateScalars = offsetof(DimShared, kp) / 4; // of them those before the arrays
 
 // ---- dimension 2: the tetrahedra e + {c, d} of a chunk's blocks whose facets
 // do not cancel. One wave a triangle e + c, its lanes the d's of the block;
@@ -864,9 +865,16 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
     const bool more = K == 2 && chunk > 0; // the tables as the launch before left them
     if (more) {
         if (chunk > nch || A.out->full) return;
-        const u32 *from = (const u32 *)A.state;
-        for (int i = tid; i < kStateWords; i += kT) ((LDS u32 *)&Sh)[i] = from[i];
-        for (int i = tid; i < kDimRows / 2; i += kT) ((LDS u32 *)rmap)[i] = from[kStateWords + i];
+        const DimShared *S = (const DimShared *)A.state;
+        const u32 *from = (const u32 *)S, *rm = from + kStateWords;
+        const int rows = S->nrows;
+        for (int i = tid; i < kStateScalars; i += kT) ((LDS u32 *)&Sh)[i] = from[i];
+        for (int i = tid; i < nslots; i += kT) {
+            Sh.sage[i] = S->sage[i];
+            Sh.urow[i] = S->urow[i];
+            Sh.sl[i] = S->sl[i];
+        }
+        for (int i = tid; 2 * i < rows; i += kT) ((LDS u32 *)rmap)[i] = rm[i];
     } else {
         if (tid == 0) {
             Sh.nact = Sh.nnz = Sh.fail = Sh.nfree = Sh.ndead = Sh.since = 0;
@@ -1390,9 +1398,16 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
     }
     __syncthreads();
     if (K == 2) {
-        u32 *to = (u32 *)A.state;
-        for (int i = tid; i < kStateWords; i += kT) to[i] = ((LDS u32 *)&Sh)[i];
-        for (int i = tid; i < kDimRows / 2; i += kT) to[kStateWords + i] = ((LDS u32 *)rmap)[i];
+        DimShared *S = (DimShared *)A.state;
+        u32 *to = (u32 *)S, *rm = to + kStateWords;
+        const int rows = min(Sh.nrows, kDimRows);
+        for (int i = tid; i < kStateScalars; i += kT) to[i] = ((LDS u32 *)&Sh)[i];
+        for (int i = tid; i < nslots; i += kT) {
+            S->sage[i] = Sh.sage[i];
+            S->urow[i] = Sh.urow[i];
+            S->sl[i] = Sh.sl[i];
+        }
+        for (int i = tid; 2 * i < rows; i += kT) rm[i] = ((LDS u32 *)rmap)[i];
         if (tid == 0) A.out->npair = 0;
     }
     if (tid == 0) {
