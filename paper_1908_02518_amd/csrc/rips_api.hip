@@ -867,14 +867,15 @@ struct SweepScal {
 
 // The per-workgroup buffers of `grid` sweep workgroups for clouds of up to
 // n_max points.
-rips_status sweep_buffers(DevCtx &C, int n_max, int64_t grid, SweepArgs &A, SweepScal **scal) {
+rips_status sweep_buffers(DevCtx &C, int n_max, uint32_t p, int64_t grid, SweepArgs &A, SweepScal **scal) {
     void *q;
     const int64_t npairs = (int64_t)n_max * (n_max - 1) / 2;
     A.nmax = n_max;
     A.d_stride = (int64_t)n_max * n_max;
     A.e_stride = (npairs + 16) / 8 * 8;
     A.sv_cap = sweep_sv_cap(n_max);
-    A.pool_stride = sweep_pool_words(n_max);
+    A.p = p;
+    A.pool_stride = sweep_pool_words(n_max, p);
     A.mask_stride = (int64_t)n_max * sweep_mask_words(n_max);
 #define ENS(id, bytes, field, T)                                                                   \
     do {                                                                                           \
@@ -896,13 +897,13 @@ rips_status sweep_buffers(DevCtx &C, int n_max, int64_t grid, SweepArgs &A, Swee
     A.queue = &(*scal)->queue;
     A.ucount = &(*scal)->ucount;
     A.status = &(*scal)->status;
-    HIP_TRY(sweep_prepare(n_max, A.sv_cap));
+    HIP_TRY(sweep_prepare(n_max, A.sv_cap, p));
     return RIPS_OK;
 }
 
 // The default method may run: no setting asks for a reduction of columns.
-bool sweep_allowed(const DevCtx &C, uint32_t p) {
-    return p == 2 && !C.arena && C.cocycle_dim < 0 && C.working_column == RIPS_WORKING_COLUMN_AUTO &&
+bool sweep_allowed(const DevCtx &C) {
+    return !C.arena && C.cocycle_dim < 0 && C.working_column == RIPS_WORKING_COLUMN_AUTO &&
            !C.by_columns && C.shortcuts == (kShortApparent | kShortEmergent | kShortClearing) &&
            C.rstore == kRStoreAuto;
 }
@@ -916,9 +917,18 @@ bool sweep_allowed(const DevCtx &C, uint32_t p) {
 // largest cloud it takes (sphere: 400 points 1.9 and 7.2 ms, 1000 points 10
 // and 36; noisy circles: 400 points 2.3 and 13.6, 1000 points 17 and 217).
 constexpr int kSweepSingleN = 256;
+// Over another field a sum costs products and remainders for every class it
+// has, and many classes are open at once where the points are spread out in
+// many dimensions: the largest sizes at which none of spheres, circles, normal
+// and uniform points of 2 to 4 dimensions was slower (without a threshold,
+// 171 points: sphere 0.72 and 2.3 ms, uniform 0.67 and 1.2, normal in R^4
+// 1.08 and 1.11; 230 points: normal in R^3 1.5 and 1.2; threshold 1.4 on
+// rotations: 100 points 0.20 and 0.35, 200 points 0.70 and 0.51).
+constexpr int kSweepOddN = 200, kSweepOddSingleN = 128;
 
 bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint32_t p) {
-    return n >= 2 && max_dim <= 1 && n <= (std::isinf(threshold) ? kSweepMaxN : kSweepSingleN) && sweep_allowed(C, p);
+    const int most = std::isinf(threshold) ? (p == 2 ? kSweepMaxN : kSweepOddN) : (p == 2 ? kSweepSingleN : kSweepOddSingleN);
+    return n >= 2 && max_dim <= 1 && n <= most && sweep_allowed(C);
 }
 
 // Edges per point between which a larger cloud's dimension 1 is swept in
@@ -933,12 +943,12 @@ constexpr int64_t kSweepDegMin = 32, kSweepDegMax = 200;
 // One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
 // report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
 // every dimension fits. *full as in batched_sweep.
-rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, BarBuf bars, int64_t cap,
-                         bool columns, hipStream_t st, RunOut &o, bool *full) {
+rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, uint32_t p,
+                         BarBuf bars, int64_t cap, bool columns, hipStream_t st, RunOut &o, bool *full) {
     SweepArgs A;
     memset(&A, 0, sizeof(A));
     SweepScal *scal;
-    rips_status rs = sweep_buffers(C, n, 1, A, &scal);
+    rips_status rs = sweep_buffers(C, n, p, 1, A, &scal);
     if (rs) return rs;
     A.X = d_in;
     A.B = 1;
@@ -1233,7 +1243,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         launch_reset_dim(P.scal, st);
         // dimension 1 over Z/2 takes the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
-        const bool sweep = k <= 2 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C, p) &&
+        const bool sweep = p == 2 && k <= 2 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C) &&
                            (k == 2 || (P.nedges >= kSweepDegMin * n / 2 && P.nedges <= kSweepDegMax * n / 2));
         SimplexList cand;
         int64_t ncand;
@@ -1901,7 +1911,7 @@ rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_off
     SweepArgs A;
     memset(&A, 0, sizeof(A));
     SweepScal *scal;
-    rips_status rs = sweep_buffers(C, n_max, grid, A, &scal);
+    rips_status rs = sweep_buffers(C, n_max, 2, grid, A, &scal);
     if (rs) return rs;
     A.X = d_points;
     A.offsets = d_offsets;
@@ -2244,7 +2254,7 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
     if (sweeps_whole(*C, n, max_dim, threshold, p)) {
         bool full = false;
         const bool room = out->birth && out->death && out->birth_simplex && out->death_simplex && out->cap > 0;
-        rs = single_sweep(*C, d_data, (int)n, dim, max_dim, threshold,
+        rs = single_sweep(*C, d_data, (int)n, dim, max_dim, threshold, p,
                           BarBuf{out->birth, out->death, out->birth_simplex, out->death_simplex}, room ? out->cap : -1,
                           false, st, o, &full);
         if (rs) return rs;
@@ -2351,7 +2361,7 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
         HIP_TRY(C->ensure(B_BAR_DS, (size_t)cap * 16, &q));
         bars.ds = as<int64_t>(q);
         full = false;
-        rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, bars, cap, true, st, o, &full);
+        rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, p, bars, cap, true, st, o, &full);
         swept_cap = full ? 0 : cap;
     }
     if (!rs && full) rs = run_single(*C, d_in, (int)n, dim, max_dim, threshold, p, st, o);

@@ -1,4 +1,4 @@
-// rips_sweep.hip -- dimensions 0 and 1 of a cloud over Z/2 in one sweep over
+// rips_sweep.hip -- dimensions 0 and 1 of a cloud over Z/p in one sweep over
 // its edges in order of length, one workgroup per cloud.
 //
 // The pairs of a filtration are those of its boundary matrix and of its
@@ -23,6 +23,11 @@
 // million triangles, 74 classes, 94 rows ever, and 6,700 edges whose
 // triangles are looked at. What is left is the distances and one scan per
 // edge for its zero apparent cofacet.
+//
+// Over Z/2 a row is bits. Over another field (kOdd) it is those bits and
+// residues, 16 bits a class, an edge holds a row and a coefficient, and the vectors are a cochain:
+// its value on the coboundary's triangle of vertices x < y < z is that of
+// (y, z) less that of (x, z) plus that of (x, y).
 #include "rips_sweep.hpp"
 
 #include <algorithm>
@@ -54,6 +59,7 @@ struct SweepShared {
     u32 cstart[kMaxChunks + 1]; // first list entry of a chunk
     u32 cbin[kMaxChunks + 1];   // first bin after a chunk
     int kp[kSweepCand], ki[kSweepCand]; // kills: class, candidate
+    u32 kinv[kSweepCand];               // and the inverse of its coefficient
 };
 
 // The dynamic LDS of a cloud of n points.
@@ -197,9 +203,97 @@ struct Rows {
         if ((int)r < nl) lds[o] = x;
         else glob[o] = x;
     }
+    // half words, after the first nm words
+    __device__ __forceinline__ u32 half(u32 r, int nm, int k) const {
+        const int o = ((int)r * W + nm) * 2 + k;
+        return (int)r < nl ? ((const LDS uint16_t *)lds)[o] : ((const uint16_t *)glob)[o];
+    }
+    __device__ __forceinline__ void set_half(u32 r, int nm, int k, u32 x) const {
+        const int o = ((int)r * W + nm) * 2 + k;
+        if ((int)r < nl) ((LDS uint16_t *)lds)[o] = (uint16_t)x;
+        else ((uint16_t *)glob)[o] = (uint16_t)x;
+    }
 };
 
 __device__ __forceinline__ u32 row_word(const Rows &P, u32 r, int w) { return r ? P.get(r, w) : 0u; }
+
+// ---- kOdd: an edge's id is a row (low half) and a coefficient in [1, p), or 0
+__device__ __forceinline__ u32 id_neg(u32 id, u32 p) { return id ? (id & 0xffffu) | ((p - (id >> 16)) << 16) : 0u; }
+__device__ __forceinline__ u32 id_if_neg(u32 id, bool neg, u32 p) { return neg ? id_neg(id, p) : id; }
+
+// A row of residues: first a bit for each class, set where it is not zero,
+// then the residues, 16 bits each, of which those without a bit are not read.
+
+// the bits of word mw of up to three of them
+__device__ __forceinline__ u32 odd_bits(const Rows &P, u32 i0, u32 i1, u32 i2, int mw) {
+    return (i0 ? P.get(i0 & 0xffffu, mw) : 0u) | (i1 ? P.get(i1 & 0xffffu, mw) : 0u) |
+           (i2 ? P.get(i2 & 0xffffu, mw) : 0u);
+}
+
+// the residue at class k of their sum
+__device__ __forceinline__ u32 odd_at(const Rows &P, u32 i0, u32 i1, u32 i2, int k, int nm, u32 p) {
+    const u32 id[3] = {i0, i1, i2};
+    u64 t = 0; // three products below 2^32
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        if (id[q] && ((P.get(id[q] & 0xffffu, k >> 5) >> (k & 31)) & 1u))
+            t += (u64)(id[q] >> 16) * P.half(id[q] & 0xffffu, nm, k);
+    return t < (1ull << 32) ? (u32)t % p : (u32)(t % p);
+}
+
+__device__ __forceinline__ bool odd_any(const Rows &P, u32 i0, u32 i1, u32 i2, int nm, u32 p) {
+    for (int mw = 0; mw < nm; ++mw)
+        for (u32 m = odd_bits(P, i0, i1, i2, mw); m; m &= m - 1)
+            if (odd_at(P, i0, i1, i2, mw * 32 + __ffs((int)m) - 1, nm, p)) return true;
+    return false;
+}
+
+// their sum, written by put(word, bits) and res(class, residue)
+template <class Put, class Res>
+__device__ __forceinline__ void odd_sum(const Rows &P, u32 i0, u32 i1, u32 i2, int nm, u32 p, Put put, Res res) {
+    for (int mw = 0; mw < nm; ++mw) {
+        u32 bits = 0;
+        for (u32 m = odd_bits(P, i0, i1, i2, mw); m; m &= m - 1) {
+            const int k = mw * 32 + __ffs((int)m) - 1;
+            const u32 x = odd_at(P, i0, i1, i2, k, nm, p);
+            if (!x) continue;
+            bits |= m & (0u - m);
+            res(k, x);
+        }
+        put(mw, bits);
+    }
+}
+
+// x less f times the candidate kv, both as rows; is anything left?
+template <class Get, class Put, class GetRes, class Res>
+__device__ __forceinline__ bool odd_less(Get get, Put put, GetRes get_res, Res res, u32 f, const LDS u32 *kv, int nm,
+                                         u32 p) {
+    const LDS uint16_t *kr = (const LDS uint16_t *)(kv + nm);
+    u32 any = 0;
+    for (int mw = 0; mw < nm; ++mw) {
+        u32 bits = get(mw);
+        const u32 take = kv[mw];
+        for (u32 m = take; m; m &= m - 1) {
+            const u32 bit = m & (0u - m);
+            const int k = mw * 32 + __ffs((int)m) - 1;
+            const u32 x = (u32)(((bits & bit ? get_res(k) : 0u) + (u64)(p - f) * kr[k]) % p);
+            if (x) res(k, x);
+            bits = x ? bits | bit : bits & ~bit;
+        }
+        if (take) put(mw, bits);
+        any |= bits;
+    }
+    return any != 0;
+}
+
+__device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
+    u32 r = 1;
+    for (u32 e = p - 2; e; e >>= 1) {
+        if (e & 1u) r = (u32)((u64)r * a % p);
+        a = (u32)((u64)a * a % p);
+    }
+    return r;
+}
 
 // The nonzero-edge bits: in LDS up to kSweepMaskBytes, else in global memory.
 template <bool kMaskLds>
@@ -221,6 +315,8 @@ struct TestArgs {
     const u32 *ids;
     int n, MW, nw, ccap;
     u64 lo, hi;
+    u32 p;
+    int nm; // kOdd: words of a row's bits
 };
 
 // The triangles of the listed edges whose vectors do not cancel, appended to
@@ -231,7 +327,7 @@ struct TestArgs {
 // used. (With one work item per edge and word, the setup of each cost more
 // than its test: circles-64x400 5.8 ms, so 41,000 items a cloud at 440
 // instructions each.)
-template <int NE, int NW, class Mask>
+template <bool kOdd, int NE, int NW, class Mask>
 __device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const Rows &P, SweepShared &Sh,
                                            const SweepLds &L, int wave, int lane) {
     constexpr int N = NE * NW;
@@ -277,8 +373,18 @@ __device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const R
                     r1[u] = ba ? r1[u] : 0u;
                     r2[u] = bv ? r2[u] : 0u;
                     // two equal rows and a zero one cancel
-                    const u32 sum = r0[g] ^ r1[u] ^ r2[u];
-                    const bool gone = sum == 0 && (r0[g] == 0 || r1[u] == 0 || r2[u] == 0);
+                    bool gone;
+                    if constexpr (kOdd) {
+                        // the edge between the triangle's ends has the minus sign
+                        const u32 i0 = id_if_neg(r0[g], c < ea[g] && c > ev[g], T.p);
+                        const u32 i1 = r1[u] = id_if_neg(r1[u], c < ev[g], T.p);
+                        const u32 i2 = r2[u] = id_if_neg(r2[u], c > ea[g], T.p);
+                        gone = (i0 == 0 && id_neg(i1, T.p) == i2) || (i1 == 0 && id_neg(i0, T.p) == i2) ||
+                               (i2 == 0 && id_neg(i0, T.p) == i1);
+                    } else {
+                        const u32 sum = r0[g] ^ r1[u] ^ r2[u];
+                        gone = sum == 0 && (r0[g] == 0 || r1[u] == 0 || r2[u] == 0);
+                    }
                     nz[u] = far <= len[g] && !gone && c < n && q + g < T.nw;
                     some = some || nz[u];
                     tie = tie || (nz[u] && far == len[g]);
@@ -297,11 +403,14 @@ __device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const R
             for (int u = 0; u < N; ++u) {
                 const int g = u / NW, a = ea[g], v = ev[g], c = (w0 + u % NW) * 64 + lane;
                 if (!__any(nz[u])) continue;
-                const u32 p0 = r0[g], p1 = r1[u], p2 = r2[u];
+                const u32 p0 = kOdd ? id_if_neg(r0[g], c < a && c > v, T.p) : r0[g], p1 = r1[u], p2 = r2[u];
+                auto word = [&](int w) { return row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w); };
                 u32 any = 0;
                 u64 key = 0;
                 if (nz[u]) {
-                    for (int w = 0; w < W; ++w) any |= row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
+                    if constexpr (kOdd) any = odd_any(P, p0, p1, p2, T.nm, T.p) ? 1u : 0u;
+                    else
+                        for (int w = 0; w < W; ++w) any |= word(w);
                     key = ((u64)__float_as_uint(len[g]) << 32) | (u64)(0xffffffffu - triangle_index(a, v, c));
                 }
                 const bool open = nz[u] && any != 0 && key > T.lo && key <= T.hi;
@@ -310,13 +419,19 @@ __device__ __forceinline__ void test_edges(const TestArgs &T, Mask mask, const R
                 while (todo) {
                     const int l = 63 - __clzll((long long)todo);
                     const u32 q1 = __builtin_amdgcn_readlane(p1, l), q2 = __builtin_amdgcn_readlane(p2, l);
-                    todo &= ~__ballot(open && ((p1 == q1 && p2 == q2) || (p1 == q2 && p2 == q1)));
+                    const u32 q0 = kOdd ? __builtin_amdgcn_readlane(p0, l) : p0;
+                    todo &= ~__ballot(open && p0 == q0 && ((p1 == q1 && p2 == q2) || (p1 == q2 && p2 == q1)));
                     if (lane == l) {
                         const int s = atomicAdd(&Sh.ncand, 1);
                         if (s < T.ccap) {
                             L.keys[s] = key;
-                            for (int w = 0; w < W; ++w)
-                                L.vec[s * W + w] = row_word(P, p0, w) ^ row_word(P, p1, w) ^ row_word(P, p2, w);
+                            if constexpr (kOdd)
+                                odd_sum(P, p0, p1, p2, T.nm, T.p, [&](int w, u32 x) { L.vec[s * W + w] = x; },
+                                        [&](int k, u32 x) {
+                                            ((LDS uint16_t *)(L.vec + s * W + T.nm))[k] = (uint16_t)x;
+                                        });
+                            else
+                                for (int w = 0; w < W; ++w) L.vec[s * W + w] = word(w);
                         }
                     }
                 }
@@ -338,7 +453,7 @@ __device__ __forceinline__ void sweep_reject(const SweepArgs &A, int b, int D1, 
     if (threadIdx.x == 0 && why) atomicOr(A.status, why);
 }
 
-template <bool kMaskLds>
+template <bool kMaskLds, bool kOdd>
 __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem, SweepShared &Sh) {
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -589,7 +704,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                     const int k = ncls + __popcll(cls & ((1ull << lane) - 1));
                     ckey[k] = key;
                     kkey[k] = ~0ull;
-                    id = (u32)k + 1;
+                    id = (u32)k + 1 + (kOdd ? 1u << 16 : 0u);
                 }
                 ids[(int64_t)a * n + v] = id;
                 ids[(int64_t)v * n + a] = id;
@@ -601,11 +716,12 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     }
     __syncthreads();
     const int S = __builtin_amdgcn_readfirstlane(Sh.ncls);
-    const int W = (S + 31) / 32;
+    const int nm = (S + 31) / 32, W = kOdd ? nm + (S + 1) / 2 : nm;
+    const u32 p = A.p;
     const Rows P{L.pool, A.pool + wg * A.pool_stride, W > 0 ? kPoolLdsWords / W : 0, W};
-    const int rcap = W > 0 ? (int)min((int64_t)(1 << 30), A.pool_stride / W) : 0;
+    const int rcap = W > 0 ? (int)min((int64_t)(kOdd ? 0xffff : 1 << 30), A.pool_stride / W) : 0;
     if (max_dim >= 1 && S > 0) {
-        if (S > kSweepMaxClasses || S + 1 >= rcap) {
+        if (S > (kOdd ? kSweepOddClasses : kSweepMaxClasses) || S + 1 >= rcap) {
             sweep_reject(A, b, D1, kSweepFull);
             __syncthreads();
             return;
@@ -670,7 +786,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
         // the unit rows of the classes
         for (int q = tid; q < S * W; q += kT) {
             const int k = q / W, w = q - k * W;
-            P.set((u32)k + 1, w, w == (k >> 5) ? 1u << (k & 31) : 0u);
+            P.set((u32)k + 1, w, w < nm ? (w == (k >> 5) ? 1u << (k & 31) : 0u) : 0x10001u);
         }
         __syncthreads();
         const int nch = __builtin_amdgcn_readfirstlane(Sh.nch);
@@ -723,8 +839,32 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                         left = true;
                         continue;
                     }
-                    u32 r = r1 == r2 ? 0u : (r1 ? (r2 ? kPending : r1) : r2);
-                    if (r == kPending) {
+                    u32 r;
+                    if constexpr (kOdd) {
+                        const u32 i1 = id_if_neg(r1, (int)c > a, p), i2 = id_if_neg(r2, (int)c < v, p);
+                        if (i1 == 0 || i2 == 0) {
+                            r = i1 | i2;
+                        } else if (((i1 ^ i2) & 0xffffu) == 0) {
+                            const u32 cf = ((i1 >> 16) + (i2 >> 16)) % p;
+                            r = cf ? (i1 & 0xffffu) | (cf << 16) : 0u;
+                        } else {
+                            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                            r = 0;
+                            if (odd_any(P, i1, i2, 0, nm, p)) {
+                                const u32 at = (u32)atomicAdd(&Sh.nrows, 1);
+                                if ((int)at < rcap) {
+                                    odd_sum(P, i1, i2, 0, nm, p, [&](int w, u32 x) { P.set(at, w, x); },
+                                            [&](int k, u32 x) { P.set_half(at, nm, k, x); });
+                                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                                    r = at | (1u << 16);
+                                } else {
+                                    Sh.fail = 1;
+                                }
+                            }
+                        }
+                    } else
+                        r = r1 == r2 ? 0u : (r1 ? (r2 ? kPending : r1) : r2);
+                    if (!kOdd && r == kPending) {
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                         u32 any = 0;
                         for (int w = 0; w < W; ++w) any |= P.get(r1, w) ^ P.get(r2, w);
@@ -784,10 +924,10 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                     if (look) Sh.work[at] = ab;
                     __syncthreads();
                     const int nw = Sh.nwork;
-                    const TestArgs TA{D, ids, n, MW, nw, ccap, lo, hi};
-                    if (MW == 1) test_edges<4, 1>(TA, mask, P, Sh, L, wave, lane);
-                    else if (MW == 2) test_edges<2, 2>(TA, mask, P, Sh, L, wave, lane);
-                    else test_edges<1, 4>(TA, mask, P, Sh, L, wave, lane);
+                    const TestArgs TA{D, ids, n, MW, nw, ccap, lo, hi, p, nm};
+                    if (MW == 1) test_edges<kOdd, 4, 1>(TA, mask, P, Sh, L, wave, lane);
+                    else if (MW == 2) test_edges<kOdd, 2, 2>(TA, mask, P, Sh, L, wave, lane);
+                    else test_edges<kOdd, 1, 4>(TA, mask, P, Sh, L, wave, lane);
                     __syncthreads();
                     if (tid == 0) Sh.nwork = 0;
                     __syncthreads();
@@ -829,27 +969,39 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                         if (mn == ~0ull) break;
                         const int src = __ffsll((unsigned long long)__ballot(best == mn)) - 1;
                         bi = __builtin_amdgcn_readlane(bi, src);
-                        const u32 wd = lane < W ? L.vec[bi * W + lane] : 0u;
+                        // the youngest class
+                        const u32 wd = lane < nm ? L.vec[bi * W + lane] : 0u;
                         const u64 nzw = __ballot(wd != 0u);
                         const int top = 63 - __clzll((long long)nzw);
                         const u32 tw = __builtin_amdgcn_readlane(wd, top);
-                        const int p = top * 32 + 31 - __clz((int)tw); // the youngest class
+                        const int cls = top * 32 + 31 - __clz((int)tw);
+                        const u32 inv = kOdd ? odd_inverse(((LDS uint16_t *)(L.vec + bi * W + nm))[cls], p) : 1u;
                         if (lane == 0) {
-                            kkey[p] = mn;
-                            Sh.kp[nk] = p;
+                            kkey[cls] = mn;
+                            Sh.kp[nk] = cls;
+                            Sh.kinv[nk] = inv;
                             Sh.ki[nk] = bi;
                             L.keys[bi] = ~0ull;
                         }
                         ++nk;
                         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                         for (int j = lane; j < nc; j += kWave) {
-                            if (L.keys[j] == ~0ull || !((L.vec[j * W + (p >> 5)] >> (p & 31)) & 1u)) continue;
+                            if (L.keys[j] == ~0ull || !((L.vec[j * W + (cls >> 5)] >> (cls & 31)) & 1u)) continue;
                             u32 any = 0;
-                            for (int w = 0; w < W; ++w) {
-                                const u32 z = L.vec[j * W + w] ^ L.vec[bi * W + w];
-                                L.vec[j * W + w] = z;
-                                any |= z;
-                            }
+                            if constexpr (kOdd) {
+                                LDS u32 *x = L.vec + j * W;
+                                LDS uint16_t *xr = (LDS uint16_t *)(x + nm);
+                                const u32 f = (u32)((u64)xr[cls] * inv % p);
+                                any = odd_less([&](int w) { return x[w]; }, [&](int w, u32 y) { x[w] = y; },
+                                               [&](int k) { return (u32)xr[k]; },
+                                               [&](int k, u32 y) { xr[k] = (uint16_t)y; }, f, L.vec + bi * W, nm, p)
+                                          ? 1u : 0u;
+                            } else
+                                for (int w = 0; w < W; ++w) {
+                                    const u32 z = L.vec[j * W + w] ^ L.vec[bi * W + w];
+                                    L.vec[j * W + w] = z;
+                                    any |= z;
+                                }
                             if (!any) L.keys[j] = ~0ull;
                             ++adds;
                         }
@@ -865,10 +1017,17 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                 unsigned long long adds = 0;
                 for (int r = 1 + tid; r < R; r += kT)
                     for (int q = 0; q < nk; ++q) {
-                        const int p = Sh.kp[q];
-                        if (!((P.get((u32)r, p >> 5) >> (p & 31)) & 1u)) continue;
+                        const int cls = Sh.kp[q];
+                        if (!((P.get((u32)r, cls >> 5) >> (cls & 31)) & 1u)) continue;
                         const LDS u32 *kv = L.vec + Sh.ki[q] * W;
-                        for (int w = 0; w < W; ++w) P.set((u32)r, w, P.get((u32)r, w) ^ kv[w]);
+                        if constexpr (kOdd) {
+                            const u32 f = (u32)((u64)P.half((u32)r, nm, cls) * Sh.kinv[q] % p);
+                            (void)odd_less([&](int w) { return P.get((u32)r, w); },
+                                           [&](int w, u32 y) { P.set((u32)r, w, y); },
+                                           [&](int k) { return P.half((u32)r, nm, k); },
+                                           [&](int k, u32 y) { P.set_half((u32)r, nm, k, y); }, f, kv, nm, p);
+                        } else
+                            for (int w = 0; w < W; ++w) P.set((u32)r, w, P.get((u32)r, w) ^ kv[w]);
                         ++adds;
                     }
                 if (adds) atomicAdd(&Sh.adds, adds);
@@ -886,8 +1045,8 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                         int a, v;
                         edge_of(e, &a, &v);
                         u32 any = 0;
-                        const u32 r = ids[(int64_t)a * n + v];
-                        for (int w = 0; w < W; ++w) any |= P.get(r, w);
+                        const u32 id = ids[(int64_t)a * n + v], r = kOdd ? id & 0xffffu : id;
+                        for (int w = 0; w < nm; ++w) any |= P.get(r, w);
                         keep = any != 0;
                         if (keep) {
                             atomicOr((u32 *)&L.vnz[a >> 5], 1u << (a & 31));
@@ -1028,12 +1187,12 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     __syncthreads();
 }
 
-template <bool kMaskLds>
+template <bool kMaskLds, bool kOdd>
 __global__ void __launch_bounds__(kT) k_sweep(SweepArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ SweepShared Sh;
     if (A.res) {
-        sweep_cloud<kMaskLds>(A, 0, smem, Sh);
+        sweep_cloud<kMaskLds, kOdd>(A, 0, smem, Sh);
         return;
     }
     for (;;) {
@@ -1042,7 +1201,7 @@ __global__ void __launch_bounds__(kT) k_sweep(SweepArgs A) {
         const int qi = Sh.cloud;
         __syncthreads();
         if (qi >= A.B) break;
-        sweep_cloud<kMaskLds>(A, A.order ? A.order[qi] : qi, smem, Sh);
+        sweep_cloud<kMaskLds, kOdd>(A, A.order ? A.order[qi] : qi, smem, Sh);
     }
 }
 
@@ -1096,8 +1255,9 @@ int sweep_sv_cap(int nmax) {
     return c;
 }
 
-int64_t sweep_pool_words(int nmax) {
-    return std::max<int64_t>(1 << 14, (int64_t)nmax * (nmax - 1));
+int64_t sweep_pool_words(int nmax, u32 p) {
+    const int64_t pairs2 = (int64_t)nmax * (nmax - 1);
+    return p == 2 ? std::max<int64_t>(1 << 14, pairs2) : std::max<int64_t>(1 << 20, 8 * pairs2);
 }
 
 size_t sweep_lds_bytes(int nmax, int sv_cap) {
@@ -1105,9 +1265,17 @@ size_t sweep_lds_bytes(int nmax, int sv_cap) {
     return keys + sweep_mask_lds(nmax) + sweep_fixed_bytes(nmax);
 }
 
-hipError_t sweep_prepare(int nmax, int sv_cap) {
-    return hipFuncSetAttribute(sweep_mask_lds(nmax) ? (const void *)k_sweep<true> : (const void *)k_sweep<false>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)sweep_lds_bytes(nmax, sv_cap));
+namespace {
+using SweepKernel = void (*)(SweepArgs);
+SweepKernel sweep_kernel(int nmax, u32 p) {
+    if (sweep_mask_lds(nmax)) return p == 2 ? k_sweep<true, false> : k_sweep<true, true>;
+    return p == 2 ? k_sweep<false, false> : k_sweep<false, true>;
+}
+} // namespace
+
+hipError_t sweep_prepare(int nmax, int sv_cap, u32 p) {
+    return hipFuncSetAttribute((const void *)sweep_kernel(nmax, p), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sweep_lds_bytes(nmax, sv_cap));
 }
 
 void launch_sweep_order(const int64_t *offsets, int B, int nmax, int *order, unsigned long long *queue,
@@ -1116,9 +1284,7 @@ void launch_sweep_order(const int64_t *offsets, int B, int nmax, int *order, uns
 }
 
 void launch_sweep(const SweepArgs &A, int grid, hipStream_t st) {
-    const size_t lds = sweep_lds_bytes(A.nmax, A.sv_cap);
-    if (sweep_mask_lds(A.nmax)) hipLaunchKernelGGL(k_sweep<true>, dim3(grid), dim3(kT), lds, st, A);
-    else hipLaunchKernelGGL(k_sweep<false>, dim3(grid), dim3(kT), lds, st, A);
+    hipLaunchKernelGGL(sweep_kernel(A.nmax, A.p), dim3(grid), dim3(kT), sweep_lds_bytes(A.nmax, A.sv_cap), st, A);
 }
 
 } // namespace rips

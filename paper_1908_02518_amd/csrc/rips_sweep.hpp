@@ -1,5 +1,5 @@
 // rips_sweep.hpp -- arguments of the sweep: dimensions 0 and 1 of one cloud
-// over Z/2 by one workgroup, in one pass over its edges in order of length.
+// over Z/p by one workgroup, in one pass over its edges in order of length.
 #pragma once
 
 #include "../../include/rips.h"
@@ -13,6 +13,7 @@ constexpr int kSweepBins = 2048;     // length bins of the edge partition
 constexpr int kSweepCand = 1024;     // triangles eliminated together
 constexpr int kSweepCandWords = 8192; // and their vectors, in words
 constexpr int kSweepMaxClasses = 2048;
+constexpr int kSweepOddClasses = 512; // over a field other than Z/2: half a word a class more
 constexpr int kSweepMaskBytes = 48 << 10; // nonzero-edge bits kept in LDS up to this size
 
 // status bit: a cloud exceeds the sweep's tables (too many loops or rows);
@@ -31,6 +32,7 @@ struct SweepArgs {
     const float *X;         // points (m > 0), or the n x n distances of one cloud (m == 0)
     const int64_t *offsets; // B + 1, or null: one cloud of nmax points
     int B, m, max_dim, nmax;
+    u32 p;
     float threshold;
     const int *order;       // clouds by decreasing size, or null
     unsigned long long *queue;
@@ -70,8 +72,8 @@ struct SweepArgs {
 __host__ __device__ inline int sweep_mask_words(int n) { return (n + 63) / 64; }
 size_t sweep_lds_bytes(int nmax, int sv_cap);
 int sweep_sv_cap(int nmax);
-int64_t sweep_pool_words(int nmax);
-hipError_t sweep_prepare(int nmax, int sv_cap);
+int64_t sweep_pool_words(int nmax, u32 p);
+hipError_t sweep_prepare(int nmax, int sv_cap, u32 p);
 void launch_sweep_order(const int64_t *offsets, int B, int nmax, int *order, unsigned long long *queue,
                         unsigned long long *ucount, int *status, hipStream_t st);
 void launch_sweep(const SweepArgs &A, int grid, hipStream_t st);

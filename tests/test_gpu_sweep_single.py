@@ -5,6 +5,8 @@ by blocks of one longest edge, on both sides of each rule, from points and from
 a distance matrix; and where a table is full, a distance overflows or edges of
 equal length meet and the other path takes over."""
 
+import itertools
+
 import numpy as np
 import pytest
 
@@ -46,6 +48,7 @@ def both(x, **kw):
         assert i1[f] == i2[f], f
     for f in ("candidates", "cleared", "apparent_col", "apparent_pivot", "columns", "bars_nonzero", "essential"):
         assert [s[f] for s in i1["stats"]] == [s[f] for s in i2["stats"]], f
+    return one
 
 
 def degree_threshold(x, degree):
@@ -65,6 +68,43 @@ def test_whole_cloud_vs_column_reduction(n, matrix, max_dim):
     for t in (INF, 0.9, 0.0):
         print(f"[case] whole cloud n={n} matrix={matrix} t={t} max_dim={max_dim}", flush=True)
         both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t, is_distance=matrix)
+
+
+@pytest.mark.parametrize("p", [3, 5, 65521])
+@pytest.mark.parametrize("n", [2, 33, 65, 127, 128, 129, 200, 201])
+def test_whole_cloud_over_another_field(n, p):
+    import torch
+    s = workloads.SEED_BASE + n
+    for x in (workloads.sphere(n, s), workloads.integer_lattice(n, 3, s, side=5),
+              workloads.noisy_circle_with_outliers(s, n - n // 8, n // 8), workloads.uniform_cube(n, 6, s)):
+        for t in (INF, 0.7):
+            print(f"[case] whole cloud n={n} p={p} m={x.shape[1]} t={t}", flush=True)
+            both(torch.from_numpy(x).cuda(), max_dim=1, threshold=t, p=p)
+
+
+def test_whole_cloud_torsion():
+    """A projective plane: one bar more over Z/2 than over Z/3."""
+    import torch
+    r = rips()
+    x = np.float32(projective_plane())
+    d = torch.from_numpy(x).cuda()
+    n1 = {}
+    for p in (2, 3):
+        n1[p] = len(both(d, max_dim=1, threshold=1.5, p=p, is_distance=True)[1][0])
+    assert n1[2] == n1[3] + 1
+
+
+def projective_plane():
+    """Distances whose complex at 1 is the barycentric subdivision of the
+    6-vertex projective plane (31 points)."""
+    tris = [(0, 1, 4), (0, 1, 5), (0, 2, 3), (0, 2, 5), (0, 3, 4), (1, 2, 3), (1, 2, 4), (1, 3, 5), (2, 4, 5), (3, 4, 5)]
+    faces = sorted({f for t in tris for k in (1, 2, 3) for f in itertools.combinations(t, k)})
+    x = np.full((len(faces), len(faces)), 2.0)
+    for i, f in enumerate(faces):
+        for j, g in enumerate(faces):
+            if set(f) <= set(g) or set(g) <= set(f):
+                x[i, j] = 0.0 if i == j else 1.0
+    return x
 
 
 @pytest.mark.parametrize("kind", ["ties", "loops", "full", "overflow"])
