@@ -262,6 +262,7 @@ enum BufId {
     B_SD_HVALS,
     B_SD_TAU,
     B_SD_BLOCK,
+    B_SD_TIED,
     B_SD_STATE,
     B_SD_QBLK,
     B_SD_BITS,
@@ -1084,9 +1085,11 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexL
         A.nall = (int)S;
         A.strict = max_dim > 2;
         A.paircap = 1 << 21;
-        ENS(B_SD_BLOCK, A.nE * 12, A.bstart, u32);
+        ENS(B_SD_BLOCK, A.nE * 8, A.bstart, u32);
         A.bcnt = A.bstart + A.nE;
-        A.tkey = A.bcnt + A.nE;
+        ENS(B_SD_TIED, (size_t)kTiedPairs * 12 + kTiedMax * 4, A.ttet, int64_t);
+        A.tplace = (u32 *)(A.ttet + kTiedPairs);
+        A.tlist = A.tplace + kTiedPairs;
         ENS(B_SD_STATE, dim_state_bytes(), A.state, void);
         ENS(B_SD_QBLK, ncand * 32 + 64, A.qblk, u32);
         A.qpar = A.qblk + ncand;

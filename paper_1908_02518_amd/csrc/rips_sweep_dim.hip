@@ -26,8 +26,8 @@
 // order by index, which moves simplices of equal diameter among themselves;
 // that cannot change a pair unless one of the two is in a block that shares
 // a simplex with another of the same length (and that simplex joins trees);
-// a class opened or closed in such a block, and a pair within it that
-// dimension 3 has to know, is left to the columns.
+// a class opened or closed in such a block is left to the columns, and the
+// pairs within it, which dimension 3 has to know, are found by k_lune_groups.
 //
 // All passes over simplices are data-parallel over the chip: the simplices by
 // diameter bin, the place of each by index, and the places that the sweep
@@ -398,7 +398,6 @@ __global__ void __launch_bounds__(256) k_lune(DimArgs A) {
             if (lane == 0) {
                 base = atomicAdd(&A.bin_n[bin], (u32)size); // the bins' first places move up to their ends
                 A.bstart[e] = base;
-                A.tkey[e] = ~0u;
             }
             base = __builtin_amdgcn_readfirstlane(base);
             if (size == 0) continue;
@@ -408,7 +407,6 @@ __global__ void __launch_bounds__(256) k_lune(DimArgs A) {
             }
         }
         LuneLds &L = Ls[kPlace ? wave : 0];
-        u32 first_tie = ~0u;
         int k = 0;
         for (int s = 0; s < cnt; s += kWave) {
             const int i = s + lane;
@@ -419,7 +417,6 @@ __global__ void __launch_bounds__(256) k_lune(DimArgs A) {
                 set_bit(A, A.tied, a, b);
                 if (x == len) set_bit(A, A.tied, a, c);
                 if (y == len) set_bit(A, A.tied, b, c);
-                first_tie = 0;
             }
             const bool ok = in && edge_before(x, a, c, len, ei) && edge_before(y, b, c, len, ei);
             const u64 hit = __ballot(ok);
@@ -460,12 +457,10 @@ __global__ void __launch_bounds__(256) k_lune(DimArgs A) {
                 const float z = D[(int64_t)c * n + d];
                 const bool adj = j < size && edge_before(z, c, d, len, ei);
                 const int lj = j < size ? (int)L.lab[j] : li;
-                if (j < size && z == len) { // a tetrahedron of two blocks: no matter, unless it joins trees
-                    first_tie = min(first_tie, ((u32)i << 16) | (u32)j);
-                    if ((lj & 0x7fff) != li) {
-                        set_bit(A, A.tied, a, b);
-                        set_bit(A, A.tied, c, d);
-                    }
+                // a tetrahedron of two blocks: no matter, unless it joins trees
+                if (j < size && z == len && (lj & 0x7fff) != li) {
+                    set_bit(A, A.tied, a, b);
+                    set_bit(A, A.tied, c, d);
                 }
                 const bool single = adj && lj == j; // bit 15 clear, and its own label
                 if (single) {
@@ -503,7 +498,6 @@ __global__ void __launch_bounds__(256) k_lune(DimArgs A) {
             A.qpar[base + i] = up == 0xffff ? ~0u : base + up;
             A.qkill[base + i] = L.kill[i];
         }
-        if (first_tie != ~0u) atomicMin(&A.tkey[e], first_tie);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
@@ -537,6 +531,156 @@ __global__ void __launch_bounds__(256) k_lune_deps(DimArgs A) {
     }
 }
 
+// ---- the pairs within blocks that share a simplex with another block of the
+// same length (a handful in a cloud of millions of triangles), for dimension
+// 3: those of the relative boundary matrix of the blocks together, reduced in
+// the filtration's own order. One workgroup a length; the tetrahedra's columns
+// are bits over the triangles.
+constexpr int kGroupEdges = 8, kGroupTri = 256, kGroupTet = 4096;
+
+__global__ void __launch_bounds__(256) k_lune_ties(DimArgs A) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < A.nE; e += stride) {
+        if (!bit_of(A, A.tied, A.E.a[e], A.E.b[e])) continue;
+        const int at = atomicAdd(&A.out->ntied, 1);
+        if (at < kTiedMax) A.tlist[at] = (u32)e;
+        else A.out->full = 1;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
+    __shared__ int ga[kGroupEdges], gb[kGroupEdges];
+    __shared__ int ng, ntri, ntet, lead, bad;
+    __shared__ int64_t tri[kGroupTri], row[kGroupTri];  // indices: as found, oldest first
+    __shared__ u32 tplace[kGroupTri];
+    __shared__ int64_t tet[kGroupTet];
+    __shared__ uint16_t order[kGroupTet];
+    __shared__ u64 stored[kGroupTri][kGroupTri / 64];
+    __shared__ int16_t owner[kGroupTri];
+    const int n = A.c.n, tid = threadIdx.x;
+    const float *D = A.c.d.D;
+    const int nt = min(A.out->ntied, kTiedMax);
+    for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+        const u32 e = A.tlist[t];
+        const float len = A.E.diam[e];
+        if (tid == 0) {
+            ng = ntri = ntet = bad = 0;
+            lead = 1;
+            for (int q = 0; q < nt; ++q) {
+                const u32 f = A.tlist[q];
+                if (A.E.diam[f] != len) continue;
+                if (f < e) lead = 0; // the group is another workgroup's
+                if (ng < kGroupEdges) {
+                    ga[ng] = A.E.a[f];
+                    gb[ng] = A.E.b[f];
+                }
+                ++ng;
+            }
+        }
+        __syncthreads();
+        const bool mine = lead != 0, few = ng <= kGroupEdges;
+        if (mine && !few && tid == 0) A.out->full = 1;
+        __syncthreads();
+        if (!mine || !few) continue;
+        // the triangles on the group's edges, each once
+        for (int g = 0; g < ng; ++g) {
+            const int a = ga[g], b = gb[g];
+            for (int c = tid; c < n; c += 256) {
+                if (c == a || c == b || D[(int64_t)a * n + c] > len || D[(int64_t)b * n + c] > len) continue;
+                bool seen = false;
+                for (int h = 0; h < g; ++h) {
+                    const bool x = ga[h] == a || ga[h] == b || ga[h] == c, y = gb[h] == a || gb[h] == b || gb[h] == c;
+                    seen = seen || (x && y);
+                }
+                if (seen) continue;
+                const int at = atomicAdd(&ntri, 1);
+                if (at < kGroupTri) tri[at] = tri_index(a, b, c);
+            }
+        }
+        __syncthreads();
+        const int M = min(ntri, kGroupTri);
+        for (int i = tid; i < M; i += 256) {
+            int r = 0;
+            for (int j = 0; j < M; ++j) r += tri[j] > tri[i] ? 1 : 0;
+            row[r] = tri[i];
+            owner[i] = -1;
+        }
+        __syncthreads();
+        for (int i = tid; i < M; i += 256) {
+            int v[3];
+            decode(row[i], 2, n, A.c.B, v);
+            tplace[i] = tri_place(A, v[0], v[1], v[2]);
+        }
+        // the tetrahedra: a triangle and a vertex, each found from the oldest of its triangles
+        for (int i = 0; i < M; ++i) {
+            int v[3];
+            decode(row[i], 2, n, A.c.B, v);
+            for (int d = tid; d < n; d += 256) {
+                if (d == v[0] || d == v[1] || d == v[2] || D[(int64_t)v[0] * n + d] > len ||
+                    D[(int64_t)v[1] * n + d] > len || D[(int64_t)v[2] * n + d] > len)
+                    continue;
+                bool first = true;
+                for (int q = 0; q < 3; ++q) {
+                    const int64_t f = tri_index(d, v[q == 0 ? 1 : 0], v[q == 2 ? 1 : 2]);
+                    for (int j = 0; j < i; ++j) first = first && row[j] != f;
+                }
+                if (!first) continue;
+                const int at = atomicAdd(&ntet, 1);
+                if (at < kGroupTet) tet[at] = (int64_t)tet_index(A, v[0], v[1], v[2], d);
+            }
+        }
+        __syncthreads();
+        const int T = min(ntet, kGroupTet);
+        if (tid == 0 && (ntri > kGroupTri || ntet > kGroupTet)) {
+            A.out->full = 1;
+            bad = 1;
+        }
+        for (int i = tid; i < T; i += 256) {
+            int r = 0;
+            for (int j = 0; j < T; ++j) r += tet[j] > tet[i] ? 1 : 0;
+            order[r] = (uint16_t)i;
+        }
+        __syncthreads();
+        if (tid == 0 && !bad) {
+            for (int k = 0; k < T; ++k) {
+                int w[4];
+                decode(tet[order[k]], 3, n, A.c.B, w);
+                u64 x[kGroupTri / 64] = {};
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t f = tri_index(w[q == 0 ? 1 : 0], w[q <= 1 ? 2 : 1], w[q == 3 ? 2 : 3]);
+                    int lo = 0, hi = M; // row is descending
+                    while (lo < hi) {
+                        const int mid = (lo + hi) / 2;
+                        if (row[mid] > f) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    if (lo < M && row[lo] == f) x[lo >> 6] |= 1ull << (lo & 63);
+                }
+                for (;;) {
+                    int pv = -1;
+                    for (int y = kGroupTri / 64 - 1; y >= 0 && pv < 0; --y)
+                        if (x[y]) pv = y * 64 + 63 - __clzll((long long)x[y]);
+                    if (pv < 0) break;
+                    if (owner[pv] < 0) {
+                        owner[pv] = (int16_t)order[k];
+                        for (int y = 0; y < kGroupTri / 64; ++y) stored[pv][y] = x[y];
+                        const int at = atomicAdd(&A.out->npairs_tied, 1);
+                        if (at < kTiedPairs) {
+                            A.tplace[at] = tplace[pv];
+                            A.ttet[at] = tet[order[k]];
+                        } else {
+                            A.out->full = 1;
+                        }
+                        break;
+                    }
+                    for (int y = 0; y < kGroupTri / 64; ++y) x[y] ^= stored[pv][y];
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // The columns that are roots of their block's forest, in column order; the
 // others pair with the tetrahedron at which their tree was joined to an older
 // one. One workgroup.
@@ -563,22 +707,32 @@ __global__ void __launch_bounds__(1024) k_lune_classes(DimArgs A, PivotHash piv)
             tri_verts(A.qverts[q], a, b, own);
             root = A.qpar[q] >= (u32)A.N;
             const u32 q1 = start + (k >> 16), q2 = start + (k & 0xffff);
-            if (root) {
-                // the block's oldest triangle pairs with the edge: no column, unless tied
-                if (start == q) {
-                    root = false;
-                    if (!bit_of(A, A.tied, a, b)) A.out->full = 1;
+            const bool tied = bit_of(A, A.tied, a, b);
+            int64_t t = -1;
+            if (root && start != q) {
+                // a class
+            } else if (tied) {
+                root = false;
+                if (A.strict) { // the forest's pair may not be the filtration's
+                    const int nt = min(A.out->npairs_tied, kTiedPairs);
+                    for (int i = 0; i < nt; ++i)
+                        if (A.tplace[i] == q) t = A.ttet[i];
+                    if (t < 0) A.out->full = 1;
                 }
+            } else if (root) { // the block's oldest triangle pairs with the edge: no column
+                root = false;
+                A.out->full = kDimBroken;
             } else if (k == ~0u || q1 >= (u32)A.N || q2 >= (u32)A.N) {
                 A.out->full = kDimBroken;
             } else {
                 tri_verts(A.qverts[q1], a1, b1, c);
                 tri_verts(A.qverts[q2], a1, b1, d);
-                (void)ph_insert(piv, (int64_t)tet_index(A, a, b, c, d), col);
-                // joined after an edge as long as the block's: the pair may be another one
-                if (A.strict && k >= A.tkey[A.qblk[q]] && bit_of(A, A.tied, a, b)) A.out->full = 1;
+                t = (int64_t)tet_index(A, a, b, c, d);
+            }
+            if (t >= 0) (void)ph_insert(piv, t, col);
+            if (!root) {
                 const int j = A.all.j[col];
-                if (j >= 0 && ((own == c && j == d) || (own == d && j == c))) ++emg;
+                if (j >= 0 && t == (int64_t)tet_index(A, a, b, own, j)) ++emg;
                 else ++red;
             }
         }
@@ -1528,6 +1682,10 @@ void launch_lune_partition(const DimArgs &A, PivotHash piv, hipStream_t st) {
     hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_n, A.bin_n, A.nbins);
     hipLaunchKernelGGL((k_lune<true>), dim3(blocks_for(A.nE, 4)), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_lune_deps, dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
+    if (A.strict) {
+        hipLaunchKernelGGL(k_lune_ties, dim3(blocks_for(A.nE, 256)), dim3(256), 0, st, A);
+        hipLaunchKernelGGL(k_lune_groups, dim3(32), dim3(256), 0, st, A);
+    }
     hipLaunchKernelGGL(k_lune_classes, dim3(1), dim3(kT), 0, st, A, piv);
 }
 

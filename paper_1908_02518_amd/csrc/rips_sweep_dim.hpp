@@ -11,6 +11,7 @@ constexpr int kDimMaxChunks = 16384;
 constexpr int kDimWords = 64;        // words of a row: 2048 classes open at once
 constexpr int kDimSlots = kDimWords * 32;
 constexpr int kDimRows = 1 << 14;    // rows
+constexpr int kTiedMax = 1024, kTiedPairs = 1 << 14;
 constexpr int kDimMaxVert = 65535;   // vertices are packed 16 bits each
 
 // What the sweep reports.
@@ -18,6 +19,7 @@ struct DimOut {
     int full;                 // 1: a table was too small, the caller reduces columns instead; 2: broken
     int nch;                  // chunks
     int npair;                // dimension 2: cofacets of the chunk that do not cancel
+    int ntied, npairs_tied;
     int nclasses;             // dimension 2: columns that no cofacet of their own block pairs
     unsigned long long adds, rows;
     int64_t nbars, nonzero, essential, emergent, reduced;
@@ -53,7 +55,9 @@ struct DimArgs {
     EdgeList E;           // the edges <= t
     int64_t nE;
     u32 *bstart, *bcnt;   // nE: first place and size of an edge's block
-    u32 *tkey;            // nE: the first edge of the lune that is as long as the block's, ~0 none
+    u32 *tlist;           // kTiedMax: edges with their bit in tied
+    u32 *tplace;          // kTiedPairs: the pairs within their blocks: place, index of the tetrahedron
+    int64_t *ttet;
     u32 *qblk, *qpar, *qkill; // N: block; parent in its forest, ~0 a root; the two ends of the edge a root fell to
     u32 *rhead, *rnext;   // N, 3 N: the triangles whose sum a triangle is part of, as lists of 3 N entries of qdep
     u32 *need;            // N bits: the sum may not be zero
@@ -61,7 +65,7 @@ struct DimArgs {
     int fw;               // words of a vertex's bits, even
     u64 *pairs;           // paircap: cofacets of the chunk that do not cancel, as (place, vertex)
     int paircap;
-    int strict;           // pairs that a tie leaves in doubt are left to the columns (a dimension follows)
+    int strict;           // a dimension follows, which has to know every pair
     void *state;          // dimension 2: the sweep's LDS between two launches, dim_state_bytes()
     Columns all;          // every column, youngest first (cols: the classes among them)
     int nall;

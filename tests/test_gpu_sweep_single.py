@@ -188,6 +188,22 @@ def test_dimension_2_by_blocks_vs_column_reduction(kind):
     both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t)
 
 
+@pytest.mark.parametrize("digits", [2, 3, 4, 5])
+@pytest.mark.parametrize("data", ["o3", "sphere"])
+def test_dimension_2_some_ties(data, digits):
+    """Distances rounded so that a few, or many, edges of equal length share
+    simplices, with a dimension that follows and without."""
+    import torch
+    s = workloads.SEED_BASE + digits
+    for seed in (s, s + 100, s + 200):
+        x = workloads.orthogonal(220, seed) if data == "o3" else workloads.sphere(44, seed)
+        d = np.sqrt(((x[:, None].astype(np.float64) - x[None]) ** 2).sum(2)).round(digits).astype(np.float32)
+        d = torch.from_numpy(np.ascontiguousarray(d)).cuda()
+        for max_dim in (2, 3):
+            print(f"[case] dimension 2 some ties {data} digits={digits} max_dim={max_dim}", flush=True)
+            both(d, max_dim=max_dim, threshold=1.8 if data == "o3" else INF, is_distance=True)
+
+
 def test_dimension_2_large_lune():
     """A lune of more points than one block's forest holds: columns."""
     import torch
