@@ -536,7 +536,7 @@ __global__ void __launch_bounds__(256) k_lune_deps(DimArgs A) {
 // 3: those of the relative boundary matrix of the blocks together, reduced in
 // the filtration's own order. One workgroup a length; the tetrahedra's columns
 // are bits over the triangles.
-constexpr int kGroupEdges = 8, kGroupTri = 256, kGroupTet = 4096;
+constexpr int kGroupEdges = 8, kGroupTri = 256, kGroupTet = 3072;
 
 __global__ void __launch_bounds__(256) k_lune_ties(DimArgs A) {
     const int64_t stride = (int64_t)gridDim.x * 256;
@@ -555,8 +555,10 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
     __shared__ u32 tplace[kGroupTri];
     __shared__ int64_t tet[kGroupTet];
     __shared__ uint16_t order[kGroupTet];
+    __shared__ u32 facet[kGroupTet]; // oldest first: the rows of its facets, a byte each, 255 none
     __shared__ u64 stored[kGroupTri][kGroupTri / 64];
     __shared__ int16_t owner[kGroupTri];
+    static_assert(kGroupTri == 256, "four words of rows");
     const int n = A.c.n, tid = threadIdx.x;
     const float *D = A.c.d.D;
     const int nt = min(A.out->ntied, kTiedMax);
@@ -631,7 +633,7 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
         }
         __syncthreads();
         const int T = min(ntet, kGroupTet);
-        if (tid == 0 && (ntri > kGroupTri || ntet > kGroupTet)) {
+        if (tid == 0 && (ntri >= kGroupTri || ntet > kGroupTet)) {
             A.out->full = 1;
             bad = 1;
         }
@@ -639,30 +641,40 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
             int r = 0;
             for (int j = 0; j < T; ++j) r += tet[j] > tet[i] ? 1 : 0;
             order[r] = (uint16_t)i;
+            int w[4];
+            decode(tet[i], 3, n, A.c.B, w);
+            u32 fs = 0;
+            for (int q = 0; q < 4; ++q) {
+                const int64_t f = tri_index(w[q == 0 ? 1 : 0], w[q <= 1 ? 2 : 1], w[q == 3 ? 2 : 3]);
+                int lo = 0, hi = M; // row is descending
+                while (lo < hi) {
+                    const int mid = (lo + hi) / 2;
+                    if (row[mid] > f) lo = mid + 1;
+                    else hi = mid;
+                }
+                fs |= (lo < M && row[lo] == f ? (u32)lo : 255u) << (8 * q);
+            }
+            facet[r] = fs;
         }
         __syncthreads();
         if (tid == 0 && !bad) {
             for (int k = 0; k < T; ++k) {
-                int w[4];
-                decode(tet[order[k]], 3, n, A.c.B, w);
                 u64 x[kGroupTri / 64] = {};
                 for (int q = 0; q < 4; ++q) {
-                    const int64_t f = tri_index(w[q == 0 ? 1 : 0], w[q <= 1 ? 2 : 1], w[q == 3 ? 2 : 3]);
-                    int lo = 0, hi = M; // row is descending
-                    while (lo < hi) {
-                        const int mid = (lo + hi) / 2;
-                        if (row[mid] > f) lo = mid + 1;
-                        else hi = mid;
-                    }
-                    if (lo < M && row[lo] == f) x[lo >> 6] |= 1ull << (lo & 63);
+                    const u32 f = (facet[k] >> (8 * q)) & 255u;
+#pragma unroll
+                    for (int y = 0; y < kGroupTri / 64; ++y)
+                        if (f != 255u && (int)(f >> 6) == y) x[y] |= 1ull << (f & 63);
                 }
                 for (;;) {
-                    int pv = -1;
-                    for (int y = kGroupTri / 64 - 1; y >= 0 && pv < 0; --y)
-                        if (x[y]) pv = y * 64 + 63 - __clzll((long long)x[y]);
+                    const int pv = x[3] ? 255 - __clzll((long long)x[3])
+                                 : x[2] ? 191 - __clzll((long long)x[2])
+                                 : x[1] ? 127 - __clzll((long long)x[1])
+                                 : x[0] ? 63 - __clzll((long long)x[0]) : -1;
                     if (pv < 0) break;
                     if (owner[pv] < 0) {
                         owner[pv] = (int16_t)order[k];
+#pragma unroll
                         for (int y = 0; y < kGroupTri / 64; ++y) stored[pv][y] = x[y];
                         const int at = atomicAdd(&A.out->npairs_tied, 1);
                         if (at < kTiedPairs) {
@@ -673,6 +685,7 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
                         }
                         break;
                     }
+#pragma unroll
                     for (int y = 0; y < kGroupTri / 64; ++y) x[y] ^= stored[pv][y];
                 }
             }
