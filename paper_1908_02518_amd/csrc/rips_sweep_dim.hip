@@ -662,7 +662,6 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
                 u64 x[kGroupTri / 64] = {};
                 for (int q = 0; q < 4; ++q) {
                     const u32 f = (facet[k] >> (8 * q)) & 255u;
-#pragma unroll
                     for (int y = 0; y < kGroupTri / 64; ++y)
                         if (f != 255u && (int)(f >> 6) == y) x[y] |= 1ull << (f & 63);
                 }
@@ -674,7 +673,6 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
                     if (pv < 0) break;
                     if (owner[pv] < 0) {
                         owner[pv] = (int16_t)order[k];
-#pragma unroll
                         for (int y = 0; y < kGroupTri / 64; ++y) stored[pv][y] = x[y];
                         const int at = atomicAdd(&A.out->npairs_tied, 1);
                         if (at < kTiedPairs) {
@@ -685,7 +683,6 @@ __global__ void __launch_bounds__(256) k_lune_groups(DimArgs A) {
                         }
                         break;
                     }
-#pragma unroll
                     for (int y = 0; y < kGroupTri / 64; ++y) x[y] ^= stored[pv][y];
                 }
             }
