@@ -300,10 +300,76 @@ __device__ __forceinline__ int uf_find(int *parent, int v, int n) {
 }
 
 constexpr int kH0Threads = 1024;
+constexpr int kH0Rounds = 40;   // guards against a fault: a round at least halves the components with an edge
 constexpr int kH0LdsMax = 2048; // union-find state of up to this many vertices lives in LDS
 
+// One round of Boruvka by the whole chip: every component's oldest outgoing
+// edge, the components hooked, every vertex sent to its root. A round of more
+// launches than one workgroup's loop is worth it once the state does not fit
+// its LDS (10,000 points, 242,330 edges: 6.8 ms by one workgroup, whose every
+// edge waits for two gathers and two atomics; now 1.1 ms).
+__global__ void __launch_bounds__(256) k_h0_start(int n, H0Scratch W, int *live) {
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v < n) {
+        W.comp[v] = v;
+        W.best[v] = ~0ull;
+    }
+    if (v < kH0Rounds + 1) live[v] = v == 0 ? 1 : 0;
+}
+
+__global__ void __launch_bounds__(256) k_h0_best(EdgeList E, const Scalars *s, H0Scratch W, const int *live) {
+    if (!*live) return; // the round before hooked nothing
+    const int64_t ne = (int64_t)s->edges, stride = (int64_t)gridDim.x * 256;
+    for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < ne; e += stride) {
+        const int ca = W.comp[E.a[e]], cb = W.comp[E.b[e]];
+        if (ca == cb) continue;
+        const u64 key = edge_key(E.diam[e], (u32)E.idx[e]);
+        if (ld(&W.best[ca]) > key) atomicMin(&W.best[ca], key);
+        if (ld(&W.best[cb]) > key) atomicMin(&W.best[cb], key);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_h0_hook(Scalars *s, int n, H0Scratch W, int *live) {
+    if (!live[0]) return;
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    const int cv = v < n ? W.comp[v] : 0;
+    int h = cv; // non-roots keep pointing at their root
+    const u64 key = v < n && cv == v ? W.best[v] : ~0ull;
+    bool hooks = false;
+    if (key != ~0ull) {
+        int a, b;
+        edge_vertices(0xffffffffu - (u32)(key & 0xffffffffu), &a, &b);
+        const int ca = W.comp[a], cb = W.comp[b];
+        const int other = ca == v ? cb : ca;
+        // mutual choices form 2-cycles: the larger root hooks
+        hooks = W.best[other] != key || v > other;
+        if (hooks) h = other;
+    }
+    const int64_t slot = wave_append(&s->mst, hooks);
+    if (hooks) {
+        if (slot < n) W.mst[slot] = key;
+        live[1] = 1;
+    }
+    if (v < n) W.hook[v] = h;
+}
+
+__global__ void __launch_bounds__(256) k_h0_jump(int n, H0Scratch W, const int *live) {
+    if (!*live) return;
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    int r = W.hook[v];
+    for (int hops = 0; hops < n; ++hops) { // the hooks form no cycle
+        const int up = W.hook[r];
+        if (up == r) break;
+        r = up;
+    }
+    W.comp[v] = r;
+    W.best[v] = ~0ull;
+}
+
+// `joined`: the forest edges are in W.mst, else they are found here
 __global__ void __launch_bounds__(kH0Threads) k_h0(EdgeList E, Scalars *s, int n, H0Scratch W,
-                                                    BarBuf out) {
+                                                    BarBuf out, bool joined) {
     __shared__ SortShared<kH0Threads> S;
     __shared__ int s_flag;
     __shared__ int s_w[kH0Threads / kWave + 1];
@@ -324,7 +390,7 @@ __global__ void __launch_bounds__(kH0Threads) k_h0(EdgeList E, Scalars *s, int n
     // Boruvka: every component picks its oldest outgoing edge. Each round at
     // least halves the number of components that still have an edge; the
     // round bound only guards against a fault.
-    for (int round = 0; round < 40; ++round) {
+    for (int round = 0; round < (joined ? 0 : kH0Rounds); ++round) {
         for (int v = tid; v < n; v += kH0Threads) st(&best[v], ~0ull);
         gsync();
         for (int64_t e = tid; e < ne; e += kH0Threads) {
@@ -1261,7 +1327,20 @@ void launch_h0(EdgeList E, Scalars *s, int n, H0Scratch W, BarBuf out, int64_t n
                hipStream_t st) {
     hipLaunchKernelGGL(k_zero_int, dim3(256), dim3(256), 0, st, (int *)W.bits, nbits_words);
     hipLaunchKernelGGL(k_reset_mst, dim3(1), dim3(1), 0, st, s);
-    hipLaunchKernelGGL(k_h0, dim3(1), dim3(kH0Threads), 0, st, E, s, n, W, out);
+    const bool wide = n > kH0LdsMax;
+    if (wide) {
+        const dim3 per_v((n + 255) / 256);
+        int *live = (int *)W.hdsimp; // free until the bars
+        hipLaunchKernelGGL(k_h0_start, per_v, dim3(256), 0, st, n, W, live);
+        int rounds = 1; // the first with nothing to hook included
+        while ((1 << rounds) < n) ++rounds;
+        for (int r = 0; r < rounds && r < kH0Rounds; ++r) {
+            hipLaunchKernelGGL(k_h0_best, dim3(1024), dim3(256), 0, st, E, s, W, live + r);
+            hipLaunchKernelGGL(k_h0_hook, per_v, dim3(256), 0, st, s, n, W, live + r);
+            hipLaunchKernelGGL(k_h0_jump, per_v, dim3(256), 0, st, n, W, live + r);
+        }
+    }
+    hipLaunchKernelGGL(k_h0, dim3(1), dim3(kH0Threads), 0, st, E, s, n, W, out, wide);
 }
 
 void launch_fill_i64(int64_t *a, int64_t n, int64_t v, hipStream_t st) {
