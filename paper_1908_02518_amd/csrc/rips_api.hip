@@ -90,6 +90,7 @@ enum BufId {
     B_SORT_HI1,
     B_SORT_V0,
     B_SORT_V1,
+    B_SORT_BINS,
     B_PH_KEYS0,  // two pivot tables, alternating by dimension
     B_PH_KEYS1,
     B_PH_VALS0,
@@ -1390,9 +1391,17 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         HIP_TRY(C.ensure(B_SORT_V1, (size_t)S * 4, &q));
         sb.val[1] = as<u32>(q);
         const int lo_bytes = bytes_for((uint64_t)choose_i64(n, k + 1));
+        // one workgroup's sort takes 0.05 ms and some 0.04 ms for every 1000
+        // columns more, the whole chip's five launches 0.06 ms
+        u32 *sort_bins = nullptr;
+        if (S >= 2048 && !C.arena) {
+            HIP_TRY(C.ensure(B_SORT_BINS, ((size_t)sort_many_bins(S) + 2) * 4, &q));
+            sort_bins = as<u32>(q);
+        }
         {
             PROF(P_SORT1 + k - 1);
-            launch_sort_columns(surv, P.scal, sb, lo_bytes, cols, st);
+            if (sort_bins) launch_sort_many(surv, S, P.ctx.t, P.scal, sb, lo_bytes, sort_bins, cols, st);
+            else launch_sort_columns(surv, P.scal, sb, lo_bytes, cols, st);
         }
         // ---- reduction
         const int slot = k & 1;

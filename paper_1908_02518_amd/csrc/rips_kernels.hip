@@ -859,11 +859,8 @@ __global__ void __launch_bounds__(256) k_filter(Ctx<Dist> c, SimplexList in, int
 // ---------------------------------------------------------------------------
 constexpr int kSortThreads = 1024;
 
-__global__ void __launch_bounds__(kSortThreads) k_sort_columns(Columns in, Scalars *s,
-                                                               SortBufs sb, int lo_bytes,
-                                                               Columns out) {
+__device__ __forceinline__ void sort_columns(Columns in, int N, SortBufs sb, int lo_bytes, Columns out) {
     __shared__ SortShared<kSortThreads> S;
-    const int N = (int)s->survivors;
     for (int e = threadIdx.x; e < N; e += kSortThreads) {
         sb.lo[0][e] = (u64)in.idx[e];
         sb.hi[0][e] = ~__float_as_uint(in.diam[e]);
@@ -878,6 +875,96 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_columns(Columns in, Scala
         out.j[q] = in.j[e];
         out.tapp[q] = in.tapp[e];
     }
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_columns(Columns in, Scalars *s,
+                                                               SortBufs sb, int lo_bytes,
+                                                               Columns out) {
+    sort_columns(in, (int)s->survivors, sb, lo_bytes, out);
+}
+
+// The same order for many columns, by the whole chip: the columns by diameter
+// bin (about four a bin), and every column's place in its bin by counting. A
+// bin of thousands (many equal diameters) is left to the one workgroup above,
+// which else finds nothing to do. 554,268 columns of 4096 orthogonal matrices:
+// 25 ms by one workgroup, now 0.5.
+constexpr int kSortBinMost = 4096;
+
+__device__ __forceinline__ int sort_bin(float d, float scale, int nbins) {
+    return nbins - 1 - min(nbins - 1, (int)(d * scale)); // larger diameters first
+}
+
+__global__ void __launch_bounds__(256) k_sort_hist(Columns in, int64_t N, float scale, int nbins, u32 *bins) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < N; e += stride)
+        atomicAdd(&bins[sort_bin(in.diam[e], scale, nbins)], 1u);
+}
+
+// exclusive scan in place, the largest bin to bins[nbins + 1]; one workgroup
+__global__ void __launch_bounds__(1024) k_sort_scan(u32 *bins, int nbins) {
+    __shared__ u32 s_w[16], s_most;
+    const int per = nbins / 1024, lane = lane_id(), w = threadIdx.x / kWave;
+    u32 sum = 0, most = 0;
+    if (threadIdx.x == 0) s_most = 0;
+    for (int i = 0; i < per; ++i) {
+        const u32 x = bins[threadIdx.x * per + i];
+        sum += x;
+        most = max(most, x);
+    }
+    u32 inc = sum;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const u32 x = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += x;
+    }
+    if (lane == kWave - 1) s_w[w] = inc;
+    __syncthreads();
+    atomicMax(&s_most, most);
+    u32 base = inc - sum;
+    for (int q = 0; q < w; ++q) base += s_w[q];
+    for (int i = 0; i < per; ++i) {
+        const u32 x = bins[threadIdx.x * per + i];
+        bins[threadIdx.x * per + i] = base;
+        base += x;
+    }
+    if (threadIdx.x == 1023) bins[nbins] = base;
+    __syncthreads();
+    if (threadIdx.x == 0) bins[nbins + 1] = s_most;
+}
+
+__global__ void __launch_bounds__(256) k_sort_place(Columns in, int64_t N, float scale, int nbins, u32 *bins,
+                                                    u32 *val) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < N; e += stride)
+        val[atomicAdd(&bins[sort_bin(in.diam[e], scale, nbins)], 1u)] = (u32)e; // the starts move to the ends
+}
+
+__global__ void __launch_bounds__(256) k_sort_rank(Columns in, int64_t N, float scale, int nbins, const u32 *bins,
+                                                   const u32 *val, Columns out) {
+    if (bins[nbins + 1] > (u32)kSortBinMost) return;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t q = blockIdx.x * 256ll + threadIdx.x; q < N; q += stride) {
+        const u32 e = val[q];
+        const float d = in.diam[e];
+        const int64_t idx = in.idx[e];
+        const int b = sort_bin(d, scale, nbins);
+        const u32 first = b ? bins[b - 1] : 0, last = bins[b];
+        u32 at = first;
+        for (u32 i = first; i < last; ++i) {
+            const u32 f = val[i];
+            const float df = in.diam[f];
+            at += df > d || (df == d && in.idx[f] < idx) ? 1u : 0u;
+        }
+        out.idx[at] = idx;
+        out.diam[at] = d;
+        out.j[at] = in.j[e];
+        out.tapp[at] = in.tapp[e];
+    }
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_rest(Columns in, Scalars *s, SortBufs sb, int lo_bytes,
+                                                            const u32 *most, Columns out) {
+    if (*most <= (u32)kSortBinMost) return;
+    sort_columns(in, (int)s->survivors, sb, lo_bytes, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1429,6 +1516,26 @@ void launch_sort_columns(Columns in, Scalars *s, SortBufs sb, int lo_bytes, Colu
                          hipStream_t st) {
     hipLaunchKernelGGL(k_sort_columns, dim3(1), dim3(kSortThreads), 0, st, in, s, sb, lo_bytes,
                        out);
+}
+
+// bins of launch_sort_many: words of its buffer less two
+int sort_many_bins(int64_t N) {
+    int b = 4096;
+    while (b < (1 << 17) && (int64_t)b * 4 < N) b <<= 1;
+    return b;
+}
+
+void launch_sort_many(Columns in, int64_t N, float t, Scalars *s, SortBufs sb, int lo_bytes, u32 *bins, Columns out,
+                      hipStream_t st) {
+    const int nbins = sort_many_bins(N);
+    const float scale = t > 0.0f ? (float)nbins / t : 0.0f;
+    const dim3 grid((unsigned)std::min<int64_t>((N + 255) / 256, 4096));
+    launch_fill_u32(bins, nbins + 2, 0u, st);
+    hipLaunchKernelGGL(k_sort_hist, grid, dim3(256), 0, st, in, N, scale, nbins, bins);
+    hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(1024), 0, st, bins, nbins);
+    hipLaunchKernelGGL(k_sort_place, grid, dim3(256), 0, st, in, N, scale, nbins, bins, sb.val[0]);
+    hipLaunchKernelGGL(k_sort_rank, grid, dim3(256), 0, st, in, N, scale, nbins, bins, sb.val[0], out);
+    hipLaunchKernelGGL(k_sort_rest, dim3(1), dim3(kSortThreads), 0, st, in, s, sb, lo_bytes, bins + nbins + 1, out);
 }
 
 hipError_t launch_reduce(const ReduceJob<DistFull> &J, u32 capD, ReduceBuffers RB, Scalars *s,

@@ -131,6 +131,10 @@ void launch_expand(int G, const Ctx<DistFull> &c, int k, SimplexList in, int64_t
                    SimplexList out, int64_t cap, bool count_only, hipStream_t st);
 void launch_bm_edge_order(EdgeList E, int nE, int n, SortBufs sb, int *pos, u32 *verts, float *len, u32 *run,
                           PairHash app_tab, int *app, hipStream_t st);
+// the same for many columns of diameters <= t; bins: sort_many_bins(N) + 2 words
+int sort_many_bins(int64_t N);
+void launch_sort_many(Columns in, int64_t N, float t, Scalars *s, SortBufs sb, int lo_bytes, u32 *bins, Columns out,
+                      hipStream_t st);
 void launch_sort_columns(Columns in, Scalars *s, SortBufs sb, int lo_bytes, Columns out,
                          hipStream_t st);
 void launch_emit(BarBuf in, Scalars *s, int reverse, BarBuf out, hipStream_t st);
