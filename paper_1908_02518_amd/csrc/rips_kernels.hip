@@ -626,7 +626,8 @@ __global__ void __launch_bounds__(256) k_expand(Ctx<Dist> c, int k, SimplexList 
             lo = a;
             hi = len;
         }
-        for (int q0 = lo; q0 < hi; q0 += G) {
+        if (!live) hi = lo;
+        for (int q0 = lo; __any(q0 < hi); q0 += G) {
             const int q = q0 + lg;
             bool ok = q < hi;
             int j = 0;
@@ -678,8 +679,7 @@ __global__ void __launch_bounds__(256) k_expand_count(Ctx<Dist> c, int k, Simple
             lo = a;
             hi = len;
         }
-        if (!live) hi = lo;
-        for (int q0 = lo; __any(q0 < hi); q0 += G) {
+        for (int q0 = lo; q0 < hi; q0 += G) {
             const int q = q0 + lg;
             bool ok = q < hi;
             if (ok) {
