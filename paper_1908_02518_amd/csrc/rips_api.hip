@@ -941,6 +941,12 @@ bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint
 // too many triangles (sphere-1000: 200 edges a point 7.7 ms swept, 9.1
 // reduced; 300: 15 and 13; 1000: 290 and 36).
 constexpr int64_t kSweepDegMin = 32, kSweepDegMax = 200;
+// Over another field sums cost more (p = 3: torus4-2000 3.9 and 12.0 ms,
+// sphere-1000 at 90 edges a point 3.3 and 5.8, noisy circles at 102 4.0 and
+// 9.4; sphere-1500 at 136 7.9 and 4.9), and with more columns than this too
+// many classes are open at once for its tables (1136 of torus4-4000 fit, 1465
+// of torus4-5000 do not).
+constexpr int64_t kSweepOddDegMax = 110, kSweepOddColumns = 1200;
 
 // One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
 // report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
@@ -999,11 +1005,11 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     return RIPS_OK;
 }
 
-// Dimension k (1 or 2) over Z/2 by the sweep: the bars in column order, the
+// Dimension 1, or 2 over Z/2, by the sweep: the bars in column order, the
 // counters and the pivot table of the next dimension's clearing. *full: a
 // table was too small (or, in dimension 2, edges of equal length met), nothing
 // is valid and the caller reduces the columns.
-rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexList cand, int64_t ncand, const int *zj,
+rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_dim, SimplexList cand, int64_t ncand, const int *zj,
                       const Columns &cols, int64_t S, PivotHash ph, uint32_t phcap, BarBuf bars, hipStream_t st,
                       RunOut &o, bool *full) {
     void *q;
@@ -1011,6 +1017,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexL
     memset(&A, 0, sizeof(A));
     const int n = P.ctx.n;
     A.c = P.ctx;
+    A.p = p;
     A.in = cand;
     A.N = ncand;
     A.zj = zj;
@@ -1026,7 +1033,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexL
     // and 150 of a mixture (4.6 to 3.7)
     A.chunk_n = k == 1 ? 0.0f : std::max(8192.0f, (float)ncand / 16.0f);
     *full = false;
-    if (ncand >= (1ll << 30)) {
+    if (ncand >= (1ll << 30) || (p != 2 && S > kSweepOddColumns)) {
         *full = true;
         return RIPS_OK;
     }
@@ -1124,8 +1131,8 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, int k, int max_dim, SimplexL
     ENS(B_SD_BQ, A.S * 4 + 16, A.bq, u32);
     ENS(B_SD_KIDX, A.S * 8 + 16, A.kidx, int64_t);
     ENS(B_SD_KDIAM, A.S * 4 + 16, A.kdiam, float);
-    A.W = std::max(1, std::min(kDimWords, (A.S + 31) / 32));
-    ENS(B_SD_POOL, (size_t)kDimRows * A.W * 4, A.pool, u32);
+    A.W = std::max(1, std::min(p == 2 ? kDimWords : kDimOddWords, (A.S + 31) / 32));
+    ENS(B_SD_POOL, dim_pool_bytes(p, A.W), A.pool, u32);
     ENS(B_SD_RSUM, (size_t)kDimRows * 8, A.rsum, u64);
     ENS(B_SD_RFREE, (size_t)kDimRows * 4, A.rfree, u32);
     ENS(B_SD_RDEAD, (size_t)kDimRows * 4, A.rdead, u32);
@@ -1247,8 +1254,9 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         launch_reset_dim(P.scal, st);
         // dimension 1 over Z/2 takes the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
-        const bool sweep = p == 2 && k <= 2 && k != swept_full && n <= kDimMaxVert && sweep_allowed(C) &&
-                           (k == 2 || (P.nedges >= kSweepDegMin * n / 2 && P.nedges <= kSweepDegMax * n / 2));
+        const bool sweep = k <= (p == 2 ? 2 : 1) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C) &&
+                           (k == 2 || (P.nedges >= kSweepDegMin * n / 2 &&
+                                       P.nedges <= (p == 2 ? kSweepDegMax : kSweepOddDegMax) * n / 2));
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {
@@ -1417,7 +1425,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
             if ((rs = ensure_bars(k, S))) return rs;
             bool full = false;
             if (S > 0)
-                rs = sweep_dim(C, P, k, max_dim, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
+                rs = sweep_dim(C, P, p, k, max_dim, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
             else
                 launch_fill_i64(ph.keys, phcap, kEmpty, st);
             if (rs) return rs;

@@ -1,6 +1,6 @@
-// rips_sweep_dim.hip -- the sweep of dimension 1 or 2 of a single cloud over
-// Z/2 (the method of rips_sweep.hip, for any number of points and for
-// triangles).
+// rips_sweep_dim.hip -- the sweep of dimension 1, or of dimension 2 over Z/2,
+// of a single cloud (the method of rips_sweep.hip, for any number of points
+// and for triangles).
 //
 // Every K-simplex carries the vector of the open K-classes; a simplex that
 // dimension K-1 has paired has the vector zero (a reduced boundary's pivot is
@@ -39,6 +39,7 @@
 #include "rips_sweep_dim.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rips {
 
@@ -47,6 +48,9 @@ namespace {
 constexpr int kT = 1024;
 constexpr int kWaves = kT / kWave;
 constexpr u32 kPending = ~0u;
+constexpr u32 kNeg = 1u << 31;      // of a place: less its vector
+constexpr int kOddWords = 20480;     // kCandWords over a field other than Z/2
+constexpr int kOddRows = 1 << 13;   // rows over a field other than Z/2
 constexpr int kDimBroken = 2;       // a place or row number out of range: a mistake, not a full table
 constexpr int kCand = 512;          // cofacets eliminated together
 constexpr int kCandWords = 16384;   // and their vectors, in words
@@ -166,7 +170,7 @@ template <int G, bool kFill>
 __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
     constexpr int K = 1;
     const int lane = lane_id(), lg = lane & (G - 1), g0 = lane & ~(G - 1);
-    const u64 gmask = G == 64 ? ~0ull : ((1ull << G) - 1) << g0;
+    const u64 gmask = G == 64 ? ~0ull : ((1ull << (G & 63)) - 1) << g0;
     const int64_t groups = (int64_t)gridDim.x * (256 / G);
     const int n = A.c.n;
     const float *D = A.c.d.D;
@@ -230,14 +234,19 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
                 if (kFill && pass == 1 && ok) {
                     const u32 e = put + (u32)__popcll(hit & ((1ull << lane) - 1));
                     u32 *o = A.tau + (int64_t)e * (K + 2);
-                    o[0] = (u32)q;
+                    // over a field other than Z/2 a place has a sign, on the
+                    // edge between the triangle's ends
+                    const bool odd = A.p != 2;
+                    const bool neg_q = odd && c < v[0] && c > v[1];
+                    o[0] = (u32)q | (neg_q ? kNeg : 0u);
 #pragma unroll
                     for (int i = 0; i <= K; ++i) {
                         int f[K + 1];
                         facet_of<K>(v, i, c, f);
                         const u32 pl = place_of<K>(A, f);
-                        o[1 + i] = pl;
-                        if (c == zj) A.qdep[(int64_t)i * A.N + q] = pl;
+                        const bool neg = odd && (i == 0 ? c > v[0] : c < v[1]);
+                        o[1 + i] = pl | (neg ? kNeg : 0u);
+                        if (c == zj) A.qdep[(int64_t)i * A.N + q] = pl | (odd && neg == neg_q ? kNeg : 0u);
                     }
                 }
                 mine += __popcll(hit);
@@ -796,6 +805,7 @@ struct DimShared {
     u64 hi_i;
     int kp[kCand], ki[kCand];
     u64 kz[kCand];                   // nonzero words of a kill's vector
+    u32 kinv[kCand];                 // kOdd: the inverse of its coefficient
     u32 cd[kCand];                   // candidates: diameter bits (~0: done)
     u64 ci[kCand], cz[kCand];        // ~index, nonzero words
     u32 sage[kDimSlots];             // class of a slot
@@ -933,10 +943,146 @@ __global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
     }
 }
 
+// ---- kOdd, a field other than Z/2: a simplex's id is a row (low half) and a
+// coefficient in [1, p), or 0. A row is its W words of bits, set where the
+// residue is not zero, and then a 16-bit residue for every slot.
+constexpr int kOddStride = 17; // words of a row for each word of bits
+
+__device__ __forceinline__ u32 odd_mul(u32 a, u32 b, u32 p) { return (u32)((u64)a * b % p); }
+__device__ __forceinline__ u32 odd_neg(u32 id, bool neg, u32 p) {
+    return id && neg ? (id & 0xffffu) | ((p - (id >> 16)) << 16) : id;
+}
+__device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
+    u32 r = 1;
+    for (u32 e = p - 2; e; e >>= 1) {
+        if (e & 1u) r = odd_mul(r, a, p);
+        a = odd_mul(a, a, p);
+    }
+    return r;
+}
+
+// what the row map makes of an id
+__device__ __forceinline__ u32 odd_resolve(const LDS u32 *rmap, u32 id, u32 p) {
+    if (!id) return 0;
+    const u32 to = rmap[id & (kOddRows - 1)];
+    return to ? (to & 0xffffu) | (odd_mul(to >> 16, id >> 16, p) << 16) : 0u;
+}
+
+// multiples of one row are added up; the number of nonzero ids left
+template <int M>
+__device__ __forceinline__ int odd_cancel(u32 (&r)[M], u32 p) {
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = i + 1; j < M; ++j)
+            if (r[i] && r[j] && ((r[i] ^ r[j]) & 0xffffu) == 0) {
+                const u32 c = ((r[i] >> 16) + (r[j] >> 16)) % p;
+                r[i] = c ? (r[i] & 0xffffu) | (c << 16) : 0u;
+                r[j] = 0;
+            }
+    int k = 0;
+#pragma unroll
+    for (int i = 0; i < M; ++i) k += r[i] != 0 ? 1 : 0;
+    return k;
+}
+
+__device__ __forceinline__ const u32 *odd_row(const DimArgs &A, u32 id) {
+    return A.pool + (int64_t)(id & 0xffffu) * (A.W * kOddStride);
+}
+
+template <int M>
+__device__ __forceinline__ u64 odd_words(const DimArgs &A, const u32 (&r)[M]) {
+    u64 z = 0;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+        if (r[i]) z |= A.rsum[r[i] & 0xffffu];
+    return z;
+}
+
+// put(slot, residue) for every nonzero residue of the sum, bits(word, bits) for every word with one
+template <int M, class Put, class Bits>
+__device__ __forceinline__ void odd_sum(const DimArgs &A, const u32 (&r)[M], Put put, Bits bits) {
+    for (u64 zz = odd_words<M>(A, r); zz; zz &= zz - 1) {
+        const int w = __ffsll((unsigned long long)zz) - 1;
+        u32 has[M], all = 0, out = 0;
+#pragma unroll
+        for (int i = 0; i < M; ++i) all |= has[i] = r[i] ? odd_row(A, r[i])[w] : 0u;
+        for (u32 m = all; m; m &= m - 1) {
+            const u32 bit = m & (0u - m);
+            const int slot = w * 32 + __ffs((int)m) - 1;
+            u64 t = 0;
+#pragma unroll
+            for (int i = 0; i < M; ++i)
+                if (has[i] & bit) t += (u64)(r[i] >> 16) * ((const uint16_t *)(odd_row(A, r[i]) + A.W))[slot];
+            const u32 x = (u32)(t % A.p);
+            if (!x) continue;
+            out |= bit;
+            put(slot, x);
+        }
+        if (out) bits(w, out);
+    }
+}
+
+template <int M>
+__device__ __forceinline__ u32 odd_row_of_sum(const DimArgs &A, DimShared &Sh, LDS u32 *rmap, u32 (&r)[M]) {
+    const int k = odd_cancel<M>(r, A.p);
+    u32 x = 0;
+#pragma unroll
+    for (int i = 0; i < M; ++i) x |= r[i];
+    if (k <= 1) return x;
+    int cnt = 0, at = 0;
+    u32 val = 0;
+    u64 z = 0;
+    odd_sum<M>(A, r, [&](int slot, u32 y) {
+        ++cnt;
+        at = slot;
+        val = y;
+    }, [&](int w, u32) { z |= 1ull << w; });
+    if (cnt == 0) return 0;
+    if (cnt == 1) return Sh.urow[at] | (val << 16);
+    const int f = atomicSub(&Sh.nfree, 1);
+    const u32 row = f > 0 ? A.rfree[f - 1] : (u32)atomicAdd(&Sh.nrows, 1);
+    if (row >= (u32)kOddRows) {
+        Sh.fail = 1;
+        return 0;
+    }
+    u32 *o = A.pool + (int64_t)row * (A.W * kOddStride);
+    for (int w = 0; w < A.W; ++w) o[w] = 0;
+    odd_sum<M>(A, r, [&](int slot, u32 y) { ((uint16_t *)(o + A.W))[slot] = (uint16_t)y; },
+               [&](int w, u32 b) { o[w] = b; });
+    A.rsum[row] = z;
+    rmap[row] = row | (1u << 16);
+    A.ract[atomicAdd(&Sh.nact, 1)] = row;
+    atomicAdd(&Sh.rows, 1ull);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    return row | (1u << 16);
+}
+
+// x less f times kv, both bits and residues, in the words z of kv; the
+// nonzero words of x, which were zx
+template <class Word, class Half>
+__device__ __forceinline__ u64 odd_less(Word *x, Half *xr, u32 f, const LDS u32 *kv, int W, u64 z, u64 zx, u32 p) {
+    const LDS uint16_t *kr = (const LDS uint16_t *)(kv + W);
+    for (u64 m = z; m; m &= m - 1) {
+        const int w = __ffsll((unsigned long long)m) - 1;
+        u32 bits = x[w];
+        for (u32 b = kv[w]; b; b &= b - 1) {
+            const u32 bit = b & (0u - b);
+            const int slot = w * 32 + __ffs((int)b) - 1;
+            const u32 y = (u32)(((bits & bit ? (u32)xr[slot] : 0u) + (u64)(p - f) * kr[slot]) % p);
+            if (y) xr[slot] = (uint16_t)y;
+            bits = y ? bits | bit : bits & ~bit;
+        }
+        x[w] = bits;
+        zx = bits ? zx | (1ull << w) : zx & ~(1ull << w);
+    }
+    return zx;
+}
+
 // The lanes with `ok` hold cofacets that do not cancel (rows r, key (kd, ki),
 // nonzero words z): of those with the same rows the oldest becomes a
 // candidate. (A cofacet that is found twice cancels in the elimination.)
-template <int M>
+template <bool kOdd, int M>
 __device__ __forceinline__ void candidates(const DimArgs &A, DimShared &Sh, LDS u32 *vec, int ccap, const u32 (&r)[M],
                                            bool ok, u32 kd, u64 ki, u64 z) {
     const int lane = lane_id();
@@ -959,7 +1105,13 @@ __device__ __forceinline__ void candidates(const DimArgs &A, DimShared &Sh, LDS 
                 Sh.cd[s] = kd;
                 Sh.ci[s] = ki;
                 Sh.cz[s] = z;
-                for (int w = 0; w < A.W; ++w) vec[s * A.W + w] = (z >> w) & 1ull ? sum_word<M>(A, r, w) : 0u;
+                if constexpr (kOdd) {
+                    LDS u32 *o = vec + s * A.W * kOddStride;
+                    for (int w = 0; w < A.W; ++w) o[w] = 0;
+                    odd_sum<M>(A, r, [&](int slot, u32 y) { ((LDS uint16_t *)(o + A.W))[slot] = (uint16_t)y; },
+                               [&](int w, u32 b) { o[w] = b; });
+                } else
+                    for (int w = 0; w < A.W; ++w) vec[s * A.W + w] = (z >> w) & 1ull ? sum_word<M>(A, r, w) : 0u;
             }
         }
     }
@@ -1014,17 +1166,27 @@ __device__ __forceinline__ u32 row_of_sum(const DimArgs &A, DimShared &Sh, LDS u
 // rmap (most sums that cancel are of two such rows, and then cost no look at
 // the vectors). Every kPurge eliminations the simplices' numbers are brought
 // up to date and the replaced rows are free again.
-template <int K>
+template <int K, bool kOdd>
 __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ DimShared Sh;
-    LDS u32 *vec = (LDS u32 *)smem;                                // kCandWords
-    LDS uint16_t *rmap = (LDS uint16_t *)(smem + kCandWords * 4);  // kDimRows
+    LDS u32 *vec = (LDS u32 *)smem;                                // kWords
+    using Map = typename std::conditional<kOdd, u32, uint16_t>::type;
+    constexpr int kRows = kOdd ? kOddRows : kDimRows, kWords = kOdd ? kOddWords : kCandWords;
+    LDS Map *rmap = (LDS Map *)(smem + kWords * 4);                // kRows
+    const u32 p = A.p;
+    // the id that an id stands for, and a row's own
+    auto resolve = [&](u32 id) -> u32 {
+        if constexpr (kOdd) return odd_resolve(rmap, id, p);
+        else return rmap[id & (kDimRows - 1)] & (kDimRows - 1);
+    };
+    auto own_id = [&](u32 row) -> u32 { return kOdd ? row | (1u << 16) : row; };
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int W = A.W;
     [[maybe_unused]] const int n = A.c.n;
-    const int nslots = W * 32, ccap = min(kCand, kCandWords / W);
+    const int PW = kOdd ? W * kOddStride : W; // words of a row
+    const int nslots = W * 32, ccap = min(kCand, kWords / PW);
     const int nch = __builtin_amdgcn_readfirstlane(A.out->nch);
     const bool more = K == 2 && chunk > 0; // the tables as the launch before left them
     if (more) {
@@ -1060,7 +1222,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
         if (vectors && s1 > s0) {
             const int ns = s1 - s0, nf = Sh.sfree, nr = Sh.nfree, top = Sh.nrows, na = Sh.nact, nz = Sh.nnz;
             const int fresh = max(0, ns - nr);
-            if (ns > nf || top + fresh > kDimRows) {
+            if (ns > nf || top + fresh > kRows) {
                 __syncthreads();
                 if (tid == 0) Sh.fail = 1;
                 __syncthreads();
@@ -1071,15 +1233,16 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 const int slot = Sh.sl[nf - 1 - i];
                 const u32 r = i < nr ? A.rfree[nr - 1 - i] : (u32)(top + i - nr);
                 Sh.sage[slot] = (u32)(s0 + i);
-                for (int w = 0; w < W; ++w) A.pool[(int64_t)r * W + w] = w == (slot >> 5) ? 1u << (slot & 31) : 0u;
+                for (int w = 0; w < W; ++w) A.pool[(int64_t)r * PW + w] = w == (slot >> 5) ? 1u << (slot & 31) : 0u;
+                if constexpr (kOdd) ((uint16_t *)(A.pool + (int64_t)r * PW + W))[slot] = 1;
                 A.rsum[r] = 1ull << (slot >> 5);
-                rmap[r] = (uint16_t)r;
+                rmap[r] = (Map)own_id(r);
                 Sh.urow[slot] = (uint16_t)r;
                 A.ract[na + i] = r;
                 const u32 pl = A.bq[s0 + i];
                 if (pl >= (u32)A.N) Sh.fail = kDimBroken;
                 const u32 q = min(pl, (u32)A.N - 1);
-                A.ids[q] = r;
+                A.ids[q] = own_id(r);
                 A.nzl[nz + i] = q;
                 if constexpr (K == 2) {
                     mark(A, q);
@@ -1105,9 +1268,10 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 u32 r[K + 1];
 #pragma unroll
                 for (int i = 0; i <= K; ++i) {
-                    const u32 pl = A.qdep[(int64_t)i * A.N + q];
+                    const u32 part = A.qdep[(int64_t)i * A.N + q], pl = kOdd ? part & ~kNeg : part;
                     if (pl >= (u32)A.N) Sh.fail = kDimBroken;
                     r[i] = ld(&A.ids[min(pl, (u32)A.N - 1)]);
+                    if (kOdd && r[i] != kPending) r[i] = odd_neg(r[i], (part & kNeg) != 0, p);
                 }
                 bool wait = false;
 #pragma unroll
@@ -1119,10 +1283,12 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 #pragma unroll
                 for (int i = 0; i <= K; ++i) {
-                    if (r[i] >= (u32)kDimRows) Sh.fail = kDimBroken;
-                    r[i] = rmap[r[i] & (kDimRows - 1)] & (kDimRows - 1);
+                    if ((kOdd ? r[i] & 0xffffu : r[i]) >= (u32)kRows) Sh.fail = kDimBroken;
+                    r[i] = resolve(r[i]);
                 }
-                const u32 x = row_of_sum<K + 1>(A, Sh, rmap, r);
+                u32 x;
+                if constexpr (kOdd) x = odd_row_of_sum<K + 1>(A, Sh, rmap, r);
+                else x = row_of_sum<K + 1>(A, Sh, rmap, r);
                 if (x) A.nzl[atomicAdd(&Sh.nnz, 1)] = q;
                 st(&A.ids[q], x);
             }
@@ -1134,7 +1300,8 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
         }
         // dimension 2: only the triangles that a nonzero one calls on. A sum
         // taken too early is taken again: its last part calls once more.
-        if (K == 2 && vectors) {
+        if constexpr (K == 2 && !kOdd)
+        if (vectors) {
             const u32 w0 = n0 >> 5, w1 = n1 > n0 ? ((n1 - 1) >> 5) + 1 : w0;
             for (int tries = 0;; ++tries) {
                 if (tid == 0) Sh.again = 0;
@@ -1212,7 +1379,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 for (int u = 0; u < kTaus; ++u) {
                     const u32 t = min(b + u * kT + (u32)lane, t1 - 1);
                     const u32 *o = A.tau + (int64_t)t * (K + 2);
-                    qs[u] = o[0];
+                    qs[u] = kOdd ? o[0] & ~kNeg : o[0];
 #pragma unroll
                     for (int i = 0; i < K + 2; ++i) rs[u][i] = o[i];
                 }
@@ -1220,17 +1387,20 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 for (int u = 0; u < kTaus; ++u)
 #pragma unroll
                     for (int i = 0; i < K + 2; ++i) {
-                        broken = broken | (rs[u][i] >= (u32)A.N);
-                        rs[u][i] = A.ids[min(rs[u][i], (u32)A.N - 1)];
+                        const u32 part = rs[u][i], pl = kOdd ? part & ~kNeg : part;
+                        broken = broken | (pl >= (u32)A.N);
+                        rs[u][i] = A.ids[min(pl, (u32)A.N - 1)];
+                        if constexpr (kOdd) rs[u][i] = odd_neg(rs[u][i], (part & kNeg) != 0, p);
                     }
 #pragma unroll
                 for (int u = 0; u < kTaus; ++u) {
 #pragma unroll
                     for (int i = 0; i < K + 2; ++i) {
-                        broken = broken | (rs[u][i] >= (u32)kDimRows);
-                        rs[u][i] = rmap[rs[u][i] & (kDimRows - 1)] & (kDimRows - 1);
+                        broken = broken | ((kOdd ? rs[u][i] & 0xffffu : rs[u][i]) >= (u32)kRows);
+                        rs[u][i] = resolve(rs[u][i]);
                     }
-                    some = some | (cancel<K + 2>(rs[u]) > 0);
+                    if constexpr (kOdd) some = some | (odd_cancel<K + 2>(rs[u], p) > 0);
+                    else some = some | (cancel<K + 2>(rs[u]) > 0);
                 }
                 if (broken) Sh.fail = kDimBroken;
                 if (!__any(some)) continue;
@@ -1248,11 +1418,15 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 ok = ok && t < t1;
                 if (!__any(ok)) continue;
                 u64 z = 0;
-                if (ok)
-                    for (u64 m = sum_words<K + 2>(A, r); m; m &= m - 1) {
-                        const int w = __ffsll((unsigned long long)m) - 1;
-                        if (sum_word<K + 2>(A, r, w)) z |= 1ull << w;
-                    }
+                if (ok) {
+                    if constexpr (kOdd)
+                        odd_sum<K + 2>(A, r, [](int, u32) {}, [&](int w, u32) { z |= 1ull << w; });
+                    else
+                        for (u64 m = sum_words<K + 2>(A, r); m; m &= m - 1) {
+                            const int w = __ffsll((unsigned long long)m) - 1;
+                            if (sum_word<K + 2>(A, r, w)) z |= 1ull << w;
+                        }
+                }
                 ok = ok && z != 0;
                 u32 kd = 0;
                 u64 ki = 0;
@@ -1260,7 +1434,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     // the cofacet's index, from its owner and the vertex that
                     // its facet opposite to the owner's first vertex adds
                     const u64 pv = A.qverts[q];
-                    const u64 pf = A.qverts[min(A.tau[(int64_t)t * (K + 2) + 1], (u32)A.N - 1)];
+                    const u64 pf = A.qverts[min(A.tau[(int64_t)t * (K + 2) + 1] & (kOdd ? ~kNeg : ~0u), (u32)A.N - 1)];
                     int v[K + 1], f[K + 1];
                     unpack<K>(pv, v);
                     unpack<K>(pf, f);
@@ -1277,10 +1451,10 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     ki = ~(u64)cofacet_index(v, K, c, A.c.B, &below);
                     ok = (first || key_less(lo_d, lo_i, kd, ki)) && !key_less(hi_d, hi_i, kd, ki);
                 }
-                candidates<K + 2>(A, Sh, vec, ccap, r, ok, kd, ki, z);
+                candidates<kOdd, K + 2>(A, Sh, vec, ccap, r, ok, kd, ki, z);
                 }
             }
-            } else {
+            } else if constexpr (!kOdd) {
                 // those that k_lune_tests has found; a lane has several in flight
                 for (int b0 = wave * kWave; b0 < np; b0 += kTaus * kT) {
                     u32 rs[kTaus][4];
@@ -1351,7 +1525,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                             ki = ~tet_index(A, va[u], vb[u], vc[u], vd[u]);
                             ok = (first || key_less(lo_d, lo_i, kd, ki)) && !key_less(hi_d, hi_i, kd, ki);
                         }
-                        candidates<4>(A, Sh, vec, ccap, rs[u], ok, kd, ki, z);
+                        candidates<kOdd, 4>(A, Sh, vec, ccap, rs[u], ok, kd, ki, z);
                     }
                 }
             }
@@ -1402,7 +1576,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                         if (bd == ~0u) break;
                         bj = __builtin_amdgcn_readfirstlane(bj);
                         // its youngest class: a lane a word, then the largest class number
-                        const u32 wd = lane < W ? vec[bj * W + lane] : 0u;
+                        const u32 wd = lane < W ? vec[bj * PW + lane] : 0u;
                         const u64 zw = __ballot(wd != 0u);
                         u32 age = 0;
                         int slot = 0;
@@ -1422,7 +1596,10 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                             }
                         }
                         slot = __builtin_amdgcn_readfirstlane(slot);
+                        u32 inv = 1;
+                        if constexpr (kOdd) inv = odd_inverse(((LDS uint16_t *)(vec + bj * PW + W))[slot], p);
                         if (lane == 0) {
+                            Sh.kinv[nk] = inv;
                             const int cls = min((int)Sh.sage[slot], A.S - 1);
                             A.kidx[cls] = (int64_t)~bi;
                             A.kdiam[cls] = __uint_as_float(bd);
@@ -1434,14 +1611,18 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                         ++nk;
                         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                         for (int j = lane; j < nc; j += kWave) {
-                            if (Sh.cd[j] == ~0u || !((vec[j * W + (slot >> 5)] >> (slot & 31)) & 1u)) continue;
+                            if (Sh.cd[j] == ~0u || !((vec[j * PW + (slot >> 5)] >> (slot & 31)) & 1u)) continue;
                             u64 z = Sh.cz[j];
-                            for (u64 m = zw; m; m &= m - 1) {
-                                const int w = __ffsll((unsigned long long)m) - 1;
-                                const u32 x = vec[j * W + w] ^ vec[bj * W + w];
-                                vec[j * W + w] = x;
-                                z = x ? z | (1ull << w) : z & ~(1ull << w);
-                            }
+                            if constexpr (kOdd) {
+                                LDS uint16_t *xr = (LDS uint16_t *)(vec + j * PW + W);
+                                z = odd_less(vec + j * PW, xr, odd_mul(xr[slot], inv, p), vec + bj * PW, W, zw, z, p);
+                            } else
+                                for (u64 m = zw; m; m &= m - 1) {
+                                    const int w = __ffsll((unsigned long long)m) - 1;
+                                    const u32 x = vec[j * W + w] ^ vec[bj * W + w];
+                                    vec[j * W + w] = x;
+                                    z = x ? z | (1ull << w) : z & ~(1ull << w);
+                                }
                             Sh.cz[j] = z;
                             if (!z) Sh.cd[j] = ~0u;
                             ++adds;
@@ -1461,19 +1642,23 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 unsigned long long adds = 0;
                 for (int i = tid; i < na; i += kT) {
                     const u32 r = A.ract[i];
-                    u32 *row = A.pool + (int64_t)r * W;
+                    u32 *row = A.pool + (int64_t)r * PW;
                     u64 z = A.rsum[r];
                     bool changed = false;
                     for (int q = 0; q < nk; ++q) {
-                        const int p = Sh.kp[q];
-                        if (!((z >> (p >> 5)) & 1ull) || !((row[p >> 5] >> (p & 31)) & 1u)) continue;
-                        const LDS u32 *kv = vec + Sh.ki[q] * W;
-                        for (u64 m = Sh.kz[q]; m; m &= m - 1) {
-                            const int w = __ffsll((unsigned long long)m) - 1;
-                            const u32 x = row[w] ^ kv[w];
-                            row[w] = x;
-                            z = x ? z | (1ull << w) : z & ~(1ull << w);
-                        }
+                        const int ks = Sh.kp[q];
+                        if (!((z >> (ks >> 5)) & 1ull) || !((row[ks >> 5] >> (ks & 31)) & 1u)) continue;
+                        const LDS u32 *kv = vec + Sh.ki[q] * PW;
+                        if constexpr (kOdd) {
+                            uint16_t *xr = (uint16_t *)(row + W);
+                            z = odd_less(row, xr, odd_mul(xr[ks], Sh.kinv[q], p), kv, W, Sh.kz[q], z, p);
+                        } else
+                            for (u64 m = Sh.kz[q]; m; m &= m - 1) {
+                                const int w = __ffsll((unsigned long long)m) - 1;
+                                const u32 x = row[w] ^ kv[w];
+                                row[w] = x;
+                                z = x ? z | (1ull << w) : z & ~(1ull << w);
+                            }
                         changed = true;
                         ++adds;
                     }
@@ -1481,9 +1666,13 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     A.rsum[r] = z;
                     u32 one = 0;
                     if (z) one = row[__ffsll((unsigned long long)z) - 1];
-                    if (!z) rmap[r] = 0;
-                    else if (is_unit(z, one))
-                        rmap[r] = Sh.urow[(__ffsll((unsigned long long)z) - 1) * 32 + __ffs((int)one) - 1];
+                    if (!z) {
+                        rmap[r] = 0;
+                    } else if (is_unit(z, one)) {
+                        const int slot = (__ffsll((unsigned long long)z) - 1) * 32 + __ffs((int)one) - 1;
+                        if constexpr (kOdd) rmap[r] = Sh.urow[slot] | ((u32)((uint16_t *)(row + W))[slot] << 16);
+                        else rmap[r] = Sh.urow[slot];
+                    }
                 }
                 if (adds) atomicAdd(&Sh.adds, adds);
                 // the closed classes' slots are free again
@@ -1492,8 +1681,8 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 // replaced rows leave the rows in use; what pointed to them
                 // points to what replaced them
                 const int nr = Sh.nrows, nz = Sh.nnz;
-                const bool purge = Sh.since >= kPurge || nr > kDimRows * 3 / 4;
-                for (int r = tid; r < nr; r += kT) rmap[r] = rmap[rmap[r]];
+                const bool purge = Sh.since >= kPurge || nr > kRows * 3 / 4;
+                for (int r = tid; r < nr; r += kT) rmap[r] = (Map)resolve(rmap[r]);
                 __syncthreads();
                 if (tid == 0) {
                     Sh.sfree += nk;
@@ -1504,7 +1693,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     const int i = q0 + tid;
                     const u32 r = i < na ? A.ract[i] : 0;
                     __syncthreads();
-                    const bool keep = i < na && rmap[r] == r;
+                    const bool keep = i < na && rmap[r] == own_id(r);
                     const int at = dim_append(keep, &Sh.nact);
                     if (keep) A.ract[at] = r; // at most i: entries already read
                     const int de = dim_append(i < na && !keep, &Sh.ndead);
@@ -1529,7 +1718,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                         __syncthreads();
                         bool keep = false;
                         if (i < nz) {
-                            const u32 r = rmap[A.ids[q] & (kDimRows - 1)] & (kDimRows - 1);
+                            const u32 r = resolve(A.ids[q]);
                             A.ids[q] = r;
                             keep = r != 0;
                             if constexpr (K == 2)
@@ -1657,7 +1846,12 @@ unsigned blocks_for(int64_t n, int per) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, 16384));
 }
 
-constexpr int kSweepLds = kCandWords * 4 + kDimRows * 2;
+template <int K, bool kOdd>
+hipError_t prepare_sweep(size_t *lds) {
+    *lds = kOdd ? kOddWords * 4 + kOddRows * 4 : kCandWords * 4 + kDimRows * 2;
+    return hipFuncSetAttribute((const void *)k_dim_sweep<K, kOdd>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)*lds);
+}
 
 } // namespace
 
@@ -1707,23 +1901,28 @@ void launch_lune_chunks(const DimArgs &A, hipStream_t st) {
 }
 
 hipError_t launch_dim_sweep(const DimArgs &A, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_dim_sweep<1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kSweepLds);
+    size_t lds;
+    const hipError_t e = A.p == 2 ? prepare_sweep<1, false>(&lds) : prepare_sweep<1, true>(&lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_dim_sweep<1>), dim3(1), dim3(kT), kSweepLds, st, A, 0);
+    if (A.p == 2) hipLaunchKernelGGL((k_dim_sweep<1, false>), dim3(1), dim3(kT), lds, st, A, 0);
+    else hipLaunchKernelGGL((k_dim_sweep<1, true>), dim3(1), dim3(kT), lds, st, A, 0);
     return hipSuccess;
 }
 
 hipError_t launch_lune_sweep(const DimArgs &A, int chunks, hipStream_t st) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_dim_sweep<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kSweepLds);
+    size_t lds;
+    const hipError_t e = prepare_sweep<2, false>(&lds);
     if (e != hipSuccess) return e;
     const unsigned grid = blocks_for((int64_t)A.chunk_n, 4);
     for (int c = 0; c <= chunks; ++c) { // those past the last chunk end at once
-        hipLaunchKernelGGL((k_dim_sweep<2>), dim3(1), dim3(kT), kSweepLds, st, A, c);
+        hipLaunchKernelGGL((k_dim_sweep<2, false>), dim3(1), dim3(kT), lds, st, A, c);
         if (c < chunks) hipLaunchKernelGGL(k_lune_tests, dim3(grid), dim3(256), 0, st, A, c);
     }
     return hipSuccess;
+}
+
+size_t dim_pool_bytes(u32 p, int W) {
+    return p == 2 ? (size_t)kDimRows * W * 4 : (size_t)kOddRows * W * kOddStride * 4;
 }
 
 size_t dim_state_bytes() { return (size_t)kStateWords * 4 + (size_t)kDimRows * 2; }

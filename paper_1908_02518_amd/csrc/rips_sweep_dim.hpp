@@ -9,6 +9,7 @@ namespace rips {
 constexpr int kDimBins = 1 << 16;    // most diameter bins of the partition
 constexpr int kDimMaxChunks = 16384;
 constexpr int kDimWords = 64;        // words of a row: 2048 classes open at once
+constexpr int kDimOddWords = 16;     // of its bits over a field other than Z/2: 512 classes open at once
 constexpr int kDimSlots = kDimWords * 32;
 constexpr int kDimRows = 1 << 14;    // rows
 constexpr int kTiedMax = 1024, kTiedPairs = 1 << 14;
@@ -33,6 +34,7 @@ struct DimArgs {
     const int *zj;        // dimension 1, per edge: third vertex of its zero apparent cofacet, -1 a column, -2 neither
     Columns cols;         // the columns, youngest first
     int S;
+    u32 p;
     int nbins;            // a power of two from 2048 to kDimBins
     float scale;          // bins per unit of diameter
     float chunk_n;        // dimension 2: simplices of a chunk
@@ -92,6 +94,7 @@ hipError_t launch_dim_sweep(const DimArgs &A, hipStream_t st);
 // dimension 2: at most `chunks` chunks, two launches each
 hipError_t launch_lune_sweep(const DimArgs &A, int chunks, hipStream_t st);
 size_t dim_state_bytes();
+size_t dim_pool_bytes(u32 p, int W);
 // the bars in column order, the counters, and the closing simplices as the
 // next dimension's pivot table
 void launch_dim_bars(int K, const DimArgs &A, BarBuf bars, PivotHash piv, hipStream_t st);

@@ -158,6 +158,20 @@ def test_chunked_sweep_vs_column_reduction(data, n, degree):
     both(torch.from_numpy(x).cuda(), max_dim=1, threshold=t)
 
 
+@pytest.mark.parametrize("p", [3, 65521])
+@pytest.mark.parametrize("data,n,t,max_dim", [("torus", 1200, 0.5, 2), ("so3", 900, 1.4, 1), ("sphere", 500, 0.8, 1),
+                                              ("circle", 600, 0.25, 2), ("lattice", 700, 2.3, 1)])
+def test_chunked_sweep_over_another_field(data, n, t, max_dim, p):
+    import torch
+    s = workloads.SEED_BASE + n
+    x = {"torus": lambda: workloads.clifford_torus(n, 0.02, s), "so3": lambda: workloads.so3(n, s),
+         "sphere": lambda: workloads.sphere(n, s),
+         "circle": lambda: workloads.noisy_circle_with_outliers(s, n - 60, 60),
+         "lattice": lambda: workloads.integer_lattice(n, 4, s, side=9)}[data]()
+    print(f"[case] chunked sweep {data} n={n} t={t} p={p}", flush=True)
+    both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t, p=p)
+
+
 def octahedra(k, seed):
     """k crosses of R^3 side by side, points slightly moved: k voids."""
     g = workloads.rng(seed)
