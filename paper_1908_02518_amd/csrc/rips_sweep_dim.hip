@@ -806,6 +806,7 @@ struct DimShared {
     int kp[kCand], ki[kCand];
     u64 kz[kCand];                   // nonzero words of a kill's vector
     u32 kinv[kCand];                 // kOdd: the inverse of its coefficient
+    uint16_t ord[kCand];             // oldest first
     u32 cd[kCand];                   // candidates: diameter bits (~0: done)
     u64 ci[kCand], cz[kCand];        // ~index, nonzero words
     u32 sage[kDimSlots];             // class of a slot
@@ -1550,52 +1551,42 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
             }
             if (nc > 0) {
                 // ---- elimination in order, by one wave
+                if (tid < nc) { // the same cofacet may be there twice
+                    const u32 d = Sh.cd[tid];
+                    const u64 x = Sh.ci[tid];
+                    int at = 0;
+                    for (int q = 0; q < nc; ++q) {
+                        const u32 dq = Sh.cd[q];
+                        const u64 xq = Sh.ci[q];
+                        at += key_less(dq, xq, d, x) || (dq == d && xq == x && q < tid) ? 1 : 0;
+                    }
+                    Sh.ord[at] = (uint16_t)tid;
+                }
+                __syncthreads();
                 if (wave == 0) {
                     int nk = 0;
                     unsigned long long adds = 0;
-                    for (;;) {
-                        u32 bd = ~0u;
-                        u64 bi = ~0ull;
-                        int bj = 0;
-                        for (int j = lane; j < nc; j += kWave)
-                            if (Sh.cd[j] != ~0u && key_less(Sh.cd[j], Sh.ci[j], bd, bi)) {
-                                bd = Sh.cd[j];
-                                bi = Sh.ci[j];
-                                bj = j;
-                            }
-                        for (int o = 32; o >= 1; o >>= 1) {
-                            const u32 xd = __shfl_xor(bd, o, kWave);
-                            const u64 xi = ((u64)__shfl_xor((u32)(bi >> 32), o, kWave) << 32) | __shfl_xor((u32)bi, o, kWave);
-                            const int xj = __shfl_xor(bj, o, kWave);
-                            if (key_less(xd, xi, bd, bi)) {
-                                bd = xd;
-                                bi = xi;
-                                bj = xj;
-                            }
-                        }
-                        if (bd == ~0u) break;
-                        bj = __builtin_amdgcn_readfirstlane(bj);
+                    for (int i = 0; i < nc; ++i) {
+                        const int bj = __builtin_amdgcn_readfirstlane((int)Sh.ord[i]);
+                        const u32 bd = __builtin_amdgcn_readfirstlane(Sh.cd[bj]);
+                        if (bd == ~0u) continue; // cancelled by older ones
+                        const u64 bi = Sh.ci[bj];
                         // its youngest class: a lane a word, then the largest class number
                         const u32 wd = lane < W ? vec[bj * PW + lane] : 0u;
                         const u64 zw = __ballot(wd != 0u);
-                        u32 age = 0;
-                        int slot = 0;
+                        u64 top = 0; // class number + 1, slot
                         for (u32 m = wd; m; m &= m - 1) {
-                            const int s = lane * 32 + __ffs((int)m) - 1;
-                            if (Sh.sage[s] + 1 > age) {
-                                age = Sh.sage[s] + 1;
-                                slot = s;
-                            }
+                            const int sl = lane * 32 + __ffs((int)m) - 1;
+                            const u64 x = ((u64)(Sh.sage[sl] + 1) << 32) | (u32)sl;
+                            top = x > top ? x : top;
                         }
-                        for (int o = 32; o >= 1; o >>= 1) {
-                            const u32 xa = __shfl_xor(age, o, kWave);
-                            const int xs = __shfl_xor(slot, o, kWave);
-                            if (xa > age) {
-                                age = xa;
-                                slot = xs;
-                            }
+                        // over the lanes with a nonzero word, few of them
+                        u64 best = 0;
+                        for (u64 m = zw; m; m &= m - 1) {
+                            const u64 x = lane_u64(top, __ffsll((unsigned long long)m) - 1);
+                            best = x > best ? x : best;
                         }
-                        slot = __builtin_amdgcn_readfirstlane(slot);
+                        const int slot = __builtin_amdgcn_readfirstlane((int)(u32)best);
                         u32 inv = 1;
                         if constexpr (kOdd) inv = odd_inverse(((LDS uint16_t *)(vec + bj * PW + W))[slot], p);
                         if (lane == 0) {
