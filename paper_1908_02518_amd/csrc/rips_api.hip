@@ -950,6 +950,11 @@ constexpr int64_t kSweepDegMin = 32, kSweepDegMax = 200;
 // many classes are open at once for its tables (1136 of torus4-4000 fit, 1465
 // of torus4-5000 do not).
 constexpr int64_t kSweepOddDegMax = 110, kSweepOddColumns = 1200;
+// Triangles from which dimension 2 is swept: below, the launches of the sweep
+// cost what the columns do (12 points on the sphere 0.58 and 0.55 ms, 24 points
+// 0.57 and 0.48, 357 rotations at 1.3, 8000 triangles, 1.31 and 1.24; 64 points
+// on the sphere, 37,000 triangles, 1.4 and 9.7).
+constexpr int64_t kSweepTriangles = 12288;
 
 // One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
 // report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
@@ -1008,7 +1013,7 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     return RIPS_OK;
 }
 
-// Dimension 1, or 2 over Z/2, by the sweep: the bars in column order, the
+// Dimension k (1 or 2) by the sweep: the bars in column order, the
 // counters and the pivot table of the next dimension's clearing. *full: a
 // table was too small (or, in dimension 2, edges of equal length met), nothing
 // is valid and the caller reduces the columns.
@@ -1036,7 +1041,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     // and 150 of a mixture (4.6 to 3.7)
     A.chunk_n = k == 1 ? 0.0f : std::max(8192.0f, (float)ncand / 16.0f);
     *full = false;
-    if (ncand >= (1ll << 30) || (p != 2 && S > kSweepOddColumns)) {
+    if (ncand >= (1ll << 30) || (p != 2 && k == 1 && S > kSweepOddColumns)) {
         *full = true;
         return RIPS_OK;
     }
@@ -1128,6 +1133,10 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
             return RIPS_OK;
         }
         A.S = h.nclasses;
+        if (p != 2 && A.S > kSweepOddColumns) {
+            *full = true;
+            return RIPS_OK;
+        }
         loc_emergent = h.loc_emergent;
         loc_reduced = h.loc_reduced;
     }
@@ -1255,11 +1264,11 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
     int swept_full = 0; // dimension whose sweep ran out of room
     for (int k = 1; k <= max_dim; ++k) {
         launch_reset_dim(P.scal, st);
-        // dimension 1 over Z/2 takes the sweep, unless a setting asks for the
+        // dimensions 1 and 2 take the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
-        const bool sweep = k <= (p == 2 ? 2 : 1) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C) &&
-                           (k == 2 || (P.nedges >= kSweepDegMin * n / 2 &&
-                                       P.nedges <= (p == 2 ? kSweepDegMax : kSweepOddDegMax) * n / 2));
+        const bool in_range = P.nedges >= kSweepDegMin * n / 2 &&
+                              P.nedges <= (p == 2 ? kSweepDegMax : kSweepOddDegMax) * n / 2;
+        bool sweep = k <= 2 && (k == 2 || in_range) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C);
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {
@@ -1284,6 +1293,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
             ncand = (int64_t)C.host_scal->list;
             if (ncand > C.hint_list[k]) C.hint_list[k] = ncand;
         }
+        if (k == 2) sweep = sweep && ncand >= kSweepTriangles;
         o.simplex_count[k] = ncand;
         // ---- enumeration / apparent-pair pass
         Columns surv, cols;

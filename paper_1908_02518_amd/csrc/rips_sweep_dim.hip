@@ -1,6 +1,5 @@
-// rips_sweep_dim.hip -- the sweep of dimension 1, or of dimension 2 over Z/2,
-// of a single cloud (the method of rips_sweep.hip, for any number of points
-// and for triangles).
+// rips_sweep_dim.hip -- the sweep of dimension 1 or 2 of a single cloud (the
+// method of rips_sweep.hip, for any number of points and for triangles).
 //
 // Every K-simplex carries the vector of the open K-classes; a simplex that
 // dimension K-1 has paired has the vector zero (a reduced boundary's pivot is
@@ -363,6 +362,12 @@ __device__ __forceinline__ void tri_verts(u64 p, int &a, int &b, int &c) {
     b = (int)((p >> 32) & 0xffff);
 }
 
+// the facet of tetrahedron {a, b, c, d} without its vertex x has the minus
+// sign in the coboundary: an odd number of the others is below x
+__device__ __forceinline__ bool minus_facet(int x, int a, int b, int c, int d) {
+    return ((a < x) + (b < x) + (c < x) + (d < x)) & 1;
+}
+
 // edge (x, y) of length d comes before edge e of length len and index ei
 __device__ __forceinline__ bool edge_before(float d, int x, int y, float len, int64_t ei) {
     return d < len || (d == len && pair_idx(x, y) < ei);
@@ -528,13 +533,15 @@ __global__ void __launch_bounds__(256) k_lune_deps(DimArgs A) {
         }
         tri_verts(A.qverts[up], a1, b1, d);
         const u32 dep[3] = {up, tri_place(A, a, c, d), tri_place(A, b, c, d)};
+        const int out[3] = {c, b, a}; // the vertex of the tetrahedron that each is without
         for (int i = 0; i < 3; ++i) {
             if (dep[i] >= (u32)A.N) {
                 A.out->full = kDimBroken;
                 break;
             }
             const u32 o = (u32)(i * A.N + q);
-            A.qdep[o] = dep[i];
+            const bool neg = A.p != 2 && minus_facet(out[i], a, b, c, d) == minus_facet(d, a, b, c, d);
+            A.qdep[o] = dep[i] | (neg ? kNeg : 0u);
             A.rnext[o] = atomicExch(&A.rhead[dep[i]], o);
         }
     }
@@ -551,6 +558,7 @@ __global__ void __launch_bounds__(256) k_lune_ties(DimArgs A) {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t e = blockIdx.x * 256ll + threadIdx.x; e < A.nE; e += stride) {
         if (!bit_of(A, A.tied, A.E.a[e], A.E.b[e])) continue;
+        if (A.p != 2) A.out->full = 1; // the groups are reduced over Z/2
         const int at = atomicAdd(&A.out->ntied, 1);
         if (at < kTiedMax) A.tlist[at] = (u32)e;
         else A.out->full = 1;
@@ -887,63 +895,6 @@ __device__ __forceinline__ void call_on(const DimArgs &A, u32 q) {
     }
 }
 
-// the sweep's LDS in global memory: DimShared, then the row map
-constexpr int kStateWords = sizeof(DimShared) / 4;
-constexpr int kStateScalars = offsetof(DimShared, kp) / 4; // of them those before the arrays
-
-// ---- dimension 2: the tetrahedra e + {c, d} of a chunk's blocks whose facets
-// do not cancel. One wave a triangle e + c, its lanes the d's of the block;
-// most have no nonzero triangle on the edges (a, c) and (b, c) and nothing to
-// do. A facet (a, c, d) can be nonzero only if each of its edges has a
-// nonzero triangle, which leaves few pairs to look up (of the 39 million
-// tetrahedra of 192 points on the sphere 1 to 2 million). By the whole chip:
-// one workgroup took 60 ms for that cloud, its lookups one line a clock.
-__global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
-    if (chunk >= A.out->nch || A.out->full) return;
-    const DimShared *S = (const DimShared *)A.state;
-    if (S->nnz == 0) return;
-    const uint16_t *rmap = (const uint16_t *)((const u32 *)A.state + kStateWords);
-    const int lane = lane_id(), n = A.c.n;
-    const float *D = A.c.d.D;
-    const u32 n0 = A.ch_n[chunk], n1 = A.ch_n[chunk + 1], waves = gridDim.x * 4;
-    for (u32 q = n0 + blockIdx.x * 4 + threadIdx.x / kWave; q < n1; q += waves) {
-        int a, b, c;
-        tri_verts(A.qverts[q], a, b, c);
-        const u32 own = rmap[A.ids[q] & (kDimRows - 1)] & (kDimRows - 1);
-        const bool fa = bit_of(A, A.fl, a, c), fb = bit_of(A, A.fl, b, c);
-        if (!own && !fa && !fb) continue;
-        const u32 blk = A.qblk[q], start = A.bstart[blk], size = A.bcnt[blk];
-        const float len = A.qdiam[q];
-        const int64_t ei = pair_idx(a, b);
-        for (u32 s = 0; s < size; s += kWave) {
-            const u32 j = s + (u32)lane, qd = min(start + min(j, size - 1), (u32)A.N - 1);
-            const int d = (int)(A.qverts[qd] & 0xffff);
-            bool ok = j < size && qd != q;
-            const float z = D[(int64_t)c * n + d];
-            const u32 other = rmap[A.ids[qd] & (kDimRows - 1)] & (kDimRows - 1);
-            const bool fc = bit_of(A, A.fl, c, d);
-            const bool ta = fc && fa && bit_of(A, A.fl, a, d), tb = fc && fb && bit_of(A, A.fl, b, d);
-            ok = ok && edge_before(z, c, d, len, ei) && (own || ta || tb);
-            // from d's side too, if that looks at it: only from the first
-            ok = ok && !(qd < q && (other || ta || tb));
-            if (!__any(ok)) continue;
-            u32 r[4] = {own, other, 0, 0};
-            if (ok && ta) r[2] = tri_place(A, a, c, d);
-            if (ok && tb) r[3] = tri_place(A, b, c, d);
-            if (ok && ((ta && r[2] >= (u32)A.N) || (tb && r[3] >= (u32)A.N))) A.out->full = kDimBroken;
-            r[2] = ta ? rmap[A.ids[min(r[2], (u32)A.N - 1)] & (kDimRows - 1)] & (kDimRows - 1) : 0;
-            r[3] = tb ? rmap[A.ids[min(r[3], (u32)A.N - 1)] & (kDimRows - 1)] & (kDimRows - 1) : 0;
-            ok = ok && cancel<4>(r) > 0;
-            bool nonzero = false;
-            if (ok)
-                for (u64 m = sum_words<4>(A, r); m && !nonzero; m &= m - 1)
-                    nonzero = sum_word<4>(A, r, __ffsll((unsigned long long)m) - 1) != 0;
-            const int at = dim_append(nonzero, &A.out->npair);
-            if (nonzero && at < A.paircap) A.pairs[at] = ((u64)q << 32) | (u32)d;
-        }
-    }
-}
-
 // ---- kOdd, a field other than Z/2: a simplex's id is a row (low half) and a
 // coefficient in [1, p), or 0. A row is its W words of bits, set where the
 // residue is not zero, and then a 16-bit residue for every slot.
@@ -963,7 +914,8 @@ __device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
 }
 
 // what the row map makes of an id
-__device__ __forceinline__ u32 odd_resolve(const LDS u32 *rmap, u32 id, u32 p) {
+template <class Map>
+__device__ __forceinline__ u32 odd_resolve(Map rmap, u32 id, u32 p) {
     if (!id) return 0;
     const u32 to = rmap[id & (kOddRows - 1)];
     return to ? (to & 0xffffu) | (odd_mul(to >> 16, id >> 16, p) << 16) : 0u;
@@ -1078,6 +1030,73 @@ __device__ __forceinline__ u64 odd_less(Word *x, Half *xr, u32 f, const LDS u32 
         zx = bits ? zx | (1ull << w) : zx & ~(1ull << w);
     }
     return zx;
+}
+
+// the sweep's LDS in global memory: DimShared, then the row map
+constexpr int kStateWords = sizeof(DimShared) / 4;
+constexpr int kStateScalars = offsetof(DimShared, kp) / 4; // of them those before the arrays
+
+// ---- dimension 2: the tetrahedra e + {c, d} of a chunk's blocks whose facets
+// do not cancel. One wave a triangle e + c, its lanes the d's of the block;
+// most have no nonzero triangle on the edges (a, c) and (b, c) and nothing to
+// do. A facet (a, c, d) can be nonzero only if each of its edges has a
+// nonzero triangle, which leaves few pairs to look up (of the 39 million
+// tetrahedra of 192 points on the sphere 1 to 2 million). By the whole chip:
+// one workgroup took 60 ms for that cloud, its lookups one line a clock.
+template <bool kOdd>
+__global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
+    if (chunk >= A.out->nch || A.out->full) return;
+    const DimShared *S = (const DimShared *)A.state;
+    if (S->nnz == 0) return;
+    using Map = typename std::conditional<kOdd, u32, uint16_t>::type;
+    const Map *rmap = (const Map *)((const u32 *)A.state + kStateWords);
+    auto resolve = [&](u32 id) -> u32 {
+        if constexpr (kOdd) return odd_resolve(rmap, id, A.p);
+        else return rmap[id & (kDimRows - 1)] & (kDimRows - 1);
+    };
+    const int lane = lane_id(), n = A.c.n;
+    const float *D = A.c.d.D;
+    const u32 n0 = A.ch_n[chunk], n1 = A.ch_n[chunk + 1], waves = gridDim.x * 4;
+    for (u32 q = n0 + blockIdx.x * 4 + threadIdx.x / kWave; q < n1; q += waves) {
+        int a, b, c;
+        tri_verts(A.qverts[q], a, b, c);
+        const u32 own = resolve(A.ids[q]);
+        const bool fa = bit_of(A, A.fl, a, c), fb = bit_of(A, A.fl, b, c);
+        if (!own && !fa && !fb) continue;
+        const u32 blk = A.qblk[q], start = A.bstart[blk], size = A.bcnt[blk];
+        const float len = A.qdiam[q];
+        const int64_t ei = pair_idx(a, b);
+        for (u32 s = 0; s < size; s += kWave) {
+            const u32 j = s + (u32)lane, qd = min(start + min(j, size - 1), (u32)A.N - 1);
+            const int d = (int)(A.qverts[qd] & 0xffff);
+            bool ok = j < size && qd != q;
+            const float z = D[(int64_t)c * n + d];
+            const u32 other = resolve(A.ids[qd]);
+            const bool fc = bit_of(A, A.fl, c, d);
+            const bool ta = fc && fa && bit_of(A, A.fl, a, d), tb = fc && fb && bit_of(A, A.fl, b, d);
+            ok = ok && edge_before(z, c, d, len, ei) && (own || ta || tb);
+            // from d's side too, if that looks at it: only from the first
+            ok = ok && !(qd < q && (other || ta || tb));
+            if (!__any(ok)) continue;
+            u32 r[4] = {own, other, 0, 0};
+            if (ok && ta) r[2] = tri_place(A, a, c, d);
+            if (ok && tb) r[3] = tri_place(A, b, c, d);
+            if (ok && ((ta && r[2] >= (u32)A.N) || (tb && r[3] >= (u32)A.N))) A.out->full = kDimBroken;
+            r[2] = ta ? resolve(A.ids[min(r[2], (u32)A.N - 1)]) : 0;
+            r[3] = tb ? resolve(A.ids[min(r[3], (u32)A.N - 1)]) : 0;
+            bool nonzero = false;
+            if constexpr (kOdd) {
+                const int out[4] = {d, c, b, a};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) r[i] = odd_neg(r[i], minus_facet(out[i], a, b, c, d), A.p);
+                if (ok && odd_cancel<4>(r, A.p) > 0) odd_sum<4>(A, r, [&](int, u32) { nonzero = true; }, [](int, u32) {});
+            } else if (ok && cancel<4>(r) > 0)
+                for (u64 m = sum_words<4>(A, r); m && !nonzero; m &= m - 1)
+                    nonzero = sum_word<4>(A, r, __ffsll((unsigned long long)m) - 1) != 0;
+            const int at = dim_append(nonzero, &A.out->npair);
+            if (nonzero && at < A.paircap) A.pairs[at] = ((u64)q << 32) | (u32)d;
+        }
+    }
 }
 
 // The lanes with `ok` hold cofacets that do not cancel (rows r, key (kd, ki),
@@ -1201,7 +1220,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
             Sh.urow[i] = S->urow[i];
             Sh.sl[i] = S->sl[i];
         }
-        for (int i = tid; 2 * i < rows; i += kT) ((LDS u32 *)rmap)[i] = rm[i];
+        for (int i = tid; i * (kOdd ? 1 : 2) < rows; i += kT) ((LDS u32 *)rmap)[i] = rm[i];
     } else {
         if (tid == 0) {
             Sh.nact = Sh.nnz = Sh.fail = Sh.nfree = Sh.ndead = Sh.since = 0;
@@ -1301,7 +1320,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
         }
         // dimension 2: only the triangles that a nonzero one calls on. A sum
         // taken too early is taken again: its last part calls once more.
-        if constexpr (K == 2 && !kOdd)
+        if constexpr (K == 2)
         if (vectors) {
             const u32 w0 = n0 >> 5, w1 = n1 > n0 ? ((n1 - 1) >> 5) + 1 : w0;
             for (int tries = 0;; ++tries) {
@@ -1320,14 +1339,18 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                         u32 r[3];
 #pragma unroll
                         for (int i = 0; i < 3; ++i) {
-                            r[i] = ld(&A.ids[min(A.qdep[(int64_t)i * A.N + q], (u32)A.N - 1)]);
-                            if (r[i] >= (u32)kDimRows) Sh.fail = kDimBroken;
+                            const u32 part = A.qdep[(int64_t)i * A.N + q];
+                            r[i] = ld(&A.ids[min(kOdd ? part & ~kNeg : part, (u32)A.N - 1)]);
+                            if ((kOdd ? r[i] & 0xffffu : r[i]) >= (u32)kRows) Sh.fail = kDimBroken;
+                            if constexpr (kOdd) r[i] = odd_neg(r[i], (part & kNeg) != 0, p);
                         }
                         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) r[i] = rmap[r[i] & (kDimRows - 1)] & (kDimRows - 1);
+                        for (int i = 0; i < 3; ++i) r[i] = resolve(r[i]);
                         const u32 was = ld(&A.ids[q]);
-                        const u32 x = row_of_sum<3>(A, Sh, rmap, r);
+                        u32 x;
+                        if constexpr (kOdd) x = odd_row_of_sum<3>(A, Sh, rmap, r);
+                        else x = row_of_sum<3>(A, Sh, rmap, r);
                         if (x == was) continue;
                         st(&A.ids[q], x);
                         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1455,7 +1478,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                 candidates<kOdd, K + 2>(A, Sh, vec, ccap, r, ok, kd, ki, z);
                 }
             }
-            } else if constexpr (!kOdd) {
+            } else {
                 // those that k_lune_tests has found; a lane has several in flight
                 for (int b0 = wave * kWave; b0 < np; b0 += kTaus * kT) {
                     u32 rs[kTaus][4];
@@ -1499,10 +1522,14 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     for (int u = 0; u < kTaus; ++u) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            broken = broken | (rs[u][i] >= (u32)kDimRows);
-                            rs[u][i] = rmap[rs[u][i] & (kDimRows - 1)] & (kDimRows - 1);
+                            broken = broken | ((kOdd ? rs[u][i] & 0xffffu : rs[u][i]) >= (u32)kRows);
+                            rs[u][i] = resolve(rs[u][i]);
+                            const int x = i == 0 ? vd[u] : i == 1 ? vc[u] : i == 2 ? vb[u] : va[u];
+                            if constexpr (kOdd)
+                                rs[u][i] = odd_neg(rs[u][i], minus_facet(x, va[u], vb[u], vc[u], vd[u]), p);
                         }
-                        oks[u] = oks[u] && cancel<4>(rs[u]) > 0;
+                        if constexpr (kOdd) oks[u] = oks[u] && odd_cancel<4>(rs[u], p) > 0;
+                        else oks[u] = oks[u] && cancel<4>(rs[u]) > 0;
                         some = some | oks[u];
                     }
                     if (broken) Sh.fail = kDimBroken;
@@ -1512,11 +1539,15 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                         bool ok = oks[u];
                         if (!__any(ok)) continue;
                         u64 z = 0;
-                        if (ok)
-                            for (u64 m = sum_words<4>(A, rs[u]); m; m &= m - 1) {
-                                const int w = __ffsll((unsigned long long)m) - 1;
-                                if (sum_word<4>(A, rs[u], w)) z |= 1ull << w;
-                            }
+                        if (ok) {
+                            if constexpr (kOdd)
+                                odd_sum<4>(A, rs[u], [](int, u32) {}, [&](int w, u32) { z |= 1ull << w; });
+                            else
+                                for (u64 m = sum_words<4>(A, rs[u]); m; m &= m - 1) {
+                                    const int w = __ffsll((unsigned long long)m) - 1;
+                                    if (sum_word<4>(A, rs[u], w)) z |= 1ull << w;
+                                }
+                        }
                         ok = ok && z != 0;
                         u32 kd = 0;
                         u64 ki = 0;
@@ -1744,14 +1775,14 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
     if (K == 2) {
         DimShared *S = (DimShared *)A.state;
         u32 *to = (u32 *)S, *rm = to + kStateWords;
-        const int rows = min(Sh.nrows, kDimRows);
+        const int rows = min(Sh.nrows, kRows);
         for (int i = tid; i < kStateScalars; i += kT) to[i] = ((LDS u32 *)&Sh)[i];
         for (int i = tid; i < nslots; i += kT) {
             S->sage[i] = Sh.sage[i];
             S->urow[i] = Sh.urow[i];
             S->sl[i] = Sh.sl[i];
         }
-        for (int i = tid; 2 * i < rows; i += kT) rm[i] = ((LDS u32 *)rmap)[i];
+        for (int i = tid; i * (kOdd ? 1 : 2) < rows; i += kT) rm[i] = ((LDS u32 *)rmap)[i];
         if (tid == 0) A.out->npair = 0;
     }
     if (tid == 0) {
@@ -1902,12 +1933,14 @@ hipError_t launch_dim_sweep(const DimArgs &A, hipStream_t st) {
 
 hipError_t launch_lune_sweep(const DimArgs &A, int chunks, hipStream_t st) {
     size_t lds;
-    const hipError_t e = prepare_sweep<2, false>(&lds);
+    const hipError_t e = A.p == 2 ? prepare_sweep<2, false>(&lds) : prepare_sweep<2, true>(&lds);
     if (e != hipSuccess) return e;
+    const auto sweep = A.p == 2 ? k_dim_sweep<2, false> : k_dim_sweep<2, true>;
+    const auto tests = A.p == 2 ? k_lune_tests<false> : k_lune_tests<true>;
     const unsigned grid = blocks_for((int64_t)A.chunk_n, 4);
     for (int c = 0; c <= chunks; ++c) { // those past the last chunk end at once
-        hipLaunchKernelGGL((k_dim_sweep<2, false>), dim3(1), dim3(kT), lds, st, A, c);
-        if (c < chunks) hipLaunchKernelGGL(k_lune_tests, dim3(grid), dim3(256), 0, st, A, c);
+        hipLaunchKernelGGL(sweep, dim3(1), dim3(kT), lds, st, A, c);
+        if (c < chunks) hipLaunchKernelGGL(tests, dim3(grid), dim3(256), 0, st, A, c);
     }
     return hipSuccess;
 }

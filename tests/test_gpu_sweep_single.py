@@ -180,9 +180,11 @@ def octahedra(k, seed):
     return x.astype(np.float32)
 
 
-@pytest.mark.parametrize("kind", ["sphere-5", "sphere-12", "sphere-64", "sphere-65", "sphere-129", "cube-70", "so3-300",
-                                  "o3-300", "mixture-90", "voids-80", "lattice-60", "line-40", "torus-1500"])
-def test_dimension_2_by_blocks_vs_column_reduction(kind):
+@pytest.mark.parametrize("p", [2, 3, 65521])
+@pytest.mark.parametrize("kind", ["sphere-5", "sphere-46", "sphere-64", "sphere-65", "sphere-129", "cube-70", "so3-300",
+                                  "so3-700", "o3-300", "o3-600", "mixture-90", "voids-1500", "lattice-60", "line-60",
+                                  "torus-1500"])
+def test_dimension_2_by_blocks_vs_column_reduction(kind, p):
     import torch
     name, n = kind.split("-")
     n = int(n)
@@ -198,8 +200,8 @@ def test_dimension_2_by_blocks_vs_column_reduction(kind):
         "line": lambda: (workloads.uniform_cube(n, 1, s), INF, 2),      # no class at all
         "torus": lambda: (workloads.clifford_torus(n, 0.02, s), 0.55, 2),
     }[name]()
-    print(f"[case] dimension 2 {kind}", flush=True)
-    both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t)
+    print(f"[case] dimension 2 {kind} p={p}", flush=True)
+    both(torch.from_numpy(x).cuda(), max_dim=max_dim, threshold=t, p=p)
 
 
 @pytest.mark.parametrize("digits", [2, 3, 4, 5])
@@ -210,12 +212,12 @@ def test_dimension_2_some_ties(data, digits):
     import torch
     s = workloads.SEED_BASE + digits
     for seed in (s, s + 100, s + 200):
-        x = workloads.orthogonal(220, seed) if data == "o3" else workloads.sphere(44, seed)
+        x = workloads.orthogonal(520, seed) if data == "o3" else workloads.sphere(52, seed)
         d = np.sqrt(((x[:, None].astype(np.float64) - x[None]) ** 2).sum(2)).round(digits).astype(np.float32)
         d = torch.from_numpy(np.ascontiguousarray(d)).cuda()
-        for max_dim in (2, 3):
-            print(f"[case] dimension 2 some ties {data} digits={digits} max_dim={max_dim}", flush=True)
-            both(d, max_dim=max_dim, threshold=1.8 if data == "o3" else INF, is_distance=True)
+        for max_dim, p in ((2, 2), (3, 2), (2, 3)):
+            print(f"[case] dimension 2 some ties {data} digits={digits} max_dim={max_dim} p={p}", flush=True)
+            both(d, max_dim=max_dim, threshold=1.8 if data == "o3" else INF, is_distance=True, p=p)
 
 
 def test_dimension_2_large_lune():
