@@ -4,10 +4,9 @@
 One step = the barcodes of the circles-64x400 batch, the largest of the five
 workloads: 64 clouds of 400 points in R^2 (360 on the unit circle with
 Gaussian noise 0.1, 40 uniform outliers in [-2, 2]^2), float32, full Rips (the
-enclosing radius), dimensions 0-1, Z/2, all in one persistent launch replayed
-from a hipGraph (distances, threshold, H0, enumeration / apparent-pair
-filter, column sort and Z/p reduction for every cloud). The input is
-resident in HBM before the timed region.
+enclosing radius), dimensions 0-1, Z/2, all in one persistent launch
+(distances, threshold, zero apparent pairs, H0 and the sweep over the edges
+for every cloud). The input is resident in HBM before the timed region.
 
 value = simplices/s = the sum over the 64 clouds of |K_0| + |K_1| + |K_2| at
 each cloud's threshold (the size of the explicit filtrations the method
@@ -160,7 +159,7 @@ def _classify(per):
             out.setdefault(f"filter_d{dim}", []).append(v)
         elif "k_reduce" in name:
             out.setdefault(f"reduce_d{dim}", []).append(v)
-        elif "k_batched" in name:
+        elif "k_batched" in name or "k_sweep<" in name:
             out.setdefault("batched", []).append(v)
         elif "copy" in name.lower() or "elementwise" in name.lower():
             copies.append(v)
@@ -258,7 +257,7 @@ def summarize_trace(trace_dir: str) -> int:
     # (a reduction relaunched after a scratch overflow has no filter of its own)
     per, nfilter, dim = {}, 0, 0
     for _, name, ns in rows:
-        short = name.split("(")[0].replace("void ", "")
+        short = name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")
         if "k_filter" in name:
             dim = 1 + nfilter % 2
             nfilter += 1
@@ -302,8 +301,8 @@ def batched_bytes(clouds, counts, stats) -> float:
     """Algorithmic HBM bytes of one batched launch: per cloud the distances
     (points read once, 4 B per pair written), one read of them by the
     threshold / H0 / enumeration passes (4 B per pair), the surviving columns
-    written (12 B each) and sorted (2 x 17 B), the reduction's columns
-    (17 B) and entries added or stored (16 B each), and the bars (24 B)."""
+    written (12 B each) and sorted (2 x 17 B), the classes (17 B) and the
+    words of the rows added or stored (4 B each), and the bars (24 B)."""
     total = 0.0
     for b, x in enumerate(clouds):
         n, m = x.shape
@@ -312,7 +311,7 @@ def batched_bytes(clouds, counts, stats) -> float:
         cols = s[1]["columns"]
         bars = s[0]["bars_nonzero"] + s[0]["essential"] + s[1]["bars_nonzero"] + s[1]["essential"]
         total += (4.0 * n * m + 4.0 * pairs + 4.0 * pairs + 12.0 * cols + 34.0 * cols
-                  + 17.0 * cols + 16.0 * (s[1]["entries_added"] + s[1]["entries_stored"])
+                  + 17.0 * cols + 4.0 * (s[1]["entries_added"] + s[1]["entries_stored"])
                   + 24.0 * bars)
     return total
 
@@ -437,8 +436,8 @@ def main() -> int:
     gach = gbytes / (glaunch * 1e-3) / 1e9
     tr = pmc.get("batched") if pmc else None
     roofline = {
-        "kernel": "k_batched (the batched launch: one hipGraph of the LPT order, the persistent "
-                  "kernel and the bar layout)",
+        "kernel": "k_sweep (the batched launch: the order of the clouds, the persistent kernel "
+                  "and the bar layout)",
         "bound": "hbm",
         "achieved": round(gach, 4),
         "peak": HBM_PEAK_GBS,
@@ -447,8 +446,8 @@ def main() -> int:
         "traffic": round(tr[0] + tr[1], 1) if tr else None,
         "bytes_per_launch": gbytes,
         "avg_launch_us": round(glaunch * 1e3, 3),
-        "note": "latency-bound: each cloud's dimension-1 reduction is a chain of dependent "
-                "column additions in one workgroup; the HBM roof is far away",
+        "note": "bound by instruction issue and latency: each cloud's edges are swept by one "
+                "workgroup in order of length; the HBM roof is far away",
     }
     elim5 = {}
     for key in ("candidates", "cleared", "apparent_col", "columns", "emergent", "reduced",

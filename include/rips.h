@@ -368,12 +368,14 @@ rips_status rips_set_reduced_storage(int32_t mode);
 rips_status rips_get_reduced_storage(int32_t *mode);
 
 /*
- * The method of dimension 1 (per device, the current one; single-cloud and
- * batched paths). AUTO takes the sweep where it applies (Z/2, every shortcut
- * and the default storage, no cocycles, a cloud that is small or of a middling
- * number of edges a point): one pass over the edges in order of length that
- * carries on every edge the vector of the open classes, closed by the first
- * triangle whose three vectors do not cancel; no coboundary column is reduced.
+ * The method of dimensions 0 to 2 (per device, the current one; single-cloud
+ * and batched paths). AUTO takes the sweep where it applies and pays (every
+ * shortcut and the default storage, no cocycles; batches over Z/2; in the
+ * single-cloud path dimensions 0 and 1 of small clouds, dimension 1 of clouds
+ * with a middling number of edges a point and dimension 2 from some 12,000
+ * triangles on): one pass over the simplices in order of diameter that carries
+ * on every simplex the vector of the open classes, closed by the first cofacet
+ * whose facets' vectors do not cancel; no coboundary column is reduced.
  * Otherwise the columns are reduced, with one of two working columns. A column's rows are
  * triangles, and over Z/2 with every shortcut on it can be held direct-mapped: one bit per
  * (longest edge, third vertex), the edges <= t in order of length, so that

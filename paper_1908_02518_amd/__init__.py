@@ -599,7 +599,7 @@ WORKING_COLUMN_GENERAL = 1
 
 def set_working_column(mode: int = WORKING_COLUMN_AUTO):
     """Method of the low dimensions: WORKING_COLUMN_AUTO takes the sweep where
-    it applies (Z/2, every shortcut on), else reduces columns, direct-mapped
+    it applies and pays (every shortcut on), else reduces columns, direct-mapped
     (one bit per longest edge and third vertex) where that fits;
     WORKING_COLUMN_GENERAL always reduces columns with the general working
     column. The bars are the same either way."""

@@ -231,3 +231,43 @@ def test_dimension_2_large_lune():
     d[far] = 3.0
     print("[case] dimension 2 large lune", flush=True)
     both(torch.from_numpy(np.ascontiguousarray(d)).cuda(), max_dim=2, threshold=2.5, is_distance=True)
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 3001])
+@pytest.mark.parametrize("data", ["torus", "lattice"])
+def test_dimension_0_on_both_sides_of_the_wide_boruvka(data, n):
+    """Many components at the threshold; the lattice: equal lengths and duplicate points."""
+    import torch
+    s = workloads.SEED_BASE + n
+    x = workloads.clifford_torus(n, 0.02, s) if data == "torus" else workloads.integer_lattice(n, 3, s, side=17)
+    t = 0.08 if data == "torus" else 1.0
+    print(f"[case] dimension 0 {data} n={n}", flush=True)
+    ref = oracle.barcode(x, max_dim=0, threshold=t, p=2)
+    got, _ = bars(torch.from_numpy(x).cuda(), max_dim=0, threshold=t)
+    want = (ref.bars[0].birth, ref.bars[0].death, ref.bars[0].birth_simplex, ref.bars[0].death_simplex)
+    for g, w in zip(got[0], want):
+        assert np.array_equal(g, w)
+
+
+@pytest.mark.parametrize("kind", ["sphere-70", "sphere-150", "sphere-65", "lattice-150"])
+def test_columns_sorted_by_the_whole_chip(kind):
+    """Without the apparent pairs every edge off the forest is a column: 2016
+    (below the rule), 2346 and 11,026, and thousands of one length, which are
+    left to one workgroup."""
+    r = rips()
+    name, n = kind.split("-")
+    s = workloads.SEED_BASE + int(n)
+    x = workloads.sphere(int(n), s) if name == "sphere" else workloads.integer_lattice(int(n), 2, s, side=2)
+    print(f"[case] wide sort {kind}", flush=True)
+    ref = oracle.barcode(x, max_dim=1, threshold=INF, p=2)
+    r.set_working_column()
+    r.set_shortcuts(r.SHORTCUT_EMERGENT | r.SHORTCUT_CLEARING)
+    try:
+        got = r.barcode(x, max_dim=1)
+    finally:
+        r.set_shortcuts()
+    for d in range(2):
+        want = (ref.bars[d].birth, ref.bars[d].death, ref.bars[d].birth_simplex, ref.bars[d].death_simplex)
+        b = got.bars[d]
+        for g, w in zip((b.birth, b.death, b.birth_simplex, b.death_simplex), want):
+            assert np.array_equal(g, w), d
