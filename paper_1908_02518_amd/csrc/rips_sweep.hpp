@@ -22,7 +22,7 @@ constexpr int kSweepFull = 512;
 
 // What the sweep of one cloud reports, in pinned host memory.
 struct SweepSingle {
-    int status; // 4: not finite, kSweepFull, else 0
+    int status; // kSweepFull (the staged path decides), else 0
     float t, renc;
     int64_t count[2];
     rips_dim_stats stats[2];
