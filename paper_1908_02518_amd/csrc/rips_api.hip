@@ -1983,6 +1983,7 @@ rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_off
     A.ucap = out->cap;
     A.seg_start = F.seg_start;
     A.seg_count = F.seg_count;
+    F.status = A.status;
     launch_sweep_order(d_offsets, B, n_max, order, A.queue, A.ucount, A.status, st);
     {
         PROF(P_BATCHED);

@@ -1122,14 +1122,18 @@ __global__ void __launch_bounds__(1024) k_batch_offsets(const int64_t *seg_count
     }
 }
 
+// All segments or none: the caller's arrays stay as they are when the bars
+// exceed cap or a cloud has given none (status). A segment's place in the
+// unordered buffer, which holds cap entries too, says nothing about its place
+// in the output: with more bars than cap a segment that fits the output may
+// lie past the buffer's end.
 __global__ void k_batch_copy(const int64_t *seg_start, const int64_t *seg_count,
                              const int64_t *offsets, int nseg, const float *ub, const float *ud,
-                             const int64_t *ubs, const int64_t *uds, int64_t cap, float *ob,
+                             const int64_t *ubs, const int64_t *uds, int64_t cap, const int *status, float *ob,
                              float *od, int64_t *obs, int64_t *ods) {
     const int sgi = blockIdx.x;
-    if (sgi >= nseg) return;
+    if (sgi >= nseg || offsets[nseg] > cap || *status) return;
     const int64_t src = seg_start[sgi], cnt = seg_count[sgi], dst = offsets[sgi];
-    if (dst + cnt > cap) return;
     for (int64_t q = threadIdx.x; q < cnt; q += blockDim.x) {
         ob[dst + q] = ub[src + q];
         od[dst + q] = ud[src + q];
@@ -1191,7 +1195,7 @@ void launch_batch_finalize(const BatchArgs &A, int64_t *offsets_out, int64_t *to
     hipLaunchKernelGGL(k_batch_offsets, dim3(1), dim3(1024), 0, st, A.seg_count, nseg, offsets_out,
                        total);
     hipLaunchKernelGGL(k_batch_copy, dim3(nseg), dim3(256), 0, st, A.seg_start, A.seg_count,
-                       offsets_out, nseg, A.ub, A.ud, A.ubs, A.uds, cap, ob, od, obs, ods);
+                       offsets_out, nseg, A.ub, A.ud, A.ubs, A.uds, cap, A.status, ob, od, obs, ods);
 }
 
 } // namespace rips
