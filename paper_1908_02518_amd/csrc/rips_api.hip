@@ -1083,15 +1083,15 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
             launch_dim_partition(A, st);
         }
         // the owned cofacets are counted: room for them
-        u32 *total_h = (u32 *)C.host_scal;
-        HIP_TRY(hipMemcpyAsync(total_h, A.bin_t + A.nbins, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(C.host_scal, A.out, sizeof(DimOut), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         prof_resolve();
-        const int64_t total = (int64_t)*total_h;
-        if (total > (1ll << 28)) { // above 3 GiB of places
+        const uint64_t total = ((const DimOut *)C.host_scal)->owned;
+        if (!owned_fit(total)) {
             *full = true;
             return RIPS_OK;
         }
+        A.ntau = (u32)total;
         ENS(B_SD_TAU, (size_t)total * 12, A.tau, u32);
     } else {
         A.E = P.E;

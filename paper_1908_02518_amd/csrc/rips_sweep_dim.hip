@@ -175,6 +175,7 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
     const float *D = A.c.d.D;
     const int64_t per_wave = kWave / G;
     const int64_t w0 = (blockIdx.x * 256ll + threadIdx.x) / kWave * per_wave;
+    unsigned long long owned = 0; // the 32-bit counts of the bins may wrap
     for (int64_t base = w0; base < A.N; base += groups) {
         const int64_t q = base + lane / G;
         const bool live = q < A.N;
@@ -230,8 +231,10 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
                     }
                 }
                 const u64 hit = __ballot(ok) & gmask;
-                if (kFill && pass == 1 && ok) {
-                    const u32 e = put + (u32)__popcll(hit & ((1ull << lane) - 1));
+                const u32 e = put + (u32)__popcll(hit & ((1ull << lane) - 1));
+                if (kFill && pass == 1 && ok && e >= A.ntau) {
+                    A.out->full = kDimBroken;
+                } else if (kFill && pass == 1 && ok) {
                     u32 *o = A.tau + (int64_t)e * (K + 2);
                     // over a field other than Z/2 a place has a sign, on the
                     // edge between the triangle's ends
@@ -254,9 +257,14 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
             if (pass == 0) {
                 total = mine; // the same in every lane of the group
                 if (live && lg == 0 && total > 0) at = atomicAdd(&A.bin_t[bin], (u32)total);
+                if (live && lg == 0) owned += (unsigned long long)total;
                 at = __shfl(at, g0, kWave);
             }
         }
+    }
+    if constexpr (!kFill) {
+        for (int o = 32; o >= G; o >>= 1) owned += __shfl_down(owned, o, kWave);
+        if (lane == 0 && owned) atomicAdd(&A.out->owned, owned);
     }
 }
 
@@ -1223,7 +1231,8 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
         for (int i = tid; i * (kOdd ? 1 : 2) < rows; i += kT) ((LDS u32 *)rmap)[i] = rm[i];
     } else {
         if (tid == 0) {
-            Sh.nact = Sh.nnz = Sh.fail = Sh.nfree = Sh.ndead = Sh.since = 0;
+            Sh.nact = Sh.nnz = Sh.nfree = Sh.ndead = Sh.since = 0;
+            Sh.fail = A.out->full; // what the passes before found
             Sh.nrows = 1; // row 0: the zero vector
             rmap[0] = 0;
             Sh.sfree = nslots;
@@ -1879,6 +1888,7 @@ hipError_t prepare_sweep(size_t *lds) {
 
 void launch_dim_partition(const DimArgs &A, hipStream_t st) {
     launch_fill_u32(A.bin_n, 3 * (kDimBins + 64), 0u, st); // bin_n, bin_t and bin_s are one buffer
+    launch_fill_u32((u32 *)A.out, sizeof(DimOut) / 4, 0u, st);
     hipLaunchKernelGGL((k_dim_hist<1>), dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_dim_scan, dim3(2), dim3(kT), 0, st, A.bin_n, A.bin_s, A.nbins);
     if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "rips_kernels.hpp"
+#include "rips_rules.hpp"
 
 namespace rips {
 
@@ -22,6 +23,7 @@ struct DimOut {
     int npair;                // dimension 2: cofacets of the chunk that do not cancel
     int ntied, npairs_tied;
     int nclasses;             // dimension 2: columns that no cofacet of their own block pairs
+    unsigned long long owned; // dimension 1: triangles counted
     unsigned long long adds, rows;
     int64_t nbars, nonzero, essential, emergent, reduced;
     int64_t loc_emergent, loc_reduced; // dimension 2: columns paired within their block
@@ -52,7 +54,8 @@ struct DimArgs {
     u32 *direct;
     PivotHash ph;
     // dimension 1: the cofacets whose youngest facet is q: q and the places of the other two
-    u32 *tau;             // total x 3, entry-major
+    u32 *tau;             // ntau x 3, entry-major
+    u32 ntau;
     // dimension 2: a block is the triangles of one longest edge, at consecutive places
     EdgeList E;           // the edges <= t
     int64_t nE;
@@ -83,7 +86,8 @@ struct DimArgs {
     DimOut *out;
 };
 
-// dimension 1: edges by bin, owned triangles counted (total in bin_t[nbins]); then written out
+// dimension 1: edges by bin, owned triangles counted (out->owned; the bins'
+// counts are good only if that is owned_fit); then written out
 void launch_dim_partition(const DimArgs &A, hipStream_t st);
 void launch_dim_fill(const DimArgs &A, hipStream_t st);
 // dimension 2: triangles by block and bin, the blocks' forests, the pairs

@@ -1,0 +1,38 @@
+"""The arithmetic of the rules that choose a method (csrc/rips_rules.hpp is
+plain C++), compiled and run on the CPU."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+def run(tmp_path, body):
+    src = tmp_path / "rules.cpp"
+    src.write_text('#include <cmath>\n#include <cstdio>\n#include <initializer_list>\n#include "rips_rules.hpp"\n'
+                   "using namespace rips;\nint main() {\n" + body + "\n}\n")
+    exe = str(tmp_path / "rules")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "paper_1908_02518_amd", "csrc"), str(src),
+                    "-o", exe], check=True)
+    return subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()
+
+
+def test_triangles_are_counted_in_64_bits(tmp_path):
+    """One cluster of 2955 to 3014 points has 2^32 triangles and fewer than
+    2^28 more: counted in 32 bits they seem to fit."""
+    got = run(tmp_path, """
+    for (uint64_t k : {1173ull, 1174ull, 2954ull, 2955ull, 3014ull, 65535ull}) {
+        uint64_t n = 0; // edge by edge, as they are counted
+        for (uint64_t i = 2; i < k; ++i) n += i * (i - 1) / 2;
+        printf("%d %d ", (int)owned_fit(n), (int)((uint32_t)n <= (1u << 28)));
+    }
+    printf("%d %d", (int)owned_fit(1ull << 28), (int)owned_fit((1ull << 28) + 1));""")
+    fits = [int(x) for x in got[0:12:2]]
+    wrapped = [int(x) for x in got[1:12:2]]
+    assert fits == [1, 0, 0, 0, 0, 0]
+    assert wrapped[3:5] == [1, 1]  # what a count of 32 bits would say
+    assert got[12:] == ["1", "0"]
