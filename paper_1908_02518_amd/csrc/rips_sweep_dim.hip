@@ -112,15 +112,23 @@ __global__ void __launch_bounds__(256) k_dim_hist(DimArgs A) {
 }
 
 // exclusive scan of the bins of one array, in place; one workgroup an array,
-// a multiple of 1024 bins
-__global__ void __launch_bounds__(1024) k_dim_scan(u32 *a0, u32 *a1, int nbins) {
+// a multiple of 1024 bins. total (or null): the sum in 64 bits, all ones if it
+// says that a bin has wrapped.
+__global__ void __launch_bounds__(1024) k_dim_scan(u32 *a0, u32 *a1, int nbins, unsigned long long *total) {
     __shared__ u32 s_w[kWaves];
+    __shared__ unsigned long long s_total;
     u32 *a = blockIdx.x == 0 ? a0 : a1;
     const int per = nbins / kT;
     const int lane = lane_id(), w = threadIdx.x / kWave;
     u32 sum = 0;
+    unsigned long long all = 0;
+    if (threadIdx.x == 0) s_total = 0;
 #pragma unroll 8
-    for (int i = 0; i < per; ++i) sum += a[threadIdx.x * per + i];
+    for (int i = 0; i < per; ++i) {
+        const u32 x = a[threadIdx.x * per + i];
+        sum += x;
+        all += x;
+    }
     u32 inc = sum;
     for (int o = 1; o < kWave; o <<= 1) {
         const u32 x = __shfl_up(inc, o, kWave);
@@ -128,6 +136,10 @@ __global__ void __launch_bounds__(1024) k_dim_scan(u32 *a0, u32 *a1, int nbins) 
     }
     if (lane == kWave - 1) s_w[w] = inc;
     __syncthreads();
+    if (total) {
+        for (int o = 32; o >= 1; o >>= 1) all += __shfl_xor(all, o, kWave);
+        if (lane == 0) atomicAdd(&s_total, all);
+    }
     u32 base = inc - sum;
     for (int q = 0; q < w; ++q) base += s_w[q];
 #pragma unroll 8
@@ -137,6 +149,8 @@ __global__ void __launch_bounds__(1024) k_dim_scan(u32 *a0, u32 *a1, int nbins) 
         base += x;
     }
     if (threadIdx.x == kT - 1) a[nbins] = base;
+    __syncthreads();
+    if (total && threadIdx.x == 0) *total |= s_total;
 }
 
 __global__ void __launch_bounds__(256) k_dim_place(DimArgs A) {
@@ -175,7 +189,6 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
     const float *D = A.c.d.D;
     const int64_t per_wave = kWave / G;
     const int64_t w0 = (blockIdx.x * 256ll + threadIdx.x) / kWave * per_wave;
-    unsigned long long owned = 0; // the 32-bit counts of the bins may wrap
     for (int64_t base = w0; base < A.N; base += groups) {
         const int64_t q = base + lane / G;
         const bool live = q < A.N;
@@ -256,15 +269,13 @@ __global__ void __launch_bounds__(256) k_dim_own(DimArgs A) {
             }
             if (pass == 0) {
                 total = mine; // the same in every lane of the group
-                if (live && lg == 0 && total > 0) at = atomicAdd(&A.bin_t[bin], (u32)total);
-                if (live && lg == 0) owned += (unsigned long long)total;
+                if (live && lg == 0 && total > 0) {
+                    at = atomicAdd(&A.bin_t[bin], (u32)total);
+                    if (!kFill && at + (u32)total < at) A.out->owned = ~0ull; // the bin has wrapped
+                }
                 at = __shfl(at, g0, kWave);
             }
         }
-    }
-    if constexpr (!kFill) {
-        for (int o = 32; o >= G; o >>= 1) owned += __shfl_down(owned, o, kWave);
-        if (lane == 0 && owned) atomicAdd(&A.out->owned, owned);
     }
 }
 
@@ -1890,12 +1901,13 @@ void launch_dim_partition(const DimArgs &A, hipStream_t st) {
     launch_fill_u32(A.bin_n, 3 * (kDimBins + 64), 0u, st); // bin_n, bin_t and bin_s are one buffer
     launch_fill_u32((u32 *)A.out, sizeof(DimOut) / 4, 0u, st);
     hipLaunchKernelGGL((k_dim_hist<1>), dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(2), dim3(kT), 0, st, A.bin_n, A.bin_s, A.nbins);
+    hipLaunchKernelGGL(k_dim_scan, dim3(2), dim3(kT), 0, st, A.bin_n, A.bin_s, A.nbins,
+                       (unsigned long long *)nullptr);
     if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);
     hipLaunchKernelGGL(k_dim_place, dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
     if (A.c.nb.off) hipLaunchKernelGGL((k_dim_own<16, false>), dim3(blocks_for(A.N, 16)), dim3(256), 0, st, A);
     else hipLaunchKernelGGL((k_dim_own<64, false>), dim3(blocks_for(A.N, 4)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_t, A.bin_t, A.nbins);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_t, A.bin_t, A.nbins, &A.out->owned);
 }
 
 void launch_dim_fill(const DimArgs &A, hipStream_t st) {
@@ -1915,7 +1927,7 @@ void launch_lune_partition(const DimArgs &A, PivotHash piv, hipStream_t st) {
     launch_fill_u32(A.need, A.N / 32 + 1, 0u, st);
     if (!A.direct) launch_fill_i64(A.ph.keys, (int64_t)A.ph.mask + 1, kEmpty, st);
     hipLaunchKernelGGL((k_lune<false>), dim3(blocks_for(A.nE, 4)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_n, A.bin_n, A.nbins);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_n, A.bin_n, A.nbins, (unsigned long long *)nullptr);
     hipLaunchKernelGGL((k_lune<true>), dim3(blocks_for(A.nE, 4)), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_lune_deps, dim3(blocks_for(A.N, 256)), dim3(256), 0, st, A);
     if (A.strict) {
@@ -1927,7 +1939,7 @@ void launch_lune_partition(const DimArgs &A, PivotHash piv, hipStream_t st) {
 
 void launch_lune_chunks(const DimArgs &A, hipStream_t st) {
     hipLaunchKernelGGL((k_dim_hist<2>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
-    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_s, A.bin_s, A.nbins);
+    hipLaunchKernelGGL(k_dim_scan, dim3(1), dim3(kT), 0, st, A.bin_s, A.bin_s, A.nbins, (unsigned long long *)nullptr);
     hipLaunchKernelGGL((k_dim_births<2>), dim3(blocks_for(A.S, 256)), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_dim_chunks, dim3(1), dim3(kT), 0, st, A);
 }
