@@ -1100,7 +1100,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
         A.all = cols;
         A.nall = (int)S;
         A.strict = max_dim > 2;
-        A.paircap = 1 << 21;
+        A.paircap = kMostPairs;
         ENS(B_SD_BLOCK, A.nE * 8, A.bstart, u32);
         A.bcnt = A.bstart + A.nE;
         ENS(B_SD_TIED, (size_t)kTiedPairs * 12 + kTiedMax * 4, A.ttet, int64_t);

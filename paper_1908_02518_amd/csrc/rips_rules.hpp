@@ -13,4 +13,9 @@ namespace rips {
 constexpr uint64_t kMostOwned = 1ull << 28;
 constexpr bool owned_fit(uint64_t triangles) { return triangles <= kMostOwned; }
 
+// Cofacets of a chunk of dimension 2 that do not cancel, of which the sweep
+// holds this many. A wave ends with its first append (64 at most) past that.
+constexpr int kMostPairs = 1 << 21;
+constexpr int64_t most_pairs(int64_t cap, int64_t waves) { return cap + waves * 64; }
+
 } // namespace rips

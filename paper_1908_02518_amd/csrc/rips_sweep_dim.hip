@@ -56,6 +56,7 @@ constexpr int kCandWords = 16384;   // and their vectors, in words
 constexpr int kPurge = 32;          // eliminations between two purges
 constexpr int kTaus = 4;            // cofacets a lane has in flight
 constexpr int kLune = 1024;         // points of a lune
+constexpr int kMostBlocks = 16384;  // of a grid
 
 __device__ __forceinline__ int dim_bin(const DimArgs &A, float d) {
     return min(A.nbins - 1, (int)(d * A.scale)); // monotone; equal diameters share a bin
@@ -1114,6 +1115,9 @@ __global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
                     nonzero = sum_word<4>(A, r, __ffsll((unsigned long long)m) - 1) != 0;
             const int at = dim_append(nonzero, &A.out->npair);
             if (nonzero && at < A.paircap) A.pairs[at] = ((u64)q << 32) | (u32)d;
+            // too many: the sweep ends after this, and the count goes no
+            // further than one append of every wave takes it
+            if (__any(nonzero && at >= A.paircap)) return;
         }
     }
 }
@@ -1885,7 +1889,7 @@ __global__ void __launch_bounds__(1024) k_dim_bars(DimArgs A, BarBuf out, PivotH
 }
 
 unsigned blocks_for(int64_t n, int per) {
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, 16384));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + per - 1) / per, kMostBlocks));
 }
 
 template <int K, bool kOdd>
@@ -1960,6 +1964,7 @@ hipError_t launch_lune_sweep(const DimArgs &A, int chunks, hipStream_t st) {
     const auto sweep = A.p == 2 ? k_dim_sweep<2, false> : k_dim_sweep<2, true>;
     const auto tests = A.p == 2 ? k_lune_tests<false> : k_lune_tests<true>;
     const unsigned grid = blocks_for((int64_t)A.chunk_n, 4);
+    static_assert(most_pairs(kMostPairs, kMostBlocks * 4) < 1ll << 31, "npair is an int");
     for (int c = 0; c <= chunks; ++c) { // those past the last chunk end at once
         hipLaunchKernelGGL(sweep, dim3(1), dim3(kT), lds, st, A, c);
         if (c < chunks) hipLaunchKernelGGL(tests, dim3(grid), dim3(256), 0, st, A, c);

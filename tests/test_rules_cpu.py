@@ -36,3 +36,10 @@ def test_triangles_are_counted_in_64_bits(tmp_path):
     assert fits == [1, 0, 0, 0, 0, 0]
     assert wrapped[3:5] == [1, 1]  # what a count of 32 bits would say
     assert got[12:] == ["1", "0"]
+
+
+def test_count_of_pairs_fits_its_type(tmp_path):
+    """However many there are: every wave of the largest grid ends with its
+    first append past the capacity."""
+    got = run(tmp_path, 'printf("%lld", (long long)most_pairs(kMostPairs, 16384 * 4));')
+    assert int(got[0]) == (1 << 21) + 65536 * 64 < 2 ** 31
