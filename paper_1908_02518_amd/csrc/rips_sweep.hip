@@ -514,8 +514,9 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                     d = INFINITY;
                 } else if (m > 0) {
                     float s = 0.0f;
+                    const float *xi = X + (int64_t)i * m, *xj = X + (int64_t)j * m;
                     for (int c = 0; c < m; ++c) {
-                        const float t = X[i * m + c] - X[j * m + c];
+                        const float t = xi[c] - xj[c];
                         const float sq = t * t;
                         s = s + sq;
                     }
