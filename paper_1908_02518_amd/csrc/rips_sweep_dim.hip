@@ -1266,7 +1266,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
         if (vectors && s1 > s0) {
             const int ns = s1 - s0, nf = Sh.sfree, nr = Sh.nfree, top = Sh.nrows, na = Sh.nact, nz = Sh.nnz;
             const int fresh = max(0, ns - nr);
-            if (ns > nf || top + fresh > kRows) {
+            if (ns > nf || top + fresh > kRows || (int64_t)nz + ns > A.N) { // (a triangle may be listed twice)
                 __syncthreads();
                 if (tid == 0) Sh.fail = 1;
                 __syncthreads();
