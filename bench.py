@@ -430,7 +430,7 @@ def main() -> int:
     st5 = [[{f: int(stats5[b, d, q]) for q, f in enumerate(fields)} for d in range(2)]
            for b in range(len(clouds5))]
     pmc = read_pmc_summary(PMC_SUMMARY_BATCH)
-    gms, gcalls = prof5["batched_graph"]
+    gms, gcalls = prof5["batched_sweep"]
     glaunch = gms / gcalls
     gbytes = batched_bytes(clouds5, counts5, st5)
     gach = gbytes / (glaunch * 1e-3) / 1e9

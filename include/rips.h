@@ -303,11 +303,13 @@ rips_status rips_backward_device(const float *d_data, int64_t n, int32_t dim, in
  * (Algorithm 2 on the coboundary matrix, section "Persistent cohomology",
  * with the shortcut of section "Emergent persistence pairs"). 1: the
  * columns one after another in one workgroup.
- * Results are bit-identical either way. A call, with any count, asks for the
- * column reduction in dimensions that the sweep would take (the counters of
- * rips_dim_stats are then those of the columns, the same for every count);
- * rips_set_working_column(RIPS_WORKING_COLUMN_AUTO) returns to the choice of
- * the method. Returns RIPS_E_INVALID_ARG for a negative count; rips_get_reduce_workgroups reads the setting back.
+ * Results are bit-identical either way. A call, with any count, 0 included,
+ * asks for the column reduction in dimensions that the sweep would take (the
+ * counters of rips_dim_stats are then those of the columns, the same for every
+ * count): it clears RIPS_SWEEP_SINGLE (rips_set_sweep, which sets it again, as
+ * rips_set_working_column(RIPS_WORKING_COLUMN_AUTO) does). Returns
+ * RIPS_E_INVALID_ARG for a negative count; rips_get_reduce_workgroups reads
+ * the setting back.
  */
 rips_status rips_set_reduce_workgroups(int32_t workgroups);
 rips_status rips_get_reduce_workgroups(int32_t *workgroups);
@@ -388,12 +390,29 @@ rips_status rips_get_reduced_storage(int32_t *mode);
  *     within 8 GiB), else the general working column;
  *   RIPS_WORKING_COLUMN_GENERAL: always the columns, with the general one
  *     (LDS delta, sorted base, far list).
+ * A call with RIPS_WORKING_COLUMN_AUTO also sets both bits of rips_set_sweep.
  * The bars are the same either way. Other values: RIPS_E_INVALID_ARG.
  */
 #define RIPS_WORKING_COLUMN_AUTO 0
 #define RIPS_WORKING_COLUMN_GENERAL 1
 rips_status rips_set_working_column(int32_t mode);
 rips_status rips_get_working_column(int32_t *mode);
+
+/*
+ * Where the sweep may run (per device, the current one): in the single-cloud
+ * path (RIPS_SWEEP_SINGLE), in the batched one (RIPS_SWEEP_BATCHED), default
+ * both. Without its bit a path reduces columns, direct-mapped where that
+ * applies. Flags outside the two bits: RIPS_E_INVALID_ARG; rips_get_sweep
+ * reads the setting back, as rips_set_reduce_workgroups and
+ * rips_set_working_column leave it. Which method ran a call, the sweep or,
+ * where a table of the sweep was full, the columns after it, is told by the
+ * kernel classes of rips_profile_enable (sweep, sweep_d1, sweep_d2,
+ * batched_sweep against reduce_d1, reduce_d2, batched_graph).
+ */
+#define RIPS_SWEEP_SINGLE 1
+#define RIPS_SWEEP_BATCHED 2
+rips_status rips_set_sweep(int32_t flags);
+rips_status rips_get_sweep(int32_t *flags);
 
 /*
  * The homology variant, for the ablation of the sections "Clearing
@@ -418,7 +437,9 @@ rips_status rips_barcode_homology(const float *data, int64_t n, int32_t dim, int
                                   float threshold, uint32_t p, rips_result **out);
 
 /*
- * Launch configuration of the batched path (per device, the current one):
+ * Launch configuration of the column reduction of the batched path (per
+ * device, the current one; the sweep, which takes most batches over Z/2, has
+ * none):
  *   delta_slots        LDS slots of each workgroup's working-column delta:
  *                      512, 1024 or 2048 (0 = default, 2048);
  *   workgroups_per_cu  persistent workgroups per compute unit, 1..4
@@ -430,7 +451,8 @@ rips_status rips_batched_set_config(int32_t delta_slots, int32_t workgroups_per_
 rips_status rips_batched_get_config(int32_t *delta_slots, int32_t *workgroups_per_cu);
 
 /*
- * Workgroups per cloud of the batched path (per device, the current one).
+ * Workgroups per cloud of the batched column reduction (per device, the
+ * current one; the sweep keeps one workgroup a cloud).
  * mode 0 (default): a batch of B clouds with at least two compute units per
  * cloud spreads each cloud over min(8, CUs / B) workgroups: one of them runs
  * the cloud's distances, H0, enumeration filter, column sort and edge order,

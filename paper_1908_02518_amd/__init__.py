@@ -47,6 +47,8 @@ EXPORTS = (
     "rips_barcode_homology",
     "rips_set_working_column",
     "rips_get_working_column",
+    "rips_set_sweep",
+    "rips_get_sweep",
     "rips_set_reduced_storage",
     "rips_get_reduced_storage",
     "rips_cocycles_free",
@@ -213,6 +215,10 @@ def _load():
     lib.rips_set_shortcuts.restype = ctypes.c_int
     lib.rips_get_shortcuts.argtypes = [ctypes.POINTER(ctypes.c_int32)]
     lib.rips_get_shortcuts.restype = ctypes.c_int
+    lib.rips_set_sweep.argtypes = [ctypes.c_int32]
+    lib.rips_set_sweep.restype = ctypes.c_int
+    lib.rips_get_sweep.argtypes = [ctypes.POINTER(ctypes.c_int32)]
+    lib.rips_get_sweep.restype = ctypes.c_int
     lib.rips_set_working_column.argtypes = [ctypes.c_int32]
     lib.rips_set_working_column.restype = ctypes.c_int
     lib.rips_get_working_column.argtypes = [ctypes.POINTER(ctypes.c_int32)]
@@ -552,8 +558,8 @@ def barcode_batched(x, offsets, n_max: int, *, max_dim: int = 1,
 def set_reduce_workgroups(workgroups: int = 0):
     """Workgroups of the single-cloud reduction: 0 = one per compute unit,
     1 = one workgroup, columns one after another (same bars either way). A
-    call asks for the column reduction where the sweep would run, until
-    set_working_column() returns to the choice of the method."""
+    call, with 0 too, clears SWEEP_SINGLE: clouds go by columns until
+    set_sweep() or set_working_column() sets it again."""
     _check(_lib.rips_set_reduce_workgroups(int(workgroups)))
 
 
@@ -606,6 +612,22 @@ def set_working_column(mode: int = WORKING_COLUMN_AUTO):
     _check(_lib.rips_set_working_column(int(mode)))
 
 
+SWEEP_SINGLE = 1
+SWEEP_BATCHED = 2
+
+
+def set_sweep(flags: int = SWEEP_SINGLE | SWEEP_BATCHED):
+    """Where the sweep may run: for single clouds, for batches, or (the
+    default) both; elsewhere columns are reduced. The bars are the same."""
+    _check(_lib.rips_set_sweep(int(flags)))
+
+
+def get_sweep() -> int:
+    a = ctypes.c_int32()
+    _check(_lib.rips_get_sweep(ctypes.byref(a)))
+    return int(a.value)
+
+
 def get_working_column() -> int:
     a = ctypes.c_int32()
     _check(_lib.rips_get_working_column(ctypes.byref(a)))
@@ -625,12 +647,12 @@ def get_shortcuts() -> int:
 
 
 def batched_set_config(delta_slots: int = 0, workgroups_per_cu: int = 0):
-    """Launch configuration of the batched path (0 = defaults)."""
+    """Launch configuration of the batched column reduction (0 = defaults)."""
     _check(_lib.rips_batched_set_config(int(delta_slots), int(workgroups_per_cu)))
 
 
 def batched_set_spread(mode: int = 0):
-    """Workgroups per cloud of the batched path: 0 (auto) spreads each cloud
+    """Workgroups per cloud of the batched column reduction: 0 (auto) spreads each cloud
     of a batch smaller than the chip over several workgroups, 1 keeps one
     workgroup per cloud. The bars are the same either way."""
     _check(_lib.rips_batched_set_spread(int(mode)))
@@ -645,9 +667,9 @@ def batched_get_config():
 def batched_autotune(x, offsets, n_max: int, *, max_dim: int = 1,
                      threshold: float = float("inf"), p: int = 2, reps: int = 2,
                      cap: int | None = None):
-    """Time every batched launch configuration on this batch and keep the
-    fastest (rips_batched_autotune). Returns (delta_slots, workgroups_per_cu,
-    ms per launch)."""
+    """Time every launch configuration of the batched column reduction on this
+    batch and keep the fastest (rips_batched_autotune; the sweep has none).
+    Returns (delta_slots, workgroups_per_cu, ms per launch)."""
     import torch
     bb = barcode_batched(x, offsets, n_max, max_dim=max_dim, threshold=threshold, p=p, cap=cap)
     B = offsets.shape[0] - 1

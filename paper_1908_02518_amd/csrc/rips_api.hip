@@ -315,7 +315,7 @@ struct DevCtx {
     int batch_wgpcu = 0; // 0 = default (1 persistent workgroup per CU)
     int batch_spread_off = 0; // 1 = one workgroup per cloud even for a small batch
     int working_column = RIPS_WORKING_COLUMN_AUTO; // rips_set_working_column
-    bool by_columns = false; // rips_set_reduce_workgroups asked for the column reduction
+    int sweep = RIPS_SWEEP_SINGLE | RIPS_SWEEP_BATCHED; // rips_set_sweep
     // the bitmap buffers are zero between columns; these record what was
     // zeroed after the last allocation (pointer and bytes) per path
     void *bm_zero_ptr[2] = {nullptr, nullptr};
@@ -524,7 +524,11 @@ enum ProfId {
     P_EXP_BUILD1 = P_COB1 + kMaxDim, // explicit coboundary matrix of dimension k
     P_EMIT = P_EXP_BUILD1 + kMaxDim,
     P_BATCHED,
-    P_NUM
+    P_BATCHED_SWEEP,
+    P_SWEEP,       // a whole cloud
+    P_SWEEP_BUILD1, // dimension k at P_SWEEP_BUILD1 + k - 1: its places, then the sweep itself
+    P_SWEEP1 = P_SWEEP_BUILD1 + 2,
+    P_NUM = P_SWEEP1 + 2
 };
 
 const char *prof_name(int i) {
@@ -548,6 +552,12 @@ const char *prof_name(int i) {
         }
         snprintf(names[P_EMIT], 32, "emit");
         snprintf(names[P_BATCHED], 32, "batched_graph");
+        snprintf(names[P_BATCHED_SWEEP], 32, "batched_sweep");
+        snprintf(names[P_SWEEP], 32, "sweep");
+        for (int k = 1; k <= 2; ++k) {
+            snprintf(names[P_SWEEP_BUILD1 + k - 1], 32, "sweep_build_d%d", k);
+            snprintf(names[P_SWEEP1 + k - 1], 32, "sweep_d%d", k);
+        }
         init = true;
     }
     return (i >= 0 && i < P_NUM) ? names[i] : "";
@@ -909,7 +919,7 @@ rips_status sweep_buffers(DevCtx &C, int n_max, uint32_t p, int64_t grid, SweepA
 // The default method may run: no setting asks for a reduction of columns.
 bool sweep_allowed(const DevCtx &C) {
     return !C.arena && C.cocycle_dim < 0 && C.working_column == RIPS_WORKING_COLUMN_AUTO &&
-           !C.by_columns && C.shortcuts == (kShortApparent | kShortEmergent | kShortClearing) &&
+           (C.sweep & RIPS_SWEEP_SINGLE) && C.shortcuts == (kShortApparent | kShortEmergent | kShortClearing) &&
            C.rstore == kRStoreAuto;
 }
 
@@ -986,7 +996,7 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     static_assert(sizeof(SweepSingle) <= sizeof(Scalars), "reported in the pinned scalar block");
     A.res = (SweepSingle *)C.host_scal;
     {
-        PROF(P_REDUCE1);
+        PROF(P_SWEEP);
         launch_sweep(A, 1, st);
     }
     HIP_TRY(hipGetLastError());
@@ -1079,7 +1089,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     if (k == 1) {
         ENS(B_SD_QZJ, ncand * 4, A.qzj, int);
         {
-            PROF(P_SORT1);
+            PROF(P_SWEEP_BUILD1);
             launch_dim_partition(A, st);
         }
         // the owned cofacets are counted: room for them
@@ -1120,7 +1130,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
         ENS(B_SD_CDIAM, S * 4, A.cols.diam, float);
         ENS(B_SD_CJ, S * 4, A.cols.j, int);
         {
-            PROF(P_COB1 + k - 1);
+            PROF(P_SWEEP_BUILD1 + k - 1);
             launch_lune_partition(A, ph, st);
         }
         HIP_TRY(hipMemcpyAsync(C.host_scal, A.out, sizeof(DimOut), hipMemcpyDeviceToHost, st));
@@ -1154,12 +1164,12 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     memset(&h, 0, sizeof(h));
     if (A.S > 0) {
         {
-            PROF(P_COB1 + k - 1);
+            PROF(P_SWEEP_BUILD1 + k - 1);
             if (k == 1) launch_dim_fill(A, st);
             else launch_lune_chunks(A, st);
         }
         {
-            PROF(P_REDUCE1 + k - 1);
+            PROF(P_SWEEP1 + k - 1);
             if (k == 1) HIP_TRY(launch_dim_sweep(A, st));
             else HIP_TRY(launch_lune_sweep(A, (int)((float)ncand / A.chunk_n) + A.S / 192 + 2, st));
         }
@@ -1986,7 +1996,7 @@ rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_off
     F.status = A.status;
     launch_sweep_order(d_offsets, B, n_max, order, A.queue, A.ucount, A.status, st);
     {
-        PROF(P_BATCHED);
+        PROF(P_BATCHED_SWEEP);
         launch_sweep(A, (int)grid, st);
     }
     launch_batch_finalize(F, out->bar_offsets, &scal->total, out->cap, out->birth, out->death,
@@ -2781,10 +2791,10 @@ rips_status rips_simplex_counts_device(const float *d_data, int64_t n, int32_t d
     return RIPS_OK;
 }
 
-rips_status rips_barcode_batched_device(const float *d_points, const int64_t *d_offsets, int32_t B,
-                                        int32_t dim, int32_t n_max, int32_t max_dim,
-                                        float threshold, uint32_t p, rips_batch_out *out,
-                                        void *hip_stream) {
+// rips_barcode_batched_device; columns: by the column reduction in any case.
+static rips_status batched_device(const float *d_points, const int64_t *d_offsets, int32_t B, int32_t dim,
+                                  int32_t n_max, int32_t max_dim, float threshold, uint32_t p, rips_batch_out *out,
+                                  void *hip_stream, bool columns) {
     g_err.clear();
     if (!d_points || !d_offsets || !out || !out->bar_offsets)
         return fail(RIPS_E_INVALID_ARG, "null pointer");
@@ -2799,7 +2809,7 @@ rips_status rips_barcode_batched_device(const float *d_points, const int64_t *d_
     rips_status rs;
     if ((rs = get_ctx(&C))) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
-    if (p == 2 && C->working_column == RIPS_WORKING_COLUMN_AUTO) {
+    if (!columns && p == 2 && C->working_column == RIPS_WORKING_COLUMN_AUTO && (C->sweep & RIPS_SWEEP_BATCHED)) {
         bool full = false;
         rs = batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
                            (hipStream_t)hip_stream, &full);
@@ -2811,6 +2821,13 @@ rips_status rips_barcode_batched_device(const float *d_points, const int64_t *d_
                           hip_stream, &retry);
         if (!retry || attempt > 8) return rs;
     }
+}
+
+rips_status rips_barcode_batched_device(const float *d_points, const int64_t *d_offsets, int32_t B,
+                                        int32_t dim, int32_t n_max, int32_t max_dim,
+                                        float threshold, uint32_t p, rips_batch_out *out,
+                                        void *hip_stream) {
+    return batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream, false);
 }
 
 rips_status rips_backward_device(const float *d_data, int64_t n, int32_t dim, int64_t nbars,
@@ -2855,7 +2872,7 @@ rips_status rips_set_reduce_workgroups(int32_t workgroups) {
     if ((rs = get_ctx(&C))) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
     C->reduce_groups = workgroups;
-    C->by_columns = true;
+    C->sweep &= ~RIPS_SWEEP_SINGLE;
     return RIPS_OK;
 }
 
@@ -2907,7 +2924,30 @@ rips_status rips_set_working_column(int32_t mode) {
     if (rs) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
     C->working_column = mode;
-    if (mode == RIPS_WORKING_COLUMN_AUTO) C->by_columns = false;
+    if (mode == RIPS_WORKING_COLUMN_AUTO) C->sweep = RIPS_SWEEP_SINGLE | RIPS_SWEEP_BATCHED;
+    return RIPS_OK;
+}
+
+rips_status rips_set_sweep(int32_t flags) {
+    g_err.clear();
+    if (flags < 0 || flags > (RIPS_SWEEP_SINGLE | RIPS_SWEEP_BATCHED))
+        return fail(RIPS_E_INVALID_ARG, "unknown sweep flags");
+    DevCtx *C;
+    rips_status rs = get_ctx(&C);
+    if (rs) return rs;
+    std::lock_guard<std::mutex> lk(C->mu);
+    C->sweep = flags;
+    return RIPS_OK;
+}
+
+rips_status rips_get_sweep(int32_t *flags) {
+    g_err.clear();
+    if (!flags) return fail(RIPS_E_INVALID_ARG, "null flags");
+    DevCtx *C;
+    rips_status rs = get_ctx(&C);
+    if (rs) return rs;
+    std::lock_guard<std::mutex> lk(C->mu);
+    *flags = C->sweep;
     return RIPS_OK;
 }
 
@@ -3009,8 +3049,8 @@ rips_status rips_batched_autotune(const float *d_points, const int64_t *d_offset
         for (int b = 0; b < 3 && rs == RIPS_OK; ++b) {
             if ((rs = rips_batched_set_config(slots[a], wgs[b]))) break;
             // untimed run: builds the graph and grows scratch
-            if ((rs = rips_barcode_batched_device(d_points, d_offsets, B, dim, n_max, max_dim,
-                                                  threshold, p, out, hip_stream)))
+            if ((rs = batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream,
+                                     false)))
                 break;
             cur.resize(noff);
             if (hipMemcpy(cur.data(), out->bar_offsets, noff * 8, hipMemcpyDeviceToHost) !=
@@ -3025,8 +3065,7 @@ rips_status rips_batched_autotune(const float *d_points, const int64_t *d_offset
             }
             (void)hipEventRecord(e0, st);
             for (int r = 0; r < reps && rs == RIPS_OK; ++r)
-                rs = rips_barcode_batched_device(d_points, d_offsets, B, dim, n_max, max_dim,
-                                                 threshold, p, out, hip_stream);
+                rs = batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream, false);
             if (rs) break;
             (void)hipEventRecord(e1, st);
             (void)hipEventSynchronize(e1);

@@ -1,0 +1,89 @@
+"""The switch between the sweep and the column reduction, and that each of them
+runs where it is meant to: what a comparison of the two compares."""
+
+import numpy as np
+import pytest
+
+import workloads
+from tests.method_of import method_of
+from tests.test_gpu_batched import lattice_batch, small_batch
+from tests.test_gpu_sweep import two_simplices
+
+pytestmark = pytest.mark.gpu
+INF = float("inf")
+
+
+def rips():
+    import paper_1908_02518_amd as r
+    return r
+
+
+SINGLE = [
+    ("whole", lambda: workloads.sphere(100, 1), dict(max_dim=1, threshold=INF), {"sweep"}, {"reduce_d1"}),
+    ("whole-p5", lambda: workloads.sphere(90, 2), dict(max_dim=1, threshold=INF, p=5), {"sweep"}, {"reduce_d1"}),
+    ("chunks", lambda: workloads.clifford_torus(2000, 0.02, 3), dict(max_dim=1, threshold=0.5), {"sweep_d1"},
+     {"reduce_d1"}),
+    ("chunks-p3", lambda: workloads.clifford_torus(2000, 0.02, 3), dict(max_dim=1, threshold=0.5, p=3), {"sweep_d1"},
+     {"reduce_d1"}),
+    ("blocks", lambda: workloads.sphere(64, 4), dict(max_dim=2, threshold=INF), {"sweep_d1", "sweep_d2"},
+     {"reduce_d1", "reduce_d2"}),
+    ("blocks-so3", lambda: workloads.so3(700, 5), dict(max_dim=2, threshold=1.4), {"sweep_d2"},
+     {"reduce_d1", "reduce_d2"}),
+]
+
+
+@pytest.mark.parametrize("name,make,kw,sweeps,columns", SINGLE, ids=[c[0] for c in SINGLE])
+def test_single_cloud_switch(name, make, kw, sweeps, columns):
+    import torch
+    r = rips()
+    x = torch.from_numpy(make()).cuda()
+    print(f"[case] method {name}", flush=True)
+    (one, _), s, c = method_of(lambda: r.barcode_device(x, **kw))
+    assert s >= sweeps and not any(f"reduce_{q[6:]}" in c for q in s if q != "sweep"), (s, c)
+    for off in ("sweep", "workgroups"):
+        if off == "sweep":
+            r.set_sweep(r.SWEEP_BATCHED)
+        else:
+            r.set_sweep()
+            r.set_reduce_workgroups(0)
+        assert r.get_sweep() == r.SWEEP_BATCHED
+        (two, _), s, c = method_of(lambda: r.barcode_device(x, **kw))
+        assert not s and c == columns, (off, s, c)
+        for a, b in zip(one, two):
+            assert all(torch.equal(u, v) for u, v in zip(a, b))
+    r.set_working_column()
+    assert r.get_sweep() == r.SWEEP_SINGLE | r.SWEEP_BATCHED
+    _, s, c = method_of(lambda: r.barcode_device(x, **kw))
+    assert s >= sweeps
+
+
+def _bars(bb):
+    n = int(bb.offsets[-1])
+    return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]
+
+
+def test_batched_columns_over_z2():
+    """The direct-mapped columns of a batch, spread out and by one workgroup a
+    cloud, the replays of their graph, and the sweep: the same bars."""
+    import torch
+    r = rips()
+    x, off, nmax = r.pack_clouds(small_batch() + lattice_batch(12))
+    print("[case] batched columns over Z/2", flush=True)
+    call = lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, p=2, cap=1 << 15))
+    want, s, c = method_of(call)
+    assert s == {"batched_sweep"} and not c
+    r.set_sweep(r.SWEEP_SINGLE)
+    for spread in (0, 1):
+        r.batched_set_spread(spread)
+        for _ in range(3):
+            got, s, c = method_of(call)
+            assert not s and c == {"batched_graph"}
+            assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
+def test_batch_with_a_full_cloud_goes_by_columns():
+    r = rips()
+    x, off, nmax = r.pack_clouds([two_simplices(40), workloads.uniform_cube(40, 80, 1)])
+    print("[case] batch with a full cloud", flush=True)
+    _, s, c = method_of(lambda: r.barcode_batched(x, off, nmax, max_dim=1))
+    assert s == {"batched_sweep"} and c == {"batched_graph"}

@@ -43,3 +43,10 @@ def test_count_of_pairs_fits_its_type(tmp_path):
     first append past the capacity."""
     got = run(tmp_path, 'printf("%lld", (long long)most_pairs(kMostPairs, 16384 * 4));')
     assert int(got[0]) == (1 << 21) + 65536 * 64 < 2 ** 31
+
+
+def test_sweep_flags_outside_the_two_bits_are_refused():
+    import paper_1908_02518_amd as rips
+    assert rips.lib().rips_set_sweep(-1) == -1  # before the device is touched
+    assert rips.lib().rips_set_sweep(4) == -1
+    assert rips.lib().rips_get_sweep(None) == -1
