@@ -464,13 +464,15 @@ rips_status rips_batched_get_config(int32_t *delta_slots, int32_t *workgroups_pe
 rips_status rips_batched_set_spread(int32_t mode);
 
 /*
- * rips_batched_autotune -- time the batched launch on the caller's batch
+ * rips_batched_autotune -- time the batched column reduction on the caller's batch
  * (same arguments as rips_barcode_batched_device) for every configuration
  * of delta_slots in {512, 1024, 2048} x workgroups_per_cu in {1, 2, 4},
  * `reps` timed replays each (hipEvents, after one untimed run), keep the
  * fastest with rips_batched_set_config and report it. Every configuration's
  * bar offsets are compared with the first one's; a mismatch returns
- * RIPS_E_HIP. `out` receives the bars of the last run. best_ms: mean
+ * RIPS_E_HIP. The sweep is left out, whatever rips_set_sweep says: the
+ * configuration serves the batches that it does not take, or gives back.
+ * `out` receives the bars of the last run. best_ms: mean
  * milliseconds per launch of the chosen configuration (any pointer may be
  * NULL).
  */

@@ -3050,7 +3050,7 @@ rips_status rips_batched_autotune(const float *d_points, const int64_t *d_offset
             if ((rs = rips_batched_set_config(slots[a], wgs[b]))) break;
             // untimed run: builds the graph and grows scratch
             if ((rs = batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream,
-                                     false)))
+                                     true)))
                 break;
             cur.resize(noff);
             if (hipMemcpy(cur.data(), out->bar_offsets, noff * 8, hipMemcpyDeviceToHost) !=
@@ -3065,7 +3065,7 @@ rips_status rips_batched_autotune(const float *d_points, const int64_t *d_offset
             }
             (void)hipEventRecord(e0, st);
             for (int r = 0; r < reps && rs == RIPS_OK; ++r)
-                rs = batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream, false);
+                rs = batched_device(d_points, d_offsets, B, dim, n_max, max_dim, threshold, p, out, hip_stream, true);
             if (rs) break;
             (void)hipEventRecord(e1, st);
             (void)hipEventSynchronize(e1);

@@ -87,3 +87,17 @@ def test_batch_with_a_full_cloud_goes_by_columns():
     print("[case] batch with a full cloud", flush=True)
     _, s, c = method_of(lambda: r.barcode_batched(x, off, nmax, max_dim=1))
     assert s == {"batched_sweep"} and c == {"batched_graph"}
+
+
+def test_autotune_times_the_columns():
+    r = rips()
+    x, off, nmax = r.pack_clouds(small_batch())
+    print("[case] autotune", flush=True)
+    want = _bars(r.barcode_batched(x, off, nmax, max_dim=1, cap=1 << 14))
+    tuned, s, c = method_of(lambda: r.batched_autotune(x, off, nmax, max_dim=1, cap=1 << 14, reps=1))
+    assert s == {"batched_sweep"} and c == {"batched_graph"}  # its first call is an ordinary one
+    assert r.batched_get_config() == tuned[:2]
+    assert r.get_sweep() == r.SWEEP_SINGLE | r.SWEEP_BATCHED
+    got, s, c = method_of(lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, cap=1 << 14)))
+    assert s == {"batched_sweep"} and not c
+    assert all(np.array_equal(a.cpu(), b.cpu()) for a, b in zip(want, got))
