@@ -923,27 +923,8 @@ bool sweep_allowed(const DevCtx &C) {
            C.rstore == kRStoreAuto;
 }
 
-// Clouds that one workgroup sweeps whole, distances to bars in one launch. The
-// staged path's launches, waits and scalar reads cost 0.3 to 0.5 ms whatever
-// the size, which the one workgroup's passes over n^2 pairs reach at about 256
-// points (threshold 0.3 on the sphere: 200 points 0.23 and 0.35 ms, 256 points
-// 0.33 and 0.37, 320 points 0.49 and 0.40). Without a threshold the complex is
-// dense and the reduction itself decides, in favour of the sweep up to the
-// largest cloud it takes (sphere: 400 points 1.9 and 7.2 ms, 1000 points 10
-// and 36; noisy circles: 400 points 2.3 and 13.6, 1000 points 17 and 217).
-constexpr int kSweepSingleN = 256;
-// Over another field a sum costs products and remainders for every class it
-// has, and many classes are open at once where the points are spread out in
-// many dimensions: the largest sizes at which none of spheres, circles, normal
-// and uniform points of 2 to 4 dimensions was slower (without a threshold,
-// 171 points: sphere 0.72 and 2.3 ms, uniform 0.67 and 1.2, normal in R^4
-// 1.08 and 1.11; 230 points: normal in R^3 1.5 and 1.2; threshold 1.4 on
-// rotations: 100 points 0.20 and 0.35, 200 points 0.70 and 0.51).
-constexpr int kSweepOddN = 200, kSweepOddSingleN = 128;
-
 bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint32_t p) {
-    const int most = std::isinf(threshold) ? (p == 2 ? kSweepMaxN : kSweepOddN) : (p == 2 ? kSweepSingleN : kSweepOddSingleN);
-    return n >= 2 && max_dim <= 1 && n <= most && sweep_allowed(C);
+    return n >= 2 && n <= whole_most(max_dim, std::isinf(threshold), p) && sweep_allowed(C);
 }
 
 // Edges per point between which a larger cloud's dimension 1 is swept in

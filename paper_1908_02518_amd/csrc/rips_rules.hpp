@@ -6,6 +6,31 @@
 
 namespace rips {
 
+// Points up to which one workgroup sweeps a cloud whole, distances to bars in
+// one launch (0: never). The staged path's launches, waits and scalar reads
+// cost 0.3 to 0.5 ms whatever the size, which the one workgroup's passes over
+// n^2 pairs reach at about 256 points with a threshold (milliseconds swept and
+// staged, 25 edges a point: torus 0.71 and 0.84, rotations 1.1 and 1.7, uniform
+// in the cube of R^5 0.94 and 0.82, normal in R^3 0.71 and 0.59; 100 edges a
+// point: 1.6 and 11.5, 3.1 and 14.0, 1.07 and 1.54, 0.92 and 1.15).
+// Without a threshold the complex is dense and the reduction itself decides,
+// for the sweep up to about 1000 points (700 points: sphere 5.3 and 46, torus
+// 34 and 112, uniform in R^3 5.5 and 32, normal in R^5 8.3 and 23; 1000 points:
+// 9.9 and 30, normal in R^3 12.2 and 12.1, in R^5 19.1 and 17.1; 2048 points:
+// sphere 43 and 101, uniform in R^3 55 and 79, normal in R^2 39 and 31, in R^3
+// 61 and 40, in R^5 191 and 67).
+// Over another field a sum costs products and remainders for every class it
+// has: half the points with a threshold, 200 without (whole_classes has the
+// rest of that rule).
+// Dimension 0 alone needs no cofacets, which the sweep looks for all the same:
+// 100 points on the sphere 0.13 and 0.18 ms, uniform in R^10 0.15 and 0.18; 200
+// points 0.24 and 0.26, 0.33 and 0.22; 1000 points 4.2 and 3.4, 6.5 and 2.2.
+constexpr int kWholeN = 256, kWholeDenseN = 1024, kWholeOddN = 128, kWholeOddDenseN = 200, kWholeForestN = 128;
+constexpr int whole_most(int max_dim, bool dense, uint32_t p) {
+    const int most = dense ? (p == 2 ? kWholeDenseN : kWholeOddDenseN) : (p == 2 ? kWholeN : kWholeOddN);
+    return max_dim == 0 ? (most < kWholeForestN ? most : kWholeForestN) : max_dim == 1 ? most : 0;
+}
+
 // Triangles of which the chunked sweep of dimension 1 holds the places (12
 // bytes each, 3 GiB in all). The number of edges says little about theirs: one
 // cluster of 2955 points has more than 2^32 of them with 100 edges a point in

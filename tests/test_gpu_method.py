@@ -57,6 +57,26 @@ def test_single_cloud_switch(name, make, kw, sweeps, columns):
     assert s >= sweeps
 
 
+@pytest.mark.parametrize("n,max_dim,t,p", [(128, 0, INF, 2), (128, 0, 0.5, 3), (256, 1, 0.5, 2), (128, 1, 0.5, 3),
+                                           (1024, 1, INF, 2), (200, 1, INF, 5)])
+def test_largest_clouds_swept_whole(n, max_dim, t, p):
+    """Swept up to n points, by the staged path from the next on, the same
+    bars as the columns on both sides."""
+    import torch
+    r = rips()
+    for k, whole in ((n, True), (n + 1, False)):
+        x = torch.from_numpy(workloads.sphere(k, k)).cuda()
+        print(f"[case] whole n={k} max_dim={max_dim} t={t} p={p}", flush=True)
+        (one, i1), s, _ = method_of(lambda: r.barcode_device(x, max_dim=max_dim, threshold=t, p=p))
+        assert ("sweep" in s) == whole
+        r.set_sweep(0)
+        (two, i2), s, _ = method_of(lambda: r.barcode_device(x, max_dim=max_dim, threshold=t, p=p))
+        r.set_sweep()
+        assert not s and i1["threshold"] == i2["threshold"]
+        for a, b in zip(one, two):
+            assert all(torch.equal(u, v) for u, v in zip(a, b))
+
+
 def _bars(bb):
     n = int(bb.offsets[-1])
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]

@@ -50,3 +50,11 @@ def test_sweep_flags_outside_the_two_bits_are_refused():
     assert rips.lib().rips_set_sweep(-1) == -1  # before the device is touched
     assert rips.lib().rips_set_sweep(4) == -1
     assert rips.lib().rips_get_sweep(None) == -1
+
+
+def test_sizes_of_clouds_swept_whole(tmp_path):
+    got = run(tmp_path, """
+    for (int d : {0, 1, 2})
+        for (bool dense : {false, true})
+            for (uint32_t p : {2u, 3u, 65521u}) printf("%d ", whole_most(d, dense, p));""")
+    assert [int(x) for x in got] == [128] * 6 + [256, 128, 128, 1024, 200, 200] + [0] * 6
