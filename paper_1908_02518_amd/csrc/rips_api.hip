@@ -960,6 +960,20 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     A.X = d_in;
     A.B = 1;
     A.m = m;
+    void *q;
+    if (m > kWholeCoords) {
+        Scalars *s;
+        HIP_TRY(C.ensure(B_D, (size_t)n * n * 4, &q));
+        float *D = as<float>(q);
+        HIP_TRY(C.ensure(B_SCAL, sizeof(Scalars), &q));
+        s = as<Scalars>(q);
+        {
+            PROF(P_DIST);
+            launch_dist(d_in, n, m, D, &s->bad, st); // what is not finite shows in D
+        }
+        A.X = D;
+        A.m = 0;
+    }
     A.max_dim = max_dim;
     A.threshold = t;
     A.ub = bars.birth;
@@ -968,7 +982,6 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     A.uds = bars.ds;
     A.ucap = cap;
     if (columns) {
-        void *q;
         HIP_TRY(C.ensure(B_COL_IDX + 1, (size_t)A.sv_cap * 8, &q));
         A.col_idx = as<int64_t>(q);
         HIP_TRY(C.ensure(B_COL_DIAM + 1, (size_t)A.sv_cap * 4, &q));

@@ -31,6 +31,14 @@ constexpr int whole_most(int max_dim, bool dense, uint32_t p) {
     return max_dim == 0 ? (most < kWholeForestN ? most : kWholeForestN) : max_dim == 1 ? most : 0;
 }
 
+// Coordinates up to which that workgroup computes the distances itself. A
+// lane's row of coordinates is as many cache lines apart from the next lane's
+// as it is long, so their cost grows with n^2 times them; beyond, the whole
+// chip does it in a launch before (100 uniform points, dimension 1, without and
+// with it: R^4 0.32 ms and the same, R^64 2.0 and 0.73, R^1024 10.8 and 0.93;
+// 128 points, dimension 0: R^8 0.21 and 0.15).
+constexpr int kWholeCoords = 4;
+
 // Triangles of which the chunked sweep of dimension 1 holds the places (12
 // bytes each, 3 GiB in all). The number of edges says little about theirs: one
 // cluster of 2955 points has more than 2^32 of them with 100 edges a point in

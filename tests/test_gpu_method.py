@@ -77,6 +77,34 @@ def test_largest_clouds_swept_whole(n, max_dim, t, p):
             assert all(torch.equal(u, v) for u, v in zip(a, b))
 
 
+@pytest.mark.parametrize("m", [1, 4, 5, 64, 700])
+@pytest.mark.parametrize("p", [2, 3])
+def test_whole_clouds_of_many_coordinates(m, p):
+    """The distances by the sweep's workgroup, and by the whole chip before it;
+    from device and from host memory, and refused where one is not finite."""
+    import torch
+    r = rips()
+    for n in (2, 33, 90):
+        x = workloads.uniform_cube(n, m, n + m)
+        d = torch.from_numpy(x).cuda()
+        print(f"[case] coordinates m={m} n={n} p={p}", flush=True)
+        (one, i1), s, c = method_of(lambda: r.barcode_device(d, max_dim=1, p=p))
+        host = r.barcode(x, max_dim=1, p=p)
+        r.set_sweep(0)
+        two, i2 = r.barcode_device(d, max_dim=1, p=p)
+        r.set_sweep()
+        assert s == {"sweep"} and not c and i1["threshold"] == i2["threshold"]
+        for a, b, h in zip(one, two, host.bars):
+            assert all(torch.equal(u, v) for u, v in zip(a, b))
+            assert np.array_equal(a[1].cpu(), h.death) and np.array_equal(a[3].cpu(), h.death_simplex)
+        for bad in (float("nan"), INF):
+            y = d.clone()
+            y[n - 1, m - 1] = bad
+            with pytest.raises(r.RipsError) as e:
+                r.barcode_device(y, max_dim=1, p=p)
+            assert e.value.status == -4
+
+
 def _bars(bb):
     n = int(bb.offsets[-1])
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]
