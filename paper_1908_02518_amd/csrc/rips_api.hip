@@ -890,6 +890,7 @@ rips_status sweep_buffers(DevCtx &C, int n_max, uint32_t p, int64_t grid, SweepA
     A.e_stride = (npairs + 16) / 8 * 8;
     A.sv_cap = sweep_sv_cap(n_max);
     A.p = p;
+    A.most_classes = 1 << 30; // as many as the tables hold
     A.pool_stride = sweep_pool_words(n_max, p);
     A.mask_stride = (int64_t)n_max * sweep_mask_words(n_max);
 #define ENS(id, bytes, field, T)                                                                   \
@@ -957,6 +958,7 @@ rips_status single_sweep(DevCtx &C, const float *d_in, int n, int m, int max_dim
     SweepScal *scal;
     rips_status rs = sweep_buffers(C, n, p, 1, A, &scal);
     if (rs) return rs;
+    A.most_classes = whole_classes(n, p);
     A.X = d_in;
     A.B = 1;
     A.m = m;
@@ -1189,8 +1191,9 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     return RIPS_OK;
 }
 
+// swept_full: dimension whose sweep has given up already (0: none)
 rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, uint32_t p,
-                       hipStream_t st, RunOut &o) {
+                       hipStream_t st, RunOut &o, int swept_full = 0) {
     memset(&o, 0, sizeof(o));
     o.n = n;
     o.max_dim = max_dim;
@@ -1265,7 +1268,6 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
     SimplexList prev_list{P.E.idx, P.E.diam};
     int64_t prev_count = P.nedges;
     PivotHash ph_prev{nullptr, nullptr, 0};
-    int swept_full = 0; // dimension whose sweep ran out of room
     for (int k = 1; k <= max_dim; ++k) {
         launch_reset_dim(P.scal, st);
         // dimensions 1 and 2 take the sweep, unless a setting asks for the
@@ -2289,6 +2291,7 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
     RunOut o;
     rips_status rs;
     bool done = false; // the bars are in the caller's buffers
+    int swept_full = 0;
     if (sweeps_whole(*C, n, max_dim, threshold, p)) {
         bool full = false;
         const bool room = out->birth && out->death && out->birth_simplex && out->death_simplex && out->cap > 0;
@@ -2297,8 +2300,9 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
                           false, st, o, &full);
         if (rs) return rs;
         done = !full;
+        swept_full = 1;
     }
-    if (!done && (rs = run_single(*C, d_data, (int)n, dim, max_dim, threshold, p, st, o))) return rs;
+    if (!done && (rs = run_single(*C, d_data, (int)n, dim, max_dim, threshold, p, st, o, swept_full))) return rs;
     int64_t need = 0;
     for (int d = 0; d <= max_dim; ++d) need = std::max(need, o.count[d]);
     out->needed_cap = need;
@@ -2386,6 +2390,7 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
     RunOut o;
     int64_t swept_cap = 0; // > 0: the bars of dimension 1 follow those of dimension 0 after so many places
     bool full = true;
+    int swept_full = 0;
     if (sweeps_whole(*C, n, max_dim, threshold, p)) {
         // internal bars of dimension 0 and 1, one after the other
         const int64_t cap = sweep_sv_cap((int)n);
@@ -2401,8 +2406,9 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
         full = false;
         rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, p, bars, cap, true, st, o, &full);
         swept_cap = full ? 0 : cap;
+        swept_full = 1;
     }
-    if (!rs && full) rs = run_single(*C, d_in, (int)n, dim, max_dim, threshold, p, st, o);
+    if (!rs && full) rs = run_single(*C, d_in, (int)n, dim, max_dim, threshold, p, st, o, swept_full);
     if (rs) return rs;
     rips_result *r = (rips_result *)calloc(1, sizeof(rips_result));
     if (!r) return fail(RIPS_E_OOM, "host allocation");

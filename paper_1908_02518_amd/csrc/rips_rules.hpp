@@ -31,6 +31,16 @@ constexpr int whole_most(int max_dim, bool dense, uint32_t p) {
     return max_dim == 0 ? (most < kWholeForestN ? most : kWholeForestN) : max_dim == 1 ? most : 0;
 }
 
+// Classes that it opens at most; with more the staged path takes over (after
+// the distances, the scan and the forest, which are a small part). The vectors
+// are as long as there are classes: over Z/2 the sweep loses above two a point
+// (uniform in R^64: 128 points, 230 classes, 1.4 ms and 1.1; 200 points, 444,
+// 3.5 and 1.5; 400 points, 1233, 33 and 16; lattices: 256 points, 495, 12 and
+// 29; 400 points, 778, 74 and 110), over another field above some 220 (200
+// points: uniform in R^5, 140 classes, 1.63 and 1.55, in R^10, 224, 2.6 and
+// 1.6, orthogonal matrices, 274, 5.7 and 3.8, lattice, 299, 22 and 6.0).
+constexpr int whole_classes(int n, uint32_t p) { return p != 2 ? 220 : n < 128 ? 256 : 2 * n; }
+
 // Coordinates up to which that workgroup computes the distances itself. A
 // lane's row of coordinates is as many cache lines apart from the next lane's
 // as it is long, so their cost grows with n^2 times them; beyond, the whole

@@ -722,7 +722,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
     const Rows P{L.pool, A.pool + wg * A.pool_stride, W > 0 ? kPoolLdsWords / W : 0, W};
     const int rcap = W > 0 ? (int)min((int64_t)(kOdd ? 0xffff : 1 << 30), A.pool_stride / W) : 0;
     if (max_dim >= 1 && S > 0) {
-        if (S > (kOdd ? kSweepOddClasses : kSweepMaxClasses) || S + 1 >= rcap) {
+        if (S > min(A.most_classes, kOdd ? kSweepOddClasses : kSweepMaxClasses) || S + 1 >= rcap) {
             sweep_reject(A, b, D1, kSweepFull);
             __syncthreads();
             return;

@@ -34,6 +34,7 @@ struct SweepArgs {
     int B, m, max_dim, nmax;
     u32 p;
     float threshold;
+    int most_classes;       // more than these: kSweepFull
     const int *order;       // clouds by decreasing size, or null
     unsigned long long *queue;
     // per workgroup (blockIdx.x)

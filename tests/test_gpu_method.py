@@ -105,6 +105,24 @@ def test_whole_clouds_of_many_coordinates(m, p):
             assert e.value.status == -4
 
 
+@pytest.mark.parametrize("n,m,p,whole", [(200, 16, 2, True), (220, 64, 2, False), (160, 5, 3, True), (200, 16, 3, False)])
+def test_whole_clouds_of_many_classes(n, m, p, whole):
+    """Up to two classes a point, or 220 over another field, by the sweep;
+    with more the staged path follows it."""
+    import torch
+    r = rips()
+    x = torch.from_numpy(workloads.uniform_cube(n, m, n)).cuda()
+    print(f"[case] classes n={n} m={m} p={p}", flush=True)
+    (one, info), s, c = method_of(lambda: r.barcode_device(x, max_dim=1, p=p, cap=4 * n))
+    most = 2 * n if p == 2 else 220
+    assert (info["stats"][1]["columns"] <= most) == whole
+    assert "sweep" in s and (not c) == whole
+    r.set_sweep(0)
+    two, _ = r.barcode_device(x, max_dim=1, p=p, cap=4 * n)
+    for a, b in zip(one, two):
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+
+
 def _bars(bb):
     n = int(bb.offsets[-1])
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]

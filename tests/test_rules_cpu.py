@@ -58,3 +58,9 @@ def test_sizes_of_clouds_swept_whole(tmp_path):
         for (bool dense : {false, true})
             for (uint32_t p : {2u, 3u, 65521u}) printf("%d ", whole_most(d, dense, p));""")
     assert [int(x) for x in got] == [128] * 6 + [256, 128, 128, 1024, 200, 200] + [0] * 6
+
+
+def test_classes_of_a_cloud_swept_whole(tmp_path):
+    got = run(tmp_path, """
+    for (int n : {2, 127, 128, 1024}) printf("%d %d ", whole_classes(n, 2), whole_classes(n, 3));""")
+    assert [int(x) for x in got] == [256, 220, 256, 220, 256, 220, 2048, 220]
