@@ -643,10 +643,21 @@ rips_status read_scalars(DevCtx &C, Scalars *d_scal, hipStream_t st) {
 
 __global__ void k_set_counter(unsigned long long *p, unsigned long long v) { *p = v; }
 
-__global__ void k_maxdeg(const int *deg, int n, int *out) {
+// the largest degree, and the sum of their squares; one workgroup
+__global__ void k_maxdeg(const int *deg, int n, Scalars *s) {
+    __shared__ unsigned long long sum;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
     int m = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = max(m, deg[i]);
-    atomicMax(out, m);
+    unsigned long long q = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        m = max(m, deg[i]);
+        q += (unsigned long long)deg[i] * (unsigned long long)deg[i];
+    }
+    atomicMax(&s->maxdeg, m);
+    atomicAdd(&sum, q);
+    __syncthreads();
+    if (threadIdx.x == 0) s->deg2 = sum;
 }
 
 struct Prepared {
@@ -658,6 +669,7 @@ struct Prepared {
     int64_t nedges;
     int *deg, *off, *nbr;
     int maxdeg;
+    uint64_t deg2; // squares of the degrees, added up
     int sparse;
     Ctx<DistFull> ctx;
 };
@@ -714,7 +726,7 @@ rips_status prepare(DevCtx &C, const float *d_in, int n, int m, int jmax, float 
             PROF(P_EDGES);
             launch_edges(P.D, n, P.scal, P.E, cap, P.deg, st);
         }
-        hipLaunchKernelGGL(k_maxdeg, dim3(1), dim3(256), 0, st, P.deg, n, &P.scal->maxdeg);
+        hipLaunchKernelGGL(k_maxdeg, dim3(1), dim3(256), 0, st, P.deg, n, P.scal);
         rips_status rs = read_scalars(C, P.scal, st);
         if (rs) return rs;
         if (C.host_scal->bad)
@@ -725,6 +737,7 @@ rips_status prepare(DevCtx &C, const float *d_in, int n, int m, int jmax, float 
     P.nedges = (int64_t)C.host_scal->edges;
     if (P.nedges > C.hint_edges) C.hint_edges = P.nedges;
     P.maxdeg = C.host_scal->maxdeg;
+    P.deg2 = C.host_scal->deg2;
     // neighbour lists pay off once the complex is sparse
     P.sparse = sparse_complex(n, P.nedges);
     P.off = P.nbr = nullptr;
@@ -928,25 +941,13 @@ bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint
     return n >= 2 && n <= whole_most(max_dim, std::isinf(threshold), p) && sweep_allowed(C);
 }
 
-// Edges per point between which a larger cloud's dimension 1 is swept in
-// chunks (rips_sweep_dim.hip). Below, the columns are few and short and the
-// chunks cost more than their work (2500 points of the Clifford torus, 25
-// edges a point: 4.0 ms swept, 2.8 reduced; 35: 4.4 and 9.0; so3-1200 at 18:
-// 2.7 and 1.4, at 25: 3.0 and 5.3). Above, the sweep's one workgroup looks at
-// too many triangles (sphere-1000: 200 edges a point 7.7 ms swept, 9.1
-// reduced; 300: 15 and 13; 1000: 290 and 36).
-constexpr int64_t kSweepDegMin = 32, kSweepDegMax = 200;
-// Over another field sums cost more (p = 3: torus4-2000 3.9 and 12.0 ms,
-// sphere-1000 at 90 edges a point 3.3 and 5.8, noisy circles at 102 4.0 and
-// 9.4; sphere-1500 at 136 7.9 and 4.9), and with more columns than this too
-// many classes are open at once for its tables (1136 of torus4-4000 fit, 1465
-// of torus4-5000 do not).
-constexpr int64_t kSweepOddDegMax = 110, kSweepOddColumns = 1200;
 // Triangles from which dimension 2 is swept: below, the launches of the sweep
 // cost what the columns do (12 points on the sphere 0.58 and 0.55 ms, 24 points
 // 0.57 and 0.48, 357 rotations at 1.3, 8000 triangles, 1.31 and 1.24; 64 points
 // on the sphere, 37,000 triangles, 1.4 and 9.7).
 constexpr int64_t kSweepTriangles = 12288;
+// Classes of dimension 2 that its sweep opens at most over another field.
+constexpr int kBlocksOddClasses = 1200;
 
 // One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
 // report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
@@ -1047,7 +1048,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     // and 150 of a mixture (4.6 to 3.7)
     A.chunk_n = k == 1 ? 0.0f : std::max(8192.0f, (float)ncand / 16.0f);
     *full = false;
-    if (ncand >= (1ll << 30) || (p != 2 && k == 1 && S > kSweepOddColumns)) {
+    if (ncand >= (1ll << 30) || (p != 2 && k == 1 && S > kChunkOddColumns)) {
         *full = true;
         return RIPS_OK;
     }
@@ -1139,7 +1140,7 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
             return RIPS_OK;
         }
         A.S = h.nclasses;
-        if (p != 2 && A.S > kSweepOddColumns) {
+        if (p != 2 && A.S > kBlocksOddClasses) {
             *full = true;
             return RIPS_OK;
         }
@@ -1272,9 +1273,8 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         launch_reset_dim(P.scal, st);
         // dimensions 1 and 2 take the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
-        const bool in_range = P.nedges >= kSweepDegMin * n / 2 &&
-                              P.nedges <= (p == 2 ? kSweepDegMax : kSweepOddDegMax) * n / 2;
-        bool sweep = k <= 2 && (k == 2 || in_range) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C);
+        const bool in_chunks = chunks_pay(n, P.nedges, P.deg2, p);
+        bool sweep = k <= 2 && (k == 2 || in_chunks) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C);
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {

@@ -42,6 +42,7 @@ struct Scalars {
     unsigned long long mst;       // forest edges
     int64_t nbars;                // bars of the current dimension
     int maxdeg;                   // largest vertex degree at the threshold
+    unsigned long long deg2;      // squares of the degrees, added up
     unsigned long long stat[kNumStats];
 };
 

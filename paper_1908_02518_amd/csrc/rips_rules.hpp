@@ -49,6 +49,35 @@ constexpr int whole_classes(int n, uint32_t p) { return p != 2 ? 220 : n < 128 ?
 // 128 points, dimension 0: R^8 0.21 and 0.15).
 constexpr int kWholeCoords = 4;
 
+// Whether dimension 1 of a larger cloud is swept in chunks, by its edges per
+// point and by how evenly they lie. What the columns cost depends on how long
+// the classes live, which nobody knows before; the sweep costs some 1.8 ns a
+// triangle and 2.2 us a class whatever they do (milliseconds swept and reduced,
+// 80 edges a point, 2000 points: rotations 5.6 and 78, torus 4.9 and 50,
+// orthogonal matrices 5.7 and 66, uniform in R^5 7.9 and 29, in R^3 5.3 and 6.1,
+// in R^2 4.6 and 4.2; 195 edges: 15 and 520, 17 and 427, 22 and 874, 17 and 51,
+// 16 and 11, 16 and 7.2). Below 32 edges a point the columns are few and short
+// (2500 points of the torus, 25 edges a point: 4.0 and 2.8; 35: 4.4 and 9.0).
+// Above 200 the sweep's one workgroup looks at too many triangles (1000 points
+// on the sphere: 200 edges a point 7.7 and 9.1, 300: 15 and 13, 1000: 290 and
+// 36). And where the points crowd, the triangles do, in the crowd, whose
+// classes are short: the mean degree seen from an edge is 1.03 times the mean
+// at most on the manifolds above, 1.06 to 1.2 in cubes, and from about 1.22 on
+// the sweep loses more than it wins (normal points of R^2, 4000, 80 edges: 1.3,
+// 10.5 and 4.6; of R^5: 1.7, 18 and 8.8; 300 of 3000 points in one ball: 2.4,
+// 17 and 6.0; 500 of them: 3.1, 57 and 14).
+// Over another field sums cost more (p = 3, 104 edges a point: torus4-2000 8.2
+// and 92, rotations 1000 4.7 and 8.4, sphere 2000 7.2 and 4.9; sphere-1500 at
+// 136 7.9 and 4.9), and with more columns than kChunkOddColumns too many classes
+// are open at once for its tables (1137 of 4000 points on the sphere fit, 1161
+// of 2000 orthogonal matrices do not).
+constexpr int64_t kChunkDegMin = 32, kChunkDegMax = 200, kChunkOddDegMax = 110, kChunkOddColumns = 1150;
+constexpr double kChunkUneven = 1.22;
+constexpr bool chunks_pay(int64_t n, int64_t edges, uint64_t deg2, uint32_t p) {
+    return edges >= kChunkDegMin * n / 2 && edges <= (p == 2 ? kChunkDegMax : kChunkOddDegMax) * n / 2 &&
+           (double)n * (double)deg2 <= kChunkUneven * 4.0 * (double)edges * (double)edges;
+}
+
 // Triangles of which the chunked sweep of dimension 1 holds the places (12
 // bytes each, 3 GiB in all). The number of edges says little about theirs: one
 // cluster of 2955 points has more than 2^32 of them with 100 edges a point in

@@ -123,6 +123,29 @@ def test_whole_clouds_of_many_classes(n, m, p, whole):
         assert all(torch.equal(u, v) for u, v in zip(a, b))
 
 
+@pytest.mark.parametrize("data,sweeps", [("even", True), ("crowded", False)])
+def test_chunks_where_the_points_lie_evenly(data, sweeps):
+    """A cloud with a crowd in it goes by columns, at the same mean degree."""
+    import torch
+    r = rips()
+    g = workloads.rng(7)
+    x = g.uniform(0.0, 1.0, (1500, 3))
+    t = 0.19
+    if data == "crowded":
+        x[:250] = 0.5 + 0.03 * g.standard_normal((250, 3))
+        t = 0.13
+    x = torch.from_numpy(x.astype(np.float32)).cuda()
+    print(f"[case] chunks {data}", flush=True)
+    (one, info), s, c = method_of(lambda: r.barcode_device(x, max_dim=1, threshold=t))
+    degree = 2 * info["simplex_count"][1] / 1500
+    assert 32 < degree < 200, degree
+    assert (s == {"sweep_d1"} and not c) if sweeps else (not s and c == {"reduce_d1"})
+    r.set_sweep(0 if sweeps else 3)
+    two, _ = r.barcode_device(x, max_dim=1, threshold=t)
+    for a, b in zip(one, two):
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+
+
 def _bars(bb):
     n = int(bb.offsets[-1])
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]

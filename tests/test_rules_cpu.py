@@ -64,3 +64,18 @@ def test_classes_of_a_cloud_swept_whole(tmp_path):
     got = run(tmp_path, """
     for (int n : {2, 127, 128, 1024}) printf("%d %d ", whole_classes(n, 2), whole_classes(n, 3));""")
     assert [int(x) for x in got] == [256, 220, 256, 220, 256, 220, 2048, 220]
+
+
+def test_clouds_whose_dimension_1_is_swept_in_chunks(tmp_path):
+    """By the mean degree, and by its mean seen from an edge; the cluster of
+    2955 among 44,000 points of no edge is out by the latter."""
+    got = run(tmp_path, """
+    auto even = [](int64_t n, int64_t d, uint32_t p) { return (int)chunks_pay(n, n * d / 2, (uint64_t)(n * d * d), p); };
+    for (uint32_t p : {2u, 3u})
+        for (int64_t d : {31, 32, 110, 111, 200, 201, 4000}) printf("%d ", even(10000, d, p));
+    // half the points of degree a, half of degree b
+    auto two = [](int64_t a, int64_t b) { return (int)chunks_pay(1000, 250 * (a + b), (uint64_t)(500 * (a * a + b * b)), 2); };
+    printf("%d %d %d ", two(100, 100), two(146, 54), two(148, 52));
+    printf("%d ", (int)chunks_pay(44000, 2955ll * 2954 / 2, 2955ull * 2954 * 2954, 2));
+    printf("%d %d", (int)chunks_pay(65535, 65535ll * 100, 65535ull * 200 * 200, 2), (int)chunks_pay(65535, 0, 0, 2));""")
+    assert got == "0 1 1 1 1 0 0  0 1 1 0 0 0 0  1 1 0  0  1 0".split()
