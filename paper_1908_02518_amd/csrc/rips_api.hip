@@ -2809,7 +2809,7 @@ static rips_status batched_device(const float *d_points, const int64_t *d_offset
     rips_status rs;
     if ((rs = get_ctx(&C))) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
-    if (!columns && p == 2 && C->working_column == RIPS_WORKING_COLUMN_AUTO && (C->sweep & RIPS_SWEEP_BATCHED)) {
+    if (!columns && batch_swept(n_max, dim, p) && C->working_column == RIPS_WORKING_COLUMN_AUTO && (C->sweep & RIPS_SWEEP_BATCHED)) {
         bool full = false;
         rs = batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
                            (hipStream_t)hip_stream, &full);

@@ -49,6 +49,17 @@ constexpr int whole_classes(int n, uint32_t p) { return p != 2 ? 220 : n < 128 ?
 // 128 points, dimension 0: R^8 0.21 and 0.15).
 constexpr int kWholeCoords = 4;
 
+// Whether a batch over Z/2 is swept. Milliseconds swept and by columns, 16
+// clouds of 300, 1000 and 2048 points on noisy circles at 0.3: 0.68 and 1.4,
+// 7.3 and 25, 57 and 172; dimension 0 alone: 0.46 and 0.92, 4.5 and 9.8, 21 and
+// 46; uniform points: 100 of R^64 0.89 and 3.2, of R^1024 1.9 and 5.9, 256 of
+// R^64 8.8 and 21. It loses where points and coordinates are many, hence also
+// the classes: 256 of R^256 38 and 27, of R^1024 57 and 44.
+constexpr int kBatchManyN = 128, kBatchManyCoords = 128;
+constexpr bool batch_swept(int n_max, int m, uint32_t p) {
+    return p == 2 && (n_max <= kBatchManyN || m <= kBatchManyCoords);
+}
+
 // Whether dimension 1 of a larger cloud is swept in chunks, by its edges per
 // point and by how evenly they lie. What the columns cost depends on how long
 // the classes live, which nobody knows before; the sweep costs some 1.8 ns a

@@ -151,6 +151,29 @@ def _bars(bb):
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]
 
 
+@pytest.mark.parametrize("m", [7, 8, 9, 16, 17, 130])
+def test_batches_of_many_coordinates(m):
+    """Distances pair by pair and coordinate by coordinate, with remainders;
+    clouds of 129 points and more than 128 coordinates go by columns."""
+    import torch
+    r = rips()
+    for n in (65, 129):
+        x, off, nmax = r.pack_clouds([workloads.uniform_cube(k, m, k) for k in (1, 2, 33, 64, n)])
+        print(f"[case] batch coordinates m={m} n={n}", flush=True)
+        call = lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, cap=1 << 13))
+        one, s, c = method_of(call)
+        assert (s, c) == ((set(), {"batched_graph"}) if n > 128 and m > 128 else ({"batched_sweep"}, set()))
+        r.set_sweep(0)
+        two = call()
+        r.set_sweep()
+        assert all(torch.equal(a, b) for a, b in zip(one, two))
+        y = x.clone()
+        y[-1, m - 1] = INF
+        with pytest.raises(r.RipsError) as e:
+            r.barcode_batched(y, off, nmax, max_dim=1)
+        assert e.value.status == -4
+
+
 def test_batched_columns_over_z2():
     """The direct-mapped columns of a batch, spread out and by one workgroup a
     cloud, the replays of their graph, and the sweep: the same bars."""

@@ -79,3 +79,11 @@ def test_clouds_whose_dimension_1_is_swept_in_chunks(tmp_path):
     printf("%d ", (int)chunks_pay(44000, 2955ll * 2954 / 2, 2955ull * 2954 * 2954, 2));
     printf("%d %d", (int)chunks_pay(65535, 65535ll * 100, 65535ull * 200 * 200, 2), (int)chunks_pay(65535, 0, 0, 2));""")
     assert got == "0 1 1 1 1 0 0  0 1 1 0 0 0 0  1 1 0  0  1 0".split()
+
+
+def test_batches_that_are_swept(tmp_path):
+    got = run(tmp_path, """
+    for (uint32_t p : {2u, 3u})
+        for (int n : {1, 128, 129, 2048})
+            for (int m : {1, 128, 129, 100000}) printf("%d ", (int)batch_swept(n, m, p));""")
+    assert [int(x) for x in got] == [1] * 8 + [1, 1, 0, 0] * 2 + [0] * 16
