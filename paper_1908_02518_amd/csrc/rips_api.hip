@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <vector>
 #include <unordered_map>
@@ -365,6 +366,22 @@ struct DevCtx {
         return hipErrorOutOfMemory;
     }
 
+    bool sweeping = false; // the sweep's buffers are in use
+
+    // The sweep's buffers given back (hipFree waits for what uses them), and
+    // the error of the allocation that failed forgotten; were there any?
+    bool release_sweep() {
+        (void)hipGetLastError();
+        bool any = false;
+        for (int i = B_SW_D; i <= B_SD_OUT; ++i) {
+            if (!buf[i]) continue;
+            any = hipFree(buf[i]) == hipSuccess || any;
+            buf[i] = nullptr;
+            cap[i] = 0;
+        }
+        return any;
+    }
+
     hipError_t ensure(int id, size_t bytes, void **out) {
         if (bytes == 0) bytes = 16;
         if (arena) {
@@ -383,6 +400,9 @@ struct DevCtx {
             }
             size_t want = bytes + bytes / 4;
             hipError_t e = hipMalloc(&buf[id], want);
+            // the columns that follow a sweep with a full table need not find
+            // room beside its scratch memory
+            if (e == hipErrorOutOfMemory && !sweeping && release_sweep()) e = hipMalloc(&buf[id], want);
             if (e != hipSuccess) {
                 buf[id] = nullptr;
                 return e;
@@ -949,6 +969,23 @@ constexpr int64_t kSweepTriangles = 12288;
 // Classes of dimension 2 that its sweep opens at most over another field.
 constexpr int kBlocksOddClasses = 1200;
 
+// The sweep's buffers are in use while this lives.
+struct Sweeping {
+    DevCtx &C;
+    explicit Sweeping(DevCtx &c) : C(c) { C.sweeping = true; }
+    ~Sweeping() { C.sweeping = false; }
+};
+
+// What a sweep returned; where it found no memory it is as if a table was
+// full, and the columns decide.
+rips_status swept(DevCtx &C, rips_status rs, bool *full) {
+    if (rs != RIPS_E_OOM) return rs;
+    (void)C.release_sweep();
+    g_err.clear();
+    *full = true;
+    return RIPS_OK;
+}
+
 // One small cloud of dimensions 0 and 1 by one workgroup in one launch; its
 // report comes back in pinned memory. bars: [d * cap, ...) of dimension d, if
 // every dimension fits. *full as in batched_sweep.
@@ -1327,10 +1364,19 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         if ((uint64_t)2 * ncand + 64 > (1ull << 31)) return fail(RIPS_E_CAPACITY, "too many candidates");
         const uint32_t appcap = next_pow2((uint64_t)2 * ncand + 64);
         int *zj = nullptr;
+        std::optional<Sweeping> hold;
         if (sweep) {
-            HIP_TRY(C.ensure(B_SD_ZJ, (size_t)ncand * 4, &q));
-            zj = as<int>(q);
-        } else if (apparent) {
+            const hipError_t e = C.ensure(B_SD_ZJ, (size_t)ncand * 4, &q);
+            if (e == hipErrorOutOfMemory) {
+                (void)C.release_sweep();
+                sweep = false;
+            } else {
+                HIP_TRY(e);
+                zj = as<int>(q);
+                hold.emplace(C);
+            }
+        }
+        if (!sweep && apparent) {
             HIP_TRY(C.ensure(B_APP_KEYS, (size_t)appcap * 8, &q));
             app.keys = as<int64_t>(q);
             HIP_TRY(C.ensure(B_APP_VALS, (size_t)appcap * 8, &q));
@@ -1447,7 +1493,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
                 rs = sweep_dim(C, P, p, k, max_dim, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
             else
                 launch_fill_i64(ph.keys, phcap, kEmpty, st);
-            if (rs) return rs;
+            if ((rs = swept(C, rs, &full))) return rs;
             if (full) {
                 swept_full = k--; // the same dimension again, by columns
                 continue;
@@ -1944,6 +1990,7 @@ __global__ void k_set_nbars(Scalars *s, int64_t v) { s->nbars = v; }
 rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_offsets, int32_t B, int32_t dim,
                           int32_t n_max, int32_t max_dim, float threshold, rips_batch_out *out,
                           hipStream_t st, bool *full) {
+    const Sweeping hold(C);
     void *q;
     const int D1 = max_dim + 1;
     const int64_t grid = std::min<int64_t>(std::max(1, C.num_cus), B);
@@ -2298,7 +2345,7 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
         rs = single_sweep(*C, d_data, (int)n, dim, max_dim, threshold, p,
                           BarBuf{out->birth, out->death, out->birth_simplex, out->death_simplex}, room ? out->cap : -1,
                           false, st, o, &full);
-        if (rs) return rs;
+        if ((rs = swept(*C, rs, &full))) return rs;
         done = !full;
         swept_full = 1;
     }
@@ -2405,6 +2452,7 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
         bars.ds = as<int64_t>(q);
         full = false;
         rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, p, bars, cap, true, st, o, &full);
+        rs = swept(*C, rs, &full);
         swept_cap = full ? 0 : cap;
         swept_full = 1;
     }
@@ -2813,6 +2861,7 @@ static rips_status batched_device(const float *d_points, const int64_t *d_offset
         bool full = false;
         rs = batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
                            (hipStream_t)hip_stream, &full);
+        rs = swept(*C, rs, &full);
         if (rs || !full) return rs;
     }
     for (int attempt = 0;; ++attempt) {
