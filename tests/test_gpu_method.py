@@ -6,7 +6,7 @@ import pytest
 
 import workloads
 from tests.method_of import method_of
-from tests.test_gpu_batched import lattice_batch, small_batch
+from tests.test_gpu_batched import small_batch
 from tests.test_gpu_sweep import two_simplices
 
 pytestmark = pytest.mark.gpu
@@ -18,6 +18,17 @@ def rips():
     return r
 
 
+def ring(n, noise=0.002):
+    g = workloads.rng(n)
+    a, r = g.uniform(0.0, 2.0 * np.pi, n), 1.0 + noise * g.standard_normal(n)
+    return np.stack([r * np.cos(a), r * np.sin(a)], axis=1).astype(np.float32)
+
+
+def rounded(x, digits):
+    d = np.sqrt(((x[:, None].astype(np.float64) - x[None]) ** 2).sum(2)).round(digits).astype(np.float32)
+    return np.ascontiguousarray(d)
+
+
 SINGLE = [
     ("whole", lambda: workloads.sphere(100, 1), dict(max_dim=1, threshold=INF), {"sweep"}, {"reduce_d1"}),
     ("whole-p5", lambda: workloads.sphere(90, 2), dict(max_dim=1, threshold=INF, p=5), {"sweep"}, {"reduce_d1"}),
@@ -27,6 +38,14 @@ SINGLE = [
      {"reduce_d1"}),
     ("blocks", lambda: workloads.sphere(64, 4), dict(max_dim=2, threshold=INF), {"sweep_d1", "sweep_d2"},
      {"reduce_d1", "reduce_d2"}),
+    # more than 2^28 possible edges: places by hashing (few classes are open at once on a ring)
+    ("chunks-hashed-places", lambda: ring(23400), dict(max_dim=1, threshold=0.006), {"sweep_d1"}, {"reduce_d1"}),
+    ("chunks-hashed-places-p3", lambda: ring(23400, 0.0001), dict(max_dim=1, threshold=0.006, p=3), {"sweep_d1"},
+     {"reduce_d1"}),
+    ("blocks-few-ties", lambda: rounded(workloads.sphere(52, workloads.SEED_BASE + 5), 5),
+     dict(max_dim=2, threshold=INF, is_distance=True), {"sweep_d2"}, {"reduce_d1", "reduce_d2"}),
+    ("blocks-few-ties-d3", lambda: rounded(workloads.orthogonal(520, workloads.SEED_BASE + 105), 5),
+     dict(max_dim=3, threshold=1.8, is_distance=True), {"sweep_d2"}, {"reduce_d1", "reduce_d2", "reduce_d3"}),
     ("blocks-so3", lambda: workloads.so3(700, 5), dict(max_dim=2, threshold=1.4), {"sweep_d2"},
      {"reduce_d1", "reduce_d2"}),
 ]
@@ -105,7 +124,8 @@ def test_whole_clouds_of_many_coordinates(m, p):
             assert e.value.status == -4
 
 
-@pytest.mark.parametrize("n,m,p,whole", [(200, 16, 2, True), (220, 64, 2, False), (160, 5, 3, True), (200, 16, 3, False)])
+@pytest.mark.parametrize("n,m,p,whole", [(200, 16, 2, True), (220, 64, 2, False), (160, 5, 3, True),
+                                           (200, 16, 3, False)])
 def test_whole_clouds_of_many_classes(n, m, p, whole):
     """Up to two classes a point, or 220 over another field, by the sweep;
     with more the staged path follows it."""
@@ -179,7 +199,8 @@ def test_batched_columns_over_z2():
     cloud, the replays of their graph, and the sweep: the same bars."""
     import torch
     r = rips()
-    x, off, nmax = r.pack_clouds(small_batch() + lattice_batch(12))
+    x, off, nmax = r.pack_clouds(small_batch() + [workloads.integer_lattice(n, 3, n, side=4) for n in (20, 64, 90)]
+                                 + [np.pad(workloads.noisy_circle_with_outliers(1, 270, 30), ((0, 0), (0, 1)))])
     print("[case] batched columns over Z/2", flush=True)
     call = lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, p=2, cap=1 << 15))
     want, s, c = method_of(call)
@@ -213,3 +234,44 @@ def test_autotune_times_the_columns():
     got, s, c = method_of(lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, cap=1 << 14)))
     assert s == {"batched_sweep"} and not c
     assert all(np.array_equal(a.cpu(), b.cpu()) for a, b in zip(want, got))
+
+
+DENSE = [("circle", 614), ("circle", 615), ("circle", 1023), ("circle", 1024), ("lattice", 614), ("lattice", 615),
+         ("sphere", 1024)]
+
+
+@pytest.mark.parametrize("data,n", DENSE, ids=[f"{d}-{n}" for d, n in DENSE])
+def test_large_dense_clouds(data, n):
+    """Every edge in: the nonzero-edge bits in LDS up to 614 points, longer
+    sorts, chunks and lists; against the columns."""
+    import torch
+    r = rips()
+    x = {"circle": lambda: workloads.noisy_circle_with_outliers(n, n - n // 10, n // 10),
+         "lattice": lambda: workloads.integer_lattice(n, 2, n, side=40),
+         "sphere": lambda: workloads.sphere(n, n)}[data]()
+    x = torch.from_numpy(x).cuda()
+    print(f"[case] dense {data} n={n}", flush=True)
+    (one, i1), s, c = method_of(lambda: r.barcode_device(x, max_dim=1))
+    assert s == {"sweep"} and not c
+    r.set_sweep(0)
+    two, i2 = r.barcode_device(x, max_dim=1)
+    assert i1["threshold"] == i2["threshold"] and i1["simplex_count"] == i2["simplex_count"]
+    for a, b in zip(one, two):
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+
+
+def test_batch_of_tiny_and_largest_clouds():
+    import torch
+    r = rips()
+    x, off, nmax = r.pack_clouds([workloads.uniform_cube(k, 2, k) for k in (1, 2, 3, 40)]
+                                 + [workloads.noisy_circle_with_outliers(3, 1900, 148),
+                                    workloads.integer_lattice(900, 2, 5, side=60)])
+    assert nmax == 2048
+    print("[case] batch of tiny and largest clouds", flush=True)
+    call = lambda: _bars(r.barcode_batched(x, off, nmax, max_dim=1, threshold=0.3))
+    one, s, c = method_of(call)
+    assert s == {"batched_sweep"} and not c
+    r.set_sweep(0)
+    two, s, c = method_of(call)
+    assert not s and c == {"batched_graph"}
+    assert all(torch.equal(a, b) for a, b in zip(one, two))
