@@ -844,6 +844,20 @@ struct DimShared {
 
 __device__ __forceinline__ bool key_less(u32 d0, u64 i0, u32 d1, u64 i1) { return d0 < d1 || (d0 == d1 && i0 < i1); }
 
+// place of candidate i among the first n by age; their keys are distinct, and
+// were they not, every place would still have one candidate
+__device__ __forceinline__ int rank_of(const DimShared &Sh, int n, int i) {
+    const u32 d = Sh.cd[i];
+    const u64 x = Sh.ci[i];
+    int at = 0;
+    for (int q = 0; q < n; ++q) {
+        const u32 dq = Sh.cd[q];
+        const u64 xq = Sh.ci[q];
+        at += key_less(dq, xq, d, x) || (dq == d && xq == x && q < i) ? 1 : 0;
+    }
+    return at;
+}
+
 __device__ __forceinline__ u64 lane_u64(u64 x, int l) {
     const u32 lo = __builtin_amdgcn_readlane((u32)x, l), hi = __builtin_amdgcn_readlane((u32)(x >> 32), l);
     return ((u64)hi << 32) | lo;
@@ -1124,7 +1138,8 @@ __global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
 
 // The lanes with `ok` hold cofacets that do not cancel (rows r, key (kd, ki),
 // nonzero words z): of those with the same rows the oldest becomes a
-// candidate. (A cofacet that is found twice cancels in the elimination.)
+// candidate. No cofacet is found twice: a triangle is owned by one edge, and a
+// tetrahedron is listed from one side of its block's edge.
 template <bool kOdd, int M>
 __device__ __forceinline__ void candidates(const DimArgs &A, DimShared &Sh, LDS u32 *vec, int ccap, const u32 (&r)[M],
                                            bool ok, u32 kd, u64 ki, u64 z) {
@@ -1591,13 +1606,9 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
             const bool last = hi_d == ~0u;
             if (nc > ccap) {
                 // too many at once: only those up to the quarter point of the stored ones
-                if (tid < ccap) {
-                    int less = 0;
-                    for (int q = 0; q < ccap; ++q) less += key_less(Sh.cd[q], Sh.ci[q], Sh.cd[tid], Sh.ci[tid]) ? 1 : 0;
-                    if (less == ccap / 4) {
-                        Sh.hi_d = Sh.cd[tid];
-                        Sh.hi_i = Sh.ci[tid];
-                    }
+                if (tid < ccap && rank_of(Sh, ccap, tid) == ccap / 4) {
+                    Sh.hi_d = Sh.cd[tid];
+                    Sh.hi_i = Sh.ci[tid];
                 }
                 __syncthreads();
                 hi_d = Sh.hi_d;
@@ -1606,17 +1617,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
             }
             if (nc > 0) {
                 // ---- elimination in order, by one wave
-                if (tid < nc) { // the same cofacet may be there twice
-                    const u32 d = Sh.cd[tid];
-                    const u64 x = Sh.ci[tid];
-                    int at = 0;
-                    for (int q = 0; q < nc; ++q) {
-                        const u32 dq = Sh.cd[q];
-                        const u64 xq = Sh.ci[q];
-                        at += key_less(dq, xq, d, x) || (dq == d && xq == x && q < tid) ? 1 : 0;
-                    }
-                    Sh.ord[at] = (uint16_t)tid;
-                }
+                if (tid < nc) Sh.ord[rank_of(Sh, nc, tid)] = (uint16_t)tid;
                 __syncthreads();
                 if (wave == 0) {
                     int nk = 0;
