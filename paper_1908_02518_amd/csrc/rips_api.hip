@@ -238,7 +238,7 @@ enum BufId {
     B_EXP_WD1,
     B_EXP_WC0,
     B_EXP_WC1,
-    // the sweep (dimensions 0 and 1 over Z/2)
+    // the sweep of whole clouds (dimensions 0 and 1)
     B_SW_D,
     B_SW_IDS,
     B_SW_ZC,

@@ -1,5 +1,5 @@
 // rips_sweep_dim.hpp -- the sweep of dimension 1 or 2 of a single cloud over
-// Z/2: buffers and launchers.
+// Z/p: buffers and launchers.
 #pragma once
 
 #include "rips_kernels.hpp"
