@@ -961,11 +961,6 @@ bool sweeps_whole(const DevCtx &C, int64_t n, int max_dim, float threshold, uint
     return n >= 2 && n <= whole_most(max_dim, std::isinf(threshold), p) && sweep_allowed(C);
 }
 
-// Triangles from which dimension 2 is swept: below, the launches of the sweep
-// cost what the columns do (12 points on the sphere 0.58 and 0.55 ms, 24 points
-// 0.57 and 0.48, 357 rotations at 1.3, 8000 triangles, 1.31 and 1.24; 64 points
-// on the sphere, 37,000 triangles, 1.4 and 9.7).
-constexpr int64_t kSweepTriangles = 12288;
 // Classes of dimension 2 that its sweep opens at most over another field.
 constexpr int kBlocksOddClasses = 1200;
 
@@ -1336,7 +1331,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
             ncand = (int64_t)C.host_scal->list;
             if (ncand > C.hint_list[k]) C.hint_list[k] = ncand;
         }
-        if (k == 2) sweep = sweep && ncand >= kSweepTriangles;
+        if (k == 2) sweep = sweep && blocks_pay(n, P.nedges, P.deg2, ncand);
         o.simplex_count[k] = ncand;
         // ---- enumeration / apparent-pair pass
         Columns surv, cols;

@@ -83,10 +83,33 @@ constexpr bool batch_swept(int n_max, int m, uint32_t p) {
 // are open at once for its tables (1137 of 4000 points on the sphere fit, 1161
 // of 2000 orthogonal matrices do not).
 constexpr int64_t kChunkDegMin = 32, kChunkDegMax = 200, kChunkOddDegMax = 110, kChunkOddColumns = 1150;
-constexpr double kChunkUneven = 1.22;
+constexpr double kUneven = 1.22;
+constexpr bool lie_evenly(int64_t n, int64_t edges, uint64_t deg2) {
+    return (double)n * (double)deg2 <= kUneven * 4.0 * (double)edges * (double)edges;
+}
 constexpr bool chunks_pay(int64_t n, int64_t edges, uint64_t deg2, uint32_t p) {
     return edges >= kChunkDegMin * n / 2 && edges <= (p == 2 ? kChunkDegMax : kChunkOddDegMax) * n / 2 &&
-           (double)n * (double)deg2 <= kChunkUneven * 4.0 * (double)edges * (double)edges;
+           lie_evenly(n, edges, deg2);
+}
+
+// Whether dimension 2 is swept by blocks: by its triangles, and by how many an
+// edge has. Few triangles cost the sweep's launches what they cost the columns
+// (12 points on the sphere 0.58 and 0.55 ms, 24 points 0.57 and 0.48, 357
+// rotations at 1.3, 8000 triangles, 1.31 and 1.24; 64 points on the sphere,
+// 37,000 triangles, 1.4 and 9.7). And with few an edge the columns are short
+// while the sweep still looks at every edge's lune: over 107 clouds that the
+// rule sends to the columns they took 0.80 of the sweep's time in the mean
+// (1200 points, 25 edges a point, triangles an edge 3 to 5: rotations 0.8,
+// uniform in R^5 0.5, in R^10 0.3, torus 1.0, sphere 1.0), over 145 that it
+// has swept, 1.5 times (45 edges a point: 0.9 to 1.9 times on all of these but
+// R^10; 80 edges a point: torus 2.5 to 8, rotations 5 to 9, sphere 3 to 10,
+// uniform in R^3 1 to 3; dense clouds: sphere 5 to 67, uniform in R^5 0.5 to
+// 0.8, normal in R^3 0.3 to 1.3, which nothing known by then tells apart).
+// The same evenness as for dimension 1: above it clusters 0.4 to 0.75, normal
+// points of R^3 and R^5 0.5 to 1.2, of R^2 0.9 to 2.3.
+constexpr int64_t kBlockTriangles = 12288, kBlockRatio = 5;
+constexpr bool blocks_pay(int64_t n, int64_t edges, uint64_t deg2, int64_t triangles) {
+    return triangles >= kBlockTriangles && triangles >= kBlockRatio * edges && lie_evenly(n, edges, deg2);
 }
 
 // Triangles of which the chunked sweep of dimension 1 holds the places (12

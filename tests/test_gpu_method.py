@@ -175,6 +175,58 @@ def test_chunks_where_the_points_lie_evenly(data, sweeps):
         assert all(torch.equal(u, v) for u, v in zip(a, b))
 
 
+@pytest.mark.parametrize("data,t,sweeps", [("so3", 1.3, True), ("so3", 1.1, False), ("crowded", 0.15, False)])
+@pytest.mark.parametrize("p", [2, 3])
+def test_blocks_where_edges_have_triangles(data, t, sweeps, p):
+    """Dimension 2 of a sparse or of a crowded cloud goes by columns."""
+    import torch
+    r = rips()
+    x = workloads.so3(1000, 11)
+    if data == "crowded":
+        g = workloads.rng(8)
+        x = g.uniform(0.0, 1.0, (900, 3))
+        x[:150] = 0.5 + 0.05 * g.standard_normal((150, 3))
+        x = x.astype(np.float32)
+    d = torch.from_numpy(x).cuda()
+    print(f"[case] blocks {data} t={t} p={p}", flush=True)
+    (one, info), s, c = method_of(lambda: r.barcode_device(d, max_dim=2, threshold=t, p=p))
+    edges, triangles = info["simplex_count"][1:3]
+    assert triangles > 12288 and (triangles >= 5 * edges) == (sweeps or data == "crowded"), (edges, triangles)
+    assert ("sweep_d2" in s) == sweeps and ("reduce_d2" in c) != sweeps, (s, c)
+    assert_reference(one, x, t, p)
+
+
+def test_blocks_of_a_lune_of_many_points():
+    """An even cloud in which two points are near 1100 others: their edge has
+    more points in its lune than one block's forest holds."""
+    import torch
+    r = rips()
+    x = workloads.sphere(6000, 12)
+    d = np.empty((6000, 6000), np.float32)
+    for i in range(0, 6000, 500):
+        d[i:i + 500] = np.sqrt(np.maximum(((x[i:i + 500, None] - x[None]) ** 2).sum(2), 0.0))
+    t = 0.2
+    d[d > t] = 9.0
+    w = t * (1.0 + 0.1 * workloads.rng(13).uniform(0.0, 1.0, (2, 1100))).astype(np.float32)
+    d[:2, 2:1102], d[2:1102, :2] = w, w.T
+    d[0, 1] = d[1, 0] = np.float32(1.2 * t)
+    x = torch.from_numpy(d).cuda()
+    out = {}
+    for flags in (3, 0):
+        print(f"[case] blocks, large lune, flags={flags}", flush=True)
+        r.set_sweep(flags)
+        r.profile_enable(True)
+        try:
+            out[flags], info = r.barcode_device(x, max_dim=2, threshold=1.2 * t, is_distance=True)
+            torch.cuda.synchronize()
+            ran = r.profile_read()
+        finally:
+            r.profile_enable(False)
+        assert ("sweep_build_d2" in ran) == (flags == 3) and "reduce_d2" in ran, sorted(ran)
+    for a, b in zip(out[3], out[0]):
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+
+
 def _bars(bb):
     n = int(bb.offsets[-1])
     return [t[:n].clone() for t in (bb.birth, bb.death, bb.birth_simplex, bb.death_simplex)] + [bb.offsets.clone()]

@@ -87,3 +87,15 @@ def test_batches_that_are_swept(tmp_path):
         for (int n : {1, 128, 129, 2048})
             for (int m : {1, 128, 129, 100000}) printf("%d ", (int)batch_swept(n, m, p));""")
     assert [int(x) for x in got] == [1] * 8 + [1, 1, 0, 0] * 2 + [0] * 16
+
+
+def test_clouds_whose_dimension_2_is_swept_by_blocks(tmp_path):
+    """By the triangles, by how many an edge has, and by evenness."""
+    got = run(tmp_path, """
+    auto even = [](int64_t n, int64_t d, int64_t t) { return (int)blocks_pay(n, n * d / 2, (uint64_t)(n * d * d), t); };
+    printf("%d %d ", even(100, 20, 12287), even(100, 20, 12288));
+    printf("%d %d ", even(2000, 50, 249999), even(2000, 50, 250000));
+    printf("%d %d ", (int)blocks_pay(1000, 50000, 12200000, 1 << 20), (int)blocks_pay(1000, 50000, 12200001, 1 << 20));
+    for (int64_t n : {42, 43, 44}) printf("%d ", even(n, n - 1, n * (n - 1) * (n - 2) / 6));
+    printf("%d", even(65535, 65534, 46907926681605ll));""")
+    assert [int(x) for x in got] == [0, 1, 0, 1, 1, 0, 0, 1, 1, 1]
