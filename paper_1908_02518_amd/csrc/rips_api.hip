@@ -1980,8 +1980,8 @@ BarBuf internal_bars(DevCtx &C, int d) {
 __global__ void k_set_nbars(Scalars *s, int64_t v) { s->nbars = v; }
 
 // The batch by the sweep, one workgroup per cloud from a queue by decreasing
-// size. *full: some cloud exceeds the sweep's tables; nothing was written to
-// the bar arrays and the caller runs the column reduction.
+// size. *full: some cloud exceeds the sweep's tables; the bar arrays may hold
+// bars of the others, and the caller runs the column reduction over all.
 rips_status batched_sweep(DevCtx &C, const float *d_points, const int64_t *d_offsets, int32_t B, int32_t dim,
                           int32_t n_max, int32_t max_dim, float threshold, rips_batch_out *out,
                           hipStream_t st, bool *full) {

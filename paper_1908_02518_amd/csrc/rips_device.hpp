@@ -835,4 +835,25 @@ __device__ __forceinline__ int64_t wave_append(unsigned long long *counter, bool
     return pred ? (int64_t)(base + __popcll(m & lt)) : -1;
 }
 
+// The same for a 32-bit counter, with no answer to the lanes without `want`.
+__device__ __forceinline__ int wave_place(bool want, int *counter) {
+    const u64 bal = __ballot(want);
+    if (!bal) return -1;
+    const int lane = lane_id(), lead = __ffsll((unsigned long long)bal) - 1;
+    int base = 0;
+    if (lane == lead) base = atomicAdd(counter, __popcll(bal));
+    base = __shfl(base, lead, kWave);
+    return base + __popcll(bal & ((1ull << lane) - 1));
+}
+
+__device__ __forceinline__ u32 odd_mul(u32 a, u32 b, u32 p) { return (u32)((u64)a * b % p); }
+__device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
+    u32 r = 1;
+    for (u32 e = p - 2; e; e >>= 1) {
+        if (e & 1u) r = odd_mul(r, a, p);
+        a = odd_mul(a, a, p);
+    }
+    return r;
+}
+
 } // namespace rips

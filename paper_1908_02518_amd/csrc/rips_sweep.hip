@@ -156,17 +156,6 @@ __device__ __forceinline__ int sweep_scan(int x, int *s_w, int *total) {
     return ex;
 }
 
-// Slot of every lane with `want` in an append buffer (one LDS atomic a wave).
-__device__ __forceinline__ int wave_append(bool want, int *counter) {
-    const u64 bal = __ballot(want);
-    if (!bal) return -1;
-    const int lane = lane_id(), lead = __ffsll((unsigned long long)bal) - 1;
-    int base = 0;
-    if (lane == lead) base = atomicAdd(counter, __popcll(bal));
-    base = __shfl(base, lead, kWave);
-    return base + __popcll(bal & ((1ull << lane) - 1));
-}
-
 // One edge's scan result: its place in the partition, or a survivor.
 __device__ __forceinline__ void scan_result(const SweepArgs &A, SweepShared &Sh, const SweepLds &L, const float *D,
                                             u32 *ids, int64_t wo, int n, bool live, int a, int b, float len,
@@ -183,7 +172,7 @@ __device__ __forceinline__ void scan_result(const SweepArgs &A, SweepShared &Sh,
         atomicAdd((u32 *)&L.hist[bin_of(len, scale)], 1u);
         *zapped += zap ? 1u : 0u;
     }
-    const int at = wave_append(live && !zap, &Sh.nsurv);
+    const int at = wave_place(live && !zap, &Sh.nsurv);
     if (live && !zap && at < A.sv_cap) sv[at] = edge_key(len, e);
 }
 
@@ -284,15 +273,6 @@ __device__ __forceinline__ bool odd_less(Get get, Put put, GetRes get_res, Res r
         any |= bits;
     }
     return any != 0;
-}
-
-__device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
-    u32 r = 1;
-    for (u32 e = p - 2; e; e >>= 1) {
-        if (e & 1u) r = (u32)((u64)r * a % p);
-        a = (u32)((u64)a * a % p);
-    }
-    return r;
 }
 
 // The nonzero-edge bits: in LDS up to kSweepMaskBytes, else in global memory.
@@ -630,7 +610,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
             ncand += edge ? 1u : 0u;
             if (v < a && !edge) A.zc[wo + pair_index(a, v)] = (uint16_t)kNotEdge;
             scan_result(A, Sh, L, D, ids, wo, n, edge && !more, a, v, len, c, scale, sv, &nzap);
-            const int at = wave_append(more, &Sh.nlong);
+            const int at = wave_place(more, &Sh.nlong);
             if (more) aux[at] = ((u32)a << 16) | (u32)v;
         }
     }
@@ -850,7 +830,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                 }
                 const u64 bal = __ballot(opens);
                 if (lane == 0 && bal) atomicAdd(&Sh.act, __popcll(bal));
-                const int at = wave_append(opens, &Sh.nnz);
+                const int at = wave_place(opens, &Sh.nnz);
                 if (opens) aux[at] = 0xffffffffu - (u32)key;
                 __syncthreads();
                 const int now = Sh.act;
@@ -961,7 +941,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                         const int a = (int)(ab >> 16), v = (int)(ab & 0xffff);
                         look = ((L.vnz[a >> 5] >> (a & 31)) & 1u) || ((L.vnz[v >> 5] >> (v & 31)) & 1u);
                     }
-                    const int at = wave_append(look, &Sh.nwork);
+                    const int at = wave_place(look, &Sh.nwork);
                     if (look) Sh.work[at] = ab;
                     __syncthreads();
                     const int nw = Sh.nwork;
@@ -1099,7 +1079,7 @@ __device__ void sweep_cloud(const SweepArgs &A, int b_cloud, unsigned char *smem
                             atomicAnd((unsigned long long *)&mask[v * MW + (a >> 6)], ~(1ull << (a & 63)));
                         }
                     }
-                    const int at = wave_append(keep, &Sh.nnz);
+                    const int at = wave_place(keep, &Sh.nnz);
                     if (keep) aux[at] = e; // at most q0 + tid: entries already read
                     __syncthreads();
                 }

@@ -900,16 +900,6 @@ __device__ __forceinline__ u32 sum_word(const DimArgs &A, const u32 (&r)[M], int
     return x;
 }
 
-__device__ __forceinline__ int dim_append(bool want, int *counter) {
-    const u64 bal = __ballot(want);
-    if (!bal) return -1;
-    const int lane = lane_id(), lead = __ffsll((unsigned long long)bal) - 1;
-    int base = 0;
-    if (lane == lead) base = atomicAdd(counter, __popcll(bal));
-    base = __shfl(base, lead, kWave);
-    return base + __popcll(bal & ((1ull << lane) - 1));
-}
-
 // the three edges of the triangle at place q have one with a nonzero vector
 __device__ __forceinline__ void mark(const DimArgs &A, u32 q) {
     int a, b, c;
@@ -934,17 +924,8 @@ __device__ __forceinline__ void call_on(const DimArgs &A, u32 q) {
 // residue is not zero, and then a 16-bit residue for every slot.
 constexpr int kOddStride = 17; // words of a row for each word of bits
 
-__device__ __forceinline__ u32 odd_mul(u32 a, u32 b, u32 p) { return (u32)((u64)a * b % p); }
 __device__ __forceinline__ u32 odd_neg(u32 id, bool neg, u32 p) {
     return id && neg ? (id & 0xffffu) | ((p - (id >> 16)) << 16) : id;
-}
-__device__ __forceinline__ u32 odd_inverse(u32 a, u32 p) { // a^(p - 2)
-    u32 r = 1;
-    for (u32 e = p - 2; e; e >>= 1) {
-        if (e & 1u) r = odd_mul(r, a, p);
-        a = odd_mul(a, a, p);
-    }
-    return r;
 }
 
 // what the row map makes of an id
@@ -1127,7 +1108,7 @@ __global__ void __launch_bounds__(256) k_lune_tests(DimArgs A, int chunk) {
             } else if (ok && cancel<4>(r) > 0)
                 for (u64 m = sum_words<4>(A, r); m && !nonzero; m &= m - 1)
                     nonzero = sum_word<4>(A, r, __ffsll((unsigned long long)m) - 1) != 0;
-            const int at = dim_append(nonzero, &A.out->npair);
+            const int at = wave_place(nonzero, &A.out->npair);
             if (nonzero && at < A.paircap) A.pairs[at] = ((u64)q << 32) | (u32)d;
             // too many: the sweep ends after this, and the count goes no
             // further than one append of every wave takes it
@@ -1741,9 +1722,9 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                     const u32 r = i < na ? A.ract[i] : 0;
                     __syncthreads();
                     const bool keep = i < na && rmap[r] == own_id(r);
-                    const int at = dim_append(keep, &Sh.nact);
+                    const int at = wave_place(keep, &Sh.nact);
                     if (keep) A.ract[at] = r; // at most i: entries already read
-                    const int de = dim_append(i < na && !keep, &Sh.ndead);
+                    const int de = wave_place(i < na && !keep, &Sh.ndead);
                     if (i < na && !keep) A.rdead[de] = r;
                     __syncthreads();
                 }
@@ -1771,7 +1752,7 @@ __global__ void __launch_bounds__(kT) k_dim_sweep(DimArgs A, int chunk) {
                             if constexpr (K == 2)
                                 if (keep) mark(A, q);
                         }
-                        const int at = dim_append(keep, &Sh.nnz);
+                        const int at = wave_place(keep, &Sh.nnz);
                         if (keep) A.nzl[at] = q;
                         __syncthreads();
                     }
