@@ -224,10 +224,11 @@ rips_status rips_simplex_counts_device(const float *d_data, int64_t n, int32_t d
  * rips_barcode_batched_device -- barcodes of B point clouds of uneven sizes
  * in one persistent launch (workgroups that take the clouds from a queue
  * ordered by decreasing size). Over Z/2 that is the sweep of
- * rips_set_working_column; for other fields, or where a cloud exceeds the
- * sweep's tables (more than 2048 open classes, say), the column reduction,
- * replayed from a cached hipGraph when the arguments repeat. Same results
- * and conventions as rips_barcode, per cloud.
+ * rips_set_working_column; for other fields, for clouds of more than 128
+ * points (n_max) and 128 coordinates, or where a cloud exceeds the sweep's
+ * tables (more than 2048 open classes, say), the column reduction, replayed
+ * from a cached hipGraph when the arguments repeat. Same results and
+ * conventions as rips_barcode, per cloud.
  *   d_points   device float32, all clouds' points concatenated row-major
  *              (dim coordinates each); cloud b has rows
  *              [d_offsets[b], d_offsets[b+1]).
@@ -372,12 +373,13 @@ rips_status rips_get_reduced_storage(int32_t *mode);
 /*
  * The method of dimensions 0 to 2 (per device, the current one; single-cloud
  * and batched paths). AUTO takes the sweep where it applies and pays (every
- * shortcut and the default storage, no cocycles; batches over Z/2; in the
- * single-cloud path dimensions 0 and 1 of small clouds, dimension 1 of clouds
- * with a middling number of edges a point and dimension 2 from some 12,000
- * triangles on): one pass over the simplices in order of diameter that carries
- * on every simplex the vector of the open classes, closed by the first cofacet
- * whose facets' vectors do not cancel; no coboundary column is reduced.
+ * shortcut and the default storage, no cocycles; most batches over Z/2; in the
+ * single-cloud path dimensions 0 and 1 of small clouds, and of larger ones
+ * whose points lie evenly dimension 1 with a middling number of edges a point
+ * and dimension 2 with triangles enough, some 12,000 and five an edge): one
+ * pass over the simplices in order of diameter that carries on every simplex
+ * the vector of the open classes, closed by the first cofacet whose facets'
+ * vectors do not cancel; no coboundary column is reduced.
  * Otherwise the columns are reduced, with one of two working columns. A column's rows are
  * triangles, and over Z/2 with every shortcut on it can be held direct-mapped: one bit per
  * (longest edge, third vertex), the edges <= t in order of length, so that
