@@ -971,6 +971,18 @@ struct Sweeping {
     ~Sweeping() { C.sweeping = false; }
 };
 
+// A run that sweeps; once more where it found no memory and sweeps before it
+// hold some.
+template <class Run>
+rips_status with_room(DevCtx &C, Run run) {
+    rips_status rs = run();
+    if (rs == RIPS_E_OOM && C.release_sweep()) {
+        g_err.clear();
+        rs = run();
+    }
+    return rs;
+}
+
 // What a sweep returned; where it found no memory it is as if a table was
 // full, and the columns decide.
 rips_status swept(DevCtx &C, rips_status rs, bool *full) {
@@ -1224,9 +1236,11 @@ rips_status sweep_dim(DevCtx &C, const Prepared &P, uint32_t p, int k, int max_d
     return RIPS_OK;
 }
 
-// swept_full: dimension whose sweep has given up already (0: none)
-rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, uint32_t p,
-                       hipStream_t st, RunOut &o, int swept_full = 0) {
+// swept_full: dimension whose sweep has given up already (0: none; kAnyDim:
+// the dimensions go by columns)
+constexpr int kAnyDim = -1;
+rips_status run_staged(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, uint32_t p,
+                       hipStream_t st, RunOut &o, int swept_full) {
     memset(&o, 0, sizeof(o));
     o.n = n;
     o.max_dim = max_dim;
@@ -1306,7 +1320,8 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         // dimensions 1 and 2 take the sweep, unless a setting asks for the
         // reduction of columns (and for cocycles, which are its V_j)
         const bool in_chunks = chunks_pay(n, P.nedges, P.deg2, p);
-        bool sweep = k <= 2 && (k == 2 || in_chunks) && k != swept_full && n <= kDimMaxVert && sweep_allowed(C);
+        bool sweep = k <= 2 && (k == 2 || in_chunks) && k != swept_full && swept_full != kAnyDim && n <= kDimMaxVert &&
+                     sweep_allowed(C);
         SimplexList cand;
         int64_t ncand;
         if (k == 1) {
@@ -1361,17 +1376,10 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         int *zj = nullptr;
         std::optional<Sweeping> hold;
         if (sweep) {
-            const hipError_t e = C.ensure(B_SD_ZJ, (size_t)ncand * 4, &q);
-            if (e == hipErrorOutOfMemory) {
-                (void)C.release_sweep();
-                sweep = false;
-            } else {
-                HIP_TRY(e);
-                zj = as<int>(q);
-                hold.emplace(C);
-            }
-        }
-        if (!sweep && apparent) {
+            HIP_TRY(C.ensure(B_SD_ZJ, (size_t)ncand * 4, &q));
+            zj = as<int>(q);
+            hold.emplace(C);
+        } else if (apparent) {
             HIP_TRY(C.ensure(B_APP_KEYS, (size_t)appcap * 8, &q));
             app.keys = as<int64_t>(q);
             HIP_TRY(C.ensure(B_APP_VALS, (size_t)appcap * 8, &q));
@@ -1488,7 +1496,7 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
                 rs = sweep_dim(C, P, p, k, max_dim, cand, ncand, zj, cols, S, ph, phcap, bars[k], st, o, &full);
             else
                 launch_fill_i64(ph.keys, phcap, kEmpty, st);
-            if ((rs = swept(C, rs, &full))) return rs;
+            if (rs) return rs;
             if (full) {
                 swept_full = k--; // the same dimension again, by columns
                 continue;
@@ -1773,6 +1781,16 @@ rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, 
         prev_count = ncand;
     }
     return RIPS_OK;
+}
+
+rips_status run_single(DevCtx &C, const float *d_in, int n, int m, int max_dim, float t, uint32_t p,
+                       hipStream_t st, RunOut &o, int swept_full = 0) {
+    auto run = [&](int full) { return run_staged(C, d_in, n, m, max_dim, t, p, st, o, full); };
+    rips_status rs = with_room(C, [&] { return run(swept_full); });
+    if (rs != RIPS_E_OOM || max_dim < 1 || !sweep_allowed(C)) return rs;
+    (void)C.release_sweep(); // no room for a sweep at all, perhaps for the columns
+    g_err.clear();
+    return run(kAnyDim);
 }
 
 // ---------------------------------------------------------------------------
@@ -2337,9 +2355,11 @@ rips_status device_barcode(DevCtx *C, const float *d_data, int64_t n, int32_t di
     if (sweeps_whole(*C, n, max_dim, threshold, p)) {
         bool full = false;
         const bool room = out->birth && out->death && out->birth_simplex && out->death_simplex && out->cap > 0;
-        rs = single_sweep(*C, d_data, (int)n, dim, max_dim, threshold, p,
-                          BarBuf{out->birth, out->death, out->birth_simplex, out->death_simplex}, room ? out->cap : -1,
-                          false, st, o, &full);
+        const BarBuf bars{out->birth, out->death, out->birth_simplex, out->death_simplex};
+        rs = with_room(*C, [&] {
+            return single_sweep(*C, d_data, (int)n, dim, max_dim, threshold, p, bars, room ? out->cap : -1, false, st,
+                                o, &full);
+        });
         if ((rs = swept(*C, rs, &full))) return rs;
         done = !full;
         swept_full = 1;
@@ -2446,7 +2466,9 @@ rips_status rips_barcode(const float *data, int64_t n, int32_t dim, int32_t max_
         HIP_TRY(C->ensure(B_BAR_DS, (size_t)cap * 16, &q));
         bars.ds = as<int64_t>(q);
         full = false;
-        rs = single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, p, bars, cap, true, st, o, &full);
+        rs = with_room(*C, [&] {
+            return single_sweep(*C, d_in, (int)n, dim, max_dim, threshold, p, bars, cap, true, st, o, &full);
+        });
         rs = swept(*C, rs, &full);
         swept_cap = full ? 0 : cap;
         swept_full = 1;
@@ -2852,10 +2874,13 @@ static rips_status batched_device(const float *d_points, const int64_t *d_offset
     rips_status rs;
     if ((rs = get_ctx(&C))) return rs;
     std::lock_guard<std::mutex> lk(C->mu);
-    if (!columns && batch_swept(n_max, dim, p) && C->working_column == RIPS_WORKING_COLUMN_AUTO && (C->sweep & RIPS_SWEEP_BATCHED)) {
+    if (!columns && batch_swept(n_max, dim, p) && C->working_column == RIPS_WORKING_COLUMN_AUTO &&
+        (C->sweep & RIPS_SWEEP_BATCHED)) {
         bool full = false;
-        rs = batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
-                           (hipStream_t)hip_stream, &full);
+        rs = with_room(*C, [&] {
+            return batched_sweep(*C, d_points, d_offsets, B, dim, n_max, max_dim, threshold, out,
+                                 (hipStream_t)hip_stream, &full);
+        });
         rs = swept(*C, rs, &full);
         if (rs || !full) return rs;
     }

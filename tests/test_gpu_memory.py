@@ -50,3 +50,44 @@ def test_columns_find_room_after_a_sweep_that_gave_up():
     _, got, _, columns = run(need + (32 << 20), 3)
     assert "reduce_d2" in columns
     assert got == want
+
+
+AFTER_A_BATCH = """
+import hashlib
+import torch
+import paper_1908_02518_amd as r
+import workloads
+from tests.method_of import method_of
+x = torch.from_numpy(workloads.so3(4000, 3)).cuda()
+pts = torch.from_numpy(workloads.sphere(512, 2)).cuda()
+r.barcode_device(pts[:300], max_dim=0)
+before = torch.cuda.mem_get_info()[0]
+r.barcode_batched(pts, torch.arange(0, 513, 8, device="cuda"), 2048, max_dim=1)
+held = before - torch.cuda.mem_get_info()[0]
+out = torch.empty(1 << 25, device="cuda")
+del out
+hog = torch.empty(torch.cuda.mem_get_info()[0] - (300 << 20), dtype=torch.uint8, device="cuda")
+results = []
+for _ in range(2):
+    (bars, _), s, c = method_of(lambda: r.barcode_device(x, max_dim=2, threshold=1.2, cap=1 << 19))
+    results.append(hashlib.sha1(b"".join(t.cpu().numpy().tobytes() for b in bars for t in b)).hexdigest())
+    del bars
+del hog
+torch.cuda.empty_cache()
+r.set_sweep(0)
+bars, _ = r.barcode_device(x, max_dim=2, threshold=1.2, cap=1 << 19)
+results.append(hashlib.sha1(b"".join(t.cpu().numpy().tobytes() for b in bars for t in b)).hexdigest())
+print("RESULT", held, "/".join(sorted(s)) or "-", len(set(results)))
+"""
+
+
+def test_a_sweep_finds_the_room_of_another():
+    """The scratch memory of a batch is given back where a cloud's sweep needs
+    some, before the columns (44 GB here) are thought of."""
+    print("[case] memory: a sweep after a large batch", flush=True)
+    p = subprocess.run([sys.executable, "-c", AFTER_A_BATCH], cwd=ROOT, capture_output=True, text=True, timeout=90,
+                       env={**os.environ, "PYTHONPATH": ROOT})
+    assert p.returncode == 0, p.stdout[-500:] + p.stderr[-1500:]
+    held, sweeps, distinct = next(ln for ln in p.stdout.splitlines() if ln.startswith("RESULT")).split()[1:]
+    assert int(held) > 4 << 30
+    assert sweeps == "sweep_d1/sweep_d2" and distinct == "1"
